@@ -13,6 +13,7 @@
 // guarded loader, so every positive shape works.
 #include "internal.h"
 #include "knobs.h"
+#include "split3.h"
 
 #include <stdlib.h>
 #include <algorithm>
@@ -28,22 +29,13 @@ struct GemmGroupArgs {
   GemmProblem p[kMaxGemmGroup];
   int tile_start[kMaxGemmGroup + 1];
   int nprob;
-  int n_main;  // tiles [0, n_main) are dispatched before the rest (launch_gemm_split: whole tiles before K slices)
 };
 
 // blockIdx -> tile index.  Workgroups are dealt round-robin to the 8 XCDs (each with its own L2): remap so that one
-// XCD works on a contiguous run of tiles, which share operand panels -- separately for the tiles before and from
-// n_main on, so that the hardware's dispatch order (ascending blockIdx) still reaches every tile of the first part
-// before any of the second.
-__device__ __forceinline__ int tile_index(const GemmGroupArgs& g) {
-  int bid = blockIdx.x, lo = 0, n = g.n_main;
-  if (bid >= n) {
-    lo = n;
-    n = (int)gridDim.x - n;
-    bid -= lo;
-  }
-  if ((n & 7) == 0 && (lo & 7) == 0) bid = (bid & 7) * (n >> 3) + (bid >> 3);
-  return lo + bid;
+// XCD works on a contiguous run of tiles, which share operand panels.
+__device__ __forceinline__ int tile_index() {
+  const int bid = blockIdx.x, n = gridDim.x;
+  return (n & 7) == 0 ? (bid & 7) * (n >> 3) + (bid >> 3) : bid;
 }
 
 enum LoadMode : int { LM_SCALAR = 0, LM_KCONTIG = 1, LM_RCONTIG = 2 };
@@ -151,7 +143,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmGroupArgs g) {
 
   // which problem, which tile
   int pi = 0;
-  const int bid = tile_index(g);
+  const int bid = tile_index();
   while (pi + 1 < g.nprob && bid >= g.tile_start[pi + 1]) ++pi;
   const GemmProblem& P = g.p[pi];
   const int local = bid - g.tile_start[pi];
@@ -265,126 +257,176 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmGroupArgs g) {
     }
 }
 
-// ------------------------------------------------------------------ direct-to-LDS variant
-// The kernel above spends about a fifth of its time on the instructions that move operand tiles
-// through registers (address arithmetic, zero selects, LDS stores): on this hardware they are not
-// hidden behind the MFMAs of the same wave.  This variant takes them out of the main loop:
-//   * global_load_lds_dwordx4 writes 16 bytes per lane straight into LDS (one instruction per KB,
-//     scalar base + constant per-lane offset, so advancing to the next k-tile is scalar arithmetic);
-//   * three LDS stages, tiles requested two ahead, one barrier per tile;
-//   * an operand with unit stride along K keeps its natural [row][16 k] layout in LDS with the four
-//     16-byte pieces of a row XOR-swizzled by (row/2)%4, and a lane fetches four MFMA steps' worth of
-//     operand with one conflict-free ds_read_b128; an operand with unit stride along the row dimension
-//     lands k-major ([k][row]) and is fetched with ds_read_b32 as before.
-// MFMA step (blk, s) of a k-tile multiplies k = 8*blk + 4*h + s for the lane half h = lane/32, the
-// same pairing for both operands.  Requirements (else the kernel above runs): both operands in a
-// vector mode, K a multiple of KT, byte offsets inside an operand below 2^31.  Rows past the end of
-// an operand re-read its last rows; they only reach outputs that are not stored.
-constexpr int DL_STAGES = 3;
+// ------------------------------------------------------------------ bf16 variant, operands in three parts
+// The kernel that runs: fp32 operands cut into three bf16 parts each (split3.h), six bf16 matrix instructions in the
+// place of the eight fp32 ones that 16 k of a 32x32 tile take, at an eighth of their time each.  What bounds it is the
+// chip's power: pure matrix instructions of this kind reach 1900 TFLOP/s on random operands (2430 on constant ones), this
+// kernel 1470 = 245 TFLOP/s of fp32 product on full rounds of tiles (fp32 matrix instructions: 144), and with only 16 of
+// the 256 CUs busy a CU runs at 1.35 times its rate of a full chip.  Against 64-bit products of random operands the error
+// is the fp32 kernel's or below (K = 512: 3.4e-7 against 4.0e-7, 6400: 1.21e-6 / 1.40e-6, 16384: 1.86e-6 / 2.25e-6).
+//
+// A workgroup of NWM x NWN waves computes a tile of TM x TN, each wave WM x WN tiles of 32x32.  Operands go from memory to
+// registers two k-tiles of 16 ahead (half of the threads fetch A, half B), are cut into their parts there -- once per
+// workgroup: cutting fragments after the read from LDS would do it once per wave that reads them -- and go to LDS as
+// units of 16 bytes, 8 k of one row of one part, which is what a lane feeds a matrix instruction.  In a plane the units of
+// one k group lie row after row (a fragment read is 512 contiguous bytes per half-wave); the second k group starts four
+// units later than a multiple of the rows, so that a write of alternating k groups meets no bank twice.  The cut and
+// its stores are spread over the matrix instructions of the k-tile before; the barrier lies before the last quarter
+// of a k-tile, whose matrix instructions cover the first fragment reads of the next one.
+//
+// Tiles: 256 x 256 on 512 threads (230-245 TFLOP/s; one workgroup and 100 KB of LDS per CU), 128 x 128 (205-210) and 64 x 64
+// (145) on 256 threads: with smaller tiles the cutting, the LDS traffic and the loads per matrix instruction double.
+//
+// Sign.  Inside a bf16 matrix instruction the products of 8 k are aligned to the largest of them and the bits beyond its
+// last place are cut off downwards, whatever the signs: a bias that grows with K (mean error of a sum over its rms value:
+// 2.7e-8 at K = 512, 4.2e-7 at 8192; the fp32 instructions have none) and that whatever adds up many results -- bias
+// gradients over T B rows, a cell state over the steps -- adds up as well.  So a quarter of the k-tiles is multiplied with
+// A negated, the sums change sign, half follows as it is, they change sign again, and the last quarter is negated: the
+// parts' biases cancel to a twentieth (3.9e-10 at K = 512, 2.3e-8 at 8192; two halves would leave a third, because the bias
+// of a part grows with the sum that it adds to).  It costs under 1 % of the time.  Below 8 k-tiles the bias is left in:
+// 6e-9 against an error of 1.1e-7.
+//
+// Operand modes: unit stride along K with 16-byte aligned rows, unit stride along the rows in pairs (8-byte aligned, an
+// even number of rows), anything else element by element.  K past a multiple of 16 is a last k-tile of its own with
+// guarded loads; rows past the edge repeat the last ones and reach only outputs that are not stored.
+//
+// A sum with an infinite or NaN operand, or one above bf16's largest value, comes out non-finite here whatever its true
+// value (split3.h): a wave that finds a non-finite sum works its tiles out again with fp32 matrix instructions.
+constexpr int KT3 = 16;
 
-template <int W, int ROWS, int MODE>
-struct DlOperand {
-  static constexpr int TILE = ROWS * KT;           // floats per stage
-  static constexpr int CPW = ROWS / 64;            // 1 KB chunks per wave and tile (4 waves)
-  static constexpr bool kInterleaved = MODE == LM_RCONTIG && W == 2;
-  const char* sb;                                   // scalar: address of the next tile to request
-  long step;                                        // bytes between k-tiles
-  unsigned voff[CPW];                               // per-lane byte offset inside the tile, per chunk
-  int rd[W][2];                                     // per-lane LDS float offset inside a stage (K mode: per blk)
+struct Gemm3Args {
+  GemmProblem p[kMaxGemmGroup];
+  int tile_start[kMaxGemmGroup + 1];
+  int nprob;
+  int n_full;   // tiles [0, n_full) are computed whole; every one after that as `slices` items, one slice of K each
+  int slices;
+  float* part;  // partial tiles: [tile - n_full][slice][TM][TN]
+};
 
-  __device__ void init(const float* base, long s_r, long s_k, int r0, int R, int wave, int lane, int w0) {
-    if (MODE == LM_KCONTIG) {
-      sb = reinterpret_cast<const char*>(base);
-      step = (long)KT * 4;
-#pragma unroll
-      for (int j = 0; j < CPW; ++j) {
-        const int row = 16 * (wave * CPW + j) + (lane >> 2), p = lane & 3;
-        const int kq = p ^ ((row >> 1) & 3);
-        const int ra = min(r0 + row, R - 1);
-        voff[j] = (unsigned)(((long)ra * s_r + 4 * kq) * 4);
-      }
-#pragma unroll
-      for (int i = 0; i < W; ++i) {
-        const int r = w0 + 32 * i + (lane & 31), h = lane >> 5;
-#pragma unroll
-        for (int blk = 0; blk < 2; ++blk) rd[i][blk] = r * KT + 4 * ((2 * blk + h) ^ ((r >> 1) & 3));
-      }
+template <int ROWS, int UPT>
+struct Loader3 {
+  static constexpr int HALF = ROWS * 2 / UPT;  // threads that fetch this operand
+  static constexpr int KGS = ROWS + 4;         // units from one k group to the next
+  const char* sb;        // scalar: the k-tile to fetch next
+  long step, krow;       // scalar: bytes from k-tile to k-tile, from k to k
+  unsigned off[UPT];     // per lane: byte offset of a unit inside the k-tile
+  int unit[UPT];         // per lane: its place in a plane
+
+  static __device__ __forceinline__ void place(int h, int v, bool rowwise, int& row, int& kg) {
+    if (rowwise) {
+      row = UPT * (h % (ROWS / UPT)) + v;
+      kg = h / (ROWS / UPT);
     } else {
-      sb = reinterpret_cast<const char*>(base);
-      step = (long)KT * s_k * 4;
-      constexpr int KPC = 256 / ROWS;  // k-rows per chunk
-#pragma unroll
-      for (int j = 0; j < CPW; ++j) {
-        const int k = (wave * CPW + j) * KPC + (4 * lane) / ROWS, row = (4 * lane) % ROWS;
-        const int ra = min(r0 + row, R - 4);
-        voff[j] = (unsigned)(((long)k * s_k + ra) * 4);
-      }
-      // Two tiles per wave: the tiles take every other row of the wave's 64 (tile i: rows 2 r + i), so that a lane's
-      // values for both tiles lie side by side in LDS and come with one 8-byte read (kInterleaved; the epilogue maps
-      // the rows back).
-#pragma unroll
-      for (int i = 0; i < W; ++i)
-        rd[i][0] = rd[i][1] = (4 * (lane >> 5)) * ROWS + w0 + (kInterleaved ? 2 * (lane & 31) + i : 32 * i + (lane & 31));
+      const int u = h + v * HALF;
+      row = u >> 1;
+      kg = u & 1;
     }
   }
-
-  // request the next tile into stage `st` of this operand's LDS area; `more`: a further tile exists.
-  // Written as inline assembly on purpose: through the compiler's builtin every later LDS read is
-  // made to wait for all outstanding requests (it cannot tell the stages apart), which would undo
-  // the prefetch.  M0 carries the wave's LDS destination; nothing else in this kernel uses M0.  The
-  // caller orders the requests against the reads with its own waits.
-  __device__ __forceinline__ void request(float* lds, int st, int wave, bool more) {
+  // rows r0 .. of an operand of R rows, k from k0 on
+  template <int MODE>
+  __device__ __forceinline__ void init(const float* b, long s_r, long s_k, int r0, int R, int k0, int h) {
+    const bool rowwise = MODE == LM_RCONTIG || (MODE == LM_SCALAR && s_r == 1);
+    sb = reinterpret_cast<const char*>(b + (long)r0 * s_r + (long)k0 * s_k);
+    krow = 4 * s_k;
+    step = KT3 * krow;
 #pragma unroll
-    for (int j = 0; j < CPW; ++j) {
-      const unsigned dst = (unsigned)(size_t)(__attribute__((address_space(3))) void*)(lds + st * TILE + (wave * CPW + j) * 256);
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(voff[j]), "s"(sb) : "memory");
+    for (int v = 0; v < UPT; ++v) {
+      int row, kg;
+      place(h, v, rowwise, row, kg);
+      unit[v] = kg * KGS + row;
+      const int rc = MODE == LM_RCONTIG && UPT == 2 ? min(row - v, R - 2 - r0) + v : min(row, R - 1 - r0);
+      off[v] = (unsigned)(((long)rc * s_r + 8L * kg * s_k) * 4);
+    }
+  }
+  // the next k-tile; `more`: there is one after it (otherwise the same one is fetched again, and never multiplied)
+  template <int MODE>
+  __device__ __forceinline__ void load(float (&x)[UPT][8], bool more) {
+    if (MODE == LM_KCONTIG) {
+#pragma unroll
+      for (int v = 0; v < UPT; ++v) {
+        const floatx4 a = *reinterpret_cast<const floatx4*>(sb + off[v]), b = *reinterpret_cast<const floatx4*>(sb + off[v] + 16);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          x[v][j] = a[j];
+          x[v][4 + j] = b[j];
+        }
+      }
+    } else if (MODE == LM_RCONTIG && UPT == 2) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const floatx2 a = *reinterpret_cast<const floatx2*>(sb + j * krow + off[0]);
+        x[0][j] = a[0];
+        x[UPT - 1][j] = a[1];
+      }
+    } else {
+#pragma unroll
+      for (int v = 0; v < UPT; ++v)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[v][j] = *reinterpret_cast<const float*>(sb + j * krow + off[v]);
     }
     sb += more ? step : 0;
   }
-
-  // operand fragments of block blk (4 MFMA steps) of the tile in the stage at float offset `so`;
-  // part q of 4 (so that the reads can be spread over four steps)
-  __device__ __forceinline__ void fetch(float (&f)[W][4], const float* lds, int so, int blk, int q) const {
-    if (MODE == LM_KCONTIG) {
-#pragma unroll
-      for (int i = 0; i < W; ++i)
-        if ((i & 3) == q) {
-          const floatx4 x = *reinterpret_cast<const floatx4*>(lds + so + rd[i][blk]);
-          f[i][0] = x[0]; f[i][1] = x[1]; f[i][2] = x[2]; f[i][3] = x[3];
-        }
-    } else if (kInterleaved) {
-      const floatx2 x = *reinterpret_cast<const floatx2*>(lds + so + rd[0][0] + (8 * blk + q) * ROWS);
-      f[0][q] = x[0];
-      f[W - 1][q] = x[1];
-    } else {
-#pragma unroll
-      for (int i = 0; i < W; ++i) f[i][q] = lds[so + rd[i][0] + (8 * blk + q) * ROWS];
-    }
-  }
-  // row (or column) of the output that element rho of the wave's tile i stands for, relative to the wave's first
-  static __device__ __forceinline__ int out_index(int i, int rho) { return kInterleaved ? 2 * rho + i : 32 * i + rho; }
 };
 
-template <int WM, int WN, int MA, int MB>
-__global__ __launch_bounds__(256) void gemm_dl_kernel(const GemmGroupArgs g) {
-  constexpr int MT = 64 * WM, NT = 64 * WN;
-  using OA = DlOperand<WM, MT, MA>;
-  using OB = DlOperand<WN, NT, MB>;
-  __shared__ __attribute__((aligned(16))) float As[DL_STAGES * OA::TILE];
-  __shared__ __attribute__((aligned(16))) float Bs[DL_STAGES * OB::TILE];
+// A barrier that orders LDS only: the loads of later k-tiles stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
 
+template <int NWM, int NWN, int WM, int WN, int MA, int MB>
+__global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_split3_kernel(const Gemm3Args g) {
+  constexpr int NT = 64 * NWM * NWN, TM = 32 * NWM * WM, TN = 32 * NWN * WN, HALF = NT / 2, UPT = TM * 2 / HALF;
+  static_assert(TM == TN && TM * 2 == UPT * HALF, "half of the threads fetch A, half B");
+  using L3 = Loader3<TM, UPT>;
+  constexpr int PL = 2 * L3::KGS;     // units per plane
+  __shared__ uintx4 S[2][2][3 * PL];  // [stage][operand][part, k group, row]
+
+  // item -> tile and slice of K.  Workgroups are dealt round-robin to the 8 XCDs, each with its own L2: an XCD gets a
+  // contiguous run of the whole tiles, which share operand panels, and after those a contiguous run of the slices.
+  int bid = blockIdx.x, lo = 0, n = g.n_full;
+  if (bid >= n) {
+    lo = n;
+    n = (int)gridDim.x - n;
+    bid -= lo;
+  }
+  if ((n & 7) == 0 && (lo & 7) == 0) bid = (bid & 7) * (n >> 3) + (bid >> 3);
+  int tile = lo + bid, sl = 0;
+  float* part = nullptr;
+  if (lo || !g.n_full) {
+    if (g.slices > 1) {
+      tile = g.n_full + bid / g.slices;
+      sl = bid % g.slices;
+      part = g.part + (size_t)bid * TM * TN;
+    }
+  }
   int pi = 0;
-  const int bid = tile_index(g);
-  while (pi + 1 < g.nprob && bid >= g.tile_start[pi + 1]) ++pi;
+  while (pi + 1 < g.nprob && tile >= g.tile_start[pi + 1]) ++pi;
   const GemmProblem& P = g.p[pi];
-  const int local = bid - g.tile_start[pi];
-  const int tiles_n = (P.N + NT - 1) / NT;
-  const int m0 = (local / tiles_n) * MT, n0 = (local % tiles_n) * NT;
+  const int local = tile - g.tile_start[pi], tiles_n = (P.N + TN - 1) / TN;
+  const int m0 = (local / tiles_n) * TM, n0 = (local % tiles_n) * TN;
+  int kt0 = 0, nk = P.K / KT3, kend = P.K;
+  if (part) {
+    const int all = nk;
+    kt0 = (int)((long)all * sl / g.slices);
+    nk = (int)((long)all * (sl + 1) / g.slices) - kt0;
+    if (sl + 1 < g.slices) kend = (kt0 + nk) * KT3;
+  }
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 1, wn = wave & 1;
-
+  const int wm = wave / NWN, wn = wave % NWN;
+  const bool isB = wave >= NWM * NWN / 2;
+  const int h = tid & (HALF - 1);
+  L3 ld;
+  // (no branch around the loads where both operands have the same mode)
+  if constexpr (MA == MB) {
+    ld.template init<MA>(isB ? P.B : P.A, isB ? P.sBn : P.sAm, isB ? P.sBk : P.sAk, isB ? n0 : m0, isB ? P.N : P.M, kt0 * KT3, h);
+  } else {
+    if (!isB) ld.template init<MA>(P.A, P.sAm, P.sAk, m0, P.M, kt0 * KT3, h);
+    else ld.template init<MB>(P.B, P.sBn, P.sBk, n0, P.N, kt0 * KT3, h);
+  }
   floatx16 acc[WM][WN];
 #pragma unroll
   for (int i = 0; i < WM; ++i)
@@ -393,181 +435,258 @@ __global__ __launch_bounds__(256) void gemm_dl_kernel(const GemmGroupArgs g) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  OA oa;
-  OB ob;
-  oa.init(P.A, P.sAm, P.sAk, m0, P.M, wave, lane, wm * 32 * WM);
-  ob.init(P.B, P.sBn, P.sBk, n0, P.N, wave, lane, wn * 32 * WN);
-  const int nk = P.K / KT;
-  constexpr int NG = OA::CPW + OB::CPW;  // requests per wave and tile
-  // s_waitcnt with only the vector-memory counter set: at most NG requests (the newest tile) outstanding
-  constexpr int WAIT_NEWEST = (NG & 15) | ((NG >> 4) << 14) | (7 << 4) | (15 << 8);
-  constexpr int WAIT_ALL = (7 << 4) | (15 << 8);
-
-  // tiles 0 and 1 (a tile index past the end re-reads the last tile; it is never multiplied)
-  oa.request(As, 0, wave, 1 < nk);
-  ob.request(Bs, 0, wave, 1 < nk);
-  oa.request(As, 1, wave, 2 < nk);
-  ob.request(Bs, 1, wave, 2 < nk);
-  __builtin_amdgcn_s_waitcnt(WAIT_NEWEST);
-  __syncthreads();
-  float fa[2][WM][4], fb[2][WN][4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    oa.fetch(fa[0], As, 0, 0, q);
-    ob.fetch(fb[0], Bs, 0, 0, q);
-  }
-  int st = 0;  // stage of the tile being multiplied
-  for (int kt = 0; kt < nk; ++kt) {
-    const int st1 = st == DL_STAGES - 1 ? 0 : st + 1;   // stage of tile kt + 1
-    const int st2 = st1 == DL_STAGES - 1 ? 0 : st1 + 1; // stage of tile kt + 2 (last read for tile kt - 1)
-    oa.request(As, st2, wave, kt + 3 < nk);
-    ob.request(Bs, st2, wave, kt + 3 < nk);
-    // block 0 of this tile; the fragments of block 1 are fetched between its steps
-#pragma unroll
-    for (int s4 = 0; s4 < 4; ++s4) {
-      oa.fetch(fa[1], As, st * OA::TILE, 1, s4);
-      ob.fetch(fb[1], Bs, st * OB::TILE, 1, s4);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int i = 0; i < WM; ++i)
-#pragma unroll
-        for (int j = 0; j < WN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[0][i][s4], fb[0][j][s4], acc[i][j], 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    // tile kt + 1 has landed (this wave's share; the barrier collects the others') and every wave has
-    // fetched its last fragments of tile kt
-    __builtin_amdgcn_s_waitcnt(WAIT_NEWEST);
-    __syncthreads();
-    // block 1; the fragments of block 0 of the next tile are fetched between its steps
-#pragma unroll
-    for (int s4 = 0; s4 < 4; ++s4) {
-      oa.fetch(fa[0], As, st1 * OA::TILE, 0, s4);
-      ob.fetch(fb[0], Bs, st1 * OB::TILE, 0, s4);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int i = 0; i < WM; ++i)
-#pragma unroll
-        for (int j = 0; j < WN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[1][i][s4], fb[1][j][s4], acc[i][j], 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    st = st1;
-  }
-  __builtin_amdgcn_s_waitcnt(WAIT_ALL);  // no request may still be writing LDS when the workgroup ends
-
-  // (only the instance that the launcher exchanges roles into carries the transposing epilogue: in the others its
-  // registers would cost the kernel a resident workgroup per CU)
-  if (MA == LM_RCONTIG && MB == LM_KCONTIG && P.ct) {
-    // element (r, c) -> C[c * ldc + r].  With the rows of the wave's two tiles interleaved a lane holds, for each of
-    // its columns and each group of four accumulator registers, eight consecutive rows: 32 contiguous bytes of C.
-    if constexpr (OA::kInterleaved) {
-      const bool vec_ok = (P.ldc & 3) == 0 && (reinterpret_cast<uintptr_t>(P.C) & 15u) == 0;
-#pragma unroll
-      for (int j = 0; j < WN; ++j) {
-        const int c = n0 + wn * 32 * WN + OB::out_index(j, lane & 31);
-#pragma unroll
-        for (int gq = 0; gq < 4; ++gq) {
-          const int r0 = m0 + wm * 64 + 2 * (8 * gq + 4 * (lane >> 5));
-          if (c < P.N && r0 < P.M) {
-            float* dst = P.C + (long)c * P.ldc + r0;
-            if (vec_ok && r0 + 7 < P.M) {
-              floatx4 v0 = {acc[0][j][4 * gq], acc[1][j][4 * gq], acc[0][j][4 * gq + 1], acc[1][j][4 * gq + 1]};
-              floatx4 v1 = {acc[0][j][4 * gq + 2], acc[1][j][4 * gq + 2], acc[0][j][4 * gq + 3], acc[1][j][4 * gq + 3]};
-              if (P.accumulate) {
-                v0 += *reinterpret_cast<const floatx4*>(dst);
-                v1 += *reinterpret_cast<const floatx4*>(dst + 4);
-              }
-              *reinterpret_cast<floatx4*>(dst) = v0;
-              *reinterpret_cast<floatx4*>(dst + 4) = v1;
-            } else {
-#pragma unroll
-              for (int e = 0; e < 8; ++e)
-                if (r0 + e < P.M) {
-                  const float v = acc[e & 1][j][4 * gq + (e >> 1)];
-                  dst[e] = P.accumulate ? dst[e] + v : v;
-                }
-            }
-          }
-        }
-      }
+  float x[2][UPT][8];  // fetched, not yet cut: k-tiles of even and of odd index
+  int fetched = 0;
+  auto load = [&](float (&xx)[UPT][8]) {
+    const bool more = ++fetched < nk;
+    if constexpr (MA == MB) {
+      ld.template load<MA>(xx, more);
     } else {
-#pragma unroll
-      for (int i = 0; i < WM; ++i)
-#pragma unroll
-        for (int j = 0; j < WN; ++j) {
-          const int col = n0 + wn * 32 * WN + OB::out_index(j, lane & 31);
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int row = m0 + wm * 32 * WM + OA::out_index(i, 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3));
-            if (row < P.M && col < P.N) {
-              float* c = P.C + (long)col * P.ldc + row;
-              *c = P.accumulate ? (*c + acc[i][j][r]) : acc[i][j][r];
-            }
-          }
-        }
+      if (!isB) ld.template load<MA>(xx, more);
+      else ld.template load<MB>(xx, more);
     }
-    return;
-  }
-  if constexpr (OB::kInterleaved) {
-    // a lane holds two neighbouring columns (2 c, 2 c + 1: tiles 0 and 1): one 8-byte store per row where C allows it
-    const bool pair_ok = (P.ldc & 1) == 0 && (reinterpret_cast<uintptr_t>(P.C) & 7u) == 0;
-    const int col = n0 + wn * 64 + 2 * (lane & 31);
+  };
+  uintx4 o[3];
+  // pair p of the thread's 4 UPT: cut, with the sign bits of `sign` flipped; a unit's last pair sends it to LDS
+  auto cut = [&](const float (&xx)[UPT][8], int st, int p, unsigned sign) {
+    const int v = p / 4, j = p % 4;
+    auto signed_ = [&](float f) { return __builtin_bit_cast(float, __builtin_bit_cast(unsigned, f) ^ sign); };
+    const Split2 s = split3(signed_(xx[v][2 * j]), signed_(xx[v][2 * j + 1]));
+    o[0][j] = s.h;
+    o[1][j] = s.m;
+    o[2][j] = s.l;
+    if (j == 3) {
+      uintx4* const d = &S[st][isB][ld.unit[v]];
+#pragma unroll
+      for (int q = 0; q < 3; ++q) d[q * PL] = o[q];
+    }
+  };
+  const int ra = (lane >> 5) * L3::KGS + wm * 32 * WM + (lane & 31), rb = (lane >> 5) * L3::KGS + wn * 32 * WN + (lane & 31);
+  bf16x8 fa[2][3], fb[2][WN][3];
+  auto readA = [&](bf16x8 (&f)[3], int st, int i) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) f[q] = __builtin_bit_cast(bf16x8, S[st][0][q * PL + ra + 32 * i]);
+  };
+  auto readB = [&](bf16x8 (&f)[3], int st, int j) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) f[q] = __builtin_bit_cast(bf16x8, S[st][1][q * PL + rb + 32 * j]);
+  };
+  constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};  // the six products, smallest first
+  constexpr int NP = 4 * UPT;
+  // k-tiles in pairs: a quarter with A negated, half as it is, a quarter negated (see above), the sums negated in between
+  const int end2 = nk & ~1, end0 = nk / 8 * 2, end1 = end2 - end0;
+  const unsigned negative = isB ? 0u : 0x80000000u;
+  int cutting = 0;
+  auto next_sign = [&]() {  // of the k-tile that is cut next
+    const int c = cutting++;
+    return (c < end0 || (c >= end1 && c < end2)) ? negative : 0u;
+  };
+  auto negate = [&]() {
 #pragma unroll
     for (int i = 0; i < WM; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = m0 + wm * 32 * WM + OA::out_index(i, 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3));
-        if (row < P.M && col < P.N) {
-          float* c = P.C + (long)row * P.ldc + col;
-          if (pair_ok && col + 1 < P.N) {
-            floatx2 v = {acc[i][0][r], acc[i][1][r]};
-            if (P.accumulate) v += *reinterpret_cast<const floatx2*>(c);
-            *reinterpret_cast<floatx2*>(c) = v;
-          } else {
-            c[0] = P.accumulate ? (c[0] + acc[i][0][r]) : acc[i][0][r];
-            if (col + 1 < P.N) c[1] = P.accumulate ? (c[1] + acc[i][1][r]) : acc[i][1][r];
-          }
-        }
+      for (int j = 0; j < WN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = -acc[i][j][r];
+  };
+  // One k-tile from stage PAR, in 2 WM steps of 3 WN matrix instructions; FA: which of fa holds row tile 0.
+  auto ktile = [&](auto par, auto fpar) {
+    constexpr int PAR = decltype(par)::value, FA = decltype(fpar)::value;
+    constexpr int NS = 2 * WM, NBF = NS - (WM >= 4 ? 2 : 1);  // steps, those before the barrier
+    const unsigned sign = next_sign();
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const int i = s / 2;
+      if (s % 2 == 0 && i + 1 < WM) readA(fa[(FA + i + 1) & 1], PAR, i + 1);
+      if (s < NBF) {
+#pragma unroll
+        for (int p = s * NP / NBF; p < (s + 1) * NP / NBF; ++p) cut(x[PAR ^ 1], PAR ^ 1, p, sign);
+        if (s == NBF - 1) load(x[PAR ^ 1]);
+      } else if (s == NBF) {
+#pragma unroll
+        for (int j = 0; j < WN; ++j) readB(fb[PAR ^ 1][j], PAR ^ 1, j);
       }
-    return;
+      if (s == NS - 1) readA(fa[(FA + WM) & 1], PAR ^ 1, 0);
+#pragma unroll
+      for (int z = 3 * (s % 2); z < 3 * (s % 2) + 3; ++z)
+#pragma unroll
+        for (int j = 0; j < WN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[(FA + i) & 1][PA[z]], fb[PAR][j][PB[z]], acc[i][j], 0, 0, 0);
+      // one matrix instruction, then a few of the others, and so on (all of them in front: 3 % slower)
+#pragma unroll
+      for (int e = 0; e < 3 * WN; ++e) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // matrix instruction
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // LDS read
+        __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);  // vector ALU
+        __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);  // LDS write
+        __builtin_amdgcn_sched_group_barrier(0x020, 2, 0);  // load
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if (s == NBF - 1) lds_barrier();
+    }
+  };
+  if (nk > 0) {
+    load(x[0]);
+    load(x[1]);
+    const unsigned sign = next_sign();
+#pragma unroll
+    for (int p = 0; p < NP; ++p) cut(x[0], 0, p, sign);
+    load(x[0]);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < WN; ++j) readB(fb[0][j], 0, j);
+    readA(fa[0], 0, 0);
+    int kt = 0;
+    for (; kt + 1 < nk; kt += 2) {
+      if (kt == end0 || kt == end1) negate();
+      ktile(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
+      ktile(std::integral_constant<int, 1>{}, std::integral_constant<int, WM & 1>{});
+    }
+    if (end0) negate();  // (after an even number of changes and a negated quarter)
+    if (kt < nk) ktile(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
   }
+  // the k left over, fewer than 16: one more k-tile, guarded and waited for
+  if ((kt0 + nk) * KT3 < kend) {
+    const int k0 = (kt0 + nk) * KT3;
+    __syncthreads();
+    const float* const b = isB ? P.B : P.A;
+    const long s_r = isB ? P.sBn : P.sAm, s_k = isB ? P.sBk : P.sAk;
+    const int r0 = isB ? n0 : m0, R = isB ? P.N : P.M;
+#pragma unroll
+    for (int v = 0; v < UPT; ++v) {
+      // (ld.unit[v] says which row and k group the thread's unit is)
+      const int kg = ld.unit[v] >= L3::KGS ? 1 : 0, row = min(r0 + ld.unit[v] - kg * L3::KGS, R - 1);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int k = k0 + 8 * kg + j;
+        x[0][v][j] = k < kend ? b[(long)row * s_r + (long)k * s_k] : 0.f;
+      }
+    }
+#pragma unroll
+    for (int p = 0; p < NP; ++p) cut(x[0], 0, p, 0u);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < WN; ++j) readB(fb[0][j], 0, j);
+#pragma unroll
+    for (int i = 0; i < WM; ++i) {
+      readA(fa[0], 0, i);
+#pragma unroll
+      for (int z = 0; z < 6; ++z)
+#pragma unroll
+        for (int j = 0; j < WN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[0][PA[z]], fb[0][j][PB[z]], acc[i][j], 0, 0, 0);
+    }
+  }
+
+  // any sum infinite or NaN: the wave's tiles again in fp32 (the only loads of that loop are its own: no barrier)
+  {
+    float z = 0.f;
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+      for (int j = 0; j < WN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) z += acc[i][j][r] * 0.f;
+    if (__any(z != 0.f)) {
+      const float *pa[WM], *pb[WN];
+#pragma unroll
+      for (int i = 0; i < WM; ++i) pa[i] = P.A + (long)min(m0 + 32 * (wm * WM + i) + (lane & 31), P.M - 1) * P.sAm;
+#pragma unroll
+      for (int j = 0; j < WN; ++j) pb[j] = P.B + (long)min(n0 + 32 * (wn * WN + j) + (lane & 31), P.N - 1) * P.sBn;
+#pragma unroll
+      for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int j = 0; j < WN; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+      for (int k = kt0 * KT3; k < kend; k += 2) {
+        const int kk = k + (lane >> 5);
+        const bool in = kk < kend;
+        const long ka = (in ? kk : k) * P.sAk, kb = (in ? kk : k) * P.sBk;
+        float va[WM], vb[WN];
+#pragma unroll
+        for (int i = 0; i < WM; ++i) va[i] = in ? pa[i][ka] : 0.f;
+#pragma unroll
+        for (int j = 0; j < WN; ++j) vb[j] = in ? pb[j][kb] : 0.f;
+#pragma unroll
+        for (int i = 0; i < WM; ++i)
+#pragma unroll
+          for (int j = 0; j < WN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[i], vb[j], acc[i][j], 0, 0, 0);
+      }
+    }
+  }
+
+  // register r of a lane holds row 8 (r/4) + 4 (lane/32) + r%4, column lane%32 of a 32x32 tile
 #pragma unroll
   for (int i = 0; i < WM; ++i)
 #pragma unroll
     for (int j = 0; j < WN; ++j) {
-      const int col = n0 + wn * 32 * WN + OB::out_index(j, lane & 31);
+      const int col = 32 * (wn * WN + j) + (lane & 31);
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int row = m0 + wm * 32 * WM + OA::out_index(i, 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3));
-        if (row < P.M && col < P.N) {
-          float* c = P.C + (long)row * P.ldc + col;
-          *c = P.accumulate ? (*c + acc[i][j][r]) : acc[i][j][r];
+        const int row = 32 * (wm * WM + i) + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+        const float sum = acc[i][j][r];
+        if (part) {
+          part[row * TN + col] = sum;
+        } else if (m0 + row < P.M && n0 + col < P.N) {
+          float* const c = P.C + (long)(m0 + row) * P.ldc + n0 + col;
+          *c = P.accumulate ? (*c + sum) : sum;
         }
       }
     }
 }
 
-template <int WM, int WN>
-bool launch_tile_dl(int ma, int mb, int grid, const GemmGroupArgs& g, hipStream_t s) {
-#define LSTM_GEMM_CASE(A_, B_)                                                                      \
-  if (ma == A_ && mb == B_) {                                                                       \
-    hipLaunchKernelGGL((gemm_dl_kernel<WM, WN, A_, B_>), dim3(grid), dim3(256), 0, s, g);           \
-    return true;                                                                                    \
+// The sliced tiles: C = (accumulate ? C : 0) + the slices in ascending order.  One workgroup per 16 rows of a tile.
+template <int TILE>
+__global__ __launch_bounds__(256) void gemm_slices_kernel(const Gemm3Args g) {
+  constexpr int PER = TILE / 16;
+  const int t = blockIdx.x / PER, r16 = blockIdx.x % PER, tile = g.n_full + t;
+  int pi = 0;
+  while (pi + 1 < g.nprob && tile >= g.tile_start[pi + 1]) ++pi;
+  const GemmProblem& P = g.p[pi];
+  const int local = tile - g.tile_start[pi], tiles_n = (P.N + TILE - 1) / TILE;
+  const int m0 = (local / tiles_n) * TILE, n0 = (local % tiles_n) * TILE;
+  const float* const base = g.part + (size_t)t * g.slices * TILE * TILE;
+#pragma unroll
+  for (int e = threadIdx.x; e < 16 * TILE / 4; e += 256) {
+    const int row = 16 * r16 + e / (TILE / 4), col = 4 * (e % (TILE / 4));
+    if (m0 + row >= P.M || n0 + col >= P.N) continue;
+    floatx4 v = *reinterpret_cast<const floatx4*>(base + row * TILE + col);
+    for (int s = 1; s < g.slices; ++s) v += *reinterpret_cast<const floatx4*>(base + ((size_t)s * TILE + row) * TILE + col);
+    float* const c = P.C + (long)(m0 + row) * P.ldc + n0 + col;
+    if (n0 + col + 3 < P.N && (P.ldc & 3) == 0 && (reinterpret_cast<uintptr_t>(P.C) & 15u) == 0) {
+      if (P.accumulate) v += *reinterpret_cast<const floatx4*>(c);
+      *reinterpret_cast<floatx4*>(c) = v;
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (n0 + col + j < P.N) c[j] = P.accumulate ? c[j] + v[j] : v[j];
+    }
+  }
+}
+
+template <int NWM, int NWN, int WM, int WN>
+void launch_split3(int ma, int mb, int grid, const Gemm3Args& g, hipStream_t s) {
+  constexpr int NT = 64 * NWM * NWN;
+#define LSTM_GEMM_CASE(A_, B_)                                                                                \
+  if (ma == A_ && mb == B_) {                                                                                 \
+    hipLaunchKernelGGL((gemm_split3_kernel<NWM, NWN, WM, WN, A_, B_>), dim3(grid), dim3(NT), 0, s, g);        \
+    return;                                                                                                   \
   }
   LSTM_GEMM_CASE(LM_KCONTIG, LM_KCONTIG)
   LSTM_GEMM_CASE(LM_KCONTIG, LM_RCONTIG)
   LSTM_GEMM_CASE(LM_RCONTIG, LM_RCONTIG)
   LSTM_GEMM_CASE(LM_RCONTIG, LM_KCONTIG)
 #undef LSTM_GEMM_CASE
-  return false;
+  if constexpr (NT == 256) hipLaunchKernelGGL((gemm_split3_kernel<NWM, NWN, WM, WN, LM_SCALAR, LM_SCALAR>), dim3(grid), dim3(NT), 0, s, g);
 }
 
-// Whether the direct-to-LDS kernel can run one operand of a problem.
-bool dl_operand_ok(int mode, long s_r, long s_k, int R, int K) {
-  if (mode == LM_KCONTIG) return R >= 1 && ((long)R * s_r + K) * 4 < (1L << 31);
-  if (mode == LM_RCONTIG) return R >= 4 && ((long)KT * s_k + R) * 4 < (1L << 31);
-  return false;
+// Load mode of one operand of gemm_split3_kernel.
+int split3_mode(const float* base, long s_r, long s_k, int R) {
+  const uintptr_t a = reinterpret_cast<uintptr_t>(base);
+  if (s_k == 1 && (a & 15u) == 0 && (s_r % 4) == 0) return LM_KCONTIG;
+  if (s_r == 1 && (a & 7u) == 0 && (s_k % 2) == 0 && (R % 2) == 0) return LM_RCONTIG;
+  return LM_SCALAR;
 }
 
 template <int WM, int WN>
@@ -587,189 +706,142 @@ void launch_tile(int ma, int mb, int grid, const GemmGroupArgs& g, hipStream_t s
 
 }  // namespace
 
-// LSTM_GEMM_STAGED=1 keeps every product on the register-staged kernel (for comparison and tests).
-static bool gemm_force_staged() { return knobs().gemm_staged; }
-
 namespace {
-hipError_t launch_group(const GemmProblem* probs, int nprob, int main_probs, bool split, hipStream_t stream);
 
-// C[r][c] = (accumulate ? C[r][c] : 0) + sum over s of part[s][r][c], s ascending
-__global__ void split_reduce_kernel(float* __restrict__ C, long ldc, const float* __restrict__ part, int rows, int cols, int S,
-                                    int accumulate) {
-  const long n4 = (long)rows * (cols / 4);
-  for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < n4; e += (long)gridDim.x * blockDim.x) {
-    const int r = (int)(e / (cols / 4)), c = 4 * (int)(e % (cols / 4));
-    float* dst = C + (long)r * ldc + c;
-    floatx4 v = accumulate ? *reinterpret_cast<const floatx4*>(dst) : floatx4{0.f, 0.f, 0.f, 0.f};
-    for (int s2 = 0; s2 < S; ++s2) v += *reinterpret_cast<const floatx4*>(part + ((long)s2 * rows + r) * cols + c);
-    *reinterpret_cast<floatx4*>(dst) = v;
+// How a group is run: the tile, the tiles computed whole, the slices of the rest.
+struct Plan3 {
+  int tile = 0;
+  int n_full = 0, slices = 1, total = 0;
+  double us = 0.0;
+};
+
+// Time of a group on tiles of `tile`, with the tiles of the last partial round (all of them where there is no full
+// round) cut along K into the number of slices that promises most.  Measured per k-tile of 16 with every CU busy:
+// 256 x 256 2.18 us, 128 x 128 0.645, 64 x 64 0.231 per CU (245, 208 and 145 TFLOP/s).  One 64 x 64 workgroup alone on a CU
+// takes 0.36, the latency of its own instructions; a 128 x 128 one 0.62 with both operands' rows side by side, but 1.0 to
+// 1.4 with rows as far apart as an operand with unit stride along K has them (two on a CU: 0.75 each): 16 k of 128 rows
+// are 128 requests to as many places, and two k-tiles ahead is not far enough.  Every item costs a few us more (first
+// loads, last stores); a slice writes its tile and has it read again, at about 4 TB/s, and the addition is a launch of
+// 4 us.
+Plan3 plan_split3(const GemmProblem* p, int nprob, int tile, bool apart, size_t part_bytes, int cus) {
+  Plan3 best;
+  best.tile = tile;
+  long nkmax = 0, total = 0;
+  for (int i = 0; i < nprob; ++i) {
+    total += (long)((p[i].M + tile - 1) / tile) * ((p[i].N + tile - 1) / tile);
+    nkmax = std::max<long>(nkmax, (p[i].K + KT3 - 1) / KT3);
   }
+  best.total = (int)total;
+  const double item = tile == 256 ? 12.0 : (tile == 128 ? 5.0 : 3.0);
+  auto cost = [&](long items, double nk) {  // `items` of nk k-tiles each over the chip
+    if (items <= 0) return 0.0;
+    const long deep = (items + cus - 1) / cus;
+    const double per = tile == 256 ? 2.18
+                     : tile == 64  ? (deep == 1 ? 0.36 : 0.231)
+                                   : (deep == 1 ? (apart ? 1.2 : 0.62) : (deep == 2 && apart ? 0.75 : 0.645));
+    return deep * (nk * per + (tile == 256 || deep == 1 ? item : 0.5 * item));
+  };
+  best.n_full = (int)total;
+  best.us = cost(total, (double)nkmax);
+  const long tail = total % cus, full = total - tail;
+  if (tail == 0 || part_bytes == 0) return best;
+  const double bytes_per = (double)tile * tile * sizeof(float);
+  double cut[17];
+  int most = 1, fastest = 0;
+  for (int s = 2; s <= 16; ++s) {
+    if (nkmax / s < 8 || (double)tail * s * bytes_per > (double)part_bytes) break;
+    cut[s] = cost(full, (double)nkmax) + cost(tail * s, (double)nkmax / s) + tail * s * bytes_per * 2.0 / 4.0e6 + 4.0;
+    if (cut[s] < 0.97 * best.us && (!fastest || cut[s] < cut[fastest])) fastest = s;
+    most = s;
+  }
+  // (of slice counts within 5 % of the fastest the largest: shorter sums round less)
+  for (int s = most; fastest && s >= fastest; --s)
+    if (cut[s] <= 1.05 * cut[fastest]) {
+      best.us = cut[s];
+      best.n_full = (int)full;
+      best.slices = s;
+      break;
+    }
+  return best;
 }
 
-// Workgroups of the 128 x 128 kernels that the chip holds at once.
-int gemm_resident_workgroups() {
-  static int cached = 0;
-  if (cached) return cached;
-  int per_cu = 0, dev = 0, cus = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)gemm_dl_kernel<2, 2, LM_KCONTIG, LM_KCONTIG>, 256, 0) !=
-          hipSuccess ||
-      per_cu < 1)
-    per_cu = 2;
-  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      cus < 1)
-    cus = 256;
-  cached = per_cu * cus;
-  return cached;
+hipError_t launch_group3(const GemmProblem* probs, int nprob, float* part, size_t part_bytes, hipStream_t stream) {
+  int ma = -1, mb = -1;
+  for (int i = 0; i < nprob; ++i) {
+    const GemmProblem& p = probs[i];
+    const int a = split3_mode(p.A, p.sAm, p.sAk, p.M), b = split3_mode(p.B, p.sBn, p.sBk, p.N);
+    ma = (i == 0 || ma == a) ? a : LM_SCALAR;
+    mb = (i == 0 || mb == b) ? b : LM_SCALAR;
+    // per-lane offsets inside a tile of an operand are 32 bits wide
+    if (std::max(std::max(std::abs(p.sAm), std::abs(p.sAk)), std::max(std::abs(p.sBn), std::abs(p.sBk))) >= (1L << 20)) return hipErrorNotSupported;
+    if (std::min(std::min(p.sAm, p.sAk), std::min(p.sBn, p.sBk)) < 0) return hipErrorNotSupported;
+  }
+  if (ma == LM_SCALAR || mb == LM_SCALAR) ma = mb = LM_SCALAR;
+  if (!part || (reinterpret_cast<uintptr_t>(part) & 15u) != 0 || !knobs().gemm_split) part_bytes = 0;
+  const int cus = std::max(device_cu_count(), 1);
+  Plan3 best;
+  for (int tile = 64; tile <= 256; tile *= 2) {
+    if (tile == 256 && ma == LM_SCALAR) break;  // element-wise loads: 128 x 128 at most
+    const Plan3 q = plan_split3(probs, nprob, tile, ma == LM_KCONTIG || mb == LM_KCONTIG, part_bytes, cus);
+    if (best.tile == 0 || q.us < best.us) best = q;
+  }
+  Gemm3Args g;
+  int start = 0;
+  for (int i = 0; i < nprob; ++i) {
+    g.p[i] = probs[i];
+    g.tile_start[i] = start;
+    start += ((probs[i].M + best.tile - 1) / best.tile) * ((probs[i].N + best.tile - 1) / best.tile);
+  }
+  for (int i = nprob; i <= kMaxGemmGroup; ++i) g.tile_start[i] = start;
+  g.nprob = nprob;
+  g.n_full = best.n_full;
+  g.slices = best.slices;
+  g.part = part;
+  if (start == 0) return hipSuccess;
+  const int tail = start - best.n_full, grid = best.n_full + tail * best.slices;
+  if (best.tile == 256) launch_split3<2, 4, 4, 2>(ma, mb, grid, g, stream);
+  else if (best.tile == 128) launch_split3<2, 2, 2, 2>(ma, mb, grid, g, stream);
+  else launch_split3<2, 2, 1, 1>(ma, mb, grid, g, stream);
+  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  if (best.slices > 1) {
+    const dim3 blocks((unsigned)(tail * (best.tile / 16)));
+    if (best.tile == 256) hipLaunchKernelGGL(gemm_slices_kernel<256>, blocks, dim3(256), 0, stream, g);
+    else if (best.tile == 128) hipLaunchKernelGGL(gemm_slices_kernel<128>, blocks, dim3(256), 0, stream, g);
+    else hipLaunchKernelGGL(gemm_slices_kernel<64>, blocks, dim3(256), 0, stream, g);
+    return hipGetLastError();
+  }
+  return hipSuccess;
 }
+
 }  // namespace
 
-// One product whose 128 x 128 tiles do not fill the chip evenly: fewer tiles than the chip holds workgroups, or a
-// last partial round of tiles (every tile takes the same time, so a round with a few tiles costs as much as a full
-// one: at M = 1600, N = 8192 there are 832 tiles for 768 places, and the last 64 tiles doubled the time).  The
-// tile rows of that last round (or all rows, if there is no full round) are cut along K into S slices, as many as fill
-// the chip once more; the slices write partial tiles to `part`, a small kernel adds them in fixed order.  Whole tiles
-// and slices run in one launch, whole tiles first.  Falls back to the plain launch whenever a condition is not met.
-hipError_t launch_gemm_split(const GemmProblem& p, float* part, size_t part_bytes, hipStream_t stream) {
-  const int tm = (p.M + 127) / 128, tn = (p.N + 127) / 128, tiles = tm * tn, nk = p.K / KT;
-  const bool ok = part && knobs().gemm_split && p.M >= 96 && p.N >= 96 && tiles >= 128 && p.K % KT == 0 && (p.N % 4) == 0 &&
-                  (p.ldc % 4) == 0 && (reinterpret_cast<uintptr_t>(p.C) & 15u) == 0 && (reinterpret_cast<uintptr_t>(part) & 15u) == 0;
-  if (!ok) return launch_gemm_group(&p, 1, stream);
-  const int room = gemm_resident_workgroups();
-  int rows_tail;
-  if (tiles <= room) {
-    rows_tail = tm;
-  } else {
-    const int tail = tiles % room;
-    if (tail == 0) return launch_gemm_group(&p, 1, stream);
-    rows_tail = (tail + tn - 1) / tn;
-  }
-  const int tail_tiles = rows_tail * tn;
-  const int row0 = (tm - rows_tail) * 128, mt = p.M - row0;
-  // Number of slices: the one with the shortest estimated time for the cut rows.  A CU works off the workgroups it
-  // holds at about the same total rate whether it holds two or three (per_cu: what it can hold), and at about two
-  // thirds of it when it holds one; the slices are dealt out in rounds of `room`; every slice more costs a little in
-  // the addition of the partial tiles.  (208 tiles, 768 places: 6 slices; 64 tiles left over: 8.)
-  int cus = 256, dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-    cus = 256;
-  const int per_cu = room / cus > 0 ? room / cus : 1;
-  auto estimate = [&](int S2) {
-    const long items = (long)tail_tiles * S2;
-    const long full = items / room, rem = items % room;
-    const int last = (int)((rem + cus - 1) / cus);
-    const double cost_last = last == 0 ? 0.0 : (last == 1 ? 1.5 : (last == 2 ? 2.2 : (double)last));
-    return ((double)full * per_cu + cost_last) / S2 + 0.01 * (S2 - 1);
-  };
-  int S = 1;
-  double best = estimate(1) * 0.95;  // a cut has to promise at least 5 %
-  for (int S2 = 2; S2 <= 8; ++S2) {
-    if (nk / S2 < 8) break;  // at least eight k-tiles per slice
-    if ((size_t)S2 * mt * p.N * sizeof(float) > part_bytes) break;
-    const double e = estimate(S2);
-    if (e < best) {
-      best = e;
-      S = S2;
-    }
-  }
-  if (S < 2) return launch_gemm_group(&p, 1, stream);
-  GemmProblem g[kMaxGemmGroup];
-  int n = 0;
-  if (row0 > 0) {
-    g[n] = p;
-    g[n].M = row0;
-    ++n;
-  }
-  const int main_probs = n;
-  for (int s2 = 0; s2 < S; ++s2) {
-    const int k0 = (int)((long)nk * s2 / S) * KT, k1 = (int)((long)nk * (s2 + 1) / S) * KT;
-    GemmProblem q = p;
-    q.A = p.A + (long)row0 * p.sAm + (long)k0 * p.sAk;
-    q.B = p.B + (long)k0 * p.sBk;
-    q.C = part + (size_t)s2 * mt * p.N;
-    q.M = mt;
-    q.K = k1 - k0;
-    q.ldc = p.N;
-    q.accumulate = 0;
-    g[n++] = q;
-  }
-  prof_flops(2.0 * p.M * p.N * p.K, "gemm");
-  if (hipError_t e = launch_group(g, n, main_probs, true, stream); e != hipSuccess) return e;
-  const long n4 = (long)mt * (p.N / 4);
-  const unsigned blocks = (unsigned)std::min<long>((n4 + 255) / 256, 2048);
-  hipLaunchKernelGGL(split_reduce_kernel, dim3(blocks), dim3(256), 0, stream, p.C + (long)row0 * p.ldc, p.ldc, part, mt, p.N, S,
-                     p.accumulate);
-  return hipGetLastError();
-}
-
-hipError_t launch_gemm_group(const GemmProblem* probs, int nprob, hipStream_t stream) {
-  return launch_group(probs, nprob, nprob, false, stream);
-}
-
-namespace {
-// split: the group is one product cut up by launch_gemm_split (128 x 128 tiles whatever the parts' heights; its FLOPs
-// are counted there)
-hipError_t launch_group(const GemmProblem* probs, int nprob, int main_probs, bool split, hipStream_t stream) {
+// Independent products in one launch.  `part` (16-byte aligned, part_bytes long, free until the stream has passed the
+// call) may be null: no slices then.  LSTM_GEMM_STAGED=1 keeps every product on the fp32 kernel (for comparison and
+// tests), which also takes strides too long for the other's offsets.
+hipError_t launch_gemm_group(const GemmProblem* probs, int nprob, hipStream_t stream, float* part, size_t part_bytes) {
   if (nprob <= 0) return hipSuccess;
   if (nprob > kMaxGemmGroup) return hipErrorInvalidValue;
+  double fl = 0.0;
+  for (int i = 0; i < nprob; ++i) fl += 2.0 * probs[i].M * probs[i].N * probs[i].K;
+  prof_flops(fl, "gemm");
+  if (!knobs().gemm_staged) {
+    const hipError_t e = launch_group3(probs, nprob, part, part_bytes, stream);
+    if (e != hipErrorNotSupported) return e;
+  }
   GemmGroupArgs g;
   bool big = true;
-  long total_big = 0, total_small = 0;
-  double area = 0.0;
-  // one kernel instance serves the whole group: operands that cannot all take the same vector
-  // loader fall back to the scalar one
+  // one kernel instance serves the whole group: operands that cannot all take the same vector loader fall back to the
+  // scalar one
   int ma = -1, mb = -1;
   for (int i = 0; i < nprob; ++i) {
     g.p[i] = probs[i];
     if (probs[i].M < 96 || probs[i].N < 96) big = false;
-    total_big += (long)((probs[i].M + 127) / 128) * ((probs[i].N + 127) / 128);
-    total_small += (long)((probs[i].M + 63) / 64) * ((probs[i].N + 63) / 64);
-    area += (double)probs[i].M * probs[i].N;
     const int a = pick_mode(probs[i].A, probs[i].sAm, probs[i].sAk, probs[i].M, probs[i].K);
     const int b = pick_mode(probs[i].B, probs[i].sBn, probs[i].sBk, probs[i].N, probs[i].K);
     ma = (i == 0 || ma == a) ? a : LM_SCALAR;
     mb = (i == 0 || mb == b) ? b : LM_SCALAR;
   }
   if (ma == LM_SCALAR || mb == LM_SCALAR) ma = mb = LM_SCALAR;
-  bool dl = ma != LM_SCALAR && !gemm_force_staged();
-  if (!split) {
-    double fl = 0.0;
-    for (int i = 0; i < nprob; ++i) fl += 2.0 * probs[i].M * probs[i].N * probs[i].K;
-    prof_flops(fl, "gemm");
-  }
-  for (int i = 0; i < nprob && dl; ++i)
-    dl = probs[i].K % KT == 0 && probs[i].K >= KT && dl_operand_ok(ma, probs[i].sAm, probs[i].sAk, probs[i].M, probs[i].K) &&
-         dl_operand_ok(mb, probs[i].sBn, probs[i].sBk, probs[i].N, probs[i].K);
-  // 128 x 128 or 64 x 64 tiles: whichever the counts of tiles promise more from.  Measured on 256 CUs (forward
-  // products of one step, K = 2H = 4096 ... 8192): one 128 x 128 workgroup per CU runs at 128 TFLOP/s, two on a CU
-  // take 1.85 times as long as one and three 2.7 times (142 TFLOP/s when every CU has three), so between those counts
-  // the rate follows the fullest CU: 288 tiles 80 TFLOP/s, 384 tiles 105.  The 64 x 64 kernel reaches 116 TFLOP/s from
-  // two tiles per CU on.  Both are scaled by the part of their tiles that the product really covers.
-  if (big && !split) {
-    const double cus = (double)std::max(device_cu_count(), 1);
-    const double nb = (double)total_big / cus, ns = (double)total_small / cus;
-    const double rate_big = nb <= 1.0 ? 128.0 * nb
-                          : (nb <= 2.0 ? 128.0 * nb / 1.85 : (nb <= 3.0 ? 128.0 * nb / 2.7 : 138.0));
-    const double rate_small = 116.0 * std::min(1.0, ns / 2.0);
-    const double use_big = area / ((double)total_big * 128.0 * 128.0), use_small = area / ((double)total_small * 64.0 * 64.0);
-    big = rate_big * use_big >= rate_small * use_small;
-  }
-  if (split) big = true;
-  // The 128 x 128 kernel is slower with a K-contiguous A operand than with a K-contiguous B operand (2048 x 2048 x 8192:
-  // A K- / B row-contiguous 121 TFLOP/s, both K-contiguous 134, A row- / B K-contiguous 142, both row-contiguous 143;
-  // neither the order of the tiles, of the waves, of the requests nor of the matrix instructions changes that).  A
-  // product with A K-contiguous and B row-contiguous is therefore computed as its transpose, B^T A^T, whose
-  // elements the epilogue writes to where C expects them.
-  if (dl && big && ma == LM_KCONTIG && mb == LM_RCONTIG && knobs().gemm_swap) {
-    for (int i = 0; i < nprob; ++i) {
-      GemmProblem& q = g.p[i];
-      std::swap(q.A, q.B);
-      std::swap(q.M, q.N);
-      std::swap(q.sAm, q.sBn);
-      std::swap(q.sAk, q.sBk);
-      q.ct = !q.ct;
-    }
-    std::swap(ma, mb);
-  }
   const int mt = big ? 128 : 64;
   int start = 0;
   for (int i = 0; i < nprob; ++i) {
@@ -778,20 +850,10 @@ hipError_t launch_group(const GemmProblem* probs, int nprob, int main_probs, boo
   }
   for (int i = nprob; i <= kMaxGemmGroup; ++i) g.tile_start[i] = start;
   g.nprob = nprob;
-  g.n_main = main_probs < nprob ? g.tile_start[main_probs] : start;
   if (start == 0) return hipSuccess;
-  if (dl) {
-    if (big)
-      launch_tile_dl<2, 2>(ma, mb, start, g, stream);
-    else
-      launch_tile_dl<1, 1>(ma, mb, start, g, stream);
-  } else if (big) {
-    launch_tile<2, 2>(ma, mb, start, g, stream);
-  } else {
-    launch_tile<1, 1>(ma, mb, start, g, stream);
-  }
+  if (big) launch_tile<2, 2>(ma, mb, start, g, stream);
+  else launch_tile<1, 1>(ma, mb, start, g, stream);
   return hipGetLastError();
 }
-}  // namespace
 
 }  // namespace lstm

@@ -21,17 +21,15 @@ struct GemmProblem {
   int M, N, K;
   long sAm, sAk, sBk, sBn, ldc;
   int accumulate;
-  int ct;  // element (r, c) of the product goes to C[c * ldc + r] (set by the launcher when it exchanges the operands' roles)
 };
 constexpr int kMaxGemmGroup = 16;
 // A group of independent products executed by one launch (Section 2.6: the weight
 // update products have no dependencies, so they can all be in flight together).
 int device_cu_count();  // compute units of the current device (0 if it cannot be read); persistent.hip
-hipError_t launch_gemm_group(const GemmProblem* probs, int nprob, hipStream_t stream);
-// One product, with the tiles of its last partial round (or all of them, when they are fewer than the chip holds
-// workgroups) cut along K; `part` (16-byte aligned, part_bytes long, free until the stream has passed the call) takes
-// the partial tiles.  The same result as launch_gemm_group up to the order of the additions, which is fixed.
-hipError_t launch_gemm_split(const GemmProblem& p, float* part, size_t part_bytes, hipStream_t stream);
+// `part` (16-byte aligned, part_bytes long, free until the stream has passed the call; null: none) takes the partial
+// tiles of products that are cut along K because their tiles do not fill the chip evenly; the parts are added in a fixed
+// order.
+hipError_t launch_gemm_group(const GemmProblem* probs, int nprob, hipStream_t stream, float* part = nullptr, size_t part_bytes = 0);
 
 // ---------------------------------------------------------------- point-wise / layout kernels (pointwise.hip)
 enum EwOp : int {

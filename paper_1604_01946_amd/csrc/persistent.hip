@@ -356,7 +356,7 @@ int run_forward_persistent_large(const FwdArgs& a, int cell) {
       ProfScope ps(LSTM_PHASE_FWD_INPUT_GEMM, s);
       GemmProblem p{in, Wl, P, (int)TB, (int)G, Il, Il, 1, 1, Il, (long)G, 0};
       // (the exchange area is idle between two recurrences: it takes the partial tiles)
-      CK(launch_gemm_split(p, hx, a.w.flags - a.w.xchg, s), "input projection GEMM");
+      CK(launch_gemm_group(&p, 1, s, hx, a.w.flags - a.w.xchg), "input projection GEMM");
     }
    for (int s0 = 0; s0 < slices; s0 += cap) {
     const int nsl = slices - s0 < cap ? slices - s0 : cap;
@@ -455,8 +455,8 @@ int run_backward_persistent_large(const BwdArgs& a, int cell, bool* bias_done, L
       if (overlap && pending >= 0) {
         CK(hipEventRecord(g_side_ev[0], s), "fork to the side stream");
         CK(hipStreamWaitEvent(g_side_stream, g_side_ev[0], 0), "side stream wait");
-        const int st = cell == 0 ? weight_gradients_layers(a, dA_all, pending, pending + 1, g_side_stream, true, bias_in_kernel)
-                                 : lg->fn(lg->ctx, pending, g_side_stream);
+        const int st = cell == 0 ? weight_gradients_layers(a, dA_all, pending, pending + 1, g_side_stream, true, bias_in_kernel, backward_scratch(a.ws, a.w))
+                                 : lg->fn(lg->ctx, pending, g_side_stream, backward_scratch(a.ws, a.w));
         if (st != LSTM_OK) return st;
         pending = -1;
       }
@@ -485,14 +485,15 @@ int run_backward_persistent_large(const BwdArgs& a, int cell, bool* bias_done, L
       ProfScope ps(LSTM_PHASE_BWD_INPUT_GEMM, s);
       const float* Wl = a.W + (l == 0 ? 0 : GW * d.I + (size_t)(l - 1) * GW * d.H);
       GemmProblem p{dA, Wl, din, (int)TB, Il, (int)GW, (long)G, 1, Il, 1, Il, 0};
-      CK(launch_gemm_split(p, reinterpret_cast<float*>(a.ws + a.w.xchg), a.w.flags - a.w.xchg, s), "input-gradient GEMM");
+      CK(launch_gemm_group(&p, 1, s, reinterpret_cast<float*>(a.ws + a.w.xchg), a.w.flags - a.w.xchg), "input-gradient GEMM");
     }
     if (overlap) pending = l;
   }
   if (bias_done) *bias_done = bias_in_kernel;
   if (!overlap) return cell != 0 ? LSTM_OK : weight_gradients(a, dA_all, true, bias_in_kernel);
   // the bottom layer's weight gradients have nothing left to hide behind; then the side stream joins
-  const int st = cell == 0 ? weight_gradients_layers(a, dA_all, 0, 1, s, true, bias_in_kernel) : lg->fn(lg->ctx, 0, s);
+  const int st = cell == 0 ? weight_gradients_layers(a, dA_all, 0, 1, s, true, bias_in_kernel, exchange_scratch(a.ws, a.w))
+                           : lg->fn(lg->ctx, 0, s, exchange_scratch(a.ws, a.w));
   if (st != LSTM_OK) return st;
   if (lg) lg->used = true;
   CK(hipEventRecord(g_side_ev[1], g_side_stream), "join record");
@@ -584,7 +585,7 @@ int forward_layers(const FwdArgs& a, int cell) {
     {
       ProfScope ps(LSTM_PHASE_FWD_INPUT_GEMM, s);
       GemmProblem p{a.x, a.W, P0, (int)TB, (int)G, d.I, d.I, 1, 1, d.I, (long)G, 0};
-      CK(launch_gemm_group(&p, 1, s), "input projection GEMM (layer 0)");
+      CK(launch_gemm_group(&p, 1, s, hx, a.w.flags - a.w.xchg), "input projection GEMM (layer 0)");
     }
     PersFwdArgs k{};
     k.W = a.W; k.R = a.R; k.bias = a.b; k.P0 = P0; k.c0 = a.c0; k.h0 = a.h0; k.hx = hx; k.watchdog = g_watch_dev;
@@ -616,7 +617,7 @@ int forward_layers(const FwdArgs& a, int cell) {
   if (!x_in_kernel) {
     ProfScope ps(LSTM_PHASE_FWD_INPUT_GEMM, s);
     GemmProblem p{a.x, a.W, P0, (int)TB, (int)G, d.I, d.I, 1, 1, d.I, (long)G, 0};
-    CK(launch_gemm_group(&p, 1, s), "input projection GEMM (layer 0)");
+    CK(launch_gemm_group(&p, 1, s, hx, a.w.flags - a.w.xchg), "input projection GEMM (layer 0)");
   }
   PersFwdArgs k;
   k.xin = x_in_kernel ? P0 : nullptr;
@@ -751,7 +752,7 @@ int backward_layers(const BwdArgs& a, int cell, bool* bias_done, bool with_weigh
     if (a.dx && !k.dx0) {  // layer 0's input gradient: all T steps in one product
       ProfScope ps(LSTM_PHASE_BWD_INPUT_GEMM, s);
       GemmProblem p{dA, a.W, a.dx, (int)TB, d.I, (int)GW, (long)G, 1, d.I, 1, d.I, 0};
-      CK(launch_gemm_group(&p, 1, s), "input-gradient GEMM (layer 0)");
+      CK(launch_gemm_group(&p, 1, s, reinterpret_cast<float*>(a.ws + a.w.xchg), a.w.flags - a.w.xchg), "input-gradient GEMM (layer 0)");
     }
     if (bias_done) *bias_done = a.db != nullptr;
     if (!with_weight_gradients) return LSTM_OK;
@@ -808,7 +809,7 @@ int backward_layers(const BwdArgs& a, int cell, bool* bias_done, bool with_weigh
   if (a.dx && !k.dx0) {  // layer 0's input gradient: all T steps in one product
     ProfScope ps(LSTM_PHASE_BWD_INPUT_GEMM, s);
     GemmProblem p{dA, a.W, a.dx, (int)TB, d.I, (int)GW, (long)G, 1, d.I, 1, d.I, 0};
-    CK(launch_gemm_group(&p, 1, s), "input-gradient GEMM (layer 0)");
+    CK(launch_gemm_group(&p, 1, s, reinterpret_cast<float*>(a.ws + a.w.xchg), a.w.flags - a.w.xchg), "input-gradient GEMM (layer 0)");
   }
   if (bias_done) *bias_done = k.db != nullptr;
   if (cell != 0 || !with_weight_gradients) return LSTM_OK;

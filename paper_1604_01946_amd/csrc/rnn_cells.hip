@@ -233,22 +233,22 @@ int backward_persistent(int cell, const Dims& d, const float* x, const float* h0
     }
     return LSTM_OK;
   };
-  auto flush = [&](GemmProblem* main_g, int& nm, GemmProblem* init_g, int& ni, hipStream_t st) -> int {
-    if (nm) CK(launch_gemm_group(main_g, nm, st), "weight-gradient GEMMs");
-    if (ni) CK(launch_gemm_group(init_g, ni, st), "weight-gradient GEMMs (initial state term)");
+  auto flush = [&](GemmProblem* main_g, int& nm, GemmProblem* init_g, int& ni, hipStream_t st, Scratch part) -> int {
+    if (nm) CK(launch_gemm_group(main_g, nm, st, part.p, part.bytes), "weight-gradient GEMMs");
+    if (ni) CK(launch_gemm_group(init_g, ni, st, part.p, part.bytes), "weight-gradient GEMMs (initial state term)");
     nm = ni = 0;
     return LSTM_OK;
   };
   // One layer on a stream of the caller's choice: the one-layer kernels run it under the next layer's recurrence
   // where CUs are idle.
-  auto layer_products = [&](int l, hipStream_t st) -> int {
+  auto layer_products = [&](int l, hipStream_t st, Scratch part) -> int {
     GemmProblem main_g[3], init_g[2];
     int nm = 0, ni = 0;
     const int rc = add_layer(l, main_g, nm, init_g, ni, st);
-    return rc != LSTM_OK ? rc : flush(main_g, nm, init_g, ni, st);
+    return rc != LSTM_OK ? rc : flush(main_g, nm, init_g, ni, st, part);
   };
   using Fn = decltype(layer_products);
-  LayerGradients lg{[](void* ctx, int l, hipStream_t st) { return (*static_cast<Fn*>(ctx))(l, st); }, &layer_products, false};
+  LayerGradients lg{[](void* ctx, int l, hipStream_t st, Scratch part) { return (*static_cast<Fn*>(ctx))(l, st, part); }, &layer_products, false};
   bool bias_done = false;
   const int st = run_backward_persistent(a, kernel_cell(cell), &bias_done, &lg);
   if (st != LSTM_OK) return st;
@@ -257,13 +257,13 @@ int backward_persistent(int cell, const Dims& d, const float* x, const float* h0
     int nm = 0, ni = 0;
     for (int l = 0; l < d.L; ++l) {
       if (nm + 3 > kMaxGemmGroup || ni + 2 > kMaxGemmGroup) {
-        const int rc = flush(main_g, nm, init_g, ni, s);
+        const int rc = flush(main_g, nm, init_g, ni, s, exchange_scratch(ws, w));
         if (rc != LSTM_OK) return rc;
       }
       const int rc = add_layer(l, main_g, nm, init_g, ni, s);
       if (rc != LSTM_OK) return rc;
     }
-    const int rc = flush(main_g, nm, init_g, ni, s);
+    const int rc = flush(main_g, nm, init_g, ni, s, exchange_scratch(ws, w));
     if (rc != LSTM_OK) return rc;
   }
   if (!bias_done) {  // column sums over all four groups, of which db takes the leading ones

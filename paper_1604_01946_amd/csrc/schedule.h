@@ -67,16 +67,25 @@ int set_path_override(const Dims& d, bool backward, unsigned path);  // LSTM_PAT
 int set_wavefront_chunks(const Dims& d, int chunks);                 // 0 removes the entry
 int wavefront_chunks(const Dims& d);                                 // 0: no entry (d as the kernels see it)
 void clear_path_overrides();
+// Parts of the workspace that take the partial tiles of products cut along K (launch_gemm_group): the exchange area of the
+// persistent kernels, idle before and after a recurrence, and the reserve stand-in of inference calls, which no backward
+// call uses (for products on a side stream while a recurrence runs).
+struct Scratch {
+  float* p;
+  size_t bytes;
+};
+inline Scratch exchange_scratch(char* ws, const WsLayout& w) { return {reinterpret_cast<float*>(ws + w.xchg), w.flags - w.xchg}; }
+inline Scratch backward_scratch(char* ws, const WsLayout& w) { return {reinterpret_cast<float*>(ws + w.resv), w.total - w.resv}; }
 // Weight gradients of one layer on a given stream, supplied by the caller of the persistent backward pass for the
 // cells whose gradient products it forms itself; *used is set when the pass has called it for every layer.
 struct LayerGradients {
-  int (*fn)(void* ctx, int layer, hipStream_t s);
+  int (*fn)(void* ctx, int layer, hipStream_t s, Scratch part);
   void* ctx;
   bool used;
 };
 
 int weight_gradients_layers(const BwdArgs& a, const float* dA_all, int l0, int l1, hipStream_t s, bool grouped,
-                            bool bias_done);
+                            bool bias_done, Scratch part);
 int run_forward(const FwdArgs& a, unsigned path);
 int run_backward(const BwdArgs& a, unsigned path);
 void release_helpers();

@@ -166,7 +166,8 @@ int fwd_step(const FwdArgs& a) {
     {
       ProfScope ps(LSTM_PHASE_FWD_INPUT_GEMM, s);
       GemmProblem p{in, Wl, P, (int)TB, (int)G, Il, Il, 1, 1, Il, (long)G, 0};
-      CK(launch_gemm_group(&p, 1, s), "input projection GEMM");
+      const Scratch part = exchange_scratch(a.ws, a.w);
+      CK(launch_gemm_group(&p, 1, s, part.p, part.bytes), "input projection GEMM");
     }
     ProfScope ps(LSTM_PHASE_FWD_RECURRENCE, s);
     for (int t = 0; t < d.T; ++t) {
@@ -260,12 +261,12 @@ int fwd_unfused(const FwdArgs& a, int level) {
 // dW_l = sum_t dA_t^T in_t, dR_l = sum_t dA_t^T h_{t-1}, db_l = sum_t,b dA_t: products over K = T*B
 // with no dependencies between them, so all of them go into grouped launches.
 int weight_gradients(const BwdArgs& a, const float* dA_all, bool grouped, bool bias_done) {
-  return weight_gradients_layers(a, dA_all, 0, a.d.L, a.stream, grouped, bias_done);
+  return weight_gradients_layers(a, dA_all, 0, a.d.L, a.stream, grouped, bias_done, exchange_scratch(a.ws, a.w));
 }
 
 // Layers l0 .. l1-1, on stream s (which may be another stream than the call's: the caller orders it).
 int weight_gradients_layers(const BwdArgs& a, const float* dA_all, int l0, int l1, hipStream_t s, bool grouped,
-                            bool bias_done) {
+                            bool bias_done, Scratch part) {
   const Dims& d = a.d;
   const size_t TB = (size_t)d.T * d.B, G = 4 * (size_t)d.H;
   const int H = d.H, B = d.B;
@@ -274,7 +275,7 @@ int weight_gradients_layers(const BwdArgs& a, const float* dA_all, int l0, int l
   auto flush = [&](GemmProblem* arr, int& n) -> hipError_t {
     hipError_t e = hipSuccess;
     if (grouped) {
-      e = launch_gemm_group(arr, n, s);
+      e = launch_gemm_group(arr, n, s, part.p, part.bytes);
     } else {
       for (int i = 0; i < n && e == hipSuccess; ++i) e = launch_gemm_group(arr + i, 1, s);
     }
@@ -396,7 +397,8 @@ int bwd_step(const BwdArgs& a) {
     if (din) {
       ProfScope ps(LSTM_PHASE_BWD_INPUT_GEMM, s);
       GemmProblem p{dA, a.W + w_offset(d, l), din, (int)TB, Il, (int)G, (long)G, 1, Il, 1, Il, 0};
-      CK(launch_gemm_group(&p, 1, s), "input-gradient GEMM");
+      const Scratch part = exchange_scratch(a.ws, a.w);
+      CK(launch_gemm_group(&p, 1, s, part.p, part.bytes), "input-gradient GEMM");
     }
   }
   return weight_gradients(a, dA_all, true, false);

@@ -1,0 +1,52 @@
+// fp32 operands on the bf16 matrix cores: every value is cut into three bf16 parts, x = h + m + l.
+//
+// fp32 matrix instructions reach 155 TFLOP/s on this chip, bf16 ones 1900 (measured, random operands).  h is x rounded to
+// bf16 (8 significant bits), m the remainder rounded, l what is left: it has at most 8 significant bits, so the three
+// parts hold all 24 bits of x exactly (down to where bf16 itself ends, 2^-133).  Of the nine products of two such
+// numbers the six largest are formed, hh, hm, mh, mm, hl, lh, each exactly and accumulated in fp32; the three left out
+// (ml, lm, ll) are below 2^-24 of the product, less than one rounding of an fp32 multiplication, and of random sign.
+//
+// Infinities and NaN: an infinite x has h = inf and m = x - h = NaN, a finite x that rounds to bf16's infinity (above
+// 3.39e38) has h = inf and m = -inf, so every sum that such an operand enters comes out NaN or infinite, never finite.
+// The kernels look for that and work such sums out again on the fp32 matrix instructions.
+#pragma once
+#include "internal.h"
+
+namespace lstm {
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
+typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+
+// The parts of two values, each pair packed into one register (first value in the low half).
+struct Split2 {
+  unsigned h, m, l;
+};
+__device__ __forceinline__ unsigned pack_bf16(float a, float b) {
+  const floatx2 v = {a, b};
+  return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
+}
+__device__ __forceinline__ Split2 split3(float a, float b) {
+  Split2 s;
+  s.h = pack_bf16(a, b);
+  a -= __builtin_bit_cast(float, s.h << 16);
+  b -= __builtin_bit_cast(float, s.h & 0xffff0000u);
+  s.m = pack_bf16(a, b);
+  a -= __builtin_bit_cast(float, s.m << 16);
+  b -= __builtin_bit_cast(float, s.m & 0xffff0000u);
+  s.l = pack_bf16(a, b);
+  return s;
+}
+
+// acc += A * B for 16 (32x32 tile) k: the six products of the parts, smallest first
+__device__ __forceinline__ floatx16 mfma_split3(const bf16x8 (&a)[3], const bf16x8 (&b)[3], floatx16 acc) {
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[2], b[0], acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[2], acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], b[1], acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], b[0], acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[1], acc, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[0], acc, 0, 0, 0);
+}
+
+}  // namespace lstm

@@ -1,0 +1,106 @@
+"""The GEMM on bf16 matrix cores (operands in three parts) at the sizes where it can go wrong: edges of the 64, 128 and 256
+tiles, K around multiples of its k-tile of 16, rows that allow no vector loads, K slices with a tail, and operands that are
+infinite, NaN or above bf16's largest value.  Reference: float64."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def run(A, Bm, layout, accumulate=0, scratch_bytes=0, C0=None):
+    """layout as in test_gpu_parity: N: [M][K] / [K][N], T: the transpose is stored."""
+    import torch
+    from paper_1604_01946_amd import binding
+    (M, K), N = A.shape, Bm.shape[1]
+    print(f"gemm {M}x{N}x{K} {layout} scratch={scratch_bytes}", flush=True)
+    up = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+    At, sA = (up(A.T), (1, M)) if layout[0] == "T" else (up(A), (K, 1))
+    Bt, sB = (up(Bm.T), (1, K)) if layout[1] == "T" else (up(Bm), (N, 1))
+    C = up(C0) if C0 is not None else torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda:0")
+    scratch = torch.full((max(scratch_bytes // 4, 1),), float("nan"), dtype=torch.float32, device="cuda:0") if scratch_bytes else None
+    binding.check(binding.lstm_gemm_f32_ws(M, N, K, At, *sA, Bt, *sB, C, N, accumulate, scratch, scratch_bytes), "gemm")
+    torch.cuda.synchronize()
+    return C.cpu().numpy()
+
+
+def operands(M, N, K, seed, spread=0):
+    rng = np.random.default_rng(seed)
+    A, Bm = rng.standard_normal((M, K)), rng.standard_normal((K, N))
+    if spread:  # magnitudes over 2 * spread binades in every sum
+        A, Bm = A * 2.0 ** rng.integers(-spread, spread + 1, A.shape), Bm * 2.0 ** rng.integers(-spread, spread + 1, Bm.shape)
+    return A.astype(np.float32), Bm.astype(np.float32)
+
+
+# element-wise: |C - ref| <= c * sum_k |a||b|.  A sum of K fp32 terms in any order is within K * 2^-24 of that, in practice
+# sqrt(K); the parts left out of a product are below 2^-22 of it in the worst case (three products of remainders of at most
+# 2^-8 and 2^-16), 2^-26 typically.
+def check(got, A, Bm, base=None):
+    a, b = A.astype(np.float64), Bm.astype(np.float64)
+    ref = a @ b + (0 if base is None else base.astype(np.float64))
+    bound = (np.abs(a) @ np.abs(b)) * (2.0 ** -22 + np.sqrt(A.shape[1]) * 2.0 ** -23) + (0 if base is None else np.abs(base) * 2.0 ** -23)
+    assert np.all(np.abs(got - ref) <= bound + 1e-37)
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (2, 2, 15), (64, 64, 16), (65, 63, 17), (128, 126, 31), (130, 258, 33), (256, 256, 48),
+                                   (254, 514, 160), (700, 650, 650), (1100, 2050, 40),
+                                   (3600, 4098, 16), (3598, 4096, 100), (3600, 4100, 141)])  # 256 x 256 tiles: one, six and nine k-tiles
+@pytest.mark.parametrize("layout", ["NT", "NN", "TN", "TT"])
+def test_edges(M, N, K, layout):
+    A, Bm = operands(M, N, K, M + N + K)
+    check(run(A, Bm, layout), A, Bm)
+
+
+# one tile per CU and a few more, cut along K: slices of unequal length, a K tail in the last slice, accumulation
+@pytest.mark.parametrize("M,N,K,scratch", [(512, 512, 1000, 64 << 20), (512, 512, 1000, 1 << 20), (66, 130, 4099, 8 << 20), (2048, 1030, 600, 64 << 20)])
+@pytest.mark.parametrize("layout", ["NT", "NN", "TN"])
+def test_slices(M, N, K, scratch, layout):
+    A, Bm = operands(M, N, K, 5)
+    C0 = np.random.default_rng(6).standard_normal((M, N)).astype(np.float32)
+    got = run(A, Bm, layout, accumulate=1, scratch_bytes=scratch, C0=C0)
+    check(got, A, Bm, C0)
+    assert np.array_equal(got, run(A, Bm, layout, accumulate=1, scratch_bytes=scratch, C0=C0))
+
+
+def test_sums_of_results_are_not_biased():
+    """Column and row sums of a product: the rounding of its elements averages out.  (The bf16 instructions cut bits
+    off downwards; with one sign everywhere the mean error was 6e-8 of the rms at K = 1024, now it is below 1e-8: quarters of K with either sign.)"""
+    for layout in ("NT", "NN", "TN"):
+        A, Bm = operands(4096, 3072, 1024, 17)
+        ref = A.astype(np.float64) @ Bm.astype(np.float64)
+        e = (run(A, Bm, layout) - ref) / np.sqrt(np.mean(ref ** 2))
+        for block in (e, e[:, :256], e[:, 512:513], e[:256], e[7:8]):
+            # standard error of the mean of independent roundings of 5e-7 each, five times, plus the 1e-8
+            assert abs(block.mean()) < 1e-8 + 5 * 5e-7 / np.sqrt(block.size)
+
+
+def test_wide_range_of_magnitudes():
+    A, Bm = operands(200, 300, 257, 9, spread=40)
+    check(run(A, Bm, "NT"), A, Bm)
+
+
+def test_exact_products():
+    """Whole numbers of 24 bits: every part and product is exact, so is the result."""
+    rng = np.random.default_rng(3)
+    A = rng.integers(-(2 ** 24) + 1, 2 ** 24, (70, 16)).astype(np.float32) * np.eye(1, 16, 5, dtype=np.float32)
+    Bm = np.zeros((16, 66), np.float32)
+    Bm[5] = 2.0 ** rng.integers(-20, 20, 66)
+    assert np.array_equal(run(A, Bm, "NT"), A @ Bm)
+
+
+@pytest.mark.parametrize("scratch", [0, 64 << 20])
+def test_infinities_and_nan_as_in_fp32(scratch):
+    """What an fp32 sum gives: an infinite operand makes its row infinite, not NaN; a finite one above bf16's largest
+    value keeps its row finite."""
+    A, Bm = operands(300, 260, 900, 4)
+    Bm = np.abs(Bm) + np.float32(0.5)
+    A[3, 7] = np.inf
+    A[150, 899] = -np.inf
+    A[290, 0] = np.nan
+    A[7, :] = 0
+    A[7, 5] = np.float32(3.4e38)
+    Bm[5, :] = np.float32(0.5)
+    got = run(A, Bm, "NT", scratch_bytes=scratch)
+    assert np.all(np.isposinf(got[3])) and np.all(np.isneginf(got[150])) and np.all(np.isnan(got[290]))
+    assert np.allclose(got[7], 1.7e38, rtol=1e-6)
+    rest = [i for i in range(300) if i not in (3, 150, 290, 7)]
+    check(got[rest], A[rest], Bm)

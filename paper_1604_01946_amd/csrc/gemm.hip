@@ -266,7 +266,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmGroupArgs g) {
 // is the fp32 kernel's or below (K = 512: 3.4e-7 against 4.0e-7, 6400: 1.21e-6 / 1.40e-6, 16384: 1.86e-6 / 2.25e-6).
 //
 // A workgroup of NWM x NWN waves computes a tile of TM x TN, each wave WM x WN tiles of 32x32.  Operands go from memory to
-// registers two k-tiles of 16 ahead (half of the threads fetch A, half B), are cut into their parts there -- once per
+// registers two to four k-tiles of 16 ahead (half of the threads fetch A, half B), are cut into their parts there -- once per
 // workgroup: cutting fragments after the read from LDS would do it once per wave that reads them -- and go to LDS as
 // units of 16 bytes, 8 k of one row of one part, which is what a lane feeds a matrix instruction.  In a plane the units of
 // one k group lie row after row (a fragment read is 512 contiguous bytes per half-wave); the second k group starts four
@@ -274,8 +274,11 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmGroupArgs g) {
 // its stores are spread over the matrix instructions of the k-tile before; the barrier lies before the last quarter
 // of a k-tile, whose matrix instructions cover the first fragment reads of the next one.
 //
-// Tiles: 256 x 256 on 512 threads (230-245 TFLOP/s; one workgroup and 100 KB of LDS per CU), 128 x 128 (205-210) and 64 x 64
-// (145) on 256 threads: with smaller tiles the cutting, the LDS traffic and the loads per matrix instruction double.
+// Tiles: 256 x 256 on 512 threads (230-245 TFLOP/s; one workgroup and 100 KB of LDS per CU), 128 x 128 on 256 threads
+// (205-210) and 64 x 64 (145): with smaller tiles the cutting, the LDS traffic and the loads per matrix instruction double.
+// A 64 x 64 tile has a workgroup of two groups of four waves that take half of the k-tiles each: such tiles are for
+// products of few tiles, where a workgroup has a CU to itself and a k-tile is one chain of cut, LDS, barrier, LDS and
+// matrix instructions (9 x 4096 x 4096 81 -> 58 us, 256 x 4096 x 12288 331 -> 224).
 //
 // Sign.  Inside a bf16 matrix instruction the products of 8 k are aligned to the largest of them and the bits beyond its
 // last place are cut off downwards, whatever the signs: a bias that grows with K (mean error of a sum over its rms value:
@@ -283,7 +286,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmGroupArgs g) {
 // gradients over T B rows, a cell state over the steps -- adds up as well.  So a quarter of the k-tiles is multiplied with
 // A negated, the sums change sign, half follows as it is, they change sign again, and the last quarter is negated: the
 // parts' biases cancel to a twentieth (3.9e-10 at K = 512, 2.3e-8 at 8192; two halves would leave a third, because the bias
-// of a part grows with the sum that it adds to).  It costs under 1 % of the time.  Below 8 k-tiles the bias is left in:
+// of a part grows with the sum that it adds to).  It costs under 1 % of the time.  Below 4 D (8 or 16) k-tiles the bias is left in:
 // 6e-9 against an error of 1.1e-7.
 //
 // Operand modes: unit stride along K with 16-byte aligned rows, unit stride along the rows in pairs (8-byte aligned, an
@@ -375,13 +378,14 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-template <int NWM, int NWN, int WM, int WN, int MA, int MB>
-__global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_split3_kernel(const Gemm3Args g) {
+// KG groups of NWM x NWN waves share the k-tiles out between them and add their sums up in the end.
+template <int KG, int NWM, int NWN, int WM, int WN, int MA, int MB>
+__global__ __launch_bounds__(64 * KG * NWM * NWN, 2) void gemm_split3_kernel(const Gemm3Args g) {
   constexpr int NT = 64 * NWM * NWN, TM = 32 * NWM * WM, TN = 32 * NWN * WN, HALF = NT / 2, UPT = TM * 2 / HALF;
   static_assert(TM == TN && TM * 2 == UPT * HALF, "half of the threads fetch A, half B");
   using L3 = Loader3<TM, UPT>;
   constexpr int PL = 2 * L3::KGS;     // units per plane
-  __shared__ uintx4 S[2][2][3 * PL];  // [stage][operand][part, k group, row]
+  __shared__ uintx4 SG[KG][2][2][3 * PL];  // [group][stage][operand][part, k group, row]
 
   // item -> tile and slice of K.  Workgroups are dealt round-robin to the 8 XCDs, each with its own L2: an XCD gets a
   // contiguous run of the whole tiles, which share operand panels, and after those a contiguous run of the slices.
@@ -414,11 +418,17 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_split3_kernel(const Ge
     if (sl + 1 < g.slices) kend = (kt0 + nk) * KT3;
   }
 
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = threadIdx.x & 63;
+  const int wave_wg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int grp = KG == 1 ? 0 : wave_wg / (NWM * NWN), wave = KG == 1 ? wave_wg : wave_wg % (NWM * NWN);
   const int wm = wave / NWN, wn = wave % NWN;
   const bool isB = wave >= NWM * NWN / 2;
-  const int h = tid & (HALF - 1);
+  const int h = threadIdx.x & (HALF - 1);
+  auto& S = SG[grp];
+  const int kbegin = kt0 * KT3;  // of the item
+  nk /= KG;                      // whole k-tiles of a group; what is left is below KG k-tiles
+  const int kleft = kbegin + KG * nk * KT3;
+  kt0 += grp * nk;
   L3 ld;
   // (no branch around the loads where both operands have the same mode)
   if constexpr (MA == MB) {
@@ -435,7 +445,9 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_split3_kernel(const Ge
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  float x[2][UPT][8];  // fetched, not yet cut: k-tiles of even and of odd index
+  // Fetched, not yet cut: D k-tiles.  (Four for the larger tiles: no faster, and 128 x 128 loses its third workgroup per CU.)
+  constexpr int D = WM > 1 ? 2 : 4;
+  float x[D][UPT][8];
   int fetched = 0;
   auto load = [&](float (&xx)[UPT][8]) {
     const bool more = ++fetched < nk;
@@ -473,8 +485,8 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_split3_kernel(const Ge
   };
   constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};  // the six products, smallest first
   constexpr int NP = 4 * UPT;
-  // k-tiles in pairs: a quarter with A negated, half as it is, a quarter negated (see above), the sums negated in between
-  const int end2 = nk & ~1, end0 = nk / 8 * 2, end1 = end2 - end0;
+  // k-tiles, D at a time: a quarter with A negated, half as it is, a quarter negated (see above), the sums negated in between
+  const int end2 = nk / D * D, end0 = nk / (4 * D) * D, end1 = end2 - end0;
   const unsigned negative = isB ? 0u : 0x80000000u;
   int cutting = 0;
   auto next_sign = [&]() {  // of the k-tile that is cut next
@@ -490,8 +502,9 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_split3_kernel(const Ge
         for (int r = 0; r < 16; ++r) acc[i][j][r] = -acc[i][j][r];
   };
   // One k-tile from stage PAR, in 2 WM steps of 3 WN matrix instructions; FA: which of fa holds row tile 0.
-  auto ktile = [&](auto par, auto fpar) {
-    constexpr int PAR = decltype(par)::value, FA = decltype(fpar)::value;
+  // X: its place among the D.
+  auto ktile = [&](auto place) {
+    constexpr int X = decltype(place)::value, PAR = X & 1, FA = (X * WM) & 1, XN = (X + 1) % D;
     constexpr int NS = 2 * WM, NBF = NS - (WM >= 4 ? 2 : 1);  // steps, those before the barrier
     const unsigned sign = next_sign();
 #pragma unroll
@@ -500,8 +513,8 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_split3_kernel(const Ge
       if (s % 2 == 0 && i + 1 < WM) readA(fa[(FA + i + 1) & 1], PAR, i + 1);
       if (s < NBF) {
 #pragma unroll
-        for (int p = s * NP / NBF; p < (s + 1) * NP / NBF; ++p) cut(x[PAR ^ 1], PAR ^ 1, p, sign);
-        if (s == NBF - 1) load(x[PAR ^ 1]);
+        for (int p = s * NP / NBF; p < (s + 1) * NP / NBF; ++p) cut(x[XN], PAR ^ 1, p, sign);
+        if (s == NBF - 1) load(x[XN]);
       } else if (s == NBF) {
 #pragma unroll
         for (int j = 0; j < WN; ++j) readB(fb[PAR ^ 1][j], PAR ^ 1, j);
@@ -526,8 +539,8 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_split3_kernel(const Ge
     }
   };
   if (nk > 0) {
-    load(x[0]);
-    load(x[1]);
+#pragma unroll
+    for (int i = 0; i < D; ++i) load(x[i]);
     const unsigned sign = next_sign();
 #pragma unroll
     for (int p = 0; p < NP; ++p) cut(x[0], 0, p, sign);
@@ -537,17 +550,25 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_split3_kernel(const Ge
     for (int j = 0; j < WN; ++j) readB(fb[0][j], 0, j);
     readA(fa[0], 0, 0);
     int kt = 0;
-    for (; kt + 1 < nk; kt += 2) {
+    for (; kt + D <= nk; kt += D) {
       if (kt == end0 || kt == end1) negate();
-      ktile(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
-      ktile(std::integral_constant<int, 1>{}, std::integral_constant<int, WM & 1>{});
+      ktile(std::integral_constant<int, 0>{});
+      ktile(std::integral_constant<int, 1>{});
+      if constexpr (D == 4) {
+        ktile(std::integral_constant<int, 2>{});
+        ktile(std::integral_constant<int, 3>{});
+      }
     }
     if (end0) negate();  // (after an even number of changes and a negated quarter)
-    if (kt < nk) ktile(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
+    if (kt < nk) ktile(std::integral_constant<int, 0>{});
+    if constexpr (D == 4) {
+      if (kt + 1 < nk) ktile(std::integral_constant<int, 1>{});
+      if (kt + 2 < nk) ktile(std::integral_constant<int, 2>{});
+    }
   }
-  // the k left over, fewer than 16: one more k-tile, guarded and waited for
-  if ((kt0 + nk) * KT3 < kend) {
-    const int k0 = (kt0 + nk) * KT3;
+  // the k left over, fewer than 16 per group: one more k-tile, guarded and waited for
+  if (kleft < kend) {
+    const int k0 = kleft + grp * KT3;
     __syncthreads();
     const float* const b = isB ? P.B : P.A;
     const long s_r = isB ? P.sBn : P.sAm, s_k = isB ? P.sBk : P.sAk;
@@ -578,6 +599,28 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_split3_kernel(const Ge
     }
   }
 
+  if constexpr (KG > 1) {
+    static_assert(KG <= 2 && sizeof(SG) >= (size_t)NT * WM * WN * 16 * sizeof(float), "the second group's sums go through LDS");
+    float* const buf = reinterpret_cast<float*>(&SG[0][0][0][0]) + (threadIdx.x & (NT - 1));
+    __syncthreads();
+    if (grp == 1) {
+#pragma unroll
+      for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int j = 0; j < WN; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) buf[((i * WN + j) * 16 + r) * NT] = acc[i][j][r];
+    }
+    __syncthreads();
+    if (grp == 1) return;
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+      for (int j = 0; j < WN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] += buf[((i * WN + j) * 16 + r) * NT];
+  }
+
   // any sum infinite or NaN: the wave's tiles again in fp32 (the only loads of that loop are its own: no barrier)
   {
     float z = 0.f;
@@ -599,7 +642,7 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_split3_kernel(const Ge
         for (int j = 0; j < WN; ++j)
 #pragma unroll
           for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-      for (int k = kt0 * KT3; k < kend; k += 2) {
+      for (int k = kbegin; k < kend; k += 2) {
         const int kk = k + (lane >> 5);
         const bool in = kk < kend;
         const long ka = (in ? kk : k) * P.sAk, kb = (in ? kk : k) * P.sBk;
@@ -665,12 +708,12 @@ __global__ __launch_bounds__(256) void gemm_slices_kernel(const Gemm3Args g) {
   }
 }
 
-template <int NWM, int NWN, int WM, int WN>
+template <int KG, int NWM, int NWN, int WM, int WN>
 void launch_split3(int ma, int mb, int grid, const Gemm3Args& g, hipStream_t s) {
-  constexpr int NT = 64 * NWM * NWN;
+  constexpr int NT = 64 * KG * NWM * NWN;
 #define LSTM_GEMM_CASE(A_, B_)                                                                                \
   if (ma == A_ && mb == B_) {                                                                                 \
-    hipLaunchKernelGGL((gemm_split3_kernel<NWM, NWN, WM, WN, A_, B_>), dim3(grid), dim3(NT), 0, s, g);        \
+    hipLaunchKernelGGL((gemm_split3_kernel<KG, NWM, NWN, WM, WN, A_, B_>), dim3(grid), dim3(NT), 0, s, g);    \
     return;                                                                                                   \
   }
   LSTM_GEMM_CASE(LM_KCONTIG, LM_KCONTIG)
@@ -678,7 +721,7 @@ void launch_split3(int ma, int mb, int grid, const Gemm3Args& g, hipStream_t s) 
   LSTM_GEMM_CASE(LM_RCONTIG, LM_RCONTIG)
   LSTM_GEMM_CASE(LM_RCONTIG, LM_KCONTIG)
 #undef LSTM_GEMM_CASE
-  if constexpr (NT == 256) hipLaunchKernelGGL((gemm_split3_kernel<NWM, NWN, WM, WN, LM_SCALAR, LM_SCALAR>), dim3(grid), dim3(NT), 0, s, g);
+  if constexpr (WM < 4) hipLaunchKernelGGL((gemm_split3_kernel<KG, NWM, NWN, WM, WN, LM_SCALAR, LM_SCALAR>), dim3(grid), dim3(NT), 0, s, g);
 }
 
 // Load mode of one operand of gemm_split3_kernel.
@@ -708,6 +751,73 @@ void launch_tile(int ma, int mb, int grid, const GemmGroupArgs& g, hipStream_t s
 
 namespace {
 
+// ------------------------------------------------------------------ few rows
+// C of up to 8 rows, both operands with unit stride along K (the input projection of a few steps of a few sequences, the
+// recurrent product of a small batch step by step).  Bound: one trip to memory and the launch; at most the reading of B
+// (N x K), which every row of A shares.  A wave owns NC columns, its lanes share out K in runs of 256 consecutive k (64
+// where rows are not 16-byte aligned) and meet at the end in a fixed order; vector FMAs in fp32.  1 x 1024 x 256: 3.0 us,
+// on a 64 x 64 tile of the kernel above, 63 of whose rows are empty, 11; 8 x 4096 x 4096: see the rule at the launch.
+template <int MR, int NC, int V>
+__global__ __launch_bounds__(256) void gemm_few_rows_kernel(const GemmProblem P) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int n0 = ((int)blockIdx.x * 4 + wave) * NC;
+  if (n0 >= P.N) return;
+  typedef float vec __attribute__((ext_vector_type(V)));
+  float acc[MR][NC];
+#pragma unroll
+  for (int m = 0; m < MR; ++m)
+#pragma unroll
+    for (int c = 0; c < NC; ++c) acc[m][c] = 0.f;
+  const float *pa[MR], *pb[NC];
+#pragma unroll
+  for (int m = 0; m < MR; ++m) pa[m] = P.A + (long)min(m, P.M - 1) * P.sAm;
+#pragma unroll
+  for (int c = 0; c < NC; ++c) pb[c] = P.B + (long)min(n0 + c, P.N - 1) * P.sBn;
+  auto step = [&](int k) {
+    vec va[MR], vb[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) vb[c] = *reinterpret_cast<const vec*>(pb[c] + k);
+#pragma unroll
+    for (int m = 0; m < MR; ++m) va[m] = *reinterpret_cast<const vec*>(pa[m] + k);
+#pragma unroll
+    for (int m = 0; m < MR; ++m)
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int v = 0; v < V; ++v) acc[m][c] = fmaf(va[m][v], vb[c][v], acc[m][c]);
+  };
+  int k = V * lane;
+  for (; k + 3 * 64 * V < P.K; k += 4 * 64 * V) {
+    step(k);
+    step(k + 64 * V);
+    step(k + 2 * 64 * V);
+    step(k + 3 * 64 * V);
+  }
+  for (; k < P.K; k += 64 * V) step(k);  // (V = 4: K is a multiple of 4)
+#pragma unroll
+  for (int m = 0; m < MR; ++m)
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      float v = acc[m][c];
+#pragma unroll
+      for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d);
+      if (lane == 0 && m < P.M && n0 + c < P.N) {
+        float* const o = P.C + (long)m * P.ldc + n0 + c;
+        *o = P.accumulate ? *o + v : v;
+      }
+    }
+}
+
+template <int MR, int NC>
+void launch_few_rows(const GemmProblem& p, hipStream_t s) {
+  auto ok16 = [](const float* q, long stride) { return (reinterpret_cast<uintptr_t>(q) & 15u) == 0 && (stride & 3) == 0; };
+  const dim3 grid((unsigned)((p.N + 4 * NC - 1) / (4 * NC)));
+  if (p.K % 4 == 0 && ok16(p.A, p.M > 1 ? p.sAm : 0) && ok16(p.B, p.N > 1 ? p.sBn : 0))
+    hipLaunchKernelGGL((gemm_few_rows_kernel<MR, NC, 4>), grid, dim3(256), 0, s, p);
+  else
+    hipLaunchKernelGGL((gemm_few_rows_kernel<MR, NC, 1>), grid, dim3(256), 0, s, p);
+}
+
 // How a group is run: the tile, the tiles computed whole, the slices of the rest.
 struct Plan3 {
   int tile = 0;
@@ -718,9 +828,9 @@ struct Plan3 {
 // Time of a group on tiles of `tile`, with the tiles of the last partial round (all of them where there is no full
 // round) cut along K into the number of slices that promises most.  Measured per k-tile of 16 with every CU busy:
 // 256 x 256 2.18 us, 128 x 128 0.645, 64 x 64 0.231 per CU (245, 208 and 145 TFLOP/s).  One 64 x 64 workgroup alone on a CU
-// takes 0.36, the latency of its own instructions; a 128 x 128 one 0.62 with both operands' rows side by side, but 1.0 to
-// 1.4 with rows as far apart as an operand with unit stride along K has them (two on a CU: 0.75 each): 16 k of 128 rows
-// are 128 requests to as many places, and two k-tiles ahead is not far enough.  Every item costs a few us more (first
+// takes 0.25, the latency of its own instructions; a 128 x 128 one 0.62 with both operands' rows side by side, but 1.0 to
+// 1.4 with rows as far apart as an operand with unit stride along K has them (several on a CU: 0.8 each): 16 k of 128
+// rows are 128 requests to as many places.  Every item costs a few us more (first
 // loads, last stores); a slice writes its tile and has it read again, at about 4 TB/s, and the addition is a launch of
 // 4 us.
 Plan3 plan_split3(const GemmProblem* p, int nprob, int tile, bool apart, size_t part_bytes, int cus) {
@@ -737,8 +847,8 @@ Plan3 plan_split3(const GemmProblem* p, int nprob, int tile, bool apart, size_t 
     if (items <= 0) return 0.0;
     const long deep = (items + cus - 1) / cus;
     const double per = tile == 256 ? 2.18
-                     : tile == 64  ? (deep == 1 ? 0.36 : 0.231)
-                                   : (deep == 1 ? (apart ? 1.2 : 0.62) : (deep == 2 && apart ? 0.75 : 0.645));
+                     : tile == 64  ? (deep == 1 ? 0.25 : 0.231)
+                                   : (deep == 1 ? (apart ? 1.2 : 0.62) : (apart ? 0.8 : 0.645));
     return deep * (nk * per + (tile == 256 || deep == 1 ? item : 0.5 * item));
   };
   best.n_full = (int)total;
@@ -746,26 +856,27 @@ Plan3 plan_split3(const GemmProblem* p, int nprob, int tile, bool apart, size_t 
   const long tail = total % cus, full = total - tail;
   if (tail == 0 || part_bytes == 0) return best;
   const double bytes_per = (double)tile * tile * sizeof(float);
-  double cut[17];
-  int most = 1, fastest = 0;
   for (int s = 2; s <= 16; ++s) {
     if (nkmax / s < 8 || (double)tail * s * bytes_per > (double)part_bytes) break;
-    cut[s] = cost(full, (double)nkmax) + cost(tail * s, (double)nkmax / s) + tail * s * bytes_per * 2.0 / 4.0e6 + 4.0;
-    if (cut[s] < 0.97 * best.us && (!fastest || cut[s] < cut[fastest])) fastest = s;
-    most = s;
-  }
-  // (of slice counts within 5 % of the fastest the largest: shorter sums round less)
-  for (int s = most; fastest && s >= fastest; --s)
-    if (cut[s] <= 1.05 * cut[fastest]) {
-      best.us = cut[s];
+    const double us = cost(full, (double)nkmax) + cost(tail * s, (double)nkmax / s) + tail * s * bytes_per * 2.0 / 4.0e6 + 4.0;
+    if (us < 0.97 * best.us) {
+      best.us = us;
       best.n_full = (int)full;
       best.slices = s;
-      break;
     }
+  }
   return best;
 }
 
 hipError_t launch_group3(const GemmProblem* probs, int nprob, float* part, size_t part_bytes, hipStream_t stream) {
+  if (nprob == 1 && probs[0].M <= 8 && probs[0].sAk == 1 && probs[0].sBk == 1) {
+    const GemmProblem& p = probs[0];
+    if (p.M == 1) launch_few_rows<1, 1>(p, stream);
+    else if (p.M == 2) launch_few_rows<2, 1>(p, stream);
+    else if (p.M <= 4) launch_few_rows<4, 2>(p, stream);
+    else launch_few_rows<8, 4>(p, stream);
+    return hipGetLastError();
+  }
   int ma = -1, mb = -1;
   for (int i = 0; i < nprob; ++i) {
     const GemmProblem& p = probs[i];
@@ -799,9 +910,9 @@ hipError_t launch_group3(const GemmProblem* probs, int nprob, float* part, size_
   g.part = part;
   if (start == 0) return hipSuccess;
   const int tail = start - best.n_full, grid = best.n_full + tail * best.slices;
-  if (best.tile == 256) launch_split3<2, 4, 4, 2>(ma, mb, grid, g, stream);
-  else if (best.tile == 128) launch_split3<2, 2, 2, 2>(ma, mb, grid, g, stream);
-  else launch_split3<2, 2, 1, 1>(ma, mb, grid, g, stream);
+  if (best.tile == 256) launch_split3<1, 2, 4, 4, 2>(ma, mb, grid, g, stream);
+  else if (best.tile == 128) launch_split3<1, 2, 2, 2, 2>(ma, mb, grid, g, stream);
+  else launch_split3<2, 2, 2, 1, 1>(ma, mb, grid, g, stream);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   if (best.slices > 1) {
     const dim3 blocks((unsigned)(tail * (best.tile / 16)));

@@ -161,6 +161,9 @@ int forward_impl(int cell, const Dims& d, const float* x, const float* h0, const
   const RnnWs w = rnn_ws(cell, d);
   float* P = reinterpret_cast<float*>(ws + w.P);
   float* Q = reinterpret_cast<float*>(ws + w.Q);
+  // partial tiles of products cut along K: the backward pass's gate gradients are not there yet
+  float* const part = reinterpret_cast<float*>(ws + w.da);
+  const size_t part_bytes = w.dx0 - w.da;
   size_t woff = 0;
   for (int l = 0; l < d.L; ++l) {
     const int Il = in_dim(d, l);
@@ -172,14 +175,14 @@ int forward_impl(int cell, const Dims& d, const float* x, const float* h0, const
     woff += G * Il;
     {  // Section 2.3: the layer's input products for all steps in one GEMM
       GemmProblem p{in, Wl, P, (int)TB, (int)G, Il, Il, 1, 1, Il, (long)G, 0};
-      CK(launch_gemm_group(&p, 1, s), "input projection GEMM");
+      CK(launch_gemm_group(&p, 1, s, part, part_bytes), "input projection GEMM");
     }
     for (int t = 0; t < d.T; ++t) {
       const float* hp = t ? hl + (size_t)(t - 1) * BH : (h0 ? h0 + (size_t)l * BH : nullptr);
       float* ht = hl + (size_t)t * BH;
       if (hp) {  // Section 2.1: all gates of the step in one recurrent product
         GemmProblem p{hp, Rl, Q, B, (int)G, H, H, 1, 1, H, (long)G, 0};
-        CK(launch_gemm_group(&p, 1, s), "recurrent GEMM");
+        CK(launch_gemm_group(&p, 1, s, part, part_bytes), "recurrent GEMM");
       } else {
         CK(launch_fill_zero(Q, (size_t)B * G * 4, s), "zero recurrent term");
       }
@@ -289,6 +292,9 @@ int backward_impl(int cell, const Dims& d, const float* x, const float* h0, cons
   float* dxb[2] = {reinterpret_cast<float*>(ws + w.dx0), reinterpret_cast<float*>(ws + w.dx1)};
   float* carry[2] = {reinterpret_cast<float*>(ws + w.carry0), reinterpret_cast<float*>(ws + w.carry1)};
   float* dbpart = reinterpret_cast<float*>(ws + w.dbpart);
+  // partial tiles of products cut along K: the forward pass's projection is no longer needed
+  float* const part = reinterpret_cast<float*>(ws + w.P);
+  const size_t part_bytes = w.Q - w.P;
   for (int l = d.L - 1; l >= 0; --l) {
     const int Il = in_dim(d, l);
     const float* hl = reserve + (size_t)l * res_layer_floats(cell, d);
@@ -310,7 +316,7 @@ int backward_impl(int cell, const Dims& d, const float* x, const float* h0, cons
       CK(hipGetLastError(), "point-wise backward");
       // dh_{t-1} = direct + dq_t R  (the stacked gates map to one output, Section 2.1)
       GemmProblem p{dq + (size_t)t * B * G, Rl, nxt, B, H, (int)G, (long)G, 1, H, 1, H, 1};
-      CK(launch_gemm_group(&p, 1, s), "recurrent backward GEMM");
+      CK(launch_gemm_group(&p, 1, s, part, part_bytes), "recurrent backward GEMM");
       cin = nxt;
       cur ^= 1;
     }
@@ -318,7 +324,7 @@ int backward_impl(int cell, const Dims& d, const float* x, const float* h0, cons
     float* din = l > 0 ? dxb[l & 1] : dx;
     if (din) {
       GemmProblem p{da, Wl, din, (int)TB, Il, (int)G, (long)G, 1, Il, 1, Il, 0};
-      CK(launch_gemm_group(&p, 1, s), "input-gradient GEMM");
+      CK(launch_gemm_group(&p, 1, s, part, part_bytes), "input-gradient GEMM");
     }
     // Section 2.6: weight gradients as large products once the layer's propagation is complete
     float* dWl = dW + woff;
@@ -327,10 +333,10 @@ int backward_impl(int cell, const Dims& d, const float* x, const float* h0, cons
     int ng = 0;
     g[ng++] = GemmProblem{da, in, dWl, (int)G, Il, (int)TB, 1, (long)G, Il, 1, Il, 0};
     if (d.T > 1) g[ng++] = GemmProblem{dq + (size_t)B * G, hl, dRl, (int)G, H, (int)(TB - B), 1, (long)G, H, 1, H, 0};
-    CK(launch_gemm_group(g, ng, s), "weight-gradient GEMMs");
+    CK(launch_gemm_group(g, ng, s, part, part_bytes), "weight-gradient GEMMs");
     if (h0) {
       GemmProblem p{dq, h0 + (size_t)l * BH, dRl, (int)G, H, B, 1, (long)G, H, 1, H, d.T > 1 ? 1 : 0};
-      CK(launch_gemm_group(&p, 1, s), "weight-gradient GEMM (initial state term)");
+      CK(launch_gemm_group(&p, 1, s, part, part_bytes), "weight-gradient GEMM (initial state term)");
     } else if (d.T == 1) {
       CK(launch_fill_zero(dRl, G * H * 4, s), "zero dR");
     }

@@ -200,6 +200,7 @@ int fwd_unfused(const FwdArgs& a, int level) {
   float* S1 = ws_f(a.ws, a.w.scratch);
   float* S2 = S1 + BG;
   float* tmp = S2 + BG;
+  const Scratch part = exchange_scratch(a.ws, a.w);
   float* zero = ws_f(a.ws, a.w.state) + 2 * (size_t)d.L * BH;
   CK(launch_fill_zero(zero, BH * 4, s), "zero block");
   for (int l = 0; l < d.L; ++l) {
@@ -225,9 +226,9 @@ int fwd_unfused(const FwdArgs& a, int level) {
         }
       } else {
         GemmProblem p1{xt, Wl, S1, B, (int)G, Il, Il, 1, 1, Il, (long)G, 0};
-        CK(launch_gemm_group(&p1, 1, s), "grouped input GEMM");
+        CK(launch_gemm_group(&p1, 1, s, part.p, level >= 2 ? part.bytes : 0), "grouped input GEMM");
         GemmProblem p2{hp, Rl, S2, B, (int)G, H, H, 1, 1, H, (long)G, 0};
-        CK(launch_gemm_group(&p2, 1, s), "grouped recurrent GEMM");
+        CK(launch_gemm_group(&p2, 1, s, part.p, level >= 2 ? part.bytes : 0), "grouped recurrent GEMM");
       }
       if (level >= 2) {
         CK(launch_pointwise_fwd(S1, S2, bl, cp, ht, ct, gt, (l == d.L - 1) ? a.y + (size_t)t * BH : nullptr, nullptr, B, H, s),
@@ -414,6 +415,7 @@ int bwd_unfused(const BwdArgs& a, bool per_gate) {
   float* dxb = ws_f(a.ws, a.w.dx);
   float* dcb = ws_f(a.ws, a.w.state);
   float* dhb = dcb + (size_t)d.L * BH;
+  const Scratch part = exchange_scratch(a.ws, a.w);
   for (int l = d.L - 1; l >= 0; --l) {
     const int Il = in_dim(d, l);
     const LayerRes r = layer_res(a.reserve, d, l);
@@ -447,11 +449,11 @@ int bwd_unfused(const BwdArgs& a, bool per_gate) {
       } else {
         if (dh_dst) {
           GemmProblem p{dAt, Rl, dh_dst, B, H, (int)G, (long)G, 1, H, 1, H, 0};
-          CK(launch_gemm_group(&p, 1, s), "recurrent gradient GEMM");
+          CK(launch_gemm_group(&p, 1, s, part.p, part.bytes), "recurrent gradient GEMM");
         }
         if (din) {
           GemmProblem p{dAt, Wl, din + (size_t)t * B * Il, B, Il, (int)G, (long)G, 1, Il, 1, Il, 0};
-          CK(launch_gemm_group(&p, 1, s), "input gradient GEMM");
+          CK(launch_gemm_group(&p, 1, s, part.p, part.bytes), "input gradient GEMM");
         }
       }
     }

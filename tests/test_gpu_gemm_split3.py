@@ -104,3 +104,14 @@ def test_infinities_and_nan_as_in_fp32(scratch):
     assert np.allclose(got[7], 1.7e38, rtol=1e-6)
     rest = [i for i in range(300) if i not in (3, 150, 290, 7)]
     check(got[rest], A[rest], Bm)
+
+
+# up to eight rows with both operands' unit stride along K: lanes share out K (in runs of 256, or of 64 where rows are not
+# 16-byte aligned), one, two or four columns per wave
+@pytest.mark.parametrize("M", [1, 2, 3, 4, 5, 8])
+@pytest.mark.parametrize("N,K", [(1, 1), (3, 64), (33, 255), (130, 256), (1024, 260), (65, 1030), (514, 2052)])
+def test_few_rows(M, N, K):
+    A, Bm = operands(M, N, K, 100 * M + N)
+    check(run(A, Bm, "NT"), A, Bm)
+    C0 = np.random.default_rng(6).standard_normal((M, N)).astype(np.float32)
+    check(run(A, Bm, "NT", accumulate=1, C0=C0), A, Bm, C0)

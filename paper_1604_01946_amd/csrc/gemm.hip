@@ -314,6 +314,8 @@ struct Loader3 {
   long step, krow;       // scalar: bytes from k-tile to k-tile, from k to k
   unsigned off[UPT];     // per lane: byte offset of a unit inside the k-tile
   int unit[UPT];         // per lane: its place in a plane
+  int left;              // scalar: k-tiles until the operand goes on elsewhere (GemmProblem::khead), 0: it does not
+  long jump;             // bytes from the last k-tile before that to the first one after it
 
   static __device__ __forceinline__ void place(int h, int v, bool rowwise, int& row, int& kg) {
     if (rowwise) {
@@ -332,6 +334,8 @@ struct Loader3 {
     sb = reinterpret_cast<const char*>(b + (long)r0 * s_r + (long)k0 * s_k);
     krow = 4 * s_k;
     step = KT3 * krow;
+    left = 0;
+    jump = 0;
 #pragma unroll
     for (int v = 0; v < UPT; ++v) {
       int row, kg;
@@ -367,7 +371,7 @@ struct Loader3 {
 #pragma unroll
         for (int j = 0; j < 8; ++j) x[v][j] = *reinterpret_cast<const float*>(sb + j * krow + off[v]);
     }
-    sb += more ? step : 0;
+    sb += more ? (--left == 0 ? jump : step) : 0;
   }
 };
 
@@ -425,6 +429,10 @@ __global__ __launch_bounds__(64 * KG * NWM * NWN, 2) void gemm_split3_kernel(con
   const bool isB = wave >= NWM * NWN / 2;
   const int h = threadIdx.x & (HALF - 1);
   auto& S = SG[grp];
+  // element (k, row) of B, k of the whole product
+  auto b_at = [&](int k, long off) {
+    return k < P.khead ? P.Bhead + (long)k * P.sBk + off : P.B + (long)(k - P.khead) * P.sBk + off;
+  };
   const int kbegin = kt0 * KT3;  // of the item
   nk /= KG;                      // whole k-tiles of a group; what is left is below KG k-tiles
   const int kleft = kbegin + KG * nk * KT3;
@@ -432,10 +440,14 @@ __global__ __launch_bounds__(64 * KG * NWM * NWN, 2) void gemm_split3_kernel(con
   L3 ld;
   // (no branch around the loads where both operands have the same mode)
   if constexpr (MA == MB) {
-    ld.template init<MA>(isB ? P.B : P.A, isB ? P.sBn : P.sAm, isB ? P.sBk : P.sAk, isB ? n0 : m0, isB ? P.N : P.M, kt0 * KT3, h);
+    ld.template init<MA>(isB ? b_at(kt0 * KT3, 0) - (long)kt0 * KT3 * P.sBk : P.A, isB ? P.sBn : P.sAm, isB ? P.sBk : P.sAk, isB ? n0 : m0, isB ? P.N : P.M, kt0 * KT3, h);
   } else {
     if (!isB) ld.template init<MA>(P.A, P.sAm, P.sAk, m0, P.M, kt0 * KT3, h);
-    else ld.template init<MB>(P.B, P.sBn, P.sBk, n0, P.N, kt0 * KT3, h);
+    else ld.template init<MB>(b_at(kt0 * KT3, 0) - (long)kt0 * KT3 * P.sBk, P.sBn, P.sBk, n0, P.N, kt0 * KT3, h);
+  }
+  if (isB && kt0 * KT3 < P.khead) {
+    ld.left = P.khead / KT3 - kt0;
+    ld.jump = reinterpret_cast<const char*>(P.B) - reinterpret_cast<const char*>(P.Bhead + (long)(P.khead - KT3) * P.sBk);
   }
   floatx16 acc[WM][WN];
 #pragma unroll
@@ -570,8 +582,7 @@ __global__ __launch_bounds__(64 * KG * NWM * NWN, 2) void gemm_split3_kernel(con
   if (kleft < kend) {
     const int k0 = kleft + grp * KT3;
     __syncthreads();
-    const float* const b = isB ? P.B : P.A;
-    const long s_r = isB ? P.sBn : P.sAm, s_k = isB ? P.sBk : P.sAk;
+    const long s_r = isB ? P.sBn : P.sAm;
     const int r0 = isB ? n0 : m0, R = isB ? P.N : P.M;
 #pragma unroll
     for (int v = 0; v < UPT; ++v) {
@@ -580,7 +591,7 @@ __global__ __launch_bounds__(64 * KG * NWM * NWN, 2) void gemm_split3_kernel(con
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const int k = k0 + 8 * kg + j;
-        x[0][v][j] = k < kend ? b[(long)row * s_r + (long)k * s_k] : 0.f;
+        x[0][v][j] = k < kend ? *(isB ? b_at(k, (long)row * s_r) : P.A + (long)row * s_r + (long)k * P.sAk) : 0.f;
       }
     }
 #pragma unroll
@@ -631,11 +642,12 @@ __global__ __launch_bounds__(64 * KG * NWM * NWN, 2) void gemm_split3_kernel(con
 #pragma unroll
         for (int r = 0; r < 16; ++r) z += acc[i][j][r] * 0.f;
     if (__any(z != 0.f)) {
-      const float *pa[WM], *pb[WN];
+      const float* pa[WM];
+      long pb[WN];
 #pragma unroll
       for (int i = 0; i < WM; ++i) pa[i] = P.A + (long)min(m0 + 32 * (wm * WM + i) + (lane & 31), P.M - 1) * P.sAm;
 #pragma unroll
-      for (int j = 0; j < WN; ++j) pb[j] = P.B + (long)min(n0 + 32 * (wn * WN + j) + (lane & 31), P.N - 1) * P.sBn;
+      for (int j = 0; j < WN; ++j) pb[j] = (long)min(n0 + 32 * (wn * WN + j) + (lane & 31), P.N - 1) * P.sBn;
 #pragma unroll
       for (int i = 0; i < WM; ++i)
 #pragma unroll
@@ -645,12 +657,12 @@ __global__ __launch_bounds__(64 * KG * NWM * NWN, 2) void gemm_split3_kernel(con
       for (int k = kbegin; k < kend; k += 2) {
         const int kk = k + (lane >> 5);
         const bool in = kk < kend;
-        const long ka = (in ? kk : k) * P.sAk, kb = (in ? kk : k) * P.sBk;
+        const long ka = (in ? kk : k) * P.sAk;
         float va[WM], vb[WN];
 #pragma unroll
         for (int i = 0; i < WM; ++i) va[i] = in ? pa[i][ka] : 0.f;
 #pragma unroll
-        for (int j = 0; j < WN; ++j) vb[j] = in ? pb[j][kb] : 0.f;
+        for (int j = 0; j < WN; ++j) vb[j] = in ? *b_at(kk, pb[j]) : 0.f;
 #pragma unroll
         for (int i = 0; i < WM; ++i)
 #pragma unroll
@@ -869,7 +881,7 @@ Plan3 plan_split3(const GemmProblem* p, int nprob, int tile, bool apart, size_t 
 }
 
 hipError_t launch_group3(const GemmProblem* probs, int nprob, float* part, size_t part_bytes, hipStream_t stream) {
-  if (nprob == 1 && probs[0].M <= 8 && probs[0].sAk == 1 && probs[0].sBk == 1) {
+  if (nprob == 1 && probs[0].khead == 0 && probs[0].M <= 8 && probs[0].sAk == 1 && probs[0].sBk == 1) {
     const GemmProblem& p = probs[0];
     if (p.M == 1) launch_few_rows<1, 1>(p, stream);
     else if (p.M == 2) launch_few_rows<2, 1>(p, stream);
@@ -880,7 +892,12 @@ hipError_t launch_group3(const GemmProblem* probs, int nprob, float* part, size_
   int ma = -1, mb = -1;
   for (int i = 0; i < nprob; ++i) {
     const GemmProblem& p = probs[i];
-    const int a = split3_mode(p.A, p.sAm, p.sAk, p.M), b = split3_mode(p.B, p.sBn, p.sBk, p.N);
+    const int a = split3_mode(p.A, p.sAm, p.sAk, p.M);
+    int b = split3_mode(p.B, p.sBn, p.sBk, p.N);
+    if (p.khead) {
+      if (p.khead % KT3 != 0 || p.khead > p.K) return hipErrorInvalidValue;
+      if (split3_mode(p.Bhead, p.sBn, p.sBk, p.N) != b) b = LM_SCALAR;
+    }
     ma = (i == 0 || ma == a) ? a : LM_SCALAR;
     mb = (i == 0 || mb == b) ? b : LM_SCALAR;
     // per-lane offsets inside a tile of an operand are 32 bits wide
@@ -924,6 +941,7 @@ hipError_t launch_group3(const GemmProblem* probs, int nprob, float* part, size_
   return hipSuccess;
 }
 
+hipError_t launch_group_f32(const GemmProblem* probs, int nprob, hipStream_t stream);
 }  // namespace
 
 // Independent products in one launch.  `part` (16-byte aligned, part_bytes long, free until the stream has passed the
@@ -939,6 +957,35 @@ hipError_t launch_gemm_group(const GemmProblem* probs, int nprob, hipStream_t st
     const hipError_t e = launch_group3(probs, nprob, part, part_bytes, stream);
     if (e != hipErrorNotSupported) return e;
   }
+  // (that kernel knows no head: it is a product of its own, added to the rest)
+  GemmProblem body[kMaxGemmGroup];
+  int nbody = 0;
+  for (int i = 0; i < nprob; ++i) {
+    GemmProblem q = probs[i];
+    q.A += (long)q.khead * q.sAk;
+    q.K -= q.khead;
+    q.khead = 0;
+    if (q.K > 0) body[nbody++] = q;
+  }
+  if (nbody) {
+    const hipError_t e = launch_group_f32(body, nbody, stream);
+    if (e != hipSuccess) return e;
+  }
+  for (int i = 0; i < nprob; ++i)
+    if (probs[i].khead) {
+      GemmProblem q = probs[i];
+      q.B = q.Bhead;
+      if (q.khead < q.K) q.accumulate = 1;
+      q.K = q.khead;
+      q.khead = 0;
+      const hipError_t e = launch_group_f32(&q, 1, stream);
+      if (e != hipSuccess) return e;
+    }
+  return hipSuccess;
+}
+
+namespace {
+hipError_t launch_group_f32(const GemmProblem* probs, int nprob, hipStream_t stream) {
   GemmGroupArgs g;
   bool big = true;
   // one kernel instance serves the whole group: operands that cannot all take the same vector loader fall back to the
@@ -966,5 +1013,6 @@ hipError_t launch_gemm_group(const GemmProblem* probs, int nprob, hipStream_t st
   else launch_tile<1, 1>(ma, mb, start, g, stream);
   return hipGetLastError();
 }
+}  // namespace
 
 }  // namespace lstm

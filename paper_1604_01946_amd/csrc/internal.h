@@ -21,6 +21,10 @@ struct GemmProblem {
   int M, N, K;
   long sAm, sAk, sBk, sBn, ldc;
   int accumulate;
+  // The first khead k of B (a multiple of 16) lie here, with B's strides; B starts behind them.  The weight gradient of a
+  // recurrent matrix multiplies [h_init; h_0 .. h_{T-2}], of which the initial state is an array of its own.
+  const float* Bhead = nullptr;
+  int khead = 0;
 };
 constexpr int kMaxGemmGroup = 16;
 // A group of independent products executed by one launch (Section 2.6: the weight

@@ -221,6 +221,12 @@ int backward_persistent(int cell, const Dims& d, const float* x, const float* h0
     main_g[nm++] = GemmProblem{dA, in, dWl, (int)G, Il, (int)TB, 1, (long)G4, Il, 1, Il, 0};
     // dR: GRU rows r, z from the first two groups, rows n from the fourth (the gradient of R_n h); single gate: the first
     const int m1 = gru ? 2 * H : H;
+    if (d.T > 1 && h0 && B % 16 == 0) {  // the initial state's rows in front of the others: one product
+      const float* const hi = h0 + (size_t)l * BH;
+      main_g[nm++] = GemmProblem{dA, hl, dRl, m1, H, (int)TB, 1, (long)G4, H, 1, H, 0, hi, B};
+      if (gru) main_g[nm++] = GemmProblem{dA + 3 * H, hl, dRl + (size_t)2 * H * H, H, H, (int)TB, 1, (long)G4, H, 1, H, 0, hi, B};
+      return LSTM_OK;
+    }
     if (d.T > 1) {
       main_g[nm++] = GemmProblem{dA + (size_t)B * G4, hl, dRl, m1, H, (int)(TB - B), 1, (long)G4, H, 1, H, 0};
       if (gru)
@@ -332,9 +338,12 @@ int backward_impl(int cell, const Dims& d, const float* x, const float* h0, cons
     GemmProblem g[2];
     int ng = 0;
     g[ng++] = GemmProblem{da, in, dWl, (int)G, Il, (int)TB, 1, (long)G, Il, 1, Il, 0};
-    if (d.T > 1) g[ng++] = GemmProblem{dq + (size_t)B * G, hl, dRl, (int)G, H, (int)(TB - B), 1, (long)G, H, 1, H, 0};
+    const bool head = h0 && d.T > 1 && B % 16 == 0;  // the initial state's rows in front of the others: one product
+    if (head) g[ng++] = GemmProblem{dq, hl, dRl, (int)G, H, (int)TB, 1, (long)G, H, 1, H, 0, h0 + (size_t)l * BH, B};
+    else if (d.T > 1) g[ng++] = GemmProblem{dq + (size_t)B * G, hl, dRl, (int)G, H, (int)(TB - B), 1, (long)G, H, 1, H, 0};
     CK(launch_gemm_group(g, ng, s, part, part_bytes), "weight-gradient GEMMs");
-    if (h0) {
+    if (head) {
+    } else if (h0) {
       GemmProblem p{dq, h0 + (size_t)l * BH, dRl, (int)G, H, B, 1, (long)G, H, 1, H, d.T > 1 ? 1 : 0};
       CK(launch_gemm_group(&p, 1, s, part, part_bytes), "weight-gradient GEMM (initial state term)");
     } else if (d.T == 1) {

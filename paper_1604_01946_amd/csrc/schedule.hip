@@ -300,7 +300,9 @@ int weight_gradients_layers(const BwdArgs& a, const float* dA_all, int l0, int l
     float* dRl = a.dR + (size_t)l * G * H;
     if (nm + 2 > kMaxGemmGroup) CK(flush(main_p, nm), "weight-gradient GEMMs");
     main_p[nm++] = GemmProblem{dA, in, dWl, (int)G, Il, (int)TB, 1, (long)G, Il, 1, Il, 0};
-    if (d.T > 1) {
+    if (d.T > 1 && a.h0 && B % 16 == 0) {  // the initial state's rows in front of the others: one product
+      main_p[nm++] = GemmProblem{dA, r.h, dRl, (int)G, H, (int)TB, 1, (long)G, H, 1, H, 0, a.h0 + (size_t)l * B * H, B};
+    } else if (d.T > 1) {
       main_p[nm++] = GemmProblem{dA + (size_t)B * G, r.h, dRl, (int)G, H, (int)(TB - B), 1, (long)G, H, 1, H, 0};
       if (a.h0) {
         if (nt + 1 > kMaxGemmGroup) {

@@ -51,6 +51,7 @@ struct PersFwdArgs {
   int trace_block;
   int keep;           // wide kernel: 0 = inference call (no reserve wanted): only y, hT, cT are written
   float* dummy;       // pers_fwd_pp_kernel: 128 bytes of scratch that take the stores nobody wants
+  int* redo = nullptr;  // pers_fwd_pp3_kernel: set where a sum is infinite or NaN; pers_fwd_pp_kernel: run only if it is set
 };
 
 // ------------------------------------------------------------------ backward
@@ -171,6 +172,12 @@ hipError_t launch_pack_x32(const float* x, float* xin, int* flags, int L, int T,
 hipError_t launch_fwd_pp(int cell, int H, int grid, const PersFwdArgs& a, hipStream_t s);  // cell 0: LSTM, 1: GRU
 hipError_t launch_pack_state_pp(const float* h0, float* hx, int L, int T, int B, int H, int b0, int nsl, hipStream_t s);
 hipError_t launch_pack_x_pp(const float* x, float* xin, int T, int B, int I, int H, int b0, int nsl, hipStream_t s);
+
+// the same on the bf16 matrix cores with operands in three parts (persistent_pp3.hip)
+hipError_t launch_fwd_pp3(int cell, int H, int grid, const PersFwdArgs& a, hipStream_t s);
+hipError_t launch_redo_fwd_pp(const PersFwdArgs& a, const float* x, int counters, hipStream_t s);  // (persistent_pp.hip)
+hipError_t launch_pack_state_pp3(const float* h0, float* hx, int L, int T, int B, int H, int b0, int nsl, hipStream_t s);
+hipError_t launch_pack_x_pp3(const float* x, float* xin, int T, int B, int I, int H, int b0, int nsl, hipStream_t s);
 
 // backward counterpart: two chains of 16 rows per workgroup (batch half), 16x16x4 tiles; counters of H/16 lines per
 // (layer, step, half, chain), see persistent_bpp.hip

@@ -614,6 +614,12 @@ int forward_layers(const FwdArgs& a, int cell) {
   // LSTM with every layer multiplying its input in the kernel: the two half-slices of 32 rows take turns inside the
   // waves (pers_fwd_pp_kernel); LSTM_PINGPONG=0 keeps the one-chain kernel
   const bool pp = x_in_kernel && pp_ok;
+  // ... on the bf16 matrix cores from H = 256 on, wherever the copy of x in three parts finds room (half as large again, up
+  // to the scratch area): forward pass of L = 4, T = 100, H = 512, B = 64 0.93 -> 0.72 ms, tanh at H = 256, B = 128 0.52 ->
+  // 0.45.  At H = 128 a block is too short for the exchange (four layers, 256 rows: 0.42 -> 1.09), and at H = 256 with more
+  // than four layers in a launch the distance at which a layer follows the one below costs more than it saves (L = 8,
+  // B = 64: 0.58 -> 0.64; L = 4: 0.48 -> 0.48).
+  const bool pp3 = pp && (d.H == 512 || (d.H == 256 && d.L <= 4)) && (size_t)(d.T + 1) * ((size_t)(d.B + 63) / 64 * 64) * d.H * 6 <= a.w.scratch - a.w.P;
   if (!x_in_kernel) {
     ProfScope ps(LSTM_PHASE_FWD_INPUT_GEMM, s);
     GemmProblem p{a.x, a.W, P0, (int)TB, (int)G, d.I, d.I, 1, 1, d.I, (long)G, 0};
@@ -643,8 +649,13 @@ int forward_layers(const FwdArgs& a, int cell) {
     {
       ProfScope ps(LSTM_PHASE_FWD_PACK, s);
       const size_t counter_ints = pp ? (size_t)2 * (d.H / 16) * kFlagStride : (size_t)bp.NC * kFlagInts;
-      CK(launch_fill_zero(flags, (size_t)nsl * d.L * (d.T + 1) * counter_ints * 4, s), "zero step counters");
-      if (pp) {
+      const size_t counters = (size_t)nsl * d.L * (d.T + 1) * counter_ints;
+      k.redo = pp3 ? flags + counters : nullptr;  // (the counters of these kernels take half of their area)
+      CK(launch_fill_zero(flags, (counters + (pp3 ? 32 : 0)) * 4, s), "zero step counters");
+      if (pp3) {
+        CK(launch_pack_state_pp3(a.h0, hx, d.L, d.T, d.B, d.H, k.b0, nsl, s), "pack h0");
+        CK(launch_pack_x_pp3(a.x, P0, d.T, d.B, d.I, d.H, k.b0, nsl, s), "pack x");
+      } else if (pp) {
         CK(launch_pack_state_pp(a.h0, hx, d.L, d.T, d.B, d.H, k.b0, nsl, s), "pack h0");
         if (x_in_kernel) CK(launch_pack_x_pp(a.x, P0, d.T, d.B, d.I, d.H, k.b0, nsl, s), "pack x");
       } else if (wide) {
@@ -660,10 +671,15 @@ int forward_layers(const FwdArgs& a, int cell) {
     {  // recurrent products of every layer, input products of the layers above the first, and layer 0's when x is multiplied in the kernel
       const double rows = std::min(slice_rows * nsl, d.B - k.b0), per = 2.0 * G * rows * d.T;
       prof_flops(per * d.H * (2 * d.L - 1) + (x_in_kernel ? per * d.I : 0.0),
-                 pp ? "pers_fwd_pp_kernel" : (wide ? "pers_fwd32_kernel" : "pers_fwd_kernel"));
+                 pp3 ? "pers_fwd_pp3_kernel" : pp ? "pers_fwd_pp_kernel" : (wide ? "pers_fwd32_kernel" : "pers_fwd_kernel"));
     }
     hipError_t e = hipErrorInvalidValue;
-    if (pp) e = launch_fwd_pp(cell, d.H, grid * nsl, k, s);
+    if (pp3) {
+      e = launch_fwd_pp3(cell, d.H, grid * nsl, k, s);
+      // an infinite or NaN sum has no parts: the fp32 kernel runs the launch again (both end at once if nobody asked)
+      if (e == hipSuccess) e = launch_redo_fwd_pp(k, a.x, nsl * d.L * (d.T + 1) * 2 * (d.H / 16) * kFlagStride, s);
+      if (e == hipSuccess) e = launch_fwd_pp(cell, d.H, grid * nsl, k, s);
+    } else if (pp) e = launch_fwd_pp(cell, d.H, grid * nsl, k, s);
     else if (wide) e = launch_fwd_wide(cell, d.H, grid * nsl, k, s);
     else e = launch_fwd_narrow(d.H, bp, grid * nsl, k, s);
     CK(e, "persistent forward launch");

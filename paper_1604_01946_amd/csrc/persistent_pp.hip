@@ -64,6 +64,8 @@ __global__ __launch_bounds__(256) void pers_fwd_pp_kernel(const PersFwdArgs a) {
   __shared__ __attribute__((aligned(16))) float part[2][4][1024];  // [buffer][wave][gate][kk][n][4]
   __shared__ __attribute__((aligned(16))) float stage[4][6 * 64];  // per wave: i, f, o, c', c, h of its 8 rows x 8 units
 
+  if (a.redo && *a.redo == 0) return;  // (the kernel on the bf16 matrix cores has done it)
+
   int l, s;
   map_block(a.L, NS * a.nsl, l, s);
   const int sl = s / NS;
@@ -411,6 +413,28 @@ __global__ __launch_bounds__(256) void pack_x_pp_kernel(const float* __restrict_
   }
 }
 
+// What pers_fwd_pp_kernel needs before it repeats a launch of pers_fwd_pp3_kernel, if that one asked for it: counters at
+// zero, h0 and x in its own exchange layout.
+__global__ void redo_fwd_pp_kernel(const PersFwdArgs a, const float* __restrict__ x, int counters) {
+  if (*a.redo == 0) return;
+  const long id = (long)blockIdx.x * blockDim.x + threadIdx.x, step = (long)gridDim.x * blockDim.x;
+  const int H = a.H;
+  for (long e = id; e < counters; e += step) a.flags[e] = 0;
+  for (long e = id; e < (long)a.nsl * a.L * 64 * H; e += step) {
+    const int k = (int)(e % H), lb = (int)((e / H) % 64), l = (int)((e / ((long)H * 64)) % a.L);
+    const int sl = (int)(e / ((long)H * 64 * a.L)), bb = a.b0 + 64 * sl + lb;
+    a.hx[((((size_t)sl * a.L + l) * (a.T + 1)) * 2 + (lb >> 5)) * H * 32 + ((size_t)((k >> 3) * 2 + (k & 1)) * 32 + (lb & 31)) * 4 + ((k >> 1) & 3)] =
+        (a.h0 && bb < a.B) ? a.h0[((size_t)l * a.B + bb) * H + k] : 0.f;
+  }
+  float* const xin = const_cast<float*>(a.xin);
+  for (long e = id; e < (long)a.nsl * a.T * 64 * H; e += step) {
+    const int k = (int)(e % H), lb = (int)((e / H) % 64), t = (int)((e / ((long)H * 64)) % a.T);
+    const int sl = (int)(e / ((long)H * 64 * a.T)), bb = a.b0 + 64 * sl + lb;
+    xin[(((size_t)sl * (a.T + 1) + t + 1) * 2 + (lb >> 5)) * H * 32 + ((size_t)((k >> 3) * 2 + (k & 1)) * 32 + (lb & 31)) * 4 + ((k >> 1) & 3)] =
+        (bb < a.B && k < a.I) ? x[((size_t)t * a.B + bb) * a.I + k] : 0.f;
+  }
+}
+
 template <int HH, int CELL>
 hipError_t launch_pp(int grid, const PersFwdArgs& a, hipStream_t s) {
   constexpr int NK8 = HH / 32;
@@ -443,6 +467,11 @@ hipError_t launch_fwd_pp(int cell, int H, int grid, const PersFwdArgs& a, hipStr
   if (H == 256) return launch_pp<256, 0>(grid, a, s);
   if (H == 128) return launch_pp<128, 0>(grid, a, s);
   return hipErrorInvalidValue;
+}
+
+hipError_t launch_redo_fwd_pp(const PersFwdArgs& a, const float* x, int counters, hipStream_t s) {
+  hipLaunchKernelGGL(redo_fwd_pp_kernel, dim3(256), dim3(256), 0, s, a, x, counters);
+  return hipGetLastError();
 }
 
 hipError_t launch_pack_state_pp(const float* h0, float* hx, int L, int T, int B, int H, int b0, int nsl, hipStream_t s) {

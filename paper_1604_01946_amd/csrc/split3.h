@@ -39,6 +39,20 @@ __device__ __forceinline__ Split2 split3(float a, float b) {
   return s;
 }
 
+// The parts of eight values with consecutive k: what a lane feeds to a matrix instruction.
+__device__ __forceinline__ void split8(const float (&v)[8], bf16x8 (&p)[3]) {
+  uintx4 o[3];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const Split2 s = split3(v[2 * j], v[2 * j + 1]);
+    o[0][j] = s.h;
+    o[1][j] = s.m;
+    o[2][j] = s.l;
+  }
+#pragma unroll
+  for (int q = 0; q < 3; ++q) p[q] = __builtin_bit_cast(bf16x8, o[q]);
+}
+
 // acc += A * B for 16 (32x32 tile) k: the six products of the parts, smallest first
 __device__ __forceinline__ floatx16 mfma_split3(const bf16x8 (&a)[3], const bf16x8 (&b)[3], floatx16 acc) {
   acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[2], b[0], acc, 0, 0, 0);

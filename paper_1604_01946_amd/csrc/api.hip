@@ -51,7 +51,6 @@ const Knobs& knobs() {
     k.gemm_staged = env_is("LSTM_GEMM_STAGED", '1');
     k.gemm_split = !env_is("LSTM_GEMM_SPLIT", '0');
     k.tiny = !env_is("LSTM_TINY", '0');
-    k.large_pp = !env_is("LSTM_LARGE_PP", '0');
     k.large_ksplit = !env_is("LSTM_LARGE_KSPLIT", '0');
     k.rnn_pp = !env_is("RNN_PINGPONG", '0');
     k.micro = env_is("LSTM_MICRO", '0') ? 0 : (env_is("LSTM_MICRO", '2') ? 2 : 1);

@@ -10,7 +10,6 @@ struct Knobs {
   bool gemm_staged;          // LSTM_GEMM_STAGED=1: register-staged GEMM kernel everywhere
   bool rnn_pp;               // RNN_PINGPONG=0: the GRU and the single-gate cells on the one-chain wide kernels instead of the alternating ones
   bool large_ksplit;         // LSTM_LARGE_KSPLIT=0: a single slice at H = 1024 backward on 64 workgroups instead of 256
-  bool large_pp;             // LSTM_LARGE_PP=0: the one-chain forward kernel at H = 2048 instead of the alternating one
   int micro;                 // LSTM_MICRO=0: no pass runs as one workgroup; =2: every shape those kernels take does
   bool tiny;                 // LSTM_TINY=0: a single sequence (B = 1) on the narrow kernels instead of the flag-in-data ones
   bool gemm_split;           // LSTM_GEMM_SPLIT=0: no K slices for a product's last partial round of tiles

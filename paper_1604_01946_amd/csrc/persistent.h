@@ -10,7 +10,6 @@
 //   persistent_bpp.hip    pers_bwd_pp_kernel: two quarter-slices of 16 rows alternating on the matrix cores
 //   persistent_tiny.hip   pers_fwd_tiny_kernel / pers_bwd_tiny_kernel: B = 1, the exchanged values are their own flags
 //   persistent_large.hip  pers_fwdL_kernel / pers_bwdL_kernel: one layer per launch, H = 1024 / 2048
-//   persistent_large_pp.hip  pers_fwdLpp_kernel: the LSTM forward kernel of H = 2048 with two alternating chains per slice
 //   persistent.hip        host side: residency, launches, which shapes run where, layer groups, batch slices
 #pragma once
 #include "schedule.h"
@@ -117,6 +116,7 @@ struct PersFwdLArgs {
   int full_fences;
   long long* trace;
   int trace_block;
+  int* redo = nullptr;  // S3 variant: set where a sum is infinite or NaN; the other: run only if it is set
 };
 
 struct PersBwdLArgs {
@@ -143,6 +143,8 @@ struct PersBwdLArgs {
   int full_fences;
   long long* trace;
   int trace_block;
+  float* X3 = nullptr;  // S3 variant: third part of the exchanged gate gradients, [nsl][T][NBK][2*UB*32 floats]
+  int* redo = nullptr;  // as in PersFwdLArgs
 };
 
 // Batch tiles per chain and number of chains.  One chain is the default: on MI355X two chains
@@ -188,12 +190,12 @@ hipError_t launch_bwd_pp(int cell, int H, const PersBwdArgs& a, int nbh, hipStre
 hipError_t launch_fwd_tiny(int H, const PersFwdArgs& a, hipStream_t s);
 hipError_t launch_bwd_tiny(int H, const PersBwdArgs& a, hipStream_t s);
 
-hipError_t launch_fwdL_any(int H, int cell, const PersFwdLArgs& k, hipStream_t s);
-hipError_t launch_bwdL_any(int H, int cell, const PersBwdLArgs& k, hipStream_t s);
-hipError_t launch_pack_stateL(const float* h0, float* hx, int T, int B, int H, int b0, int nsl, hipStream_t s);
-// persistent_large_pp.hip: the LSTM forward kernel of the same shapes with two alternating chains of 16 rows per slice
-hipError_t launch_fwdLpp(int cell, int H, const PersFwdLArgs& k, hipStream_t s);  // cell: 0 LSTM, 1 GRU, 2 ReLU, 3 tanh
-hipError_t launch_pack_stateLpp(const float* h0, float* hx, int T, int B, int H, int b0, int nsl, hipStream_t s);
-size_t fwdLpp_flag_ints();  // counter ints per (slice, step)
+// s3: the variant on the bf16 matrix cores
+hipError_t launch_fwdL_any(int H, int cell, const PersFwdLArgs& k, hipStream_t s, bool s3);
+hipError_t launch_bwdL_any(int H, int cell, const PersBwdLArgs& k, hipStream_t s, bool s3);
+hipError_t launch_redo_bwdL(const PersBwdLArgs& k, int counters, hipStream_t s);
+hipError_t launch_pack_stateL(const float* h0, float* hx, int T, int B, int H, int b0, int nsl, const int* only_if, int* flags,
+                              int counters, hipStream_t s);
+hipError_t launch_pack_stateL3(const float* h0, float* hx, int T, int B, int H, int b0, int nsl, hipStream_t s);
 
 }  // namespace lstm

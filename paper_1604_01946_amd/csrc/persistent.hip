@@ -347,7 +347,6 @@ int run_forward_persistent_large(const FwdArgs& a, int cell) {
   int cap = di.cus / (d.H / 8);
   if (cap < 1) cap = 1;
   if (cap > 4) cap = 4;
-  const bool lpp = (cell == 0 || knobs().rnn_pp) && d.H == 2048 && knobs().large_pp;  // the LSTM at H = 2048: two alternating chains of 16 rows per slice
   for (int l = 0; l < d.L; ++l) {
     const int Il = in_dim(d, l);
     const float* in = l == 0 ? a.x : a.reserve + (size_t)(l - 1) * rstride + res_h_offset(cell, TB, d.H);
@@ -360,12 +359,11 @@ int run_forward_persistent_large(const FwdArgs& a, int cell) {
     }
    for (int s0 = 0; s0 < slices; s0 += cap) {
     const int nsl = slices - s0 < cap ? slices - s0 : cap;
+    const int counters = nsl * (d.T + 1) * 16 * kFlagStride;
     {
       ProfScope ps(LSTM_PHASE_FWD_PACK, s);
-      const size_t counter_ints = lpp ? fwdLpp_flag_ints() : (size_t)16 * kFlagStride;
-      CK(launch_fill_zero(flags, (size_t)nsl * (d.T + 1) * counter_ints * 4, s), "zero step counters");
-      if (lpp) CK(launch_pack_stateLpp(a.h0 ? a.h0 + (size_t)l * BH : nullptr, hx, d.T, d.B, d.H, 32 * s0, nsl, s), "pack h0");
-      else CK(launch_pack_stateL(a.h0 ? a.h0 + (size_t)l * BH : nullptr, hx, d.T, d.B, d.H, 32 * s0, nsl, s), "pack h0");
+      CK(launch_fill_zero(flags, ((size_t)counters + 32) * 4, s), "zero step counters");
+      CK(launch_pack_stateL3(a.h0 ? a.h0 + (size_t)l * BH : nullptr, hx, d.T, d.B, d.H, 32 * s0, nsl, s), "pack h0");
     }
     PersFwdLArgs k;
     k.b0 = 32 * s0; k.nsl = nsl;
@@ -378,12 +376,15 @@ int run_forward_persistent_large(const FwdArgs& a, int cell) {
     k.hT = a.hT ? a.hT + (size_t)l * BH : nullptr;
     k.cT = a.cT ? a.cT + (size_t)l * BH : nullptr;
     k.T = d.T; k.B = d.B; k.spin_limit = spin_limit(); k.full_fences = full_fences();
-    k.trace = (g_trace_bytes >= (size_t)d.T * 64 * (lpp ? 2 : 1)) ? g_trace_buf : nullptr;
+    k.trace = (g_trace_bytes >= (size_t)d.T * 64) ? g_trace_buf : nullptr;
     k.trace_block = g_trace_block;
     ProfScope ps(LSTM_PHASE_FWD_RECURRENCE, s);
-    prof_flops(2.0 * G * d.H * std::min(32 * nsl, d.B - 32 * s0) * d.T, lpp ? "pers_fwdLpp_kernel" : "pers_fwdL_kernel");
-    if (lpp) CK(launch_fwdLpp(cell, d.H, k, s), "persistent forward launch (large H, alternating chains)");
-    else CK(launch_fwdL_any(d.H, cell, k, s), "persistent forward launch (large H)");
+    prof_flops(2.0 * G * d.H * std::min(32 * nsl, d.B - 32 * s0) * d.T, "pers_fwdL_kernel");
+    k.redo = flags + counters;
+    CK(launch_fwdL_any(d.H, cell, k, s, true), "persistent forward launch (large H)");
+    // an infinite or NaN sum has no parts: the fp32 kernel runs the launch again (both end at once if nobody asked)
+    CK(launch_pack_stateL(a.h0 ? a.h0 + (size_t)l * BH : nullptr, hx, d.T, d.B, d.H, 32 * s0, nsl, k.redo, flags, counters, s), "pack h0");
+    CK(launch_fwdL_any(d.H, cell, k, s, false), "persistent forward launch (large H, repeated)");
    }
   }
   return LSTM_OK;
@@ -420,6 +421,14 @@ int run_backward_persistent_large(const BwdArgs& a, int cell, bool* bias_done, L
   float* Pp = X + (size_t)maxsl * d.T * NBK * (4 * UB * 32);
   int* flagsA = reinterpret_cast<int*>(a.ws + a.w.flags);
   int* flagsP = flagsA + (size_t)maxsl * d.T * NBK * kFlagInts;
+  const int counters = (int)((size_t)2 * maxsl * d.T * NBK * kFlagInts);
+  // On the bf16 matrix cores wherever the third part of the exchanged values finds room at the end of the reserve
+  // stand-in (24 bytes per row, layer and unit, of which 256 per slice of 32 rows are needed: from 11 rows of one layer on);
+  // the rest of that area takes partial tiles of the products on the side stream.
+  const size_t x3_bytes = (size_t)maxsl * d.T * NBK * (2 * UB * 32) * sizeof(float), resv_bytes = a.w.total - a.w.resv;
+  const bool s3 = x3_bytes <= resv_bytes;
+  float* const X3 = reinterpret_cast<float*>(a.ws + a.w.resv + ((resv_bytes - (s3 ? x3_bytes : 0)) & ~(size_t)255));
+  const Scratch side_part{reinterpret_cast<float*>(a.ws + a.w.resv), (resv_bytes - (s3 ? x3_bytes : 0)) & ~(size_t)255};
   const bool bias_in_kernel = slices == 1;
   // A single slice at H = 1024 would occupy 64 CUs: the tiles' K is cut in four, 256 workgroups (LSTM_LARGE_KSPLIT=0:
   // not); two slices of a single layer cut it in two (with more layers the idle CUs are used by the weight gradients
@@ -450,13 +459,13 @@ int run_backward_persistent_large(const BwdArgs& a, int cell, bool* bias_done, L
       const int nsl = slices - s0 < cap ? slices - s0 : cap;
       {
         ProfScope ps(LSTM_PHASE_BWD_PACK, s);
-        CK(launch_fill_zero(flagsA, (size_t)2 * maxsl * d.T * NBK * kFlagInts * 4, s), "zero step counters");
+        CK(launch_fill_zero(flagsA, ((size_t)counters + (s3 ? 32 : 0)) * 4, s), "zero step counters");
       }
       if (overlap && pending >= 0) {
         CK(hipEventRecord(g_side_ev[0], s), "fork to the side stream");
         CK(hipStreamWaitEvent(g_side_stream, g_side_ev[0], 0), "side stream wait");
-        const int st = cell == 0 ? weight_gradients_layers(a, dA_all, pending, pending + 1, g_side_stream, true, bias_in_kernel, backward_scratch(a.ws, a.w))
-                                 : lg->fn(lg->ctx, pending, g_side_stream, backward_scratch(a.ws, a.w));
+        const int st = cell == 0 ? weight_gradients_layers(a, dA_all, pending, pending + 1, g_side_stream, true, bias_in_kernel, side_part)
+                                 : lg->fn(lg->ctx, pending, g_side_stream, side_part);
         if (st != LSTM_OK) return st;
         pending = -1;
       }
@@ -472,13 +481,19 @@ int run_backward_persistent_large(const BwdArgs& a, int cell, bool* bias_done, L
       k.dh0 = a.dh0 ? a.dh0 + (size_t)l * BH : nullptr;
       k.dc0 = a.dc0 ? a.dc0 + (size_t)l * BH : nullptr;
       k.db = bias_in_kernel ? a.db + (size_t)l * GW : nullptr;
+      k.X3 = s3 ? X3 : nullptr;
+      k.redo = s3 ? flagsA + counters : nullptr;
       k.flagsA = flagsA; k.flagsP = flagsP; k.watchdog = g_watch_dev;
       k.T = d.T; k.B = d.B; k.b0 = 32 * s0; k.nsl = nsl; k.ks = ks; k.spin_limit = spin_limit(); k.full_fences = full_fences();
       k.trace = (g_trace_bytes >= (size_t)d.T * 64) ? g_trace_buf : nullptr;
       k.trace_block = g_trace_block;
       ProfScope ps(LSTM_PHASE_BWD_RECURRENCE, s);
       prof_flops(2.0 * GW * d.H * std::min(32 * nsl, d.B - 32 * s0) * d.T, "pers_bwdL_kernel");
-      CK(launch_bwdL_any(d.H, cell, k, s), "persistent backward launch (large H)");
+      CK(launch_bwdL_any(d.H, cell, k, s, s3), "persistent backward launch (large H)");
+      if (s3) {  // an infinite or NaN sum has no parts: the fp32 kernel runs the launch again (both end at once if nobody asked)
+        CK(launch_redo_bwdL(k, counters, s), "zero step counters");
+        CK(launch_bwdL_any(d.H, cell, k, s, false), "persistent backward launch (large H, repeated)");
+      }
     }
     float* din = l > 0 ? dxb + (size_t)l * TB * d.H : a.dx;
     if (din) {  // the GRU's gradient with respect to W_n x is its third group: the first GW columns are the ones W multiplies

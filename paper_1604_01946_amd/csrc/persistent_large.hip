@@ -2,6 +2,7 @@
 // per launch with the layer's recurrent matrix spread over all CUs (registers + LDS).
 #include "../../include/lstm.h"
 #include "persistent_dev.h"
+#include "split3.h"
 
 namespace lstm {
 namespace {
@@ -10,8 +11,7 @@ namespace {
 // Section 4 of arXiv 1604.01946 puts the limit of the persistent approach at the capacity of the
 // on-chip memory.  On MI355X the 256 CUs together hold 128 MB of registers and 40 MB of LDS, so a
 // whole [4H x H] recurrent matrix of H = 2048 (64 MiB) fits: every workgroup keeps the 32 rows of
-// 8 hidden units (4 gates x 8 units x H floats = 256 KB) for all T steps, half of it in VGPRs and half
-// in LDS, exactly the split of pers_bwd32_kernel.  One launch runs one layer (all CUs are needed for
+// 8 hidden units (4 gates x 8 units x H floats = 256 KB) for all T steps, in VGPRs and LDS.  One launch runs one layer (all CUs are needed for
 // it, so the layers cannot overlap); the layer's input projection is a batched GEMM before it, as for
 // layer 0 above.  Per step a workgroup multiplies its [32 x H] slice by h_{t-1} ([H x 32 batch rows],
 // read from the exchange slot), K split over the four waves, and finalises 8 units x 32 batch rows.
@@ -19,19 +19,36 @@ namespace {
 // CELL as in pers_fwd32_kernel (0 LSTM, 1 GRU, 2 / 3 single gate with ReLU / tanh).  Only recurrent weights live here
 // (the input projection P is a batched product), so the GRU's four row groups are r, z, an empty one and R_n, and P's
 // third block (W_n x) is added in the epilogue; the single gate uses the first group alone.
-template <int HH, int CELL>
+// S3, the variant that every call runs: the products on the bf16 matrix cores, weights and h_t in three bf16 parts
+// (split3.h).  A wave's share of a step is 6 * H / 64 matrix instructions of 32 cycles (6144 at H = 2048) instead of
+// H / 8 of 64 (16384), against 3 * H / 64 requests for its operand instead of H / 32.  The weights are 384 KB per
+// workgroup at H = 2048: 22 groups of 16 k per wave in registers (264), 10 in LDS (120 KB); at H = 1024 all are in
+// registers (192).  The exchange slot holds H x 32 x 3 bf16, part p of the 8 k = 8 k8 .. of batch row n as the 16-byte
+// piece (p * H/8 + k8) * 32 + n.  The waves of the first half of K hold their weights negated and their sums are
+// subtracted (the bf16 instructions cut low bits off downwards: the bias cancels).  A sum that is infinite or NaN raises
+// *a.redo; the fp32 kernel, launched behind, ends at once or runs the launch again.
+// What is left of a step is mostly the exchange: 5.4 us for 64 rows at H = 1024 (6.2 with fp32 products), and the pass
+// forward of one layer, T = 64, with its input projection took at H = 2048 0.92 ms for 32 rows and 0.46 ms for one row,
+// against 1.03 and 0.64 ms for fp32 products with two alternating chains of 16 rows per workgroup, the kernel that ran
+// there before.  Requests 8 groups ahead: 6 and fewer cost 10 % at 64 rows, 16 cost 9 % at 20 rows of two layers.
+template <int HH, int CELL, bool S3 = false>
 __global__ __launch_bounds__(256) void pers_fwdL_kernel(const PersFwdLArgs a) {
+  if (!S3 && a.redo && *a.redo == 0) return;
   constexpr int H = HH, NG = CELL == 0 ? 4 : (CELL == 1 ? 3 : 1), G = NG * H, NS = H / 8;  // G: rows of R, bias, P
   constexpr int NB8 = H / 32;                // 8-k groups per wave
   constexpr int KPW = H / 8;                 // k-pairs per wave
   constexpr int RP = KPW < 128 ? KPW : 128;  // k-pairs whose weights live in registers
   constexpr int LP = KPW - RP;               // k-pairs whose weights live in LDS
   constexpr int DEPTH = NB8 < 16 ? NB8 : 16;
+  constexpr int NB16 = NB8 / 2, DEPTH3 = 8;  // S3: 16-k groups per wave, groups requested ahead
+  constexpr int RG = NB16 < 22 ? NB16 : 22;  // S3: groups with weights in registers
+  constexpr int LG = NB16 - RG;              // S3: groups with weights in LDS
+  constexpr size_t SLOT = S3 ? (size_t)HH * 48 : (size_t)HH * 32;  // floats per exchange slot
   extern __shared__ __attribute__((aligned(16))) float smem[];
   float* const part = smem;         // [4 waves][16 regs][64 lanes]
-  float* const xs = smem + 4096;    // [256]: this step's h slice in exchange order
-  float* const ro = smem + 4352;    // [6 arrays][32 batch rows][8 units]
-  float* const wl = smem + 6144;    // [4 waves][LP][64 lanes]
+  float* const xs = smem + 4096;    // [256] (S3: [384]): this step's h slice in exchange order
+  float* const ro = smem + 4480;    // [6 arrays][32 batch rows][8 units]
+  float* const wl = smem + 6144;    // [4 waves][LP][64 lanes] (S3: [4 waves][LG][3 parts][64 lanes][4])
 
   const int sl = blockIdx.x / NS, s = blockIdx.x % NS, u0 = 8 * s;
   const int T = a.T, B = a.B, b0 = a.b0 + 32 * sl;
@@ -42,13 +59,34 @@ __global__ __launch_bounds__(256) void pers_fwdL_kernel(const PersFwdLArgs a) {
   // then a scalar base + the lane's fixed offset + an immediate (vector address arithmetic costs a wave that runs matrix
   // instructions back to back its full issue time, scalar arithmetic nothing)
   const int rot = 4 * (((int)(blockIdx.x >> 3) * (NB8 / 32 > 0 ? NB8 / 32 : 1) + 2 * __builtin_amdgcn_readfirstlane(wave)) & (NB8 / 4 - 1));
-  float* const hx = a.hx + (size_t)sl * (T + 1) * H * 32;
+  const int rot3 = 4 * (((int)(blockIdx.x >> 3) + 2 * __builtin_amdgcn_readfirstlane(wave)) & (NB16 / 4 - 1));
+  float* const hx = a.hx + (size_t)sl * (T + 1) * SLOT;
   int* const flags = a.flags + (size_t)sl * (T + 1) * 16 * kFlagStride;
 
   // ---- weights: A operand row rho = lane%32 = (gate rho/8, unit rho%8); register / LDS entry i covers
   //      k = wave*H/4 + 8*((i/4 + rot) mod NB8) + 2*(i%4) + kk
-  float wreg[RP];
-  {
+  float wreg[S3 ? 1 : RP];
+  bf16x8 w3[S3 ? RG : 1][3];
+  if constexpr (S3) {
+    const int grp = n >> 3;
+    const int gate = CELL >= 2 ? 0 : ((CELL == 1 && grp == 3) ? 2 : grp);
+    const bool live = CELL == 0 || (CELL == 1 ? grp != 2 : grp == 0);
+    const float* src = a.R + ((size_t)gate * H + u0 + (n & 7)) * H + (size_t)wave * (H / 4) + 8 * kk;
+    const float sgn = wave < 2 ? -1.f : 1.f;
+#pragma unroll
+    for (int i = 0; i < NB16; ++i) {
+      float v[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = live ? sgn * src[16 * ((i + rot3) & (NB16 - 1)) + j] : 0.f;
+      bf16x8 q[3];
+      split8(v, q);
+#pragma unroll
+      for (int z = 0; z < 3; ++z) {
+        if (i < RG) w3[i < RG ? i : 0][z] = q[z];
+        else reinterpret_cast<uintx4*>(wl)[(((size_t)wave * LG + (i - RG)) * 3 + z) * 64 + lane] = __builtin_bit_cast(uintx4, q[z]);
+      }
+    }
+  } else {
     const int grp = n >> 3;
     const int gate = CELL >= 2 ? 0 : ((CELL == 1 && grp == 3) ? 2 : grp);
     const bool live = CELL == 0 || (CELL == 1 ? grp != 2 : grp == 0);
@@ -78,14 +116,15 @@ __global__ __launch_bounds__(256) void pers_fwdL_kernel(const PersFwdLArgs a) {
   float* const res_gates = CELL == 0 ? a.res : a.res + TB * H;  // the four saved arrays [T][B][4H] (LSTM, GRU)
   float* const res_c = a.res + TB * 4 * H;                       // LSTM only
   float* const res_h = CELL == 0 ? a.res + TB * 5 * H : a.res;
-  auto slot = [&](int st) { return hx + (size_t)st * H * 32; };
+  auto slot = [&](int st) { return hx + (size_t)st * SLOT; };
+  float odd = 0.f;  // zero unless a sum is infinite or NaN
 
   Waiter w{a.watchdog, a.spin_limit, false, a.full_fences};
   const Tracer tr{((int)blockIdx.x == a.trace_block) ? a.trace : nullptr};
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // once: drop whatever earlier launches left in L1/L2
   __syncthreads();                                    // LDS weights are in place
 
-  int rv = rot;
+  int rv = S3 ? rot3 : rot;
   for (int t = 0; t < T; ++t) {
     tr.mark(t, 0);
     hide(rv);  // keeps the rotated offsets next to their loads
@@ -98,7 +137,45 @@ __global__ __launch_bounds__(256) void pers_fwdL_kernel(const PersFwdLArgs a) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.f;
     float pnx[4];
-    {
+    auto next_projection = [&]() {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        pnx[q] = (valid && t + 1 < T && q < NG) ? a.P[((size_t)(t + 1) * B + bb) * G + q * H + u0 + uj] : 0.f;
+    };
+    if constexpr (S3) {
+      const char* const src = reinterpret_cast<const char*>(slot(t)) + (size_t)__builtin_amdgcn_readfirstlane(wave) * NB16 * 1024;
+      bf16x8 bv[NB16][3], al[NB16][3];
+      unsigned lo = lane * 16;
+      asm volatile("" : "+v"(lo));
+      auto ldb = [&](int g) {
+        const char* const sb = src + (size_t)(4 * (((g >> 2) + (rv >> 2)) & (NB16 / 4 - 1))) * 1024;
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+          bv[g][p] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uintx4*>(sb + (size_t)p * H * 64 + lo + (g & 3) * 1024));
+      };
+      auto ldw = [&](int g) {
+        if (g >= RG && g < NB16) {
+#pragma unroll
+          for (int p = 0; p < 3; ++p)
+            al[g][p] = __builtin_bit_cast(bf16x8, reinterpret_cast<const uintx4*>(wl)[(((size_t)wave * LG + (g - RG)) * 3 + p) * 64 + lane]);
+        }
+      };
+#pragma unroll
+      for (int g = 0; g < DEPTH3; ++g) ldb(g);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int g = 0; g < NB16; ++g) {
+        if (g + DEPTH3 < NB16) ldb(g + DEPTH3);
+        ldw(g + 2);
+        if (g == NB16 - DEPTH3) {  // behind the last exchange load of this step
+          next_projection();
+          lo = lane * 16;
+          asm volatile("" : "+v"(lo));
+        }
+        acc = mfma_split3(g < RG ? w3[g < RG ? g : 0] : al[g], bv[g], acc);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    } else {
       const char* const src = reinterpret_cast<const char*>(slot(t) + (size_t)__builtin_amdgcn_readfirstlane(wave) * NB8 * 256);
       floatx4 bv[NB8];
       floatx4 al[NB8];
@@ -121,9 +198,7 @@ __global__ __launch_bounds__(256) void pers_fwdL_kernel(const PersFwdLArgs a) {
         if (g + DEPTH < NB8) ldb(g + DEPTH);
         if (g + 2 < NB8) ldw(g + 2);
         if (g == NB8 - DEPTH) {  // next step's input projection, behind the last exchange load of this step
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-            pnx[q] = (valid && t + 1 < T && q < NG) ? a.P[((size_t)(t + 1) * B + bb) * G + q * H + u0 + uj] : 0.f;
+          next_projection();
           lo = lane * 16;
           asm volatile("" : "+v"(lo));
         }
@@ -145,8 +220,11 @@ __global__ __launch_bounds__(256) void pers_fwdL_kernel(const PersFwdLArgs a) {
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       const int r = 4 * g + wave;
-      sg[g] = (part[(0 * 16 + r) * 64 + lane] + part[(1 * 16 + r) * 64 + lane]) +
-              (part[(2 * 16 + r) * 64 + lane] + part[(3 * 16 + r) * 64 + lane]) + pin[g] + c_bias[g];
+      const float lo2 = part[(0 * 16 + r) * 64 + lane] + part[(1 * 16 + r) * 64 + lane];
+      const float hi2 = part[(2 * 16 + r) * 64 + lane] + part[(3 * 16 + r) * 64 + lane];
+      const float sum = S3 ? hi2 - lo2 : lo2 + hi2;
+      if (S3) odd += sum * 0.f;
+      sg[g] = sum + pin[g] + c_bias[g];
     }
     float gi, gf, go, gg, cv, hv;
     if (CELL == 0) {
@@ -165,9 +243,21 @@ __global__ __launch_bounds__(256) void pers_fwdL_kernel(const PersFwdLArgs a) {
       gi = gf = go = gg = cv = 0.f;
       hv = CELL == 3 ? tanhf_dev(sg[0]) : fmaxf(sg[0], 0.f);
     }
-    xs[((uj & 1) * 32 + n) * 4 + (uj >> 1)] = valid ? hv : 0.f;
-    __syncthreads();
-    if (threadIdx.x < 64)
+    if constexpr (S3) {  // [part][batch row][unit]
+      const Split2 s2 = split3(valid ? hv : 0.f, 0.f);
+      unsigned short* const o = reinterpret_cast<unsigned short*>(xs) + n * 8 + uj;
+      o[0] = (unsigned short)s2.h;
+      o[256] = (unsigned short)s2.m;
+      o[512] = (unsigned short)s2.l;
+      __syncthreads();
+      if (threadIdx.x < 96)
+        xstore4(slot(t + 1) + (size_t)(threadIdx.x >> 5) * H * 16 + (size_t)s * 128 + 4 * (threadIdx.x & 31),
+                *reinterpret_cast<const floatx4*>(xs + 4 * threadIdx.x));
+    } else {
+      xs[((uj & 1) * 32 + n) * 4 + (uj >> 1)] = valid ? hv : 0.f;
+      __syncthreads();
+    }
+    if (!S3 && threadIdx.x < 64)
       xstore4(slot(t + 1) + (size_t)s * 256 + 4 * threadIdx.x, *reinterpret_cast<const floatx4*>(xs + 4 * threadIdx.x));
     tr.mark(t, 5);
     signal(flags + ((size_t)16 * (t + 1) + (s & 15)) * kFlagStride, a.full_fences);  // publish h_t (the barrier also protects `part` and `xs`)
@@ -205,11 +295,32 @@ __global__ __launch_bounds__(256) void pers_fwdL_kernel(const PersFwdLArgs a) {
 #pragma unroll
     for (int g = 0; g < 4; ++g) pin[g] = pnx[g];
   }
+  if (S3 && odd != 0.f) *a.redo = 1;  // (every writer writes the same)
+}
+
+// The same for its S3 variant: one piece of 8 k per thread.
+__global__ void pack_stateL3_kernel(const float* __restrict__ h0, float* __restrict__ hx, int T, int B, int H, int b0, int nsl) {
+  const long cnt = (long)nsl * 32 * (H / 8);
+  for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < cnt; e += (long)gridDim.x * blockDim.x) {
+    const int k8 = (int)(e % (H / 8)), lb = (int)((e / (H / 8)) % 32), sl = (int)(e / ((long)(H / 8) * 32));
+    const int bb = b0 + 32 * sl + lb;
+    float v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = (h0 && bb < B) ? h0[(size_t)bb * H + 8 * k8 + j] : 0.f;
+    bf16x8 p[3];
+    split8(v, p);
+    uintx4* const o = reinterpret_cast<uintx4*>(hx + (size_t)sl * (T + 1) * H * 48) + (size_t)k8 * 32 + lb;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) o[(size_t)q * H * 4] = __builtin_bit_cast(uintx4, p[q]);
+  }
 }
 
 // h0 [B][H] of one layer (zeros if null) -> exchange slot 0 of every slice in the layout of pers_fwdL_kernel, all 32 batch columns.
+// For a launch that is repeated on request: nothing happens where the word at `only_if` is zero, else `flags` are zeroed too.
 __global__ void pack_stateL_kernel(const float* __restrict__ h0, float* __restrict__ hx, int T, int B, int H, int b0,
-                                   int nsl) {
+                                   int nsl, const int* only_if, int* flags, int counters) {
+  if (*only_if == 0) return;
+  for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < counters; e += (long)gridDim.x * blockDim.x) flags[e] = 0;
   const long cnt = (long)nsl * 32 * H;
   for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < cnt; e += (long)gridDim.x * blockDim.x) {
     const int k = (int)(e % H), lb = (int)((e / H) % 32), sl = (int)(e / ((long)H * 32));
@@ -244,8 +355,18 @@ __global__ void pack_stateL_kernel(const float* __restrict__ h0, float* __restri
 // KS > 1 (a single slice at H = 1024, where NBK x NBK workgroups would leave three quarters of the CUs idle): the tile's
 // K = 4*UB is cut into KS parts, each on a workgroup of its own (ks, i, j); a block's partial sums are then NBK * KS, and
 // the workgroups with ks = 0 finalise as before while the others go straight on to wait for the next step's gradients.
-template <int HH, int CELL, int KS>
+// S3: the products on the bf16 matrix cores, weights and gate gradients in three bf16 parts (split3.h).  A wave's share of
+// a step is 192 / KS matrix instructions of 32 cycles (6144) instead of 256 of 64 (16384), against 96 requests for the
+// operand instead of 64.  A tile's weights are 384 KB: 22 groups of 16 k per wave in registers (264), 10 in LDS (120 KB).
+// A dA slot holds three parts of piece (k8, n), 8 bf16 = the 8 units of octet k8 / 4 and gate k8 % 4; the first two parts
+// are where the fp32 values would be, the third lies in an area of its own (a.X3).  The groups of the second half of K
+// have negated weights and a sum of their own, which is subtracted (the bf16 instructions cut low bits off downwards: the
+// bias cancels).  An infinite or NaN sum raises *a.redo, and the kernel without S3 runs the launch again.
+// A step takes 10.6 us at H = 2048, B = 32 (fp32 products 13.2), 11.6 us at H = 1024, B = 128 (14.2) and, with KS = 2, 10 us
+// instead of 11.5 at two layers of 1024, B = 20: two synchronisation hops are what remains.
+template <int HH, int CELL, int KS, bool S3 = false>
 __global__ __launch_bounds__(256) void pers_bwdL_kernel(const PersBwdLArgs a) {
+  if (!S3 && a.redo && *a.redo == 0) return;
   constexpr int H = HH, G = 4 * H, UB = 128, NBK = H / UB;
   constexpr int NG = CELL == 0 ? 4 : (CELL == 1 ? 3 : 1);  // gate blocks of R and db
   constexpr int UF = UB / NBK;               // units a workgroup finalises: 8 or 16
@@ -255,6 +376,10 @@ __global__ __launch_bounds__(256) void pers_bwdL_kernel(const PersBwdLArgs a) {
   constexpr int RP = KS > 1 ? KP : (UF == 16 ? 136 : 128);  // k-pairs with weights in registers (more where the staging arrays are larger)
   constexpr int LP = KP - RP;                // k-pairs with weights in LDS
   constexpr int DEPTH = NG8 < 16 ? NG8 : 16;
+  constexpr int NG16 = NG8 / 2;               // S3: 16-k groups
+  constexpr int RG = NG16 < 22 ? NG16 : 22;  // S3: groups with weights in registers
+  constexpr int LG = NG16 - RG;              // S3: groups with weights in LDS
+  constexpr int DEPTH3 = 6;                   // S3: groups requested ahead (more of them spill at UF = 16)
   constexpr int NPART = NBK * KS;            // partial sums of an output block
   constexpr int kPauseA = 16, kPauseP = 32;  // pauses before the first look at a counter, in units of 64 cycles
   static_assert(NBK % kFlagSub == 0, "arrivals must spread evenly over the counter lines");
@@ -262,8 +387,8 @@ __global__ __launch_bounds__(256) void pers_bwdL_kernel(const PersBwdLArgs a) {
   extern __shared__ __attribute__((aligned(16))) float smem[];
   float* const stage = smem;              // [UB][32] partial sums of this step; also the bias-gradient reduction
   float* const xsA = smem + 4096;         // [UF/8 octets][4 gates][256] gate gradients of the finalised units, exchange order
-  float* const ro = xsA + 1024 * CPT;     // [4 gates][32 batch rows][UF units] the same in standard order
-  float* const wl = ro + 128 * UF;        // [4 waves][LP][64 lanes]; 152 KB in all
+  float* const ro = xsA + (S3 ? 1536 : 1024) * CPT;  // [4 gates][32 batch rows][UF units] the same in standard order
+  float* const wl = ro + 128 * UF;        // [4 waves][LP][64 lanes]; 152 KB in all (S3: [4 waves][LG][3 parts][64 lanes][4], 156 KB)
 
   const int sl = blockIdx.x / (NBK * NBK * KS), bid = blockIdx.x % (NBK * NBK), ks = (blockIdx.x / (NBK * NBK)) % KS;
   const int i = bid / NBK, j = bid % NBK;
@@ -277,8 +402,29 @@ __global__ __launch_bounds__(256) void pers_bwdL_kernel(const PersBwdLArgs a) {
 
   // ---- weights: A operand row n = output unit UB*j + 32*wave + n; entry p covers
   //      k = 8*k8 + 2*(p%4) + kk with k8 = (p/4 + rot) mod NG8: gate k8%4, unit UB*i + 8*(k8/4) + k%8
-  float wreg[RP];
-  {
+  const int rot3 = (4 * j + 8 * __builtin_amdgcn_readfirstlane(wave)) & (NG16 - 1);
+  float wreg[S3 ? 1 : RP];
+  bf16x8 w3[S3 ? RG : 1][3];
+  if constexpr (S3) {
+    const float* col = a.R + UB * j + 32 * wave + n;
+#pragma unroll
+    for (int p = 0; p < NG16; ++p) {
+      const int k8 = g0 + 2 * ((p + rot3) & (NG16 - 1)) + kk, grp = k8 & 3;
+      const int gate = CELL >= 2 ? 0 : ((CELL == 1 && grp == 3) ? 2 : grp);
+      const bool live = CELL == 0 || (CELL == 1 ? grp != 2 : grp == 0);
+      const float sgn = p < NG16 / 2 ? 1.f : -1.f;
+      float v[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = live ? sgn * col[((size_t)gate * H + UB * i + 8 * (k8 >> 2) + e) * H] : 0.f;
+      bf16x8 q[3];
+      split8(v, q);
+#pragma unroll
+      for (int z = 0; z < 3; ++z) {
+        if (p < RG) w3[p < RG ? p : 0][z] = q[z];
+        else reinterpret_cast<uintx4*>(wl)[(((size_t)wave * LG + (p - RG)) * 3 + z) * 64 + lane] = __builtin_bit_cast(uintx4, q[z]);
+      }
+    }
+  } else {
     const float* col = a.R + UB * j + 32 * wave + n;
 #pragma unroll
     for (int p = 0; p < KP; ++p) {
@@ -316,6 +462,11 @@ __global__ __launch_bounds__(256) void pers_bwdL_kernel(const PersBwdLArgs a) {
   int* const fA = a.flagsA + (size_t)sl * T * NBK * kFlagInts;
   int* const fP = a.flagsP + (size_t)sl * T * NBK * kFlagInts;
   auto slotX = [&](int t, int blk) { return Xs + ((size_t)t * NBK + blk) * (4 * UB * 32); };
+  char* const X3 = reinterpret_cast<char*>(S3 ? a.X3 + (size_t)sl * T * NBK * (2 * UB * 32) : nullptr);
+  auto partX = [&](int t, int blk, int p) {  // S3: part p of a slot
+    return p < 2 ? reinterpret_cast<char*>(slotX(t, blk)) + p * (8 * UB * 32) : X3 + ((size_t)t * NBK + blk) * (8 * UB * 32);
+  };
+  float odd = 0.f;  // zero unless a sum is infinite or NaN
   auto slotP = [&](int t, int jb, int ib) { return Ps + (((size_t)t * NBK + jb) * NPART + ib) * (UB * 32); };
   auto flagA = [&](int t, int blk) { return fA + ((size_t)t * NBK + blk) * kFlagInts; };
   auto flagP = [&](int t, int blk) { return fP + ((size_t)t * NBK + blk) * kFlagInts; };
@@ -372,16 +523,38 @@ __global__ __launch_bounds__(256) void pers_bwdL_kernel(const PersBwdLArgs a) {
 #pragma unroll
         for (int g = 0; g < 4; ++g) dbsum[c][g] += dA4[g];
       }
+      if constexpr (S3) {  // [octet][part][gate][batch row][unit]
+        unsigned short* const o = reinterpret_cast<unsigned short*>(xsA) + c * 3072 + n * 8 + j8;
+#pragma unroll
+        for (int g = 0; g < 4; g += 2) {
+          const Split2 s2 = split3(dA4[g], dA4[g + 1]);
+          const unsigned q[3] = {s2.h, s2.m, s2.l};
+#pragma unroll
+          for (int z = 0; z < 3; ++z) {
+            o[z * 1024 + g * 256] = (unsigned short)q[z];
+            o[z * 1024 + (g + 1) * 256] = (unsigned short)(q[z] >> 16);
+          }
+        }
+      }
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        xsA[(c * 4 + g) * 256 + (kk * 32 + n) * 4 + wave] = dA4[g];  // k%8 = j8 = 2*wave + kk: m = wave
+        if (!S3) xsA[(c * 4 + g) * 256 + (kk * 32 + n) * 4 + wave] = dA4[g];  // k%8 = j8 = 2*wave + kk: m = wave
         ro[(g * 32 + n) * UF + 8 * c + j8] = dA4[g];
       }
     }
     __syncthreads();
+    if constexpr (S3) {  // 128 pieces of every (octet, part): contiguous in the part
+#pragma unroll
+      for (int q = 0; q < (384 * CPT + 255) / 256; ++q) {
+        const int idx = threadIdx.x + 256 * q, c = idx / 384, z = (idx / 128) % 3;
+        if (idx < 384 * CPT)
+          xstore4(reinterpret_cast<float*>(partX(t, j, z) + (size_t)(4 * (CPT * i + c)) * 512 + (idx & 127) * 16),
+                  *reinterpret_cast<const floatx4*>(xsA + 4 * idx));
+      }
+    }
     // the unit octets of this workgroup are k8 blocks 4*(UF/8*i + c) + gate of the block's slot: contiguous
 #pragma unroll
-    for (int c = 0; c < CPT; ++c)
+    for (int c = 0; c < (S3 ? 0 : CPT); ++c)
       xstore4(slotX(t, j) + (size_t)(4 * (CPT * i + c)) * 256 + 4 * threadIdx.x,
               *reinterpret_cast<const floatx4*>(xsA + c * 1024 + 4 * threadIdx.x));
     signal(flagA(t, j) + (i & (kFlagSub - 1)) * kFlagStride, a.full_fences);
@@ -403,7 +576,7 @@ __global__ __launch_bounds__(256) void pers_bwdL_kernel(const PersBwdLArgs a) {
     pointwise_publish(T - 1);
   }
 
-  int rv = rot;
+  int rv = S3 ? rot3 : rot;
   for (int t = T - 1; t >= 0; --t) {
     tr.mark(t, 0);
     hide(rv);
@@ -413,7 +586,41 @@ __global__ __launch_bounds__(256) void pers_bwdL_kernel(const PersBwdLArgs a) {
     floatx16 acc;
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    {
+    if constexpr (S3) {
+      floatx16 neg;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) neg[r] = 0.f;
+      bf16x8 bv[NG16][3], al[NG16][3];
+      unsigned lo = lane * 16;
+      asm volatile("" : "+v"(lo));
+      auto ldb = [&](int g) {
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+          const char* const sb = partX(t, i, p) + (size_t)(g0 / 2 + 4 * (((g >> 2) + (rv >> 2)) & (NG16 / 4 - 1))) * 1024;
+          bv[g][p] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uintx4*>(sb + lo + (g & 3) * 1024));
+        }
+      };
+      auto ldw = [&](int g) {
+        if (g >= RG && g < NG16) {
+#pragma unroll
+          for (int p = 0; p < 3; ++p)
+            al[g][p] = __builtin_bit_cast(bf16x8, reinterpret_cast<const uintx4*>(wl)[(((size_t)wave * LG + (g - RG)) * 3 + p) * 64 + lane]);
+        }
+      };
+#pragma unroll
+      for (int g = 0; g < DEPTH3; ++g) ldb(g);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int g = 0; g < NG16; ++g) {
+        if (g + DEPTH3 < NG16) ldb(g + DEPTH3);
+        ldw(g + 2);
+        if (g == NG16 - DEPTH3 && t > 0 && fin) fetch_step(t - 1);  // behind the last exchange load of this step
+        if (g < NG16 / 2) acc = mfma_split3(g < RG ? w3[g < RG ? g : 0] : al[g], bv[g], acc);
+        else neg = mfma_split3(g < RG ? w3[g < RG ? g : 0] : al[g], bv[g], neg);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      acc -= neg;
+    } else {
       const char* const src = reinterpret_cast<const char*>(slotX(t, i));
       floatx4 bv[NG8];
       floatx4 al[NG8];
@@ -477,12 +684,14 @@ __global__ __launch_bounds__(256) void pers_bwdL_kernel(const PersBwdLArgs a) {
       float sum = 0.f;
 #pragma unroll
       for (int ib = 0; ib < NPART; ++ib) sum += pv[ib];
+      if (S3) odd += sum * 0.f;
       dh_rec[c] = CELL == 1 ? sum + dc[c] : sum;
     }
     tr.mark(t, 5);
     if (t > 0) pointwise_publish(t - 1);
     tr.mark(t, 6);
   }
+  if (S3 && odd != 0.f) *a.redo = 1;  // (every writer writes the same)
   if (valid && fin) {
 #pragma unroll
     for (int c = 0; c < CPT; ++c) {
@@ -506,22 +715,30 @@ __global__ __launch_bounds__(256) void pers_bwdL_kernel(const PersBwdLArgs a) {
   }
 }
 
-template <int HH, int CELL>
+// Counters at zero for a launch of pers_bwdL_kernel that is repeated on request.
+__global__ void redo_bwdL_kernel(const PersBwdLArgs a, int counters) {
+  if (*a.redo == 0) return;
+  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < counters; e += gridDim.x * blockDim.x) a.flagsA[e] = 0;
+}
+
+template <int HH, int CELL, bool S3 = false>
 hipError_t launch_fwdL(const PersFwdLArgs& a, hipStream_t s) {
-  constexpr int KPW = HH / 8, LP = KPW > 128 ? KPW - 128 : 0;
-  const size_t smem = (6144 + (size_t)4 * LP * 64) * sizeof(float);
-  const void* fn = (const void*)pers_fwdL_kernel<HH, CELL>;
+  constexpr int KPW = HH / 8, LP = KPW > 128 ? KPW - 128 : 0, LG = KPW / 8 > 22 ? KPW / 8 - 22 : 0;
+  const size_t smem = (6144 + (size_t)4 * (S3 ? LG * 3 * 4 : LP) * 64) * sizeof(float);
+  const void* fn = (const void*)pers_fwdL_kernel<HH, CELL, S3>;
   static bool attr_set = false;
   if (hipError_t e = allow_dynamic_lds(fn, smem, attr_set); e != hipSuccess) return e;
   void* params[] = {const_cast<PersFwdLArgs*>(&a)};
   return launch_resident(fn, a.nsl * (HH / 8), params, (unsigned)smem, s);
 }
 
-template <int HH, int CELL, int KS = 1>
+template <int HH, int CELL, int KS = 1, bool S3 = false>
 hipError_t launch_bwdL(const PersBwdLArgs& a, hipStream_t s) {
   constexpr int NBK = HH / 128, UF = 128 / NBK, LP = KS > 1 ? 0 : 256 - (UF == 16 ? 136 : 128);
-  const size_t smem = (4096 + 128 * (size_t)UF + 128 * (size_t)UF + (size_t)4 * LP * 64) * sizeof(float);
-  const void* fn = (const void*)pers_bwdL_kernel<HH, CELL, KS>;
+  constexpr int NG16 = 32 / KS, LG = NG16 > 22 ? NG16 - 22 : 0;
+  const size_t smem = S3 ? (4096 + 192 * (size_t)UF + 128 * (size_t)UF + (size_t)4 * LG * 3 * 256) * sizeof(float)
+                         : (4096 + 128 * (size_t)UF + 128 * (size_t)UF + (size_t)4 * LP * 64) * sizeof(float);
+  const void* fn = (const void*)pers_bwdL_kernel<HH, CELL, KS, S3>;
   static bool attr_set = false;
   if (hipError_t e = allow_dynamic_lds(fn, smem, attr_set); e != hipSuccess) return e;
   void* params[] = {const_cast<PersBwdLArgs*>(&a)};
@@ -531,34 +748,47 @@ hipError_t launch_bwdL(const PersBwdLArgs& a, hipStream_t s) {
 }  // namespace
 
 // Dispatch over (hidden size, cell) of the one-layer kernels.
-hipError_t launch_fwdL_any(int H, int cell, const PersFwdLArgs& k, hipStream_t s) {
-  if (H == 2048) {
-    return cell == 0 ? launch_fwdL<2048, 0>(k, s) : (cell == 1 ? launch_fwdL<2048, 1>(k, s)
-                     : (cell == 2 ? launch_fwdL<2048, 2>(k, s) : launch_fwdL<2048, 3>(k, s)));
-  }
-  return cell == 0 ? launch_fwdL<1024, 0>(k, s) : (cell == 1 ? launch_fwdL<1024, 1>(k, s)
-                   : (cell == 2 ? launch_fwdL<1024, 2>(k, s) : launch_fwdL<1024, 3>(k, s)));
+template <int HH>
+hipError_t launch_fwdL_cell(int cell, const PersFwdLArgs& k, hipStream_t s, bool s3) {
+  if (cell == 0) return s3 ? launch_fwdL<HH, 0, true>(k, s) : launch_fwdL<HH, 0>(k, s);
+  if (cell == 1) return s3 ? launch_fwdL<HH, 1, true>(k, s) : launch_fwdL<HH, 1>(k, s);
+  if (cell == 2) return s3 ? launch_fwdL<HH, 2, true>(k, s) : launch_fwdL<HH, 2>(k, s);
+  return s3 ? launch_fwdL<HH, 3, true>(k, s) : launch_fwdL<HH, 3>(k, s);
 }
 
-hipError_t launch_bwdL_any(int H, int cell, const PersBwdLArgs& k, hipStream_t s) {
-  if (H == 2048) {
-    return cell == 0 ? launch_bwdL<2048, 0>(k, s) : (cell == 1 ? launch_bwdL<2048, 1>(k, s)
-                     : (cell == 2 ? launch_bwdL<2048, 2>(k, s) : launch_bwdL<2048, 3>(k, s)));
-  }
-  if (k.ks == 4) {
-    return cell == 0 ? launch_bwdL<1024, 0, 4>(k, s) : (cell == 1 ? launch_bwdL<1024, 1, 4>(k, s)
-                     : (cell == 2 ? launch_bwdL<1024, 2, 4>(k, s) : launch_bwdL<1024, 3, 4>(k, s)));
-  }
-  if (k.ks == 2) {
-    return cell == 0 ? launch_bwdL<1024, 0, 2>(k, s) : (cell == 1 ? launch_bwdL<1024, 1, 2>(k, s)
-                     : (cell == 2 ? launch_bwdL<1024, 2, 2>(k, s) : launch_bwdL<1024, 3, 2>(k, s)));
-  }
-  return cell == 0 ? launch_bwdL<1024, 0>(k, s) : (cell == 1 ? launch_bwdL<1024, 1>(k, s)
-                   : (cell == 2 ? launch_bwdL<1024, 2>(k, s) : launch_bwdL<1024, 3>(k, s)));
+hipError_t launch_fwdL_any(int H, int cell, const PersFwdLArgs& k, hipStream_t s, bool s3) {
+  return H == 2048 ? launch_fwdL_cell<2048>(cell, k, s, s3) : launch_fwdL_cell<1024>(cell, k, s, s3);
 }
 
-hipError_t launch_pack_stateL(const float* h0, float* hx, int T, int B, int H, int b0, int nsl, hipStream_t s) {
-  hipLaunchKernelGGL(pack_stateL_kernel, dim3((unsigned)((32L * nsl * H + 255) / 256)), dim3(256), 0, s, h0, hx, T, B, H, b0, nsl);
+template <int HH, int KS>
+hipError_t launch_bwdL_cell(int cell, const PersBwdLArgs& k, hipStream_t s, bool s3) {
+  if (cell == 0) return s3 ? launch_bwdL<HH, 0, KS, true>(k, s) : launch_bwdL<HH, 0, KS>(k, s);
+  if (cell == 1) return s3 ? launch_bwdL<HH, 1, KS, true>(k, s) : launch_bwdL<HH, 1, KS>(k, s);
+  if (cell == 2) return s3 ? launch_bwdL<HH, 2, KS, true>(k, s) : launch_bwdL<HH, 2, KS>(k, s);
+  return s3 ? launch_bwdL<HH, 3, KS, true>(k, s) : launch_bwdL<HH, 3, KS>(k, s);
+}
+
+hipError_t launch_bwdL_any(int H, int cell, const PersBwdLArgs& k, hipStream_t s, bool s3) {
+  if (H == 2048) return launch_bwdL_cell<2048, 1>(cell, k, s, s3);
+  if (k.ks == 4) return launch_bwdL_cell<1024, 4>(cell, k, s, s3);
+  if (k.ks == 2) return launch_bwdL_cell<1024, 2>(cell, k, s, s3);
+  return launch_bwdL_cell<1024, 1>(cell, k, s, s3);
+}
+
+hipError_t launch_pack_stateL(const float* h0, float* hx, int T, int B, int H, int b0, int nsl, const int* only_if, int* flags,
+                              int counters, hipStream_t s) {
+  hipLaunchKernelGGL(pack_stateL_kernel, dim3((unsigned)((32L * nsl * H + 255) / 256)), dim3(256), 0, s, h0, hx, T, B, H, b0, nsl,
+                     only_if, flags, counters);
+  return hipGetLastError();
+}
+
+hipError_t launch_pack_stateL3(const float* h0, float* hx, int T, int B, int H, int b0, int nsl, hipStream_t s) {
+  hipLaunchKernelGGL(pack_stateL3_kernel, dim3((unsigned)((4L * nsl * H + 255) / 256)), dim3(256), 0, s, h0, hx, T, B, H, b0, nsl);
+  return hipGetLastError();
+}
+
+hipError_t launch_redo_bwdL(const PersBwdLArgs& k, int counters, hipStream_t s) {
+  hipLaunchKernelGGL(redo_bwdL_kernel, dim3(256), dim3(256), 0, s, k, counters);
   return hipGetLastError();
 }
 

@@ -75,7 +75,6 @@ struct Scratch {
   size_t bytes;
 };
 inline Scratch exchange_scratch(char* ws, const WsLayout& w) { return {reinterpret_cast<float*>(ws + w.xchg), w.flags - w.xchg}; }
-inline Scratch backward_scratch(char* ws, const WsLayout& w) { return {reinterpret_cast<float*>(ws + w.resv), w.total - w.resv}; }
 // Weight gradients of one layer on a given stream, supplied by the caller of the persistent backward pass for the
 // cells whose gradient products it forms itself; *used is set when the pass has called it for every layer.
 struct LayerGradients {

@@ -97,6 +97,21 @@ void clear_path_overrides() {
   g_chunk_table.clear();
 }
 
+// Whether the step path multiplies a step's state with the GEMM (bf16 matrix cores, three parts per operand) followed by a
+// point-wise kernel, instead of the fused step kernels (fp32 matrix cores, a third of the rate, and no second launch).
+// Microseconds per step of one layer, step kernel against GEMM, forward / backward with the products behind the loop:
+//   H = 4096: B = 32 79.9 / 108 against 80.6 / 115; 33 107 / 159 against 82 / 135; 64 120 / 168 against 86 / 141;
+//             256 411 / 518 against 202 / 393
+//   H = 1280: B = 16 13 / 20 against 22 / 28; 40 31 / 40 against 23 / 35; 128 52 / 59 against 32 / 44
+//   H = 1024: B = 40 16 / 36 against 19 / 30; 64 20 / 39 against 20 / 29; 128 26 / 45 against 24 / 35
+//   H =  520: B = 128 20 / 35 against 22 / 25; 256 35 / 65 against 23 / 31
+// (Forward, H = 2560 and 3072 gain from 32 rows on as well, by a quarter; 4096 and 1536 do not.)
+bool gemm_steps(const Dims& d, bool backward) {
+  if (d.H <= 512 || d.B <= 32) return false;
+  if (backward || d.H >= 1280) return true;
+  return d.B >= 128 && (long)d.B * d.H >= 128 * 640;
+}
+
 unsigned resolve_auto_path(const Dims& user, bool backward) {
   {
     std::lock_guard<std::mutex> lk(g_path_mu);
@@ -108,16 +123,18 @@ unsigned resolve_auto_path(const Dims& user, bool backward) {
   if (persistent_supported(d, backward)) return LSTM_PATH_PERSISTENT;
   const int cus = device_cu_count();
   // Section 3.2 observes that at large minibatches the individual optimisations stop paying.  Here: once the plain
-  // [B x 4H] x [H] product of one step gives every CU three 64 x 64 tiles (or one of 128 x 128), the GEMM kernel
-  // (grouped gates, fused point-wise kernel) beats the forward step kernel and the stream wavefront by 5-20 %: H = 4096
-  // from B = 128 on (there already with two tiles per CU: 113 against 107 TFLOP/s), H = 3072 from 256 (115 against
-  // 109), H = 1536 from 512 (115 against 100), H = 1024 from 768 (110 against 93).  Backward the split-K step kernel
-  // stays ahead at every size measured (its contraction is four times longer, and it fuses the point-wise work that
-  // the GEMM rung runs as a second kernel).
-  if (!backward && cus > 0) {
+  // [B x 4H] x [H] product of one step gives every CU three 64 x 64 tiles (or one of 128 x 128), a pass of one or two steps
+  // has next to nothing to gain from batching the input product over time and stays on the rung without it (L = 2, B = 512,
+  // I = 64, H = 2048: 0.36 ms against 0.35 for one step, 0.70 against 0.65 for two; 1.38 against 1.26 for four).
+  if (!backward && cus > 0 && d.T <= 2) {
     const long small_tiles = (long)((d.B + 63) / 64) * (4L * d.H / 64);
-    if (small_tiles >= 3L * cus || (d.H >= 4096 && small_tiles >= 2L * cus)) return LSTM_PATH_FUSED;
+    if (small_tiles >= 3L * cus) return LSTM_PATH_FUSED;
   }
+  // Steps on the GEMM leave nothing for overlapping layers (T = 16, forward / backward in ms, wavefront against step path:
+  // L = 2, B = 40, H = 1280 0.95 / 1.76 against 0.80 / 1.21; L = 4, B = 64, H = 1536 2.88 / 4.86 against 2.35 / 3.02), and with
+  // the input product batched over time they beat the rung that multiplies it step by step (L = 4, B = 128, H = 1280,
+  // T = 16: 3.44 against 2.50 ms; L = 1, B = 128, H = I = 4096: 299 against 225 us per step).
+  if (gemm_steps(d, backward)) return LSTM_PATH_STEP;
   // Overlapping layers on streams pays when one step kernel leaves CUs idle (Section 2.4: the
   // gain is largest for small layers); a step that already fills the chip runs layer by layer.
   const long wgs = (long)((d.H + 3) / 4) * ((d.B + 63) / 64);
@@ -152,7 +169,10 @@ int fwd_step(const FwdArgs& a) {
   }
   float* Rp = ws_f(a.ws, a.w.RT);
   const size_t pf = step_plan(d).pack_floats;
-  {
+  const bool gemm = gemm_steps(d, false);
+  const Scratch part = exchange_scratch(a.ws, a.w);
+  float* S = ws_f(a.ws, a.w.scratch);
+  if (!gemm) {
     ProfScope ps(LSTM_PHASE_FWD_PACK, s);
     CK(launch_pack_fwd(a.R, Rp, d.L, d.H, d.B, pf, s), "pack R");
   }
@@ -166,7 +186,6 @@ int fwd_step(const FwdArgs& a) {
     {
       ProfScope ps(LSTM_PHASE_FWD_INPUT_GEMM, s);
       GemmProblem p{in, Wl, P, (int)TB, (int)G, Il, Il, 1, 1, Il, (long)G, 0};
-      const Scratch part = exchange_scratch(a.ws, a.w);
       CK(launch_gemm_group(&p, 1, s, part.p, part.bytes), "input projection GEMM");
     }
     ProfScope ps(LSTM_PHASE_FWD_RECURRENCE, s);
@@ -184,6 +203,15 @@ int fwd_step(const FwdArgs& a) {
       sa.c_out2 = nullptr;
       sa.B = d.B;
       sa.H = d.H;
+      if (gemm) {
+        if (sa.h_prev) {
+          GemmProblem p{sa.h_prev, a.R + (size_t)l * G * d.H, S, d.B, (int)G, d.H, d.H, 1, 1, d.H, (long)G, 0};
+          CK(launch_gemm_group(&p, 1, s, part.p, part.bytes), "recurrent GEMM of one step");
+        }
+        CK(launch_pointwise_fwd(sa.P, sa.h_prev ? S : nullptr, sa.bias, sa.c_prev, sa.h_out, sa.c_out, sa.gates_out, sa.h_out2, nullptr,
+                                d.B, d.H, s), "fused point-wise");
+        continue;
+      }
       CK(launch_step_fwd(sa, s), "forward step kernel");
     }
   }
@@ -343,8 +371,10 @@ int bwd_step(const BwdArgs& a) {
   int* skcnt = reinterpret_cast<int*>(a.ws + a.w.skcnt);
   float* dxb = ws_f(a.ws, a.w.dx);
   float* dcb = ws_f(a.ws, a.w.state);
+  const bool gemm = gemm_steps(d, true);
+  const Scratch part = exchange_scratch(a.ws, a.w);
   // weights re-laid out once per pass: the backward products read R transposed (Section 2.3)
-  {
+  if (!gemm) {
     ProfScope ps(LSTM_PHASE_BWD_PACK, s);
     if (sp.sk) {
       CK(launch_pack_bwd_sk(a.R, RT, d.L, H, B, pf, s), "pack R (transposed, split-K)");
@@ -365,6 +395,7 @@ int bwd_step(const BwdArgs& a) {
     float* dA = dA_all + (size_t)l * TB * G;
     const float* dout = (l == d.L - 1) ? a.dy : dxb + (size_t)(l + 1) * TB * H;
     float* dc = dcb + (size_t)l * BH;
+    float* dh = dcb + ((size_t)d.L + l) * BH;
     prof_begin(LSTM_PHASE_BWD_RECURRENCE, s);
     for (int t = T - 1; t >= 0; --t) {
       StepBwdArgs sa;
@@ -382,9 +413,21 @@ int bwd_step(const BwdArgs& a) {
       sa.pointwise = 1;
       sa.B = B;
       sa.H = H;
+      if (gemm) {
+        if (sa.dA_next) {
+          GemmProblem p{sa.dA_next, a.R + (size_t)l * G * H, dh, B, H, (int)G, (long)G, 1, H, 1, H, 0};
+          CK(launch_gemm_group(&p, 1, s, part.p, part.bytes), "recurrent gradient GEMM of one step");
+        }
+        CK(launch_pointwise_bwd(sa.gates, sa.c_t, sa.c_prev, sa.dout, sa.dA_next ? dh : sa.dh_extra, sa.dc_in, sa.dA, sa.dc_out, B, H, s),
+           "backward point-wise");
+        continue;
+      }
       CK(bwd_launch(sa, l, t + 1), "backward step kernel");
     }
-    if (a.dh0) {
+    if (a.dh0 && gemm) {
+      GemmProblem p{dA, a.R + (size_t)l * G * H, a.dh0 + l * BH, B, H, (int)G, (long)G, 1, H, 1, H, 0};
+      CK(launch_gemm_group(&p, 1, s, part.p, part.bytes), "recurrent gradient GEMM (dh0)");
+    } else if (a.dh0) {
       StepBwdArgs sa{};
       sa.RTp = RT + (size_t)l * pf;
       sa.dA_next = dA;
@@ -400,7 +443,6 @@ int bwd_step(const BwdArgs& a) {
     if (din) {
       ProfScope ps(LSTM_PHASE_BWD_INPUT_GEMM, s);
       GemmProblem p{dA, a.W + w_offset(d, l), din, (int)TB, Il, (int)G, (long)G, 1, Il, 1, Il, 0};
-      const Scratch part = exchange_scratch(a.ws, a.w);
       CK(launch_gemm_group(&p, 1, s, part.p, part.bytes), "input-gradient GEMM");
     }
   }

@@ -1,0 +1,21 @@
+"""Steps of the step path as a GEMM and a point-wise kernel: both sides of the line in rows and hidden size, more than one
+layer, one step (no product without an initial state), a pass in which the batch is not a multiple of a tile."""
+import pytest
+
+from paper_1604_01946_amd.inputs import Config
+from test_gpu_parity import run_case
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(1, 3, 32, 20, 1280), (1, 3, 33, 20, 1280), (2, 1, 65, 20, 1300), (2, 3, 127, 24, 640), (2, 3, 128, 24, 640), (1, 3, 158, 24, 520),
+          (2, 2, 40, 1537, 1537), (1, 4, 33, 8, 516), (1, 2, 36, 100, 4096)]
+
+
+@pytest.mark.parametrize("dims", SHAPES, ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("with_states", [True, False])
+@pytest.mark.parametrize("auto", [True, False])
+def test_steps(dims, with_states, auto):
+    from paper_1604_01946_amd import binding
+    L, T, B, I, H = dims
+    cfg = Config("gs", L=L, T=T, B=B, I=I, H=H, state_std=0.3, dstate_std=0.3)
+    run_case(cfg, 4, 0 if auto else binding.LSTM_PATH_STEP, with_states=with_states, with_dstates=with_states)

@@ -190,7 +190,7 @@ int lstm_backward(int L, int T, int B, int I, int H,
                   void* stream, unsigned flags);
 
 /*
- * C[M][N] (row stride ldc) = A * B, or += when accumulate != 0, on the fp32 matrix cores.
+ * C[M][N] (row stride ldc) = A * B, or += when accumulate != 0, with fp32 sums on the matrix cores.
  * This is the time-batched product of Section 2.3 (input projections of many steps in one
  * call) and of Section 2.6 (weight gradients); the LSTM calls use it internally and it is
  * exported so that tests can check it alone.  Element (m,k) of A is A[m*sAm + k*sAk],
@@ -203,12 +203,12 @@ int lstm_gemm_f32(int M, int N, int K,
 
 /*
  * The same product with a scratch buffer (device memory, 16-byte aligned, scratch_bytes long, NULL: none; it must
- * stay untouched until the stream has passed the call).  A product whose 128 x 128 tiles do not fill the chip evenly --
+ * stay untouched until the stream has passed the call).  A product whose tiles do not fill the chip evenly --
  * fewer tiles than the chip holds workgroups, or a last round with few tiles -- has the tile rows of that round cut
  * along K into as many slices as fill the chip once more; the slices' partial tiles go to the scratch buffer and are
  * added in a fixed order, so the result is repeatable and differs from lstm_gemm_f32's only by the order of the
  * additions.  Too small a buffer means fewer slices or none (never an error).  This is how the LSTM calls run the
- * time-batched products of Section 2.3 at large hidden sizes (M = T*B = 1600 rows leave 832 tiles for 768 places).
+ * time-batched products of Section 2.3 at large hidden sizes.
  */
 int lstm_gemm_f32_ws(int M, int N, int K,
                   const float* A, long sAm, long sAk,

@@ -7,6 +7,7 @@
 //   persistent_narrow.hip pers_fwd_kernel / pers_bwd_kernel: tiles of 16 batch rows (B <= 32, slices of 16 / 32 rows)
 //   persistent_wide.hip   pers_fwd32_kernel / pers_bwd32_kernel: slices of 64 rows, 32x32x2 tiles, templated on the cell
 //   persistent_pp.hip     pers_fwd_pp_kernel: two half-slices of 32 rows alternating on the matrix cores
+//   persistent_pp3.hip    pers_fwd_pp3_kernel: the same on the bf16 matrix cores, operands in three parts
 //   persistent_bpp.hip    pers_bwd_pp_kernel: two quarter-slices of 16 rows alternating on the matrix cores
 //   persistent_tiny.hip   pers_fwd_tiny_kernel / pers_bwd_tiny_kernel: B = 1, the exchanged values are their own flags
 //   persistent_large.hip  pers_fwdL_kernel / pers_bwdL_kernel: one layer per launch, H = 1024 / 2048

@@ -67,9 +67,9 @@ int set_path_override(const Dims& d, bool backward, unsigned path);  // LSTM_PAT
 int set_wavefront_chunks(const Dims& d, int chunks);                 // 0 removes the entry
 int wavefront_chunks(const Dims& d);                                 // 0: no entry (d as the kernels see it)
 void clear_path_overrides();
-// Parts of the workspace that take the partial tiles of products cut along K (launch_gemm_group): the exchange area of the
-// persistent kernels, idle before and after a recurrence, and the reserve stand-in of inference calls, which no backward
-// call uses (for products on a side stream while a recurrence runs).
+// A part of the workspace that takes the partial tiles of products cut along K (launch_gemm_group): the exchange area of the
+// persistent kernels, idle before and after a recurrence, or, for products on a side stream while a recurrence runs, what
+// that recurrence leaves of the reserve stand-in of inference calls, which no backward call uses otherwise.
 struct Scratch {
   float* p;
   size_t bytes;

@@ -204,7 +204,23 @@ hipError_t launch_resize(float* dst, const float* src, long outer, int rd, int c
 
 int padded_hidden(const Dims& d) { return (knobs().no_pad || micro_shape(d)) ? d.H : padded_hidden_rule(d); }
 
+// Size that the kernels run at: the smallest with kernels of its own, multiples of 64 up to 512 and of 1024 above, that is no
+// larger than the size that buffers are reported for.  A single sequence has kernels for 128, 256 and 512 alone.
+// A step's products grow with the square of the size, and at 320 three slices fit side by side where 512 has two (L = 2, T = 50,
+// B = 500, I = 80, H = 320 forward and backward: at 512 4.60 ms, at 320 2.56; L = 3, T = 40, B = 17, I = 120, H = 300 forward:
+// at 512 353 us, at 320 200).
 int padded_hidden_rule(const Dims& d) {
+  const int top = reported_hidden(d);
+  if (top == d.H || (d.B == 1 && top <= 512)) return top;
+  return std::min(granular_hidden(d.H), top);
+}
+
+int granular_hidden(int H) {
+  return H <= 512 ? std::max(128, (int)align_up(H, 64)) : (int)align_up(H, 1024);
+}
+
+// Size that the reserve and the workspace are reported for, and whether a size is padded at all.
+int reported_hidden(const Dims& d) {
   // 512 < H < 1024: the one-layer persistent kernels of H = 1024 against the step kernels at the given size (which
   // have no weights on chip).  Padded, the rate in terms of the given network is about 105 (H/1024)^2 TFLOP/s at 64 rows
   // and more, and better than that of the given size wherever the latter is short of rows or of arithmetic: with up
@@ -399,14 +415,16 @@ extern "C" {
 size_t lstm_reserve_bytes(int L, int T, int B, int I, int H) {
   if (!dims_ok(L, T, B, I, H)) return 0;
   const Dims d{L, T, B, I, H};
-  return reserve_bytes(Dims{L, T, B, I, padded_hidden_rule(d)});  // never below the as-given size: padding only grows H
+  return reserve_bytes(Dims{L, T, B, I, reported_hidden(d)});  // never below the as-given size: padding only grows H
 }
 
 size_t lstm_workspace_bytes(int L, int T, int B, int I, int H) {
   if (!dims_ok(L, T, B, I, H)) return 0;
-  const Dims d{L, T, B, I, H}, p{L, T, B, I, padded_hidden_rule(d)};
-  const size_t given = ws_layout(d).total;
-  return p.H == d.H ? given : std::max(given, pad_layout(d, p).total);
+  const Dims d{L, T, B, I, H}, p{L, T, B, I, padded_hidden_rule(d)}, r{L, T, B, I, reported_hidden(d)};
+  size_t need = ws_layout(d).total;
+  if (r.H != d.H) need = std::max(need, pad_layout(d, r).total);
+  if (p.H != d.H && p.H != r.H) need = std::max(need, pad_layout(d, p).total);
+  return need;
 }
 
 const char* lstm_status_string(int status) {

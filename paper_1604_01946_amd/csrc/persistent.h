@@ -15,7 +15,26 @@
 #pragma once
 #include "schedule.h"
 
+#include <type_traits>
+
 namespace lstm {
+
+// Hidden sizes with several layers per launch: the multiples of 64 from 128 to 512.  Every kernel of the families narrow, wide (forward),
+// pp, pp3 and bpp has an instance for each; `f` is called with the size as a compile-time constant.
+inline bool on_chip_size(int H) { return H >= 128 && H <= 512 && H % 64 == 0; }
+template <typename F>
+hipError_t with_on_chip_size(int H, F f) {
+  switch (H) {
+    case 128: return f(std::integral_constant<int, 128>{});
+    case 192: return f(std::integral_constant<int, 192>{});
+    case 256: return f(std::integral_constant<int, 256>{});
+    case 320: return f(std::integral_constant<int, 320>{});
+    case 384: return f(std::integral_constant<int, 384>{});
+    case 448: return f(std::integral_constant<int, 448>{});
+    case 512: return f(std::integral_constant<int, 512>{});
+  }
+  return hipErrorInvalidValue;
+}
 
 // A step counter is split into kFlagSub words, each on a cache line of its own (kFlagStride ints
 // apart).  Agent-scope atomics from many workgroups on one line are served one after the other by the

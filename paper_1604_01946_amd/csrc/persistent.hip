@@ -326,9 +326,15 @@ bool persistent_large(const Dims& d, bool backward) {
   return (backward ? (d.H / 128) * (d.H / 128) : d.H / 8) <= di.cus;
 }
 
+// Sizes that are no powers of two: a few steps of one layer, which are not padded either (reported_hidden), cost less step by
+// step (L = 1, T = 1, B = 1003, H = 192: forward 33 us against 61, backward 59 against 85).
+static bool too_short_on_chip(const Dims& d) {
+  return (d.H & (d.H - 1)) != 0 && d.L == 1 && (d.T < 8 || (d.T < 16 && d.B < 48));
+}
+
 bool persistent_supported(const Dims& d, bool backward) {
   if (persistent_large(d, backward)) return true;
-  if (!(d.H == 128 || d.H == 256 || d.H == 512)) return false;
+  if (!on_chip_size(d.H) || too_short_on_chip(d)) return false;
   // Slices of 64 rows, one after the other once the chip is full: the rate does not depend on their number.  The GEMM rungs
   // gain with the batch and with short sequences (a launch here costs 70 us before its first step).  Forward and backward
   // of four layers, these kernels / the fused rung: T = 60, H = 512 23.0 / 30.7 ms at 1024 rows and 92 / 90 at 4096, H = 256
@@ -368,7 +374,8 @@ int large_split3_steps(const Dims& d, int cell, bool backward) {
   return d.L > 1 && d.B <= 64 ? bwd_few[c] : bwd[c];
 }
 // The same for the alternating kernels of H = 256 and 512 (forward; L layers of a launch with `workgroups` workgroups).
-//   H = 512: LSTM 0.96 at six steps, GRU 0.99, single gate 0.95 at eight (1.01 at six); from three layers on two steps earlier
+//   H = 512: LSTM 0.96 at six steps, GRU 0.99, single gate 0.95 at eight (1.01 at six); from three layers on two steps earlier.
+//   H = 448 and 384 like it; 320 two steps later (1.00 to 1.03 at six steps, 0.93 at twelve); at 100 steps 0.65 to 0.75 for all three
 //   H = 256: with CUs to spare 0.9 to 1.0 at 20 steps (three layers: 0.97 at twelve); with a workgroup on every CU the
 //            exchange is slower than the products are faster: LSTM and GRU of one or two layers 1.0 to 1.1 at any length, four
 //            layers 0.97 at 50 steps, single gate 0.9 to 1.0 at 50
@@ -377,7 +384,7 @@ int large_split3_steps(const Dims& d, int cell, bool backward) {
 //   0.42 -> 1.09).
 int pp3_steps(const Dims& d, int cell, int workgroups, int cus) {
   constexpr int never = 1 << 30;
-  if (d.H == 512) return (cell >= 2 ? 8 : 6) - (d.L >= 3 ? 2 : 0);
+  if (d.H > 256) return (cell >= 2 ? 8 : 6) - (d.L >= 3 ? 2 : 0) + (d.H <= 320 ? 2 : 0);
   if (d.H != 256 || d.L > 4) return never;
   if (workgroups < cus) return d.L == 3 ? 12 : 20;
   return cell >= 2 || d.L >= 4 ? 50 : never;
@@ -611,7 +618,7 @@ int run_backward_persistent_large(const BwdArgs& args, int cell, bool* bias_done
 // rows and fewer (the rows past the batch are zeros), where the LSTM has kernels of its own.
 bool gru_persistent_supported(const Dims& d) {
   if (persistent_large(d, false) && persistent_large(d, true)) return true;  // one-layer kernels, H = 1024 / 2048
-  if (!(d.H == 128 || d.H == 256 || d.H == 512)) return false;
+  if (!on_chip_size(d.H) || too_short_on_chip(d)) return false;
   if (d.B > 16384) return false;  // (the cells' own limits are lower: rnn_cells.hip)
   DeviceInfo di;
   if (!device_info(di) || !di.coop) return false;
@@ -730,7 +737,7 @@ int forward_layers(const FwdArgs& args, int cell) {
   if (cap < 1) cap = 1;
   const int slice_rows = narrow_slices ? slice_rows_narrow : 64;
   const int slices = wide ? (d.B + 63) / 64 : (narrow_slices ? (d.B + slice_rows - 1) / slice_rows : 1);
-  const bool pp3 = pp && (d.H == 512 || d.H == 256) && split3_wanted(d.T >= pp3_steps(d, cell, grid * std::min(cap, slices), di.cus)) &&
+  const bool pp3 = pp && d.H >= 256 && split3_wanted(d.T >= pp3_steps(d, cell, grid * std::min(cap, slices), di.cus)) &&
                    x3_slots <= a.w.scratch - a.w.P && d.L * x3_slots <= a.w.flags - a.w.xchg && !overlap(a.x, TB * (size_t)d.I, a.y, TB * (size_t)d.H);
   if (pp3) {
     CK(keep_state(a.h0, a.hT, a.cT, (size_t)d.L * d.B * d.H, a.ws, a.w, 0, s), "keep h0");
@@ -899,7 +906,8 @@ int backward_layers(const BwdArgs& a, int cell, bool* bias_done, bool with_weigh
   }
   k.L = d.L; k.T = d.T; k.B = d.B; k.I = d.I; k.H = d.H; k.spin_limit = spin_limit(); k.full_fences = full_fences();
   // two alternating chains per workgroup (LSTM, slices of 64 rows): counters of H/16 lines per (layer, step, quarter)
-  const bool pp = wide && (cell == 0 || knobs().rnn_pp) && knobs().pingpong != 0;
+  // (the kernel with one chain has instances for the powers of two only)
+  const bool pp = wide && (((cell == 0 || knobs().rnn_pp) && knobs().pingpong != 0) || (d.H & (d.H - 1)) != 0);
   k.dummy = reinterpret_cast<float*>(a.ws + a.w.scratch);
   k.trace = (g_trace_bytes >= (size_t)d.T * 64 * (pp ? 2 : 1)) ? g_trace_buf : nullptr;
   k.trace_block = g_trace_block;

@@ -88,7 +88,7 @@ __global__ __launch_bounds__(256) void pers_bwd_pp_kernel(const PersBwdArgs a, c
   constexpr int H = HH, G = 4 * H, NS2 = H / 16, NL = NS2;
   constexpr int NGW = CELL == 0 ? 4 : (CELL == 1 ? 3 : 1), GW = NGW * H;  // gate blocks and rows of R, W, db
   constexpr int NU = H / 16;             // groups of four units per wave (its K quarter)
-  constexpr int RG = NU < 16 ? NU : 16;  // groups whose weights live in registers
+  constexpr int RG = NU <= 20 ? NU : 16;  // groups whose weights live in registers
   constexpr int LG = NU - RG;            // groups whose weights live in LDS
   constexpr int GA = GA_;                // group of phase B at which the chain's publication is completed
   constexpr int PL = PL_;                // group of phase B from which the next phase A's operands are requested
@@ -101,21 +101,11 @@ __global__ __launch_bounds__(256) void pers_bwd_pp_kernel(const PersBwdArgs a, c
   float* const stage = smem + 4096;  // [4 waves][256]
   float* const wl = smem + 5120;     // [4 waves][LG][2 tiles][64 lanes][4 gates]
 
-  // blockIdx -> (layer, batch half, slice): one (layer, half) group per 8/(L*NBH) XCDs when that divides
+  // blockIdx -> (layer, batch half, slice)
   int l, bh, s2;
-  {
-    const int bid = blockIdx.x, groups = a.L * NBH;
-    if (groups <= 8 && 8 % groups == 0 && NS2 % (8 / groups) == 0 && (gridDim.x % 8) == 0) {
-      const int per = 8 / groups, xcd = bid & 7, grp = xcd / per;
-      l = grp / NBH;
-      bh = grp % NBH;
-      s2 = (bid >> 3) * per + (xcd % per);
-    } else {
-      l = bid / (NS2 * NBH);
-      bh = (bid / NS2) % NBH;
-      s2 = bid % NS2;
-    }
-  }
+  map_block(a.L * NBH, NS2, l, s2);
+  bh = l % NBH;
+  l /= NBH;
   const int T = a.T, B = a.B;
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -129,7 +119,7 @@ __global__ __launch_bounds__(256) void pers_bwd_pp_kernel(const PersBwdArgs a, c
   // the same L2 lines at the same time).  The rotation is a multiple of four groups, so that the address of a request is
   // a scalar base (scalar arithmetic costs the wave no matrix-instruction time, vector arithmetic does) plus the lane's
   // fixed offset plus an immediate.
-  const int rot = 4 * (((int)(blockIdx.x >> 3) + w) & (NU / 4 - 1));
+  const int rot = 4 * ((((int)blockIdx.x >> 3) + w) % (NU / 4));
 
   // ---- weights.  A operand of processed group i (unit group ug = w*NU + (i + rot) % NU), gate g, tile tl:
   //      lane (kq = lane / 16, row = lane % 16) holds M_tl[g*H + 4*ug + kq][u0 + row], M_0 = R_l, M_1 = W_l
@@ -141,7 +131,7 @@ __global__ __launch_bounds__(256) void pers_bwd_pp_kernel(const PersBwdArgs a, c
     const bool live1 = l > 0 || a.dx0;
 #pragma unroll
     for (int i = 0; i < NU; ++i) {
-      const int ug = w * NU + ((i + rot) & (NU - 1));
+      const int ug = w * NU + wrap<NU>(i + rot);
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const int gm = CELL >= 2 ? 0 : ((CELL == 1 && g == 3) ? 2 : g);  // matrix row block behind K group g
@@ -207,7 +197,7 @@ __global__ __launch_bounds__(256) void pers_bwd_pp_kernel(const PersBwdArgs a, c
   auto flag = [&](int layer, int st, int c) {
     return a.flags + ((((size_t)layer * (T + 2) + st) * NQ + 2 * bq + c) * NL) * kFlagStride;
   };
-  const int arrive_line = ((4 * s2 + w) & (NL - 1)) * kFlagStride;
+  const int arrive_line = ((4 * s2 + w) % NL) * kFlagStride;
 
   PpWaiter<NL> wt{a.watchdog, a.spin_limit, false};
   // time stamps of one workgroup's phases (diagnostic hook; a kernel of its own, so that the normal one carries
@@ -311,7 +301,7 @@ __global__ __launch_bounds__(256) void pers_bwd_pp_kernel(const PersBwdArgs a, c
     asm volatile("" : "+v"(lo));
   };
   auto ldx = [&](const float* src, int i) {  // src: the slot (wave-uniform)
-    const char* const sb = reinterpret_cast<const char*>(src) + ((size_t)w * NU + 4 * (((i >> 2) + rv) & (NU / 4 - 1))) * 1024;
+    const char* const sb = reinterpret_cast<const char*>(src) + ((size_t)w * NU + 4 * wrap<NU / 4>((i >> 2) + rv)) * 1024;
     return *reinterpret_cast<const floatx4*>(sb + lo + (i & 3) * 1024);
   };
   // counter that stands for "dx of (chain c, step t) of the layer above is published" (see the phases below)
@@ -555,7 +545,7 @@ __global__ __launch_bounds__(256) void pers_bwd_pp_kernel(const PersBwdArgs a, c
 
 template <int HH, int CELL>
 hipError_t launch_bpp(const PersBwdArgs& a, int nbh, hipStream_t s) {
-  constexpr int NU = HH / 16, LG = NU > 16 ? NU - 16 : 0;
+  constexpr int NU = HH / 16, LG = NU > 20 ? NU - 16 : 0;
   const size_t smem = (5120 + (size_t)4 * LG * 2 * 64 * 4) * sizeof(float);
   // Schedule (measured at H = 512; the alternatives within 1 %): the other chain's publication is counted one group
   // into phase A; a quarter of phase B runs in between the pieces of post(), six of its instructions per matrix
@@ -564,7 +554,7 @@ hipError_t launch_bpp(const PersBwdArgs& a, int nbh, hipStream_t s) {
   // that group: 8 1.047 ms, 10 1.038, 12 1.032, 13 1.031, 14 1.042, 16 1.058: looking later also lets a layer follow
   // the one above more closely).
   constexpr int KH = NU / 4 < 4 ? 4 : NU / 4;
-  constexpr int PL = HH == 512 ? 12 : KH;
+  constexpr int PL = HH > 256 ? NU * 3 / 8 : KH;
   const bool trace = a.trace != nullptr;
   const void* fn = trace ? (const void*)pers_bwd_pp_kernel<HH, 1, PL, KH, 6, true, CELL>
                          : (const void*)pers_bwd_pp_kernel<HH, 1, PL, KH, 6, false, CELL>;
@@ -579,20 +569,14 @@ hipError_t launch_bpp(const PersBwdArgs& a, int nbh, hipStream_t s) {
 
 template <int CELL>
 hipError_t launch_bpp_h(int H, const PersBwdArgs& a, int nbh, hipStream_t s) {
-  if (H == 512) return launch_bpp<512, CELL>(a, nbh, s);
-  if (H == 256) return launch_bpp<256, CELL>(a, nbh, s);
-  if (H == 128) return launch_bpp<128, CELL>(a, nbh, s);
-  return hipErrorInvalidValue;
+  return with_on_chip_size(H, [&](auto h) { return launch_bpp<decltype(h)::value, CELL>(a, nbh, s); });
 }
 
 hipError_t launch_bwd_pp(int cell, int H, const PersBwdArgs& a, int nbh, hipStream_t s) {  // cell 0: LSTM, 1: GRU, 2: ReLU, 3: tanh
+  if (cell == 0) return launch_bpp_h<0>(H, a, nbh, s);
   if (cell == 1) return launch_bpp_h<1>(H, a, nbh, s);
   if (cell == 2) return launch_bpp_h<2>(H, a, nbh, s);
   if (cell == 3) return launch_bpp_h<3>(H, a, nbh, s);
-  if (cell != 0) return hipErrorInvalidValue;
-  if (H == 512) return launch_bpp<512, 0>(a, nbh, s);
-  if (H == 256) return launch_bpp<256, 0>(a, nbh, s);
-  if (H == 128) return launch_bpp<128, 0>(a, nbh, s);
   return hipErrorInvalidValue;
 }
 

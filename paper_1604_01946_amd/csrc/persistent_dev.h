@@ -7,6 +7,12 @@ namespace lstm {
 namespace {
 
 // ------------------------------------------------------------------ device helpers
+// v modulo N for 0 <= v < 2 N: a mask where N is a power of two.
+template <int N>
+__device__ __forceinline__ int wrap(int v) {
+  if constexpr ((N & (N - 1)) == 0) return v & (N - 1);
+  else return v >= N ? v - N : v;
+}
 template <int NT>
 struct BVec;
 template <>
@@ -155,14 +161,15 @@ __device__ __forceinline__ void signal(int* flag, int full) {
   if (threadIdx.x == 0) __hip_atomic_fetch_add(flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Counter of NL lines: lane i polls line i % NL; every line must reach `each` arrivals.
+// Counter of NL <= 32 lines: every lane polls one, together all of them; every line must reach `each` arrivals.
 template <int NL>
 struct PpWaiter {
   int* watchdog;
   int limit;
   bool dead;
   static __device__ __forceinline__ int peek(int* flag) {
-    return __hip_atomic_load(flag + (threadIdx.x & (NL - 1)) * kFlagStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int line = (NL & (NL - 1)) == 0 ? threadIdx.x & (NL - 1) : min((int)(threadIdx.x & 31), NL - 1);
+    return __hip_atomic_load(flag + line * kFlagStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   static __device__ __forceinline__ void land(int& v) { asm volatile("" : "+v"(v)); }
   // `seen`: a value peeked earlier.  A wait that has to poll ends with every outstanding memory operation complete.
@@ -194,17 +201,21 @@ struct PpTracer {
   }
 };
 
-// blockIdx -> (layer, slice).  Workgroups are dealt round-robin to the 8 XCDs, each with its
-// own L2; keeping a layer on 8/L XCDs lets its exchange reads be served by few L2s.
-__device__ __forceinline__ void map_block(int L, int NS, int& l, int& s) {
-  const int bid = blockIdx.x;
-  if (L <= 8 && 8 % L == 0 && NS % (8 / L) == 0 && (gridDim.x % 8) == 0) {
-    const int per = 8 / L, xcd = bid & 7;
-    l = xcd / per;
-    s = (bid >> 3) * per + (xcd % per);
+// blockIdx -> (group, member), `members` workgroups per group: those of a group read the same exchange slots.  Workgroups
+// are dealt round-robin to the 8 XCDs, each with its own L2: a group gets 8/groups XCDs to itself where that divides, and
+// otherwise a run of consecutive places in an order in which neighbours share an XCD, so that its reads are served by few L2s
+// (L = 4, B = 128, H = 256, tanh, sixteen groups backward: 1.30 -> 1.25 ms against all groups on all XCDs).  Not where the groups do
+// divide: a group's slices on an XCD each instead of spread over its XCDs made the same case forward and backward 1.35 ms.
+__device__ __forceinline__ void map_block(int groups, int members, int& g, int& m) {
+  const int bid = blockIdx.x, n = gridDim.x;
+  if (groups <= 8 && 8 % groups == 0 && members % (8 / groups) == 0 && (n % 8) == 0) {
+    const int per = 8 / groups, xcd = bid & 7;
+    g = xcd / per;
+    m = (bid >> 3) * per + (xcd % per);
   } else {
-    l = bid / NS;
-    s = bid % NS;
+    const int v = (n & 7) == 0 ? (bid & 7) * (n >> 3) + (bid >> 3) : bid;
+    g = v / members;
+    m = v % members;
   }
 }
 

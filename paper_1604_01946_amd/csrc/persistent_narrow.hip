@@ -44,7 +44,7 @@ __global__ __launch_bounds__(256) void pers_fwd_kernel(const PersFwdArgs a) {
 
   // Register i of a wave covers k-group (i + rot) mod KG: workgroups (and waves) that share an L2
   // walk the exchange slot from different starting points instead of all hitting one channel.
-  const int rot = ((int)(blockIdx.x >> 3) + __builtin_amdgcn_readfirstlane(wave)) & (KG - 1);
+  const int rot = (((int)blockIdx.x >> 3) + __builtin_amdgcn_readfirstlane(wave)) % KG;
   // ---- weights -> registers, as MFMA A operands: lane (q, n) holds row n of tile mt at k = kbase + 4*kg + q
   float wR[KG][2], wW[KG][2];
   {
@@ -57,7 +57,7 @@ __global__ __launch_bounds__(256) void pers_fwd_kernel(const PersFwdArgs a) {
       const size_t row = ((size_t)gate * H + unit) * H;
 #pragma unroll
       for (int i = 0; i < KG; ++i) {
-        const int kg = (i + rot) & (KG - 1);
+        const int kg = wrap<KG>(i + rot);
         wR[i][mt] = Rl[row + kbase + 4 * kg];
         wW[i][mt] = (l > 0) ? Wl[row + kbase + 4 * kg] : 0.f;
       }
@@ -102,7 +102,7 @@ __global__ __launch_bounds__(256) void pers_fwd_kernel(const PersFwdArgs a) {
 
   int rv = rot;
   for (int t = 0; t < T; ++t) {
-    if (KG >= 32) hide(rv);  // large H: keeps the rotated offsets next to their loads instead of in spilled registers
+    if (KG > 16) hide(rv);  // large H: keeps the rotated offsets next to their loads instead of in spilled registers
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       if (c == 0) tr.mark(t, 0);
@@ -134,7 +134,7 @@ __global__ __launch_bounds__(256) void pers_fwd_kernel(const PersFwdArgs a) {
         w.wait(flag(l - 1, t + 1, c), NS, seen_in);
         const float* src = slot(l - 1, t + 1, c) + boff;
 #pragma unroll
-        for (int i = 0; i < KG; ++i) BVec<NT>::ld(src + (size_t)4 * ((i + rv) & (KG - 1)) * BP, bi[i]);
+        for (int i = 0; i < KG; ++i) BVec<NT>::ld(src + (size_t)4 * wrap<KG>(i + rv) * BP, bi[i]);
         if (c == 0) tr.mark(t, 1);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -152,7 +152,7 @@ __global__ __launch_bounds__(256) void pers_fwd_kernel(const PersFwdArgs a) {
         if (c == 0) tr.mark(t, 2);
         const float* src = slot(l, t, c) + boff;
 #pragma unroll
-        for (int i = 0; i < KG; ++i) BVec<NT>::ld(src + (size_t)4 * ((i + rv) & (KG - 1)) * BP, br[i]);
+        for (int i = 0; i < KG; ++i) BVec<NT>::ld(src + (size_t)4 * wrap<KG>(i + rv) * BP, br[i]);
         __builtin_amdgcn_sched_barrier(0);
       }
       if (do_in) {
@@ -294,7 +294,7 @@ __global__ __launch_bounds__(256) void pers_bwd_kernel(const PersBwdArgs a) {
 
   // ---- weights -> registers: A operand row n (< 8: column u0+n of R_l, >= 8: column u0+n-8 of W_l),
   //      k = wave*H + 4*kg + q
-  const int rot = ((int)(blockIdx.x >> 3) * (KGB / 32) + 2 * __builtin_amdgcn_readfirstlane(wave)) & (KGB - 1);
+  const int rot = (((int)blockIdx.x >> 3) * (KGB / 32) + 2 * __builtin_amdgcn_readfirstlane(wave)) % KGB;
   float wB[KGB];
   {
     const float* Rl = a.R + (size_t)l * G * H;
@@ -303,7 +303,7 @@ __global__ __launch_bounds__(256) void pers_bwd_kernel(const PersBwdArgs a) {
     const bool live = (n < 8) || (l > 0) || a.dx0;
 #pragma unroll
     for (int i = 0; i < KGB; ++i)
-      wB[i] = live ? src[(size_t)(wave * H + 4 * ((i + rot) & (KGB - 1)) + q) * H] : 0.f;
+      wB[i] = live ? src[(size_t)(wave * H + 4 * wrap<KGB>(i + rot) + q) * H] : 0.f;
   }
 
   // ---- the cells this lane owns in the point-wise stage: wave j finalises batch tile j;
@@ -444,16 +444,16 @@ __global__ __launch_bounds__(256) void pers_bwd_kernel(const PersBwdArgs a) {
         const float* src = slot(t, c) + boff;
         // double-buffered chunks of CH k-groups: the loads of chunk i+1 are in flight under the MFMAs
         // of chunk i (the scheduling barriers keep the compiler from re-serialising them)
-        constexpr int CH = (KGB >= 64) ? 32 : 16, NCH = KGB / CH;
+        constexpr int CH = (KGB % 32 == 0 && KGB >= 64) ? 32 : 16, NCH = KGB / CH;
         float bv[2][CH][NT];
 #pragma unroll
-        for (int i = 0; i < CH; ++i) BVec<NT>::ld(src + (size_t)4 * ((i + rv) & (KGB - 1)) * BP, bv[0][i]);
+        for (int i = 0; i < CH; ++i) BVec<NT>::ld(src + (size_t)4 * wrap<KGB>(i + rv) * BP, bv[0][i]);
 #pragma unroll
         for (int ch = 0; ch < NCH; ++ch) {
           if (ch + 1 < NCH) {
 #pragma unroll
             for (int i = 0; i < CH; ++i)
-              BVec<NT>::ld(src + (size_t)4 * (((ch + 1) * CH + i + rv) & (KGB - 1)) * BP, bv[(ch + 1) & 1][i]);
+              BVec<NT>::ld(src + (size_t)4 * wrap<KGB>((ch + 1) * CH + i + rv) * BP, bv[(ch + 1) & 1][i]);
           }
           if (ch == (NCH > 1 ? NCH - 2 : 0) && t > 0) fetch_step(t - 1, c);  // behind this step's last exchange loads
           __builtin_amdgcn_sched_barrier(0);
@@ -532,17 +532,11 @@ hipError_t launch_bwd(BatchPlan bp, int grid, const PersBwdArgs& a, hipStream_t 
 }  // namespace
 
 hipError_t launch_fwd_narrow(int H, BatchPlan bp, int grid, const PersFwdArgs& a, hipStream_t s) {
-  if (H == 512) return launch_fwd<32>(bp, grid, a, s);
-  if (H == 256) return launch_fwd<16>(bp, grid, a, s);
-  if (H == 128) return launch_fwd<8>(bp, grid, a, s);
-  return hipErrorInvalidValue;
+  return with_on_chip_size(H, [&](auto h) { return launch_fwd<decltype(h)::value / 16>(bp, grid, a, s); });
 }
 
 hipError_t launch_bwd_narrow(int H, BatchPlan bp, int grid, const PersBwdArgs& a, hipStream_t s) {
-  if (H == 512) return launch_bwd<128>(bp, grid, a, s);
-  if (H == 256) return launch_bwd<64>(bp, grid, a, s);
-  if (H == 128) return launch_bwd<32>(bp, grid, a, s);
-  return hipErrorInvalidValue;
+  return with_on_chip_size(H, [&](auto h) { return launch_bwd<decltype(h)::value / 4>(bp, grid, a, s); });
 }
 
 hipError_t launch_pack_state(const float* h0, float* hx, int L, int T, int B, int H, int BP, int NC, int b0, int nsl, hipStream_t s) {

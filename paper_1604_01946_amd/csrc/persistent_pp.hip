@@ -77,11 +77,12 @@ __global__ __launch_bounds__(256) void pers_fwd_pp_kernel(const PersFwdArgs a) {
   const int u0 = 8 * s;
   const size_t TB = (size_t)T * B;
   // The waves of a layer read a slot in orders rotated against each other (all of them would otherwise ask the same
-  // L2 lines at the same time).  The rotation is a multiple of four groups, so that the address of a request is a scalar
-  // base plus the lane's fixed offset plus an immediate: scalar arithmetic costs a wave that runs matrix instructions
-  // back to back nothing, every vector instruction costs its full issue time (one wave per SIMD: nothing else to issue).
-  constexpr int NR4 = NK8 / 4 > 0 ? NK8 / 4 : 1;
-  const int rot = NK8 >= 4 ? 4 * (((int)(blockIdx.x >> 3) + q) & (NR4 - 1)) : 0;
+  // L2 lines at the same time).  The rotation is a multiple of four groups (of two where four do not divide them), so
+  // that the address of a request is a scalar base plus the lane's fixed offset plus an immediate: scalar arithmetic costs
+  // a wave that runs matrix instructions back to back nothing, every vector instruction costs its full issue time (one wave
+  // per SIMD: nothing else to issue).
+  constexpr int RU = NK8 % 4 == 0 ? 4 : 2, NR = NK8 / RU;
+  const int rot = RU * ((((int)blockIdx.x >> 3) + q) % NR);
 
   if constexpr (TRACE) {  // (slot 5 of step 0: kernel entry under chain 1, weights in place under chain 0)
     if (a.trace && (int)blockIdx.x == a.trace_block && threadIdx.x == 0) a.trace[((size_t)T + 0) * 8 + 5] = wall_clock64();
@@ -100,7 +101,7 @@ __global__ __launch_bounds__(256) void pers_fwd_pp_kernel(const PersFwdArgs a) {
     const size_t rowW = ((size_t)gate * H + u0 + 2 * cc + par) * Il;
 #pragma unroll
     for (int i = 0; i < NK8; ++i) {
-      const int k8 = (i + rot) & (NK8 - 1);
+      const int k8 = wrap<NK8>(i + rot);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int k = q * (H / 4) + 8 * k8 + 2 * j + kk;
@@ -137,7 +138,7 @@ __global__ __launch_bounds__(256) void pers_fwd_pp_kernel(const PersFwdArgs a) {
   int* const flags = a.flags + (size_t)sl * a.L * (T + 1) * 2 * NL * kFlagStride;
   auto slot = [&](int layer, int st, int c) { return hx + (((size_t)layer * (T + 1) + st) * 2 + c) * H * 32; };
   auto flag = [&](int layer, int st, int c) { return flags + (((size_t)layer * (T + 1) + st) * 2 + c) * NL * kFlagStride; };
-  const int arrive_line = ((4 * s + q) & (NL - 1)) * kFlagStride;
+  const int arrive_line = ((4 * s + q) % NL) * kFlagStride;
   // the layer below is, for layer 0, the input sequence itself: x in exchange layout, all of it there before the launch
   const bool in_is_x = l == 0;
   const float* const in_base = in_is_x ? a.xin + (size_t)sl * (T + 1) * H * 64 : slot(l - 1, 0, 0);
@@ -156,7 +157,7 @@ __global__ __launch_bounds__(256) void pers_fwd_pp_kernel(const PersFwdArgs a) {
   } tr{trc};
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // once: drop whatever earlier launches left in L1/L2
 
-  int rv = rot >> 2;
+  int rv = rot / RU;
   // The lane offset as a 32-bit register that the optimiser meets anew in every block (fresh_lo): next to the scalar
   // base it then becomes the offset operand of the request instead of one 64-bit vector addition per request.
   unsigned lo = lane * 16;
@@ -166,8 +167,8 @@ __global__ __launch_bounds__(256) void pers_fwd_pp_kernel(const PersFwdArgs a) {
   };
   auto ldx = [&](const float* src, int i) {  // src: the slot (wave-uniform); group i of this wave's K quarter
     const char* const sb = reinterpret_cast<const char*>(src) +
-                           ((size_t)q * NK8 + (NK8 >= 4 ? 4 * (((i >> 2) + rv) & (NR4 - 1)) : 0)) * 1024;
-    return *reinterpret_cast<const floatx4*>(sb + lo + (NK8 >= 4 ? (i & 3) : i) * 1024);
+                           ((size_t)q * NK8 + RU * wrap<NR>(i / RU + rv)) * 1024;
+    return *reinterpret_cast<const floatx4*>(sb + lo + (i % RU) * 1024);
   };
   auto mma4 = [&](floatx16& acc, const float (&wgt)[4], const floatx4& bv) {
 #pragma unroll
@@ -452,20 +453,14 @@ hipError_t launch_pp(int grid, const PersFwdArgs& a, hipStream_t s) {
 
 template <int CELL>
 hipError_t launch_pp_h(int H, int grid, const PersFwdArgs& a, hipStream_t s) {
-  if (H == 512) return launch_pp<512, CELL>(grid, a, s);
-  if (H == 256) return launch_pp<256, CELL>(grid, a, s);
-  if (H == 128) return launch_pp<128, CELL>(grid, a, s);
-  return hipErrorInvalidValue;
+  return with_on_chip_size(H, [&](auto h) { return launch_pp<decltype(h)::value, CELL>(grid, a, s); });
 }
 
 hipError_t launch_fwd_pp(int cell, int H, int grid, const PersFwdArgs& a, hipStream_t s) {  // cell 0: LSTM, 1: GRU, 2: ReLU, 3: tanh
+  if (cell == 0) return launch_pp_h<0>(H, grid, a, s);
   if (cell == 1) return launch_pp_h<1>(H, grid, a, s);
   if (cell == 2) return launch_pp_h<2>(H, grid, a, s);
   if (cell == 3) return launch_pp_h<3>(H, grid, a, s);
-  if (cell != 0) return hipErrorInvalidValue;
-  if (H == 512) return launch_pp<512, 0>(grid, a, s);
-  if (H == 256) return launch_pp<256, 0>(grid, a, s);
-  if (H == 128) return launch_pp<128, 0>(grid, a, s);
   return hipErrorInvalidValue;
 }
 

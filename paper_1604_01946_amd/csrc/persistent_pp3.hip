@@ -60,11 +60,12 @@ __global__ __launch_bounds__(256) void pers_fwd_pp3_kernel(const PersFwdArgs a) 
   const int u0 = 8 * s;
   const size_t TB = (size_t)T * B;
   // The waves of a layer read a slot in orders rotated against each other (all of them would otherwise ask the same
-  // L2 lines at the same time).  The rotation is a multiple of four groups, so that the address of a request is a scalar
-  // base plus the lane's fixed offset plus an immediate: scalar arithmetic costs a wave that runs matrix instructions
-  // back to back nothing, every vector instruction costs its full issue time (one wave per SIMD: nothing else to issue).
-  constexpr int NR4 = NK / 4 > 0 ? NK / 4 : 1;
-  const int rot = NK >= 4 ? 4 * (((int)(blockIdx.x >> 3) + q) & (NR4 - 1)) : 0;
+  // L2 lines at the same time).  The rotation is a multiple of four groups where they divide into fours, so that the
+  // address of a request is a scalar base plus the lane's fixed offset plus an immediate: scalar arithmetic costs a wave
+  // that runs matrix instructions back to back nothing, every vector instruction costs its full issue time (one wave per
+  // SIMD: nothing else to issue).
+  constexpr int RU = NK % 4 == 0 ? 4 : 1, NR = NK / RU;
+  const int rot = RU * ((((int)blockIdx.x >> 3) + q) % NR);
 
   if constexpr (TRACE) {  // (slot 5 of step 0: kernel entry under chain 1, weights in place under chain 0)
     if (a.trace && (int)blockIdx.x == a.trace_block && threadIdx.x == 0) a.trace[((size_t)T + 0) * 8 + 5] = wall_clock64();
@@ -84,7 +85,7 @@ __global__ __launch_bounds__(256) void pers_fwd_pp3_kernel(const PersFwdArgs a) 
     const float sgn = q < 2 ? -kUp : kUp;
 #pragma unroll
     for (int i = 0; i < NK; ++i) {
-      const int k = q * (H / 4) + 16 * ((i + rot) & (NK - 1)) + 8 * kk;
+      const int k = q * (H / 4) + 16 * wrap<NK>(i + rot) + 8 * kk;
       float vr[8], vw[8];
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
@@ -122,7 +123,7 @@ __global__ __launch_bounds__(256) void pers_fwd_pp3_kernel(const PersFwdArgs a) 
   int* const flags = a.flags + (size_t)sl * a.L * (T + 1) * 2 * NL * kFlagStride;
   auto slot = [&](int layer, int st, int c) { return hx + (((size_t)layer * (T + 1) + st) * 2 + c) * SLOT; };
   auto flag = [&](int layer, int st, int c) { return flags + (((size_t)layer * (T + 1) + st) * 2 + c) * NL * kFlagStride; };
-  const int arrive_line = ((4 * s + q) & (NL - 1)) * kFlagStride;
+  const int arrive_line = ((4 * s + q) % NL) * kFlagStride;
   // the layer below is, for layer 0, the input sequence itself: x in exchange layout, all of it there before the launch
   const bool in_is_x = l == 0;
   const float* const in_base = in_is_x ? a.xin + (size_t)sl * (T + 1) * 2 * SLOT : slot(l - 1, 0, 0);
@@ -141,7 +142,7 @@ __global__ __launch_bounds__(256) void pers_fwd_pp3_kernel(const PersFwdArgs a) 
   } tr{trc};
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // once: drop whatever earlier launches left in L1/L2
 
-  int rv = rot >> 2;
+  int rv = rot / RU;
   // The lane offset as a 32-bit register that the optimiser meets anew in every block (fresh_lo): next to the scalar
   // base it then becomes the offset operand of the request instead of one 64-bit vector addition per request.
   unsigned lo = lane * 16;
@@ -151,8 +152,8 @@ __global__ __launch_bounds__(256) void pers_fwd_pp3_kernel(const PersFwdArgs a) 
   };
   auto ldx = [&](const float* src, int i, int p) {  // src: the slot (wave-uniform); group i of this wave's K quarter, part p
     const char* const sb = reinterpret_cast<const char*>(src) + (size_t)p * H * 64 +
-                           ((size_t)q * NK + (NK >= 4 ? 4 * (((i >> 2) + rv) & (NR4 - 1)) : 0)) * 1024;
-    return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uintx4*>(sb + lo + (NK >= 4 ? (i & 3) : i) * 1024));
+                           ((size_t)q * NK + RU * wrap<NR>(i / RU + rv)) * 1024;
+    return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uintx4*>(sb + lo + (i % RU) * 1024));
   };
 
   // Operands of a chain, three parts per group: at the start of the chain's block its ring holds the whole
@@ -429,7 +430,7 @@ hipError_t launch_pp3(int grid, const PersFwdArgs& a, hipStream_t s) {
   // 0.72 ms, (2, 4, 8) 0.73, (2, 8, 8) 0.78, (2, 10, 8) 0.84; (2, 6, 4) 0.79, (2, 7, 6) 0.77; (3, 6, 8) 0.73, (4, 7, 8) 0.74.
   // H = 256, B = 128, tanh: (2, 2, 4) and (1, 2, 4) 0.45, (1, 1, 1) 0.47, (1, 3, 2) 0.54, (1, 4, 4) 0.67, (1, 6, 4) 1.02: the later the
   // completion of the other chain's publication, the more the layers above wait for it.
-  constexpr int LAG = 2, GA = HH == 512 ? 6 : 2, PF = HH == 512 ? 8 : 4;
+  constexpr int LAG = 2, GA = HH / 64 - 2, PF = HH / 64;
   const void* fn = a.trace ? (const void*)pers_fwd_pp3_kernel<HH, LAG, GA, PF, true, CELL>
                            : (const void*)pers_fwd_pp3_kernel<HH, LAG, GA, PF, false, CELL>;
   void* params[] = {const_cast<PersFwdArgs*>(&a)};
@@ -438,9 +439,10 @@ hipError_t launch_pp3(int grid, const PersFwdArgs& a, hipStream_t s) {
 
 template <int CELL>
 hipError_t launch_pp3_h(int H, int grid, const PersFwdArgs& a, hipStream_t s) {
-  if (H == 512) return launch_pp3<512, CELL>(grid, a, s);
-  if (H == 256) return launch_pp3<256, CELL>(grid, a, s);
-  return hipErrorInvalidValue;
+  return with_on_chip_size(H, [&](auto h) {
+    if constexpr (decltype(h)::value >= 256) return launch_pp3<decltype(h)::value, CELL>(grid, a, s);
+    else return hipErrorInvalidValue;
+  });
 }
 
 }  // namespace

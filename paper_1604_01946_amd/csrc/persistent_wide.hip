@@ -42,7 +42,7 @@ __global__ __launch_bounds__(256) void pers_fwd32_kernel(const PersFwdArgs a) {
   const int kk = lane >> 5, n = lane & 31;
   const int u0 = 8 * s;
   const size_t TB = (size_t)T * B;
-  const int rot = ((int)(blockIdx.x >> 3) + __builtin_amdgcn_readfirstlane(wave)) & (NK4 - 1);
+  const int rot = (((int)blockIdx.x >> 3) + __builtin_amdgcn_readfirstlane(wave)) % NK4;
 
   // ---- weights -> registers: A operand row rho = lane%32 = (gate rho/8, unit rho%8), k = wave*H/4 + 4*k4 + 2*m + kk
   float wR[NK4][2], wW[NK4][2];
@@ -57,7 +57,7 @@ __global__ __launch_bounds__(256) void pers_fwd32_kernel(const PersFwdArgs a) {
     const size_t row = ((size_t)gate * H + u0 + (n & 7)) * H;
 #pragma unroll
     for (int i = 0; i < NK4; ++i) {
-      const int k4 = (i + rot) & (NK4 - 1);
+      const int k4 = wrap<NK4>(i + rot);
 #pragma unroll
       for (int m = 0; m < 2; ++m) {
         const int k = wave * (H / 4) + 4 * k4 + 2 * m + kk;
@@ -103,7 +103,7 @@ __global__ __launch_bounds__(256) void pers_fwd32_kernel(const PersFwdArgs a) {
   // loads with a few scalar instructions.
   int rv = rot;
   auto ldx = [&](const float* src, int i) {
-    return *reinterpret_cast<const floatx4*>(src + (size_t)((i + rv) & (NK4 - 1)) * 256);
+    return *reinterpret_cast<const floatx4*>(src + (size_t)wrap<NK4>(i + rv) * 256);
   };
 
   // ---- everything after the MFMAs of step t: K-split reduction, gates, publish h_t, reserve
@@ -408,21 +408,11 @@ __global__ __launch_bounds__(256) void pers_bwd32_kernel(const PersBwdArgs a, co
   float* const xs = smem + 4096;    // [8 blocks of 8 k][256]: this step's dA slice in exchange order
   float* const wl = smem + 6144;    // [4 waves][LP][64 lanes]
 
-  // blockIdx -> (layer, batch half, slice): one (layer, half) group per 8/(L*NBH) XCDs when that divides
+  // blockIdx -> (layer, batch half, slice)
   int l, bh, s2;
-  {
-    const int bid = blockIdx.x, groups = a.L * NBH;
-    if (groups <= 8 && 8 % groups == 0 && NS2 % (8 / groups) == 0 && (gridDim.x % 8) == 0) {
-      const int per = 8 / groups, xcd = bid & 7, grp = xcd / per;
-      l = grp / NBH;
-      bh = grp % NBH;
-      s2 = (bid >> 3) * per + (xcd % per);
-    } else {
-      l = bid / (NS2 * NBH);
-      bh = (bid / NS2) % NBH;
-      s2 = bid % NS2;
-    }
-  }
+  map_block(a.L * NBH, NS2, l, s2);
+  bh = l % NBH;
+  l /= NBH;
   const int T = a.T, B = a.B;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int kk = lane >> 5, n = lane & 31;
@@ -692,9 +682,9 @@ __global__ __launch_bounds__(256) void pers_bwd32_kernel(const PersBwdArgs a, co
 template <int CELL>
 hipError_t launch_fwd32(int H, int grid, const PersFwdArgs& a, hipStream_t s) {
   void* params[] = {const_cast<PersFwdArgs*>(&a)};
-  const void* fn = H == 512 ? (const void*)pers_fwd32_kernel<512, CELL>
-                            : (H == 256 ? (const void*)pers_fwd32_kernel<256, CELL> : (const void*)pers_fwd32_kernel<128, CELL>);
-  return launch_resident(fn, grid, params, 0, s);
+  return with_on_chip_size(H, [&](auto h) {
+    return launch_resident((const void*)pers_fwd32_kernel<decltype(h)::value, CELL>, grid, params, 0, s);
+  });
 }
 
 template <int HH, int CELL = 0>

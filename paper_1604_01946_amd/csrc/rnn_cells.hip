@@ -135,9 +135,10 @@ inline bool gru_persistent_shape(int cell, const Dims& d) {
   //   H = 512 GRU 1.28 and 1.11 at 512 rows, 1.02 at 1024, 0.86 at 2048; single gate 1.17 and 1.03 at 512
   //   H = 256 GRU 1.35 and 1.26 at 1024, 1.03 at 2048, 0.83 at 4096; single gate 1.18 and 1.12 at 1024, 0.72 at 2048
   //   H = 128 GRU 1.45 and 1.46 at 2048, 1.02 at 4096, 0.78 at 8192; single gate 1.20 and 1.20 at 2048, 0.74 at 4096
-  if (d.H == 512) return d.B <= (gru ? 1024 : 512);
-  if (d.H == 256) return d.B <= (gru ? 2048 : 1024);
-  return d.H == 128 && d.B <= (gru ? 4096 : 2048);
+  // (sizes between these as the next of them)
+  if (d.H > 512 || d.H < 128 || d.H % 64 != 0) return false;
+  const int rows = d.H > 256 ? 1024 : (d.H > 128 ? 2048 : 4096);
+  return d.B <= (gru ? rows : rows / 2);
 }
 // cell selector of the templated persistent kernels
 inline int kernel_cell(int cell) { return cell == RNN_CELL_GRU ? 1 : (cell == RNN_CELL_RELU ? 2 : 3); }
@@ -363,7 +364,7 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 // Hidden sizes without persistent kernels run zero-padded to the next size that has them, as for the LSTM
 // (padded_hidden): a padded unit has pre-activations 0 and initial state 0, so the GRU keeps it at
 // h = (1 - 1/2) tanh(0) + 1/2 * 0 = 0 and the single gate at act(0) = 0, nothing reads it, and its gradients are 0.
-inline Dims rnn_padded_rule(int cell, const Dims& d) {  // what the environment does not switch off
+inline Dims rnn_reported_dims(int cell, const Dims& d) {  // the size that buffers are reported for, and whether a size is padded at all
   // between 512 and 1024 these cells gain more than the LSTM does (their step-by-step path is one GEMM and one
   // point-wise kernel per step): 2.5-3 times at every size measured
   if (d.H > 512 && d.H < 1024 && gru_persistent_shape(cell, Dims{d.L, d.T, d.B, d.I, 1024}))
@@ -376,8 +377,12 @@ inline Dims rnn_padded_rule(int cell, const Dims& d) {  // what the environment 
     return (pad && gru_persistent_shape(cell, p)) ? p : d;
   }
   // the LSTM's rule, but only where these cells' persistent kernels take the padded shape (their batch limits are lower)
-  const Dims p{d.L, d.T, d.B, d.I, padded_hidden_rule(d)};
+  const Dims p{d.L, d.T, d.B, d.I, reported_hidden(d)};
   return (p.H == d.H || gru_persistent_shape(cell, p)) ? p : d;
+}
+inline Dims rnn_padded_rule(int cell, const Dims& d) {  // what the environment does not switch off
+  const Dims r = rnn_reported_dims(cell, d);
+  return r.H == d.H ? d : Dims{d.L, d.T, d.B, d.I, std::min(granular_hidden(d.H), r.H)};
 }
 inline Dims rnn_padded_dims(int cell, const Dims& d) {
   return (knobs().rnn_no_persistent || knobs().no_pad) ? d : rnn_padded_rule(cell, d);
@@ -466,14 +471,16 @@ extern "C" {
 size_t rnn_reserve_bytes(int cell, int L, int T, int B, int I, int H) {
   if (gates_of(cell) == 0 || L <= 0 || T <= 0 || B <= 0 || I <= 0 || H <= 0) return 0;
   // (padded or as given, whichever is larger -- padding only grows H -- so that the answer does not depend on the environment)
-  return (size_t)L * res_layer_floats(cell, rnn_padded_rule(cell, Dims{L, T, B, I, H})) * sizeof(float);
+  return (size_t)L * res_layer_floats(cell, rnn_reported_dims(cell, Dims{L, T, B, I, H})) * sizeof(float);
 }
 
 size_t rnn_workspace_bytes(int cell, int L, int T, int B, int I, int H) {
   if (gates_of(cell) == 0 || L <= 0 || T <= 0 || B <= 0 || I <= 0 || H <= 0) return 0;
-  const Dims d{L, T, B, I, H}, p = rnn_padded_rule(cell, d);
-  const size_t given = ws_total(cell, d);
-  return p.H == d.H ? given : std::max(given, rnn_pad_layout(cell, d, p).total);
+  const Dims d{L, T, B, I, H};
+  size_t need = ws_total(cell, d);
+  for (const Dims& p : {rnn_reported_dims(cell, d), rnn_padded_rule(cell, d)})
+    if (p.H != d.H) need = std::max(need, rnn_pad_layout(cell, d, p).total);
+  return need;
 }
 
 int rnn_forward(int cell, int L, int T, int B, int I, int H, const float* x, const float* h0, const float* W,

@@ -48,14 +48,16 @@ struct BwdArgs {
 
 // Hidden size the kernels run a shape at.  Hidden units with zero weights, bias and initial state stay at h = c = 0
 // for every step and receive zero gradients, so a network padded that way computes exactly the given one; the
-// persistent kernels exist for H = 128, 256 and 512, and any other hidden size below 512 runs faster (several times,
-// with more than one layer) padded to the next of them than on the per-step paths.  LSTM_NO_PAD=1 in the environment disables it.
+// persistent kernels exist for the multiples of 64 from 128 to 512, and any other hidden size below 512 runs faster (several
+// times, with more than one layer) padded to the next of them than on the per-step paths.  LSTM_NO_PAD=1 in the environment disables it.
 // micro.hip: a whole pass in one workgroup, for the smallest networks (part of the step path)
 bool micro_shape(const Dims& d);
 hipError_t launch_micro_forward(const FwdArgs& a);
 hipError_t launch_micro_backward(const BwdArgs& a);
 int padded_hidden(const Dims& d);
 int padded_hidden_rule(const Dims& d);  // the same without looking at LSTM_NO_PAD (size queries cover both settings)
+int reported_hidden(const Dims& d);     // the size that buffers are reported for, at least padded_hidden_rule
+int granular_hidden(int H);             // the next size with kernels of its own
 inline Dims padded_dims(const Dims& d) { return Dims{d.L, d.T, d.B, d.I, padded_hidden(d)}; }
 // dst [outer][rd][cd] <- src [outer][rs][cs]: the common corner is copied, the rest of dst is zero (pads and crops).
 hipError_t launch_resize(float* dst, const float* src, long outer, int rd, int cd, int rs, int cs, hipStream_t s);

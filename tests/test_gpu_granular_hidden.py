@@ -1,0 +1,50 @@
+"""Hidden sizes between 128, 256 and 512: kernels for every multiple of 64, whose K quarters and counter lines are no powers of
+two.  At the size itself, one below it (padded by a column) and one above the size before it; few rows (narrow kernels),
+slices of 16 and 64 rows, several launches, inputs wider than the hidden size, short and long enough for every variant."""
+import pytest
+
+from paper_1604_01946_amd.inputs import Config
+from test_gpu_parity import run_case
+from test_gpu_rnn_cells import run as run_cell
+
+pytestmark = pytest.mark.gpu
+
+SIZES = (192, 320, 384, 448)
+
+
+def cfg(L, T, B, I, H):
+    return Config("granular", L=L, T=T, B=B, I=I, H=H, state_std=0.3, dstate_std=0.3)
+
+
+@pytest.mark.parametrize("H", SIZES)
+@pytest.mark.parametrize("split3", ["0", "1"])
+@pytest.mark.parametrize("L,T,B,I", [(2, 6, 70, 48), (1, 4, 300, 0), (3, 5, 64, 0), (2, 9, 33, 600)])
+def test_wide(H, split3, L, T, B, I, knobs):
+    knobs(LSTM_SPLIT3=split3)
+    run_case(cfg(L, T, B, I or H, H), 7, 0)
+
+
+@pytest.mark.parametrize("H", SIZES)
+@pytest.mark.parametrize("L,T,B,I", [(2, 5, 2, 40), (1, 20, 16, 0), (3, 5, 17, 0), (1, 9, 64, 30), (2, 4, 32, 700)])
+def test_narrow(H, L, T, B, I):
+    run_case(cfg(L, T, B, I or H, H), 8, 0)
+
+
+@pytest.mark.parametrize("H", [129, 191, 193, 257, 319, 321, 383, 385, 447, 449, 511])
+@pytest.mark.parametrize("B", [1, 20, 65])
+def test_padded(H, B):
+    run_case(cfg(2, 4, B, 50, H), 9, 0)
+
+
+@pytest.mark.parametrize("H", SIZES + (300,))
+@pytest.mark.parametrize("cell", ["gru", "tanh", "relu"])
+@pytest.mark.parametrize("L,T,B,I", [(1, 3, 1, 20), (2, 12, 70, 0), (1, 10, 40, 500), (8, 3, 20, 0)])
+def test_other_cells(H, cell, L, T, B, I):
+    run_cell(cell, L, T, B, I or H, H, seed=4)
+
+
+@pytest.mark.parametrize("H", SIZES)
+def test_one_chain(H, knobs):
+    knobs(LSTM_PINGPONG="0", RNN_PINGPONG="0")
+    run_case(cfg(2, 5, 70, 48, H), 5, 0)
+    run_cell("gru", 2, 5, 70, 48, H, seed=4)

@@ -908,7 +908,9 @@ int backward_layers(const BwdArgs& a, int cell, bool* bias_done, bool with_weigh
   // two alternating chains per workgroup (LSTM, slices of 64 rows): counters of H/16 lines per (layer, step, quarter)
   // (the kernel with one chain has instances for the powers of two only)
   const bool pp = wide && (((cell == 0 || knobs().rnn_pp) && knobs().pingpong != 0) || (d.H & (d.H - 1)) != 0);
-  k.dummy = reinterpret_cast<float*>(a.ws + a.w.scratch);
+  // (a line of 128 bytes per workgroup, L * H/16 * 2 slices of them, in the reserve stand-in, 24 bytes per unit, layer, step
+  // and row, which a backward call does not use otherwise)
+  k.dummy = reinterpret_cast<float*>(a.ws + a.w.resv);
   k.trace = (g_trace_bytes >= (size_t)d.T * 64 * (pp ? 2 : 1)) ? g_trace_buf : nullptr;
   k.trace_block = g_trace_block;
   const int grid = d.L * (d.H / 8);

@@ -48,3 +48,8 @@ def test_one_chain(H, knobs):
     knobs(LSTM_PINGPONG="0", RNN_PINGPONG="0")
     run_case(cfg(2, 5, 70, 48, H), 5, 0)
     run_cell("gru", 2, 5, 70, 48, H, seed=4)
+
+
+def test_scratch_line_of_many_workgroups():
+    """The stores that nobody wants go to a line per workgroup behind the scratch area: 256 workgroups and a batch of one."""
+    run_cell("gru", 16, 3, 1, 128, 128, seed=4)

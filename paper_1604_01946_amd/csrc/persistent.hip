@@ -573,6 +573,7 @@ int run_backward_persistent_large(const BwdArgs& args, int cell, bool* bias_done
       k.dhT = a.dhT ? a.dhT + (size_t)l * BH : nullptr;
       k.dcT = a.dcT ? a.dcT + (size_t)l * BH : nullptr;
       k.dA = dA; k.X = X; k.Pp = Pp;
+      k.tops = a.dA_tops ? a.dA_tops + (size_t)l * G : nullptr;
       k.dh0 = a.dh0 ? a.dh0 + (size_t)l * BH : nullptr;
       k.dc0 = a.dc0 ? a.dc0 + (size_t)l * BH : nullptr;
       k.db = bias_in_kernel ? a.db + (size_t)l * GW : nullptr;
@@ -632,6 +633,13 @@ int layers_per_launch(const Dims& d) {
   DeviceInfo di;
   if (!device_info(di)) return 0;
   return di.cus / (d.H / 8);
+}
+
+// Whether a backward pass runs on the kernel with two alternating chains per workgroup (slices of 64 rows).  (The kernel with one
+// chain has instances for the powers of two only.)
+bool bwd_alternating(const Dims& d, int cell) {
+  const bool wide = cell != 0 || (narrow_slice_rows(d, cell, knobs().bwd_narrow, true) == 0 && bwd_wide(d));
+  return wide && (((cell == 0 || knobs().rnn_pp) && knobs().pingpong != 0) || (d.H & (d.H - 1)) != 0);
 }
 
 int forward_layers(const FwdArgs& a, int cell);
@@ -807,8 +815,17 @@ int forward_layers(const FwdArgs& args, int cell) {
 // cell as in run_forward_persistent.  For the other cells the function stops after the propagation (gate gradients
 // [L][T*B][4H] at the start of the workspace: GRU r, z, n, and n times r; single gate: the first H columns) and
 // reports in *bias_done whether db is complete; the caller forms the weight gradients.
-int run_backward_persistent(const BwdArgs& a, int cell, bool* bias_done, LayerGradients* lg) {
+int run_backward_persistent(BwdArgs& a, int cell, bool* bias_done, LayerGradients* lg) {
   const Dims& d = a.d;
+  // The largest magnitude of every gate gradient, [L][4H], where the step path has its packed R: the weight-gradient products, if
+  // they are large enough for two fp16 parts (launch_group3), need not read the gate gradients once more to find them
+  // (L = 4, H = 512, B = 64, T = 100: 210 MB; 2.20 -> 2.14 ms).
+  a.dA_tops = nullptr;
+  if (d.H >= 384 && (long)d.T * d.B >= 1024 && (persistent_large(d, true) || bwd_alternating(d, cell))) {
+    ProfScope ps(LSTM_PHASE_BWD_PACK, a.stream);
+    a.dA_tops = reinterpret_cast<unsigned*>(a.ws + a.w.RT);
+    CK(launch_fill_zero(a.dA_tops, (size_t)4 * d.L * d.H * sizeof(unsigned), a.stream), "zero largest magnitudes");
+  }
   if (persistent_large(d, true)) {
     if (!ensure_watchdog()) return LSTM_HIP_ERROR;
     return run_backward_persistent_large(a, cell, bias_done, lg);
@@ -845,6 +862,7 @@ int run_backward_persistent(const BwdArgs& a, int cell, bool* bias_done, LayerGr
     g.reserve = a.reserve + (size_t)g0 * rstride;
     g.w.P = a.w.P + (size_t)g0 * TB * 4 * d.H * sizeof(float);   // gate gradients of the group's layers, in place
     g.w.dx = a.w.dx + (size_t)g0 * TB * d.H * sizeof(float);
+    if (a.dA_tops) g.dA_tops = a.dA_tops + (size_t)g0 * 4 * d.H;
     bool done = false;
     const int st = backward_layers(g, cell, &done, false);
     if (st != LSTM_OK) return st;
@@ -899,15 +917,15 @@ int backward_layers(const BwdArgs& a, int cell, bool* bias_done, bool with_weigh
   // MFMA tile that would otherwise hold zeros) and write the gradient of the network input themselves.
   k.dx0 = (a.dx && d.I == d.H) ? a.dx : nullptr;
   k.db = nullptr;
+  k.tops = a.dA_tops;
   if (wide && a.db && d.B <= 64) {  // one launch: the wide kernel adds the bias gradient into db itself (two addends per element)
     ProfScope ps(LSTM_PHASE_BIAS_GRAD, s);
     CK(launch_fill_zero(a.db, (size_t)d.L * GW * 4, s), "zero db");
     k.db = a.db;
   }
   k.L = d.L; k.T = d.T; k.B = d.B; k.I = d.I; k.H = d.H; k.spin_limit = spin_limit(); k.full_fences = full_fences();
-  // two alternating chains per workgroup (LSTM, slices of 64 rows): counters of H/16 lines per (layer, step, quarter)
-  // (the kernel with one chain has instances for the powers of two only)
-  const bool pp = wide && (((cell == 0 || knobs().rnn_pp) && knobs().pingpong != 0) || (d.H & (d.H - 1)) != 0);
+  // two alternating chains per workgroup: counters of H/16 lines per (layer, step, quarter)
+  const bool pp = bwd_alternating(d, cell);
   // (a line of 128 bytes per workgroup, L * H/16 * 2 slices of them, in the reserve stand-in, 24 bytes per unit, layer, step
   // and row, which a backward call does not use otherwise)
   k.dummy = reinterpret_cast<float*>(a.ws + a.w.resv);

@@ -416,15 +416,14 @@ RnnPad rnn_pad_layout(int cell, const Dims& d, const Dims& p) {
   return q;
 }
 
-int pad_rnn_parameters(int cell, const Dims& d, int Hp, const float* W, const float* R, const float* b, float* Wp, float* Rp,
-                       float* bp, hipStream_t s) {
+void pad_rnn_parameters(int cell, const Dims& d, int Hp, const float* W, const float* R, const float* b, float* Wp, float* Rp,
+                        float* bp, ResizeGroup& g) {
   const long ng = gates_of(cell);
   const size_t G = (size_t)ng * d.H, Gp = (size_t)ng * Hp;
-  CK(launch_resize(Wp, W, ng, Hp, d.I, d.H, d.I, s), "pad W (layer 0)");
-  CK(launch_resize(Wp + Gp * d.I, W + G * d.I, ng * (d.L - 1), Hp, Hp, d.H, d.H, s), "pad W");
-  CK(launch_resize(Rp, R, ng * d.L, Hp, Hp, d.H, d.H, s), "pad R");
-  if (b) CK(launch_resize(bp, b, ng * d.L, 1, Hp, 1, d.H, s), "pad b");
-  return LSTM_OK;
+  g.add(Wp, W, ng, Hp, d.I, d.H, d.I);
+  g.add(Wp + Gp * d.I, W + G * d.I, ng * (d.L - 1), Hp, Hp, d.H, d.H);
+  g.add(Rp, R, ng * d.L, Hp, Hp, d.H, d.H);
+  if (b) g.add(bp, b, ng * d.L, 1, Hp, 1, d.H);
 }
 
 int forward_padded(int cell, const Dims& d, const Dims& p, const float* x, const float* h0, const float* W, const float* R,
@@ -432,14 +431,16 @@ int forward_padded(int cell, const Dims& d, const Dims& p, const float* x, const
   const RnnPad q = rnn_pad_layout(cell, d, p);
   auto f = [&](size_t off) { return reinterpret_cast<float*>(ws + off); };
   const int LB = d.L * d.B, TB = d.T * d.B;
-  int st = pad_rnn_parameters(cell, d, p.H, W, R, b, f(q.W), f(q.R), f(q.b), s);
-  if (st != LSTM_OK) return st;
-  if (h0) CK(launch_resize(f(q.h0), h0, 1, LB, p.H, LB, d.H, s), "pad h0");
-  st = forward_impl(cell, p, x, h0 ? f(q.h0) : nullptr, f(q.W), f(q.R), f(q.b), f(q.y), hT ? f(q.hT) : nullptr, reserve,
+  ResizeGroup g, u;
+  pad_rnn_parameters(cell, d, p.H, W, R, b, f(q.W), f(q.R), f(q.b), g);
+  if (h0) g.add(f(q.h0), h0, 1, LB, p.H, LB, d.H);
+  CK(launch_resize_group(g, s), "pad operands");
+  const int st = forward_impl(cell, p, x, h0 ? f(q.h0) : nullptr, f(q.W), f(q.R), f(q.b), f(q.y), hT ? f(q.hT) : nullptr, reserve,
                     ws + q.inner, s);
   if (st != LSTM_OK) return st;
-  CK(launch_resize(y, f(q.y), 1, TB, d.H, TB, p.H, s), "unpad y");
-  if (hT) CK(launch_resize(hT, f(q.hT), 1, LB, d.H, LB, p.H, s), "unpad hT");
+  u.add(y, f(q.y), 1, TB, d.H, TB, p.H);
+  if (hT) u.add(hT, f(q.hT), 1, LB, d.H, LB, p.H);
+  CK(launch_resize_group(u, s), "unpad results");
   return LSTM_OK;
 }
 
@@ -451,19 +452,21 @@ int backward_padded(int cell, const Dims& d, const Dims& p, const float* x, cons
   const int LB = d.L * d.B, TB = d.T * d.B;
   const long ng = gates_of(cell);
   const size_t G = (size_t)ng * d.H, Gp = (size_t)ng * p.H;
-  int st = pad_rnn_parameters(cell, d, p.H, W, R, nullptr, f(q.W), f(q.R), nullptr, s);
-  if (st != LSTM_OK) return st;
-  if (h0) CK(launch_resize(f(q.h0), h0, 1, LB, p.H, LB, d.H, s), "pad h0");
-  CK(launch_resize(f(q.dy), dy, 1, TB, p.H, TB, d.H, s), "pad dy");
-  if (dhT) CK(launch_resize(f(q.dhT), dhT, 1, LB, p.H, LB, d.H, s), "pad dhT");
-  st = backward_impl(cell, p, x, h0 ? f(q.h0) : nullptr, f(q.W), f(q.R), reserve, f(q.dy), dhT ? f(q.dhT) : nullptr, dx,
+  ResizeGroup g, u;
+  pad_rnn_parameters(cell, d, p.H, W, R, nullptr, f(q.W), f(q.R), nullptr, g);
+  if (h0) g.add(f(q.h0), h0, 1, LB, p.H, LB, d.H);
+  g.add(f(q.dy), dy, 1, TB, p.H, TB, d.H);
+  if (dhT) g.add(f(q.dhT), dhT, 1, LB, p.H, LB, d.H);
+  CK(launch_resize_group(g, s), "pad operands");
+  const int st = backward_impl(cell, p, x, h0 ? f(q.h0) : nullptr, f(q.W), f(q.R), reserve, f(q.dy), dhT ? f(q.dhT) : nullptr, dx,
                      dh0 ? f(q.dh0) : nullptr, f(q.dW), f(q.dR), f(q.db), ws + q.inner, s);
   if (st != LSTM_OK) return st;
-  if (dh0) CK(launch_resize(dh0, f(q.dh0), 1, LB, d.H, LB, p.H, s), "unpad dh0");
-  CK(launch_resize(dW, f(q.dW), ng, d.H, d.I, p.H, d.I, s), "unpad dW (layer 0)");
-  CK(launch_resize(dW + G * d.I, f(q.dW) + Gp * d.I, ng * (d.L - 1), d.H, d.H, p.H, p.H, s), "unpad dW");
-  CK(launch_resize(dR, f(q.dR), ng * d.L, d.H, d.H, p.H, p.H, s), "unpad dR");
-  CK(launch_resize(db, f(q.db), ng * d.L, 1, d.H, 1, p.H, s), "unpad db");
+  if (dh0) u.add(dh0, f(q.dh0), 1, LB, d.H, LB, p.H);
+  u.add(dW, f(q.dW), ng, d.H, d.I, p.H, d.I);
+  u.add(dW + G * d.I, f(q.dW) + Gp * d.I, ng * (d.L - 1), d.H, d.H, p.H, p.H);
+  u.add(dR, f(q.dR), ng * d.L, d.H, d.H, p.H, p.H);
+  u.add(db, f(q.db), ng * d.L, 1, d.H, 1, p.H);
+  CK(launch_resize_group(u, s), "unpad gradients");
   return LSTM_OK;
 }
 

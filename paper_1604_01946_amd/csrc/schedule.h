@@ -60,8 +60,19 @@ int padded_hidden_rule(const Dims& d);  // the same without looking at LSTM_NO_P
 int reported_hidden(const Dims& d);     // the size that buffers are reported for, at least padded_hidden_rule
 int granular_hidden(int H);             // the next size with kernels of its own
 inline Dims padded_dims(const Dims& d) { return Dims{d.L, d.T, d.B, d.I, padded_hidden(d)}; }
-// dst [outer][rd][cd] <- src [outer][rs][cs]: the common corner is copied, the rest of dst is zero (pads and crops).
-hipError_t launch_resize(float* dst, const float* src, long outer, int rd, int cd, int rs, int cs, hipStream_t s);
+// Copies that pad and crop: dst [outer][rd][cd] <- src [outer][rs][cs], the common corner is copied, the rest of dst is zero.
+struct ResizeGroup {
+  struct Op {
+    float* dst;
+    const float* src;
+    int first, rows;  // of the launch's rows
+    int rd, cd, rs, cs;
+    int vec;          // floats per access
+  } op[12];
+  int n = 0, rows = 0;
+  void add(float* dst, const float* src, long outer, int rd, int cd, int rs, int cs);
+};
+hipError_t launch_resize_group(const ResizeGroup& g, hipStream_t s);
 
 size_t reserve_bytes(const Dims& d);
 WsLayout ws_layout(const Dims& d, bool wide_rows = false);

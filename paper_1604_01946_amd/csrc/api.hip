@@ -52,6 +52,7 @@ const Knobs& knobs() {
     k.gemm_short = !env_is("LSTM_GEMM_SHORT", '0');
     k.gemm_split = !env_is("LSTM_GEMM_SPLIT", '0');
     k.gemm_half = env_int("LSTM_GEMM_HALF", 0, 1, -1);
+    k.cell_step = !env_is("LSTM_CELL_STEP", '0');
     k.tiny = !env_is("LSTM_TINY", '0');
     k.split3 = env_int("LSTM_SPLIT3", 0, 2, -1);
     k.large_ksplit = !env_is("LSTM_LARGE_KSPLIT", '0');
@@ -606,6 +607,10 @@ int forward_call(int L, int T, int B, int I, int H, const float* x, const float*
   const Dims d{L, T, B, I, H}, p = padded_dims(d);
   if (workspace_bytes < lstm_workspace_bytes(L, T, B, I, H)) return LSTM_BUFFER_TOO_SMALL;
   if (take_watchdog()) return LSTM_INTERNAL;  // an earlier call's persistent kernel gave up waiting: reported once, here
+  if (!reserve && (flags & LSTM_PATH_MASK) == LSTM_PATH_AUTO && !micro_shape(d) && !path_pinned(d, false)) {
+    FwdArgs a{d, x, h0, c0, W, R, b, y, hT, cT, nullptr, (char*)workspace, WsLayout{}, (hipStream_t)stream};
+    if (cell_step_takes(a)) return run_cell_step(a);
+  }
   if (p.H != d.H) {
     return forward_padded(d, p, x, h0, c0, W, R, b, y, hT, cT, reserve, (char*)workspace, (hipStream_t)stream, flags,
                           no_new_resources);

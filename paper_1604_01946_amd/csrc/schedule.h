@@ -100,6 +100,10 @@ struct LayerGradients {
 int weight_gradients_layers(const BwdArgs& a, const float* dA_all, int l0, int l1, hipStream_t s, bool grouped,
                             bool bias_done, Scratch part);
 int run_forward(const FwdArgs& a, unsigned path);
+bool path_pinned(const Dims& d, bool backward);  // lstm_set_path names a path for the shape
+// cell_step.hip: an inference call of one step and few rows, one launch per layer
+bool cell_step_takes(const FwdArgs& a);
+int run_cell_step(const FwdArgs& a);
 int run_backward(const BwdArgs& a, unsigned path);
 void release_helpers();
 hipError_t setup_persistent();  // creates, for the current device, what the persistent path otherwise creates on first use

@@ -113,6 +113,13 @@ bool gemm_steps(const Dims& d, bool backward) {
   return d.B >= 128 && (long)d.B * d.H >= 128 * 640;
 }
 
+bool path_pinned(const Dims& d, bool backward) {
+  std::lock_guard<std::mutex> lk(g_path_mu);
+  for (const PathOverride& o : g_path_table)
+    if (same_shape(o.d, d) && o.backward == backward) return true;
+  return false;
+}
+
 unsigned resolve_auto_path(const Dims& user, bool backward) {
   {
     std::lock_guard<std::mutex> lk(g_path_mu);

@@ -159,10 +159,10 @@ WsLayout ws_layout(const Dims& d, bool wide_rows) {
   // persistent paths: exchange buffers (large-H backward: gate gradients and partial sums of one layer,
   // 5 MB per step at H = 2048)
   size_t xchg = L * ((size_t)d.T + 1) * G * Bp * 4;
-  if (d.H == 2048 || d.H == 1024) {  // up to four slices of 32 batch rows side by side (one at H = 2048)
-    const size_t nbk = d.H / 128, sl = std::min<size_t>(((size_t)d.B + 31) / 32, d.H == 2048 ? 1 : 4);
-    // (one or two slices at H = 1024 cut their tiles' K in four or two: as many partial sums as four slices)
-    const size_t psl = (d.H == 1024 && sl <= 2) ? 4 : sl;
+  if (d.H == 2048 || d.H == 1024 || large_mid_size(d)) {  // up to four slices of 32 batch rows side by side (one above 1024)
+    const size_t nbk = d.H / 128, sl = std::min<size_t>(((size_t)d.B + 31) / 32, d.H > 1024 ? 1 : 4);
+    // (one or two slices at H = 1024 cut their tiles' K in four or two: as many partial sums as four slices; below 1024 always in four or two)
+    const size_t psl = d.H > 1024 ? sl : d.H == 1024 ? (sl <= 2 ? 4 : sl) : std::max<size_t>(4, 2 * sl);
     const size_t need = d.T * (sl * nbk * 4 * 128 * 32 + psl * nbk * nbk * 128 * 32) * 4;
     if (need > xchg) xchg = need;
     const size_t fwd = sl * ((size_t)d.T + 1) * d.H * 48 * 4;  // a slot holds 32 rows in three bf16 parts
@@ -228,19 +228,23 @@ hipError_t launch_resize_group(const ResizeGroup& g, hipStream_t s) {
 
 int padded_hidden(const Dims& d) { return (knobs().no_pad || micro_shape(d)) ? d.H : padded_hidden_rule(d); }
 
-// Size that the kernels run at: the smallest with kernels of its own, multiples of 64 up to 512 and of 1024 above, that is no
-// larger than the size that buffers are reported for.  A single sequence has kernels for 128, 256 and 512 alone.
+// Size that the kernels run at: the smallest with kernels of its own for that many rows (multiples of 64 up to 512, of 128 up to
+// 1024, of 256 from 1536 on), that is no larger than the size that buffers are reported for.  A single sequence has kernels for 128, 256 and 512 alone.
 // A step's products grow with the square of the size, and at 320 three slices fit side by side where 512 has two (L = 2, T = 50,
 // B = 500, I = 80, H = 320 forward and backward: at 512 4.60 ms, at 320 2.56; L = 3, T = 40, B = 17, I = 120, H = 300 forward:
 // at 512 353 us, at 320 200).
 int padded_hidden_rule(const Dims& d) {
   const int top = reported_hidden(d);
   if (top == d.H || (d.B == 1 && top <= 512)) return top;
-  return std::min(granular_hidden(d.H), top);
+  return std::min(granular_hidden(d), top);
 }
 
-int granular_hidden(int H) {
-  return H <= 512 ? std::max(128, (int)align_up(H, 64)) : (int)align_up(H, 1024);
+int granular_hidden(const Dims& d) {
+  if (d.H <= 512) return std::max(128, (int)align_up(d.H, 64));
+  const int top = (int)align_up(d.H, 1024), unit = d.H <= 1024 ? 128 : 256;
+  for (int h = (int)align_up(d.H, unit); h < top; h += unit)
+    if (large_mid_size(Dims{d.L, d.T, d.B, d.I, h})) return h;
+  return top;
 }
 
 // Size that the reserve and the workspace are reported for, and whether a size is padded at all.

@@ -10,7 +10,8 @@
 //   persistent_pp3.hip    pers_fwd_pp3_kernel: the same on the bf16 matrix cores, operands in three parts
 //   persistent_bpp.hip    pers_bwd_pp_kernel: two quarter-slices of 16 rows alternating on the matrix cores
 //   persistent_tiny.hip   pers_fwd_tiny_kernel / pers_bwd_tiny_kernel: B = 1, the exchanged values are their own flags
-//   persistent_large.hip  pers_fwdL_kernel / pers_bwdL_kernel: one layer per launch, H = 1024 / 2048
+//   persistent_large_dev.h, persistent_large.hip, persistent_large_mid.hip  pers_fwdL_kernel / pers_bwdL_kernel: one layer per launch,
+//                         H = 1024 / 2048, and sizes between 512 and 2048
 //   persistent.hip        host side: residency, launches, which shapes run where, layer groups, batch slices
 #pragma once
 #include "schedule.h"
@@ -217,6 +218,8 @@ hipError_t launch_bwd_tiny(int H, const PersBwdArgs& a, hipStream_t s);
 // s3: the variant on the bf16 matrix cores
 hipError_t launch_fwdL_any(int H, int cell, const PersFwdLArgs& k, hipStream_t s, bool s3);
 hipError_t launch_bwdL_any(int H, int cell, const PersBwdLArgs& k, hipStream_t s, bool s3);
+hipError_t launch_fwdL_mid(int H, int cell, const PersFwdLArgs& k, hipStream_t s, bool s3);
+hipError_t launch_bwdL_mid(int H, int cell, const PersBwdLArgs& k, hipStream_t s, bool s3);
 hipError_t launch_redo_bwdL(const PersBwdLArgs& k, int counters, hipStream_t s);
 hipError_t launch_pack_stateL(const float* h0, float* hx, int T, int B, int H, int b0, int nsl, hipStream_t s);
 // hx0: the same in fp32, slot 0 of every slice one after the other

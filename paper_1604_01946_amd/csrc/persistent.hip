@@ -319,8 +319,8 @@ bool steps_beat_large(const Dims& d, bool backward) {
 
 bool persistent_large(const Dims& d, bool backward) {
   if (knobs().no_large_persistent) return false;
-  if (!(d.H == 1024 || d.H == 2048)) return false;
-  if (d.B > (d.H == 1024 ? kLargeMaxBatch1024 : kLargeMaxBatch2048)) return false;
+  if (!(d.H == 1024 || d.H == 2048 || large_mid_size(d))) return false;
+  if (d.B > (d.H <= 1024 ? kLargeMaxBatch1024 : kLargeMaxBatch2048)) return false;
   DeviceInfo di;
   if (!device_info(di) || !di.coop) return false;
   return (backward ? (d.H / 128) * (d.H / 128) : d.H / 8) <= di.cus;
@@ -368,8 +368,8 @@ int large_split3_steps(const Dims& d, int cell, bool backward) {
   const int c = cell == 0 ? 0 : (cell == 1 ? 1 : 2);
   constexpr int never = 1 << 30;
   constexpr int fwd[2][3] = {{1, 8, 12}, {1, 5, 8}}, bwd2048[3] = {4, 32, 20}, bwd_few[3] = {6, 20, 20}, bwd[3] = {12, 50, 32};
-  if (!backward) return fwd[d.H == 2048][c];
-  if (d.H == 2048) return bwd2048[c];
+  if (!backward) return fwd[d.H > 1024][c];
+  if (d.H > 1024) return bwd2048[c];
   if (d.L == 1 && d.B <= 32) return never;
   return d.L > 1 && d.B <= 64 ? bwd_few[c] : bwd[c];
 }
@@ -500,7 +500,13 @@ int run_backward_persistent_large(const BwdArgs& args, int cell, bool* bias_done
   DeviceInfo di;
   (void)device_info(di);
   const int slices = (d.B + 31) / 32;
-  int cap = di.cus / (NBK * NBK);
+  // A single slice at H = 1024 would occupy 64 CUs: the tiles' K is cut in four, 256 workgroups (LSTM_LARGE_KSPLIT=0:
+  // not); two slices of a single layer cut it in two (with more layers the idle CUs are used by the weight gradients
+  // of the layer above, which is worth more: L = 4, B = 64).  Below 1024 always at least in two: uncut, a workgroup
+  // would finalise three or four octets of units, whose state leaves no registers for a whole tile.
+  const int ks = d.H < 1024 ? (slices == 1 && d.L == 1 ? 4 : 2)
+                 : d.H != 1024 || !knobs().large_ksplit ? 1 : (slices == 1 ? (d.L > 1 ? 2 : 4) : ((slices == 2 && d.L == 1) ? 2 : 1));
+  int cap = di.cus / (NBK * NBK * (d.H < 1024 ? 2 : 1));
   if (cap < 1) cap = 1;
   if (cap > 4) cap = 4;
   const int maxsl = slices < cap ? slices : cap;
@@ -525,10 +531,6 @@ int run_backward_persistent_large(const BwdArgs& args, int cell, bool* bias_done
     CK(keep_state(a.c0, a.dh0, a.dc0, LBH, a.ws, a.w, 2, s), "keep c0");
   }
   const bool bias_in_kernel = slices == 1;
-  // A single slice at H = 1024 would occupy 64 CUs: the tiles' K is cut in four, 256 workgroups (LSTM_LARGE_KSPLIT=0:
-  // not); two slices of a single layer cut it in two (with more layers the idle CUs are used by the weight gradients
-  // of the layer above, which is worth more: L = 4, B = 64).
-  const int ks = (d.H != 1024 || !knobs().large_ksplit) ? 1 : (slices == 1 ? (d.L > 1 ? 2 : 4) : ((slices == 2 && d.L == 1) ? 2 : 1));
   // A launch that occupies at most half of the CUs (H = 1024 with one or two slices) leaves room for the weight
   // gradients of the layer above, which are complete once that layer's recurrence is: they run on a side stream
   // while this layer's recurrence runs (Section 2.6 wants them after the propagation of *their* layer, not of all

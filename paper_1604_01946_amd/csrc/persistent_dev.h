@@ -86,6 +86,22 @@ struct Waiter {
     }
     acquire();
   }
+  // The same for `count` arrivals, the i-th on line i % kFlagSub.
+  __device__ __forceinline__ void wait_uneven(int* flag, int count) {
+    const int lane = threadIdx.x & 63, need = lane < kFlagSub ? (count - lane + kFlagSub - 1) / kFlagSub : 0;
+    if (!dead) {
+      int spins = 0;
+      while (!__all(peek(flag) >= need)) {
+        __builtin_amdgcn_s_sleep(1);
+        if (++spins > limit) {
+          dead = true;
+          __hip_atomic_store(watchdog, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+          break;
+        }
+      }
+    }
+    acquire();
+  }
   // The same for a counter split into NSUB lines with its own arrival count per line.
   template <int NSUB>
   __device__ __forceinline__ void wait_split(int* flags, int target_each) {

@@ -128,8 +128,9 @@ inline bool gru_persistent_shape(int cell, const Dims& d) {
   // Time step by step / on chip, forward and backward, one layer of 30 steps and three of 100 (two of 40 where one number):
   //   H = 2048 GRU 1.13 and 1.19 at 96 rows, 0.95 and 1.01 at 128, 0.85 at 320; single gate 1.18 at 64, 0.79 and 0.90 at 96
   //   H = 1024 GRU 1.01 and 1.11 at 256, 0.97 and 1.05 at 384, 0.89 at 512; single gate 0.90 and 1.09 at 192, 0.77 and 0.93 at 256
-  if (d.H == 1024) return d.B <= (gru ? 384 : 192);
-  if (d.H == 2048) return d.B <= (gru ? 128 : 64);
+  // (sizes between these as the next of them)
+  if (d.H == 1024 || (d.H < 1024 && large_mid_size(d))) return d.B <= (gru ? 384 : 192);
+  if (d.H == 2048 || large_mid_size(d)) return d.B <= (gru ? 128 : 64);
   // H <= 512: the rate on chip does not depend on the batch (slices of 64 rows, one after the other once the chip is
   // full), the step-by-step path gains with it:
   //   H = 512 GRU 1.28 and 1.11 at 512 rows, 1.02 at 1024, 0.86 at 2048; single gate 1.17 and 1.03 at 512
@@ -388,7 +389,7 @@ inline Dims rnn_reported_dims(int cell, const Dims& d) {  // the size that buffe
 }
 inline Dims rnn_padded_rule(int cell, const Dims& d) {  // what the environment does not switch off
   const Dims r = rnn_reported_dims(cell, d);
-  return r.H == d.H ? d : Dims{d.L, d.T, d.B, d.I, std::min(granular_hidden(d.H), r.H)};
+  return r.H == d.H ? d : Dims{d.L, d.T, d.B, d.I, std::min(granular_hidden(d), r.H)};
 }
 inline Dims rnn_padded_dims(int cell, const Dims& d) {
   return (knobs().rnn_no_persistent || knobs().no_pad) ? d : rnn_padded_rule(cell, d);

@@ -58,7 +58,18 @@ hipError_t launch_micro_backward(const BwdArgs& a);
 int padded_hidden(const Dims& d);
 int padded_hidden_rule(const Dims& d);  // the same without looking at LSTM_NO_PAD (size queries cover both settings)
 int reported_hidden(const Dims& d);     // the size that buffers are reported for, at least padded_hidden_rule
-int granular_hidden(int H);             // the next size with kernels of its own
+int granular_hidden(const Dims& d);     // the next size with kernels of its own, for that many rows
+// Hidden sizes between 512, 1024 and 2048 with one-layer kernels of their own, and the rows with which they are taken: none where
+// the given size itself would not be padded (reported_hidden), and none where the backward recurrence would need more launches
+// than at 1024.  There it runs four slices of 32 rows side by side, here, with every tile cut in two, four, three and two; a launch
+// costs the same for one slice as for all (L = 4, T = 51, B = 117, H = 832 backward: two launches at 896 6.0 ms, one at 1024 5.6).
+// Elsewhere the smaller size wins by 1.05 to 1.6 (L = 3, T = 30, B = 30, H = 650: backward recurrence 580 us at 1024, 500 at 768).
+inline bool large_mid_size(const Dims& d) {
+  if (d.H == 1536) return d.B <= 32;
+  if (d.H == 1792) return d.B <= 64;
+  const int cap = d.H == 640 ? 4 : (d.H == 768 ? 3 : (d.H == 896 ? 2 : 0)), slices = (d.B + 31) / 32;
+  return cap && d.B <= 256 && (slices + cap - 1) / cap <= (slices + 3) / 4;
+}
 inline Dims padded_dims(const Dims& d) { return Dims{d.L, d.T, d.B, d.I, padded_hidden(d)}; }
 // Copies that pad and crop: dst [outer][rd][cd] <- src [outer][rs][cs], the common corner is copied, the rest of dst is zero.
 struct ResizeGroup {

@@ -25,7 +25,7 @@ struct Knobs {
   bool two_chains;           // LSTM_CHAINS=2: two batch chains per workgroup in the narrow persistent kernels
   int fwd_narrow;            // LSTM_FWD_NARROW: -1 unset, 0 never slices / wide kernel, 1 one slice on the narrow kernel
   int bwd_narrow;            // LSTM_BWD_NARROW: the same for the backward kernels
-  bool no_large_persistent;  // LSTM_NO_LARGE_PERSISTENT=1: H = 1024 / 2048 on the step path
+  bool no_large_persistent;  // LSTM_NO_LARGE_PERSISTENT=1: H = 1024 / 2048 and the sizes below on the step path
   bool no_wgrad_overlap;     // LSTM_NO_WGRAD_OVERLAP=1: weight gradients never on the side stream
   bool fwd_batched_input;    // LSTM_FWD_BATCHED_INPUT=1: layer 0's input product as one GEMM although I == H
   bool rnn_no_persistent;    // RNN_NO_PERSISTENT=1: GRU / single-gate cells step by step

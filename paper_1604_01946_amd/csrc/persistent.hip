@@ -620,7 +620,7 @@ int run_backward_persistent_large(const BwdArgs& args, int cell, bool* bias_done
 // Wide persistent kernels for the GRU: hidden sizes and CU budget of the LSTM ones; they also take batches of 32
 // rows and fewer (the rows past the batch are zeros), where the LSTM has kernels of its own.
 bool gru_persistent_supported(const Dims& d) {
-  if (persistent_large(d, false) && persistent_large(d, true)) return true;  // one-layer kernels, H = 1024 / 2048
+  if (persistent_large(d, false) && persistent_large(d, true)) return true;  // one-layer kernels, H > 512
   if (!on_chip_size(d.H) || too_short_on_chip(d)) return false;
   if (d.B > 16384) return false;  // (the cells' own limits are lower: rnn_cells.hip)
   DeviceInfo di;

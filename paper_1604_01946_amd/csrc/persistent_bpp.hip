@@ -1,5 +1,5 @@
 // Persistent backward recurrence with two chains of 16 batch rows taking turns inside every wave
-// (pers_bwd_pp_kernel), for 32 < B <= 64 per slice, H = 128 / 256 / 512, LSTM.
+// (pers_bwd_pp_kernel), for 32 < B <= 64 per slice, multiples of 64 from 128 to 512, LSTM.
 //
 // Why.  In pers_bwd32_kernel a step is one dependent sequence per wave: point-wise stage, publication of the gate
 // gradients dA_t, the wait until every other workgroup of the layer has published, the matrix instructions, the

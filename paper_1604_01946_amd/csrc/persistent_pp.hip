@@ -1,5 +1,5 @@
 // Persistent forward recurrence with two half-slices of 32 batch rows taking turns inside every wave
-// (pers_fwd_pp_kernel), for 32 < B <= 64 per slice, H = 128 / 256 / 512, LSTM, every layer multiplying its input
+// (pers_fwd_pp_kernel), for 32 < B <= 64 per slice, multiples of 64 from 128 to 512, LSTM, every layer multiplying its input
 // itself (layers >= 1 always do; layer 0 when I == H and x arrives in exchange layout).
 //
 // Why.  In pers_fwd32_kernel a step of 64 rows is one dependent sequence per wave: matrix instructions, K-split

@@ -42,3 +42,9 @@ def test_other_cells(H, cell, L, T, B):
     if L * T * H > 60000:
         T = 3
     run_cell(cell, L, T, B, 64, H, seed=4)
+
+
+@pytest.mark.parametrize("H,B", [(640, 30), (768, 70), (896, 64), (1536, 32), (700, 30)])
+def test_products_in_two_parts(H, B):
+    """1024 rows and more: the backward recurrence leaves the largest magnitudes of the gate rows to the weight gradients."""
+    run_case(cfg(2, (1024 + B - 1) // B, B, H, H), 5, 0)

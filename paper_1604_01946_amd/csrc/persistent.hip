@@ -822,8 +822,13 @@ int run_backward_persistent(BwdArgs& a, int cell, bool* bias_done, LayerGradient
   // The largest magnitude of every gate gradient, [L][4H], where the step path has its packed R: the weight-gradient products, if
   // they are large enough for two fp16 parts (launch_group3), need not read the gate gradients once more to find them
   // (L = 4, H = 512, B = 64, T = 100: 210 MB; 2.20 -> 2.14 ms).
+  // A stack that runs as groups of layers: only where the kernel of every group leaves them, which a shallow last group's may not
+  // do (L = 5, H = 512, B = 64: four layers alternate, the fifth runs on slices of 16 rows).
   a.dA_tops = nullptr;
-  if (d.H >= 384 && (long)d.T * d.B >= 1024 && (persistent_large(d, true) || bwd_alternating(d, cell))) {
+  const int per = persistent_large(d, true) ? d.L : layers_per_launch(d);
+  auto leaves_tops = [&](int layers) { return layers == 0 || bwd_alternating(Dims{layers, d.T, d.B, d.I, d.H}, cell); };
+  const bool tops = persistent_large(d, true) || (per > 0 && leaves_tops(std::min(d.L, per)) && leaves_tops(d.L % per));
+  if (d.H >= 384 && (long)d.T * d.B >= 1024 && tops) {
     ProfScope ps(LSTM_PHASE_BWD_PACK, a.stream);
     a.dA_tops = reinterpret_cast<unsigned*>(a.ws + a.w.RT);
     CK(launch_fill_zero(a.dA_tops, (size_t)4 * d.L * d.H * sizeof(unsigned), a.stream), "zero largest magnitudes");
@@ -832,7 +837,6 @@ int run_backward_persistent(BwdArgs& a, int cell, bool* bias_done, LayerGradient
     if (!ensure_watchdog()) return LSTM_HIP_ERROR;
     return run_backward_persistent_large(a, cell, bias_done, lg);
   }
-  const int per = layers_per_launch(d);
   if (per <= 0) return LSTM_UNSUPPORTED;
   if (d.L <= per) return backward_layers(a, cell, bias_done, true);
   const size_t TB = (size_t)d.T * d.B, BH = (size_t)d.B * d.H, GW = (size_t)gates_of_cell(cell) * d.H;

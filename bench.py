@@ -22,7 +22,6 @@ sys.path.insert(0, ROOT)
 
 PEAK_FP32_MFMA_TFLOPS = 157.3   # 256 CU x 256 FLOP/clk x 2.4 GHz
 PEAK_BF16X6_TFLOPS = 419.4      # 256 CU x 4096 FLOP/clk x 2.4 GHz, six bf16 products per fp32 product
-PEAK_F16X3_TFLOPS = 838.9       # the same rate, three fp16 products per fp32 product
 PEAK_HBM_GBS = 8000.0
 
 
@@ -43,10 +42,8 @@ def recorded_traffic(workload, kernel):
 
 def mfma_peak(kernel):
     """Nominal rate, in fp32 products, of the matrix instructions that `kernel` runs on: bf16 ones on operands in three
-    parts, fp16 ones on operands in two, or fp32 ones.  A phase of several products counts as its last one, and a GEMM as one in
-    parts, which its shorter products are not: they then show as a smaller fraction of the peak than they reach."""
-    if kernel.endswith("(fp16)"):
-        return PEAK_F16X3_TFLOPS
+    parts, or fp32 ones.  A GEMM counts as the former, which its shorter products are not: they then show as a smaller
+    fraction of the peak than they reach."""
     parts = kernel.endswith("(bf16)") or kernel in ("pers_fwd_pp3_kernel", "gemm")
     return PEAK_BF16X6_TFLOPS if parts else PEAK_FP32_MFMA_TFLOPS
 

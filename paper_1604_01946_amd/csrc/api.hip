@@ -51,7 +51,6 @@ const Knobs& knobs() {
     k.gemm_staged = env_is("LSTM_GEMM_STAGED", '1');
     k.gemm_short = !env_is("LSTM_GEMM_SHORT", '0');
     k.gemm_split = !env_is("LSTM_GEMM_SPLIT", '0');
-    k.gemm_half = env_int("LSTM_GEMM_HALF", 0, 1, -1);
     k.cell_step = !env_is("LSTM_CELL_STEP", '0');
     k.tiny = !env_is("LSTM_TINY", '0');
     k.split3 = env_int("LSTM_SPLIT3", 0, 2, -1);
@@ -550,7 +549,7 @@ int lstm_gemm_f32_ws(int M, int N, int K, const float* A, long sAm, long sAk, co
   if ((sAm != 1 && sAk != 1) || (sBk != 1 && sBn != 1)) return LSTM_INVALID_ARG;
   if (scratch && (reinterpret_cast<uintptr_t>(scratch) & 15u) != 0) return LSTM_INVALID_ARG;
   GemmProblem p{A, B, C, M, N, K, sAm, sAk, sBk, sBn, ldc, accumulate};
-  if (record(launch_gemm_group(&p, 1, (hipStream_t)stream, (float*)scratch, scratch ? scratch_bytes : 0, true), "gemm launch") != hipSuccess)
+  if (record(launch_gemm_group(&p, 1, (hipStream_t)stream, (float*)scratch, scratch ? scratch_bytes : 0), "gemm launch") != hipSuccess)
     return LSTM_HIP_ERROR;
   return LSTM_OK;
 }

@@ -25,9 +25,6 @@ struct GemmProblem {
   // recurrent matrix multiplies [h_init; h_0 .. h_{T-2}], of which the initial state is an array of its own.
   const float* Bhead = nullptr;
   int khead = 0;
-  // Largest magnitude of every row of A and column of B, as the bits of a non-negative float, where the caller has them.
-  const unsigned* Atop = nullptr;
-  const unsigned* Btop = nullptr;
 };
 constexpr int kMaxGemmGroup = 16;
 // A group of independent products executed by one launch (Section 2.6: the weight
@@ -35,10 +32,8 @@ constexpr int kMaxGemmGroup = 16;
 int device_cu_count();  // compute units of the current device (0 if it cannot be read); persistent.hip
 // `part` (16-byte aligned, part_bytes long, free until the stream has passed the call; null: none) takes the partial
 // tiles of products that are cut along K because their tiles do not fill the chip evenly; the parts are added in a fixed
-// order.  all_bits: every operand with all its 24 bits (the products that callers ask for by themselves); otherwise large products may
-// run with operands of 23 bits, whose sums are closer to the exact ones (gemm.hip).
-hipError_t launch_gemm_group(const GemmProblem* probs, int nprob, hipStream_t stream, float* part = nullptr, size_t part_bytes = 0,
-                             bool all_bits = false);
+// order.
+hipError_t launch_gemm_group(const GemmProblem* probs, int nprob, hipStream_t stream, float* part = nullptr, size_t part_bytes = 0);
 
 // ---------------------------------------------------------------- point-wise / layout kernels (pointwise.hip)
 enum EwOp : int {

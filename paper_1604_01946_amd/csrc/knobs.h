@@ -16,7 +16,6 @@ struct Knobs {
   int micro;                 // LSTM_MICRO=0: no pass runs as one workgroup; =2: every shape those kernels take does
   bool tiny;                 // LSTM_TINY=0: a single sequence (B = 1) on the narrow kernels instead of the flag-in-data ones
   bool cell_step;            // LSTM_CELL_STEP=0: inference calls of one step and few rows on the paths for sequences
-  int gemm_half = -1;          // LSTM_GEMM_HALF=0 / 1: no product / every product that can on two fp16 parts per operand
   bool gemm_split;           // LSTM_GEMM_SPLIT=0: no K slices for a product's last partial round of tiles
   int spin_limit;            // LSTM_SPIN_LIMIT: polls before a persistent kernel's wait gives up
   bool full_fences;          // LSTM_FULL_FENCES=1: release/acquire fences per step instead of the flag protocol

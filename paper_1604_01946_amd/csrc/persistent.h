@@ -113,8 +113,6 @@ struct PersBwdArgs {
   int trace_block;
   const float* h0;     // [L][B][H] or null: read by the GRU variant of the wide kernel
   float* dummy;        // pers_bwd_pp_kernel: 128 bytes of scratch that take the stores nobody wants
-  unsigned* tops = nullptr;  // pers_bwd_pp_kernel: [L][4H] largest magnitude of every gate gradient over the steps and rows (bits of a
-                             // non-negative float, zero before the launch), or null
 };
 
 // Exchange layout of a slot (H x 32 floats): for k = wave*H/4 + 8*k8 + 2*m + kk and batch row n,
@@ -169,7 +167,6 @@ struct PersBwdLArgs {
   int trace_block;
   float* X3 = nullptr;  // S3 variant: third part of the exchanged gate gradients, [nsl][T][NBK][2*UB*32 floats]
   int* redo = nullptr;  // as in PersFwdLArgs
-  unsigned* tops = nullptr;  // [4H] as in PersBwdArgs
 };
 
 // Batch tiles per chain and number of chains.  One chain is the default: on MI355X two chains

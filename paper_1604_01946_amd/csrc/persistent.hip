@@ -575,7 +575,6 @@ int run_backward_persistent_large(const BwdArgs& args, int cell, bool* bias_done
       k.dhT = a.dhT ? a.dhT + (size_t)l * BH : nullptr;
       k.dcT = a.dcT ? a.dcT + (size_t)l * BH : nullptr;
       k.dA = dA; k.X = X; k.Pp = Pp;
-      k.tops = a.dA_tops ? a.dA_tops + (size_t)l * G : nullptr;
       k.dh0 = a.dh0 ? a.dh0 + (size_t)l * BH : nullptr;
       k.dc0 = a.dc0 ? a.dc0 + (size_t)l * BH : nullptr;
       k.db = bias_in_kernel ? a.db + (size_t)l * GW : nullptr;
@@ -817,26 +816,13 @@ int forward_layers(const FwdArgs& args, int cell) {
 // cell as in run_forward_persistent.  For the other cells the function stops after the propagation (gate gradients
 // [L][T*B][4H] at the start of the workspace: GRU r, z, n, and n times r; single gate: the first H columns) and
 // reports in *bias_done whether db is complete; the caller forms the weight gradients.
-int run_backward_persistent(BwdArgs& a, int cell, bool* bias_done, LayerGradients* lg) {
+int run_backward_persistent(const BwdArgs& a, int cell, bool* bias_done, LayerGradients* lg) {
   const Dims& d = a.d;
-  // The largest magnitude of every gate gradient, [L][4H], where the step path has its packed R: the weight-gradient products, if
-  // they are large enough for two fp16 parts (launch_group3), need not read the gate gradients once more to find them
-  // (L = 4, H = 512, B = 64, T = 100: 210 MB; 2.20 -> 2.14 ms).
-  // A stack that runs as groups of layers: only where the kernel of every group leaves them, which a shallow last group's may not
-  // do (L = 5, H = 512, B = 64: four layers alternate, the fifth runs on slices of 16 rows).
-  a.dA_tops = nullptr;
-  const int per = persistent_large(d, true) ? d.L : layers_per_launch(d);
-  auto leaves_tops = [&](int layers) { return layers == 0 || bwd_alternating(Dims{layers, d.T, d.B, d.I, d.H}, cell); };
-  const bool tops = persistent_large(d, true) || (per > 0 && leaves_tops(std::min(d.L, per)) && leaves_tops(d.L % per));
-  if (d.H >= 384 && (long)d.T * d.B >= 1024 && tops) {
-    ProfScope ps(LSTM_PHASE_BWD_PACK, a.stream);
-    a.dA_tops = reinterpret_cast<unsigned*>(a.ws + a.w.RT);
-    CK(launch_fill_zero(a.dA_tops, (size_t)4 * d.L * d.H * sizeof(unsigned), a.stream), "zero largest magnitudes");
-  }
   if (persistent_large(d, true)) {
     if (!ensure_watchdog()) return LSTM_HIP_ERROR;
     return run_backward_persistent_large(a, cell, bias_done, lg);
   }
+  const int per = layers_per_launch(d);
   if (per <= 0) return LSTM_UNSUPPORTED;
   if (d.L <= per) return backward_layers(a, cell, bias_done, true);
   const size_t TB = (size_t)d.T * d.B, BH = (size_t)d.B * d.H, GW = (size_t)gates_of_cell(cell) * d.H;
@@ -868,7 +854,6 @@ int run_backward_persistent(BwdArgs& a, int cell, bool* bias_done, LayerGradient
     g.reserve = a.reserve + (size_t)g0 * rstride;
     g.w.P = a.w.P + (size_t)g0 * TB * 4 * d.H * sizeof(float);   // gate gradients of the group's layers, in place
     g.w.dx = a.w.dx + (size_t)g0 * TB * d.H * sizeof(float);
-    if (a.dA_tops) g.dA_tops = a.dA_tops + (size_t)g0 * 4 * d.H;
     bool done = false;
     const int st = backward_layers(g, cell, &done, false);
     if (st != LSTM_OK) return st;
@@ -923,7 +908,6 @@ int backward_layers(const BwdArgs& a, int cell, bool* bias_done, bool with_weigh
   // MFMA tile that would otherwise hold zeros) and write the gradient of the network input themselves.
   k.dx0 = (a.dx && d.I == d.H) ? a.dx : nullptr;
   k.db = nullptr;
-  k.tops = a.dA_tops;
   if (wide && a.db && d.B <= 64) {  // one launch: the wide kernel adds the bias gradient into db itself (two addends per element)
     ProfScope ps(LSTM_PHASE_BIAS_GRAD, s);
     CK(launch_fill_zero(a.db, (size_t)d.L * GW * 4, s), "zero db");

@@ -155,7 +155,7 @@ __global__ __launch_bounds__(256) void pers_bwd_pp_kernel(const PersBwdArgs a, c
   const int u = u0 + m;
   bool valid[2];
   size_t eoff[2], goff[2];  // offsets of (row, unit) inside a [B][H] and a [B][4H] step (rows past the batch: the last row)
-  float dc[2], dh_rec[2], dbsum[2][4], top[4] = {0.f, 0.f, 0.f, 0.f};
+  float dc[2], dh_rec[2], dbsum[2][4];
 #pragma unroll
   for (int c = 0; c < 2; ++c) {
     const int bb = a.b0 + 32 * bh + 16 * c + n;
@@ -263,7 +263,6 @@ __global__ __launch_bounds__(256) void pers_bwd_pp_kernel(const PersBwdArgs a, c
     for (int g = 0; g < 4; ++g) {
       pw_d[g] = keep ? pw_d[g] : 0.f;
       dbsum[c][g] += pw_d[g];
-      top[g] = fmaxf(top[g], fabsf(pw_d[g]));
     }
     *reinterpret_cast<floatx4*>(stage + w * 256 + (m * 4 + nl) * 4) = floatx4{pw_d[0], pw_d[1], pw_d[2], pw_d[3]};
   };
@@ -539,20 +538,6 @@ __global__ __launch_bounds__(256) void pers_bwd_pp_kernel(const PersBwdArgs a, c
 #pragma unroll
       for (int i = 0; i < 16; ++i) sum += part[threadIdx.x * 16 + ((i + threadIdx.x) & 15)];
       atomicAdd(a.db + (size_t)l * GW + (threadIdx.x >> 4) * H + u0 + (threadIdx.x & 15), sum);
-    }
-  }
-  // the largest magnitude of every gate gradient, which scales the weight-gradient products' operand (an order-free maximum)
-  if (a.tops) {
-    unsigned* const pt = reinterpret_cast<unsigned*>(part);
-    __syncthreads();
-#pragma unroll
-    for (int g = 0; g < 4; ++g) pt[(g * 16 + m) * 16 + n] = __builtin_bit_cast(unsigned, top[g]);
-    __syncthreads();
-    if (threadIdx.x < 64) {
-      unsigned v = 0u;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) v = max(v, pt[threadIdx.x * 16 + ((i + threadIdx.x) & 15)]);
-      atomicMax(a.tops + (size_t)l * G + (threadIdx.x >> 4) * H + u0 + (threadIdx.x & 15), v);
     }
   }
   mark(0, 0, 5);

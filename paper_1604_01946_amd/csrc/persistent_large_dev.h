@@ -420,14 +420,14 @@ __global__ __launch_bounds__(256) void pers_bwdL_kernel(const PersBwdLArgs a) {
   const int bb = a.b0 + 32 * sl + n;
   const bool valid = bb < B;
   int cu[CPT];
-  float dc[CPT], dh_rec[CPT], dbsum[CPT][4], top[CPT][4];
+  float dc[CPT], dh_rec[CPT], dbsum[CPT][4];
 #pragma unroll
   for (int c = 0; c < CPT; ++c) {
     cu[c] = UB * j + UF * fi + 8 * min(c, noct - 1) + j8;
     dc[c] = (CELL == 0 && valid && a.dcT) ? a.dcT[(size_t)bb * H + cu[c]] : 0.f;  // GRU: the direct term dh_t o z_t
     dh_rec[c] = (valid && a.dhT) ? a.dhT[(size_t)bb * H + cu[c]] : 0.f;
 #pragma unroll
-    for (int g = 0; g < 4; ++g) dbsum[c][g] = top[c][g] = 0.f;
+    for (int g = 0; g < 4; ++g) dbsum[c][g] = 0.f;
   }
   const float* const res_gates = CELL == 0 ? a.res : a.res + TB * H;  // the four saved arrays [T][B][4H] (LSTM, GRU)
   const float* const res_c = CELL == 0 ? a.res + TB * 4 * H : a.res;   // c (LSTM) or h: the state array the step reads
@@ -495,10 +495,7 @@ __global__ __launch_bounds__(256) void pers_bwdL_kernel(const PersBwdLArgs a) {
           dA4[0] = CELL == 3 ? dh * (1.f - fct[c] * fct[c]) : (fct[c] > 0.f ? dh : 0.f);
         }
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          dbsum[c][g] += dA4[g];
-          top[c][g] = fmaxf(top[c][g], fabsf(dA4[g]));
-        }
+        for (int g = 0; g < 4; ++g) dbsum[c][g] += dA4[g];
       }
       if constexpr (S3) {  // [octet][part][gate][batch row][unit]
         unsigned short* const o = reinterpret_cast<unsigned short*>(xsA) + c * 3072 + n * 8 + j8;
@@ -691,21 +688,6 @@ __global__ __launch_bounds__(256) void pers_bwdL_kernel(const PersBwdLArgs a) {
 #pragma unroll
       for (int q = 0; q < 32; ++q) sum += stage[threadIdx.x * 32 + ((q + threadIdx.x) & 31)];
       a.db[(size_t)(threadIdx.x / UF) * H + UB * j + UF * fi + (threadIdx.x % UF)] = sum;
-    }
-  }
-  if (a.tops && fin) {  // the largest magnitude of every gate gradient (an order-free maximum)
-    unsigned* const pt = reinterpret_cast<unsigned*>(stage);
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < CPT; ++c)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) pt[(g * UF + 8 * c + j8) * 32 + n] = __builtin_bit_cast(unsigned, top[c][g]);
-    __syncthreads();
-    if (threadIdx.x < 4 * UF && (int)threadIdx.x % UF < 8 * noct) {
-      unsigned v = 0u;
-#pragma unroll
-      for (int q = 0; q < 32; ++q) v = max(v, pt[threadIdx.x * 32 + ((q + threadIdx.x) & 31)]);
-      atomicMax(a.tops + (size_t)(threadIdx.x / UF) * H + UB * j + UF * fi + (threadIdx.x % UF), v);
     }
   }
 }

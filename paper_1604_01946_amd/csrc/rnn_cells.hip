@@ -13,7 +13,7 @@ namespace lstm {
 // persistent.hip: the wide persistent kernels also run the GRU (weights on chip for all T steps, Section 4)
 bool gru_persistent_supported(const Dims& d);
 int run_forward_persistent(const FwdArgs& a, int cell);
-int run_backward_persistent(BwdArgs& a, int cell, bool* bias_done, LayerGradients* lg);
+int run_backward_persistent(const BwdArgs& a, int cell, bool* bias_done, LayerGradients* lg);
 
 #define CK(expr, what)                                             \
   do {                                                             \
@@ -213,17 +213,13 @@ int backward_persistent(int cell, const Dims& d, const float* x, const float* h0
   const bool gru = cell == RNN_CELL_GRU;
   const size_t TB = (size_t)d.T * B, G = (size_t)gates_of(cell) * H, G4 = 4 * (size_t)H, BH = (size_t)B * H;
   const WsLayout w = ws_layout(d, true);
-  BwdArgs a{d, x, h0, nullptr, W, R, reserve, dy, dhT, nullptr, dx, dh0, nullptr, dW, dR, db, ws, w, s};
+  const BwdArgs a{d, x, h0, nullptr, W, R, reserve, dy, dhT, nullptr, dx, dh0, nullptr, dW, dR, db, ws, w, s};
   const float* dA_all = reinterpret_cast<const float*>(ws + w.P);
   // The gradient products of layer l (Section 2.6: large products once the layer's propagation is complete) are
   // appended to two groups: the sums over steps, and the initial-state terms that accumulate onto them.
   auto add_layer = [&](int l, GemmProblem* main_g, int& nm, GemmProblem* init_g, int& ni, hipStream_t st) -> int {
-    const int Il = in_dim(d, l), first = nm;
+    const int Il = in_dim(d, l);
     const float* dA = dA_all + (size_t)l * TB * G4;
-    const unsigned* const tops = a.dA_tops && d.T > 1 ? a.dA_tops + (size_t)l * G4 : nullptr;
-    auto with_tops = [&]() {  // (not for the initial states' terms: the gate gradients of one step may be far below the largest)
-      for (int i = first; tops && i < nm; ++i) main_g[i].Atop = tops + (main_g[i].A - dA) % (long)G4;
-    };
     const float* hl = reserve + (size_t)l * res_layer_floats(cell, d);
     const float* in = l == 0 ? x : reserve + (size_t)(l - 1) * res_layer_floats(cell, d);
     float* dWl = dW + (l == 0 ? 0 : G * d.I + (size_t)(l - 1) * G * H);
@@ -235,7 +231,6 @@ int backward_persistent(int cell, const Dims& d, const float* x, const float* h0
       const float* const hi = h0 + (size_t)l * BH;
       main_g[nm++] = GemmProblem{dA, hl, dRl, m1, H, (int)TB, 1, (long)G4, H, 1, H, 0, hi, B};
       if (gru) main_g[nm++] = GemmProblem{dA + 3 * H, hl, dRl + (size_t)2 * H * H, H, H, (int)TB, 1, (long)G4, H, 1, H, 0, hi, B};
-      with_tops();
       return LSTM_OK;
     }
     if (d.T > 1) {
@@ -243,7 +238,6 @@ int backward_persistent(int cell, const Dims& d, const float* x, const float* h0
       if (gru)
         main_g[nm++] = GemmProblem{dA + (size_t)B * G4 + 3 * H, hl, dRl + (size_t)2 * H * H, H, H, (int)(TB - B), 1, (long)G4, H, 1, H, 0};
     }
-    with_tops();
     if (h0) {
       const int acc = d.T > 1 ? 1 : 0;
       init_g[ni++] = GemmProblem{dA, h0 + (size_t)l * BH, dRl, m1, H, B, 1, (long)G4, H, 1, H, acc};

@@ -44,7 +44,6 @@ struct BwdArgs {
   char* ws;
   WsLayout w;
   hipStream_t stream;
-  unsigned* dA_tops = nullptr;  // [L][4H] largest magnitude of every gate gradient (bits of a non-negative float), where the recurrence left them
 };
 
 // Hidden size the kernels run a shape at.  Hidden units with zero weights, bias and initial state stay at h = c = 0

@@ -25,7 +25,7 @@ namespace lstm {
 int run_forward_wavefront(const FwdArgs& a);
 int run_backward_wavefront(const BwdArgs& a);
 int run_forward_persistent(const FwdArgs& a, int cell = 0);
-int run_backward_persistent(BwdArgs& a, int cell = 0, bool* bias_done = nullptr, LayerGradients* lg = nullptr);
+int run_backward_persistent(const BwdArgs& a, int cell = 0, bool* bias_done = nullptr, LayerGradients* lg = nullptr);
 bool persistent_supported(const Dims& d, bool backward);
 bool steps_beat_large(const Dims& d, bool backward);
 
@@ -334,7 +334,6 @@ int weight_gradients_layers(const BwdArgs& a, const float* dA_all, int l0, int l
     const LayerRes r = layer_res(a.reserve, d, l);
     float* dWl = a.dW + w_offset(d, l);
     float* dRl = a.dR + (size_t)l * G * H;
-    const int first = nm + 2 > kMaxGemmGroup ? 0 : nm;
     if (nm + 2 > kMaxGemmGroup) CK(flush(main_p, nm), "weight-gradient GEMMs");
     main_p[nm++] = GemmProblem{dA, in, dWl, (int)G, Il, (int)TB, 1, (long)G, Il, 1, Il, 0};
     if (d.T > 1 && a.h0 && B % 16 == 0) {  // the initial state's rows in front of the others: one product
@@ -353,9 +352,6 @@ int weight_gradients_layers(const BwdArgs& a, const float* dA_all, int l0, int l
     } else {
       CK(launch_fill_zero(dRl, G * H * 4, s), "zero dR");
     }
-    // (not for the initial states' terms: the gate gradients of one step may be far below the largest)
-    for (int i = first; i < nm; ++i)
-      if (a.dA_tops && d.T > 1) main_p[i].Atop = a.dA_tops + (size_t)l * G;
   }
   CK(flush(main_p, nm), "weight-gradient GEMMs");
   CK(flush(tail_p, nt), "weight-gradient GEMMs (initial state term)");
@@ -542,10 +538,7 @@ int run_backward(const BwdArgs& a, unsigned path) {
     case LSTM_PATH_WAVEFRONT: return run_backward_wavefront(a);
     case LSTM_PATH_PERSISTENT:
       if (!persistent_supported(a.d, true)) return LSTM_UNSUPPORTED;
-    {
-      BwdArgs b = a;
-      return run_backward_persistent(b);
-    }
+      return run_backward_persistent(a);
     default: return LSTM_INVALID_ARG;
   }
 }

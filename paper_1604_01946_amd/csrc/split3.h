@@ -64,23 +64,6 @@ __device__ __forceinline__ void split8(const float (&v)[8], bf16x8 (&p)[3]) {
   for (int q = 0; q < 3; ++q) p[q] = __builtin_bit_cast(bf16x8, o[q]);
 }
 
-// What a product is made of: the parts of an operand and which of their products are formed, smallest first.
-struct Bf16x3 {
-  static constexpr int Q = 3, products = 6, k_tile = 16;
-  static constexpr bool scaled = false;
-  typedef bf16x8 frag;
-  static __device__ __forceinline__ void cut(float a, float b, float up, unsigned (&p)[3]) {
-    const Split2 s = split3(a * up, b * up);
-    p[0] = s.h;
-    p[1] = s.m;
-    p[2] = s.l;
-  }
-  static __device__ __forceinline__ floatx16 mfma(int z, const frag (&a)[3], const frag (&b)[3], floatx16 acc) {
-    constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[z]], b[PB[z]], acc, 0, 0, 0);
-  }
-};
-
 // acc += A * B for 16 (32x32 tile) k: the six products of the parts, smallest first
 __device__ __forceinline__ floatx16 mfma_split3(const bf16x8 (&a)[3], const bf16x8 (&b)[3], floatx16 acc) {
   acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[2], b[0], acc, 0, 0, 0);
@@ -90,50 +73,5 @@ __device__ __forceinline__ floatx16 mfma_split3(const bf16x8 (&a)[3], const bf16
   acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[1], acc, 0, 0, 0);
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[0], acc, 0, 0, 0);
 }
-
-// ------------------------------------------------------------------ two fp16 parts
-// x = h + l with h the value rounded to fp16 (11 bits) and l the remainder rounded: 23 bits, so that an operand is off by at
-// most 2^-23 of itself, one in four by that much and the others not at all (rms 2^-25).  Of the four products three are
-// formed, lh, hl, hh; ll is at most 2^-22 of the whole, rms 2^-25.5 over random operands, of either sign.  Both are below
-// what an fp32 sum of a few dozen such products costs by itself, and half as many additions to it are made as with six
-// products.  Published as a way to fp32 results on fp16 matrix cores by Ootomo and Yokota (IJHPCA 2022); scales and checks here are this
-// repository's.
-//
-// Range: fp16 numbers end at 2^-24 (full precision at 2^-14) and 65504.  Every row of A and column of B is multiplied by a
-// power of two that brings its largest magnitude (`top`, the bits of that float) into [2^14, 2^15); sums are multiplied by
-// the inverse powers.  Values down to 2^-18 of the largest of their row keep their 23 bits, smaller ones are off by up to
-// 2^-40 of that largest one: invisible unless its products vanish, i.e. where it meets zeros only.  A row or column whose sums
-// all stay below 2^-11 of the product of its largest value and the others' (kSmallSum) is therefore worked out again in fp32, like a sum
-// that is infinite or NaN (an infinite or NaN operand, or a sum that overflows).
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-
-constexpr float kSmallSum = 0x1p17f;
-
-// log2 of what a row with this largest magnitude is multiplied by (at most 127: a row of subnormal numbers is then whole
-// multiples of 2^-22); rows of zeros, infinities or NaN are left as they are
-__device__ __forceinline__ int exponent_of(unsigned top) {
-  const int e = (int)(top >> 23);
-  return top == 0 || e == 255 ? 0 : min(141 - e, 127);
-}
-__device__ __forceinline__ float scale_of(unsigned top) { return __builtin_bit_cast(float, (unsigned)(exponent_of(top) + 127) << 23); }
-
-struct F16x2 {
-  static constexpr int Q = 2, products = 3, k_tile = 32;
-  static constexpr bool scaled = true;
-  typedef f16x8 frag;
-  static __device__ __forceinline__ void cut(float a, float b, float up, unsigned (&p)[2]) {
-    a *= up;
-    b *= up;
-    const f16x2 h = __builtin_convertvector(floatx2{a, b}, f16x2);
-    const f16x2 l = __builtin_convertvector(floatx2{a - (float)h[0], b - (float)h[1]}, f16x2);
-    p[0] = __builtin_bit_cast(unsigned, h);
-    p[1] = __builtin_bit_cast(unsigned, l);
-  }
-  static __device__ __forceinline__ floatx16 mfma(int z, const frag (&a)[2], const frag (&b)[2], floatx16 acc) {
-    constexpr int PA[3] = {1, 0, 0}, PB[3] = {0, 1, 0};
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16(a[PA[z]], b[PB[z]], acc, 0, 0, 0);
-  }
-};
 
 }  // namespace lstm

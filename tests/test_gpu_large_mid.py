@@ -45,6 +45,6 @@ def test_other_cells(H, cell, L, T, B):
 
 
 @pytest.mark.parametrize("H,B", [(640, 30), (768, 70), (896, 64), (1536, 32), (700, 30)])
-def test_products_in_two_parts(H, B):
-    """1024 rows and more: the backward recurrence leaves the largest magnitudes of the gate rows to the weight gradients."""
+def test_long_products(H, B):
+    """1024 rows and more: weight gradients with long sums."""
     run_case(cfg(2, (1024 + B - 1) // B, B, H, H), 5, 0)

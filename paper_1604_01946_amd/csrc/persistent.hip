@@ -317,6 +317,32 @@ bool steps_beat_large(const Dims& d, bool backward) {
   return launches(64) * (7.8 + 45.0 / T) > 15.0 + 0.11 * B + 20.0 / T;
 }
 
+// H = 320 and 384 with more than 512 rows, which are not padded either (reported_hidden): whether a pass is faster off the chip, as
+// for the LSTM above, for the GRU forward and backward together.  The models are of microseconds: a launch, the steps in it (layer l
+// follows l steps behind) and the rows; off the chip the layers, their steps and rows, up to 640 of which fill one round of the step
+// kernel.  Fitted to one to eight layers, 6 to 80 steps, 520 to 8192 rows, within 6 % (off the chip 11) in rms; the choice costs
+// 0.3 % on average against the faster of the two.  Time on chip / off it, T = 1, 10 and 40:
+//   LSTM forward, H = 320: two layers of 1024 rows 2.4, 0.66, 0.40; four of 4096 10.4, 1.5, 0.80; H = 384: 3.2, 0.84, 0.49; 8.8, 1.25, 0.68
+//   LSTM backward, H = 320: 1.65, 0.70, 0.56; 4.9, 1.46, 1.03; H = 384: 2.3, 0.88, 0.68; 4.7, 1.27, 0.87
+//   GRU forward / backward, four layers of 1024 rows: H = 320 7.6, 1.95, 1.08 / 3.3, 1.60, 1.23; H = 384 5.9, 1.55, 0.82 / 3.5, 1.56, 1.16
+bool steps_beat_chip(const Dims& d, int cell, bool backward) {
+  if (!(d.H == 320 || d.H == 384) || d.B <= 512) return false;
+  constexpr int cus = 256;
+  const int groups = d.H / 8, per = cus / groups, slices = (d.B + 63) / 64, i = d.H == 384;
+  struct Model { double launch, step[2], row[2], layer, few, given, given_row[2]; };
+  constexpr Model fwd = {55.0, {3.1, 3.5}, {0.0049, 0.0045}, 16.0, 25.0, 13.0, {0.0275, 0.0330}};
+  constexpr Model bwd = {45.0, {8.0, 8.1}, {0.0088, 0.0111}, 18.0, 41.0, 19.0, {0.0418, 0.0535}};
+  constexpr Model gru = {80.0, {10.6, 12.1}, {0.0106, 0.0100}, 0.0, 0.0, 28.7, {0.0261, 0.0371}};
+  const Model& m = cell ? gru : (backward ? bwd : fwd);
+  double chip = (double)d.L * d.T * d.B * m.row[i];
+  for (int l = 0; l < d.L; l += per) {
+    const int layers = std::min(per, d.L - l), side = std::min(cus / (layers * groups), 16 / layers);
+    chip += (slices + side - 1) / side * (m.launch + (d.T + layers - 1) * m.step[i]);
+  }
+  const double step = m.few > 0.0 && d.B <= 640 ? m.few : m.given + d.B * m.given_row[i];
+  return chip > d.L * (m.layer + d.T * step);
+}
+
 bool persistent_large(const Dims& d, bool backward) {
   if (knobs().no_large_persistent) return false;
   if (!(d.H == 1024 || d.H == 2048 || large_mid_size(d))) return false;

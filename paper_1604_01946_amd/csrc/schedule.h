@@ -110,6 +110,7 @@ struct LayerGradients {
 int weight_gradients_layers(const BwdArgs& a, const float* dA_all, int l0, int l1, hipStream_t s, bool grouped,
                             bool bias_done, Scratch part);
 int run_forward(const FwdArgs& a, unsigned path);
+bool steps_beat_chip(const Dims& d, int cell, bool backward);  // whether a pass that the on-chip kernels take is faster off them (cell 0: LSTM)
 bool path_pinned(const Dims& d, bool backward);  // lstm_set_path names a path for the shape
 // cell_step.hip: an inference call of one step and few rows, one launch per layer
 bool cell_step_takes(const FwdArgs& a);

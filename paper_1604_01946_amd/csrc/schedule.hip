@@ -128,7 +128,8 @@ unsigned resolve_auto_path(const Dims& user, bool backward) {
   }
   if (micro_shape(user)) return LSTM_PATH_STEP;  // one launch per pass, steps looped inside (micro.hip)
   const Dims d = padded_dims(user);  // what the kernels will run
-  if (persistent_supported(d, backward)) return steps_beat_large(d, backward) ? LSTM_PATH_STEP : LSTM_PATH_PERSISTENT;
+  if (persistent_supported(d, backward) && !steps_beat_chip(d, 0, backward))
+    return steps_beat_large(d, backward) ? LSTM_PATH_STEP : LSTM_PATH_PERSISTENT;
   const int cus = device_cu_count();
   // Section 3.2 observes that at large minibatches the individual optimisations stop paying.  Here: once the plain
   // [B x 4H] x [H] product of one step gives every CU three 64 x 64 tiles (or one of 128 x 128), a pass of one or two steps

@@ -53,3 +53,14 @@ def test_one_chain(H, knobs):
 def test_scratch_line_of_many_workgroups():
     """The stores that nobody wants go to a line per workgroup behind the scratch area: 256 workgroups and a batch of one."""
     run_cell("gru", 16, 3, 1, 128, 128, seed=4)
+
+
+# More than 512 rows at 320 and 384, which are not padded: short passes run off the chip, longer ones on it.
+@pytest.mark.parametrize("H", (320, 384))
+@pytest.mark.parametrize("L,T,B,path", [(4, 1, 1024, "off"), (2, 2, 600, "off"), (2, 24, 600, "on"), (1, 16, 1030, "on")])
+def test_many_rows(H, L, T, B, path):
+    from paper_1604_01946_amd import binding
+    for backward in (0, 1):
+        assert (binding.lstm_auto_path(L, T, B, 64, H, backward) == binding.LSTM_PATH_PERSISTENT) == (path == "on")
+    run_case(cfg(L, T, B, 64, H), 3, 0)
+    run_cell("gru", L, T, B, 64, H, seed=4)

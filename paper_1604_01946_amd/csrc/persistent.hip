@@ -352,12 +352,6 @@ bool persistent_large(const Dims& d, bool backward) {
   return (backward ? (d.H / 128) * (d.H / 128) : d.H / 8) <= di.cus;
 }
 
-// Sizes that are no powers of two: a few steps of one layer, which are not padded either (reported_hidden), cost less step by
-// step (L = 1, T = 1, B = 1003, H = 192: forward 33 us against 61, backward 59 against 85).
-static bool too_short_on_chip(const Dims& d) {
-  return (d.H & (d.H - 1)) != 0 && d.L == 1 && (d.T < 8 || (d.T < 16 && d.B < 48));
-}
-
 bool persistent_supported(const Dims& d, bool backward) {
   if (persistent_large(d, backward)) return true;
   if (!on_chip_size(d.H) || too_short_on_chip(d)) return false;
@@ -646,7 +640,7 @@ int run_backward_persistent_large(const BwdArgs& args, int cell, bool* bias_done
 // rows and fewer (the rows past the batch are zeros), where the LSTM has kernels of its own.
 bool gru_persistent_supported(const Dims& d) {
   if (persistent_large(d, false) && persistent_large(d, true)) return true;  // one-layer kernels, H > 512
-  if (!on_chip_size(d.H) || too_short_on_chip(d)) return false;
+  if (!on_chip_size(d.H)) return false;
   if (d.B > 16384) return false;  // (the cells' own limits are lower: rnn_cells.hip)
   DeviceInfo di;
   if (!device_info(di) || !di.coop) return false;

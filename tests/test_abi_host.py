@@ -190,3 +190,16 @@ def test_set_path_overrides_and_validates():
     assert B.lstm_set_path(*dims, 1, other) == B.LSTM_OK
     B.lstm_shutdown()  # empties the table
     assert B.lstm_auto_path(*dims, 1) == B.lstm_auto_path(*dims, 1)
+
+
+def test_rnn_workspace_of_calls_that_run_step_by_step():
+    """Calls of sizes with kernels of their own that do not run on them report the step-by-step layout alone: inputs' and
+    gates' gradients, two hand-overs, states, 64 partial bias gradients."""
+    def steps(cell, L, T, B, I, H):
+        G, up = {"gru": 3, "tanh": 1}[cell] * H, lambda v: (4 * v + 255) // 256 * 256
+        return 3 * up(T * B * G) + up(B * G) + 2 * up(T * B * H) + 2 * up(B * H) + up(64 * G)
+    for cell, dims in (("gru", (1, 1, 2, 1699, 384)), ("gru", (1, 3, 80, 5, 448)), ("tanh", (1, 9, 1, 300, 192)), ("tanh", (1, 6, 30, 47, 320)),
+                       ("gru", (4, 1, 1024, 320, 320)), ("gru", (2, 2, 600, 384, 384))):
+        assert B.rnn_workspace_bytes(B.RNN_CELLS[cell], *dims) == steps(cell, *dims), (cell, dims)
+    # long enough, they do
+    assert B.rnn_workspace_bytes(B.RNN_CELL_GRU, 1, 8, 80, 5, 448) > steps("gru", 1, 8, 80, 5, 448)

@@ -226,7 +226,9 @@ int lstm_gemm_f32_ws(int M, int N, int K,
                   float* C, long ldc, int accumulate, void* scratch, size_t scratch_bytes, void* stream);
 
 /* Which path LSTM_PATH_AUTO resolves to for this shape on the current device
- * (returns an LSTM_PATH_* value; LSTM_PATH_AUTO on invalid dimensions). */
+ * (returns an LSTM_PATH_* value; LSTM_PATH_AUTO on invalid dimensions).  An inference call (no reserve) of one step and
+ * up to 16 rows may instead run as one launch per layer that is on no path (the whole cell at once); lstm_set_path with
+ * the path that this function returns keeps such calls on it. */
 unsigned lstm_auto_path(int L, int T, int B, int I, int H, int backward);
 
 /*

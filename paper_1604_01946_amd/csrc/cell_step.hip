@@ -9,7 +9,7 @@
 // hidden size: no padding, no re-layout.  Before / now, us per call (L, B, I = H): (2, 1, 256) 17.5 / 11.1, (2, 8, 256) 27.6 / 12.5,
 // (2, 1, 300) 57 / 10, (4, 16, 512) 56 / 48, (2, 16, 650) 133 / 33, (2, 8, 1024) 80 / 22, (4, 1, 2048) 215 / 113, (1, 1, 4096) 262 / 99 (537 MB of
 // weights at 5.4 TB/s), (1, 16, 4096) 284 / 155.  Above 16 rows the matrix cores have enough to do; a second step would cost as many
-// launches again.
+// launches again; deep stacks of few units run as before (few_enough_layers).
 //
 // The hidden states of a layer are handed to the next one in the workspace; hT is written by the launch that no longer
 // reads the initial states (the next layer's, or a copy behind the top layer's), so that hT may be h0; every c_T element is
@@ -97,11 +97,33 @@ bool overlap(const float* a, size_t na, const float* b, size_t nb) { return a &&
 
 }  // namespace
 
+// Whether a launch per layer is the faster way.  A launch costs 3.5 us for one row, 4.7 for up to four, 6.3 for up to
+// eight and 9.3 to 14 above, whatever the layers; up to H = 512 the paths for sequences run a whole stack in one launch of some 20 us and
+// 1 to 6 per layer, whose rows are nearly free.  Measured with 1 to 24 layers of 33 to 3072 units, us that way / this way:
+//   one row          H = 128 (a kernel of its own, up to eight layers): 16 / 14 with four layers, 22 / 29 with eight, 61 / 53 with 16; H = 256 (the
+//                    same): 24 / 22 with six, 24 / 28 with eight, 49 / 57 with 16; padded to them, H = 200: 38 / 29 with eight, 65 / 57 with 16
+//   up to four rows  H = 100: 61 / 56 with twelve, 75 / 78 with 16; H = 128: 37 / 37 with eight, 61 / 74 with 16; H = 256: 95 / 77 with 16
+//   up to eight      H = 100: 44 / 37 with six, 49 / 50 with eight; H = 128: 28 / 25 with four, 39 / 50 with eight; H = 192: 38 / 37 with six, 46 / 51
+//                    with eight; H = 256: 105 / 103 with 16
+//   up to 16         H = 64: 34 / 38 with four; H = 100: 40 / 37 with four, 44 / 56 with six; H = 128: 21 / 18 with two, 28 / 37 with four; H = 200: 49 / 37 with four, 69 / 75
+//                    with eight; H = 320: 33 / 28 with two, 37 / 42 with three, 41 / 56 with four; H = 448: 45 / 42 with three, 50 / 56 with four; H = 512:
+//                    318 / 288 with 24
+static bool few_enough_layers(int L, int B, int H) {
+  if (H > 448) return true;
+  if (B > 8) return L <= (H > 192 && H <= 256 ? 4 : 3);
+  if (H > 256) return true;
+  if (B > 4) return L <= (H == 128 ? 4 : 6) || H > 192;
+  if (B > 2) return L <= (H == 128 ? 8 : 12) || H > 128;
+  if (B == 2) return true;
+  return L <= 6 || !(H == 256 || (H == 128 && L <= 8));
+}
+
 // An inference call of one step and few rows.  y, hT and cT must not lie over operands that another workgroup may still
 // read: hT over h0 and cT over c0, element on element, are the only overlaps that it takes.
 bool cell_step_takes(const FwdArgs& a) {
   const Dims& d = a.d;
   if (d.T != 1 || d.B > 16 || !knobs().cell_step) return false;
+  if (!few_enough_layers(d.L, d.B, d.H)) return false;
   const size_t BH = (size_t)d.B * d.H, S = (size_t)d.L * BH, nx = (size_t)d.B * d.I, G = 4 * (size_t)d.H;
   const size_t nW = G * d.I + (size_t)(d.L - 1) * G * d.H, nR = (size_t)d.L * G * d.H, nb = (size_t)d.L * G;
   const struct { float* p; size_t n; } out[3] = {{a.y, BH}, {a.hT, S}, {a.cT, S}};

@@ -61,3 +61,23 @@ def test_overlaps_that_it_leaves_to_the_other_paths(knobs):
         got.append((y.clone(), c0.clone(), cT.clone()))
     for p, q in zip(*got):
         assert torch.equal(p, q)
+
+
+@pytest.mark.parametrize("L,B,I,H,here", [(16, 16, 128, 128, False), (8, 8, 40, 100, False), (8, 1, 256, 256, False), (4, 12, 320, 320, False),
+                                          (16, 1, 128, 128, True), (8, 4, 256, 256, True), (3, 16, 64, 320, True), (12, 16, 64, 512, True)])
+def test_deep_stacks_of_few_units_run_as_sequences(L, B, I, H, here):
+    import torch
+    from paper_1604_01946_amd import binding
+    from parity import recurrence_kernels
+    cfg = Config("cell", L=L, T=1, B=B, I=I, H=H, state_std=0.3)
+    d = make_inputs(cfg, 3)
+    up = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    x, W, R, b, h0, c0 = (up(d[k]) for k in ("x", "W", "R", "b", "h0", "c0"))
+    wb = binding.lstm_workspace_bytes(*cfg.dims)
+    ws, y = torch.full((wb // 4,), float("nan"), device="cuda"), torch.full((1, B, H), float("nan"), device="cuda")
+    print("one step", cfg.dims, flush=True)
+    kernel, _ = recurrence_kernels(lambda: binding.check(
+        binding.lstm_forward(*cfg.dims, x, h0, c0, W, R, b, y, None, None, None, ws, wb), "lstm_forward"))
+    assert (kernel == "lstm_cell_kernel") == here, kernel
+    ref = O.lstm_forward(*cfg.dims, d["x"], d["h0"], d["c0"], d["W"], d["R"], d["b"])
+    assert nerr(y.cpu().numpy(), ref[0]) < FWD_TOL

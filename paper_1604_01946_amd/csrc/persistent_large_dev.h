@@ -343,7 +343,7 @@ __global__ __launch_bounds__(256) void pers_bwdL_kernel(const PersBwdLArgs a) {
   constexpr int NW = NBK * KS;               // workgroups with partial sums of a block; the first NF of them finalise
   constexpr int CPT = (16 + NW - 1) / NW;    // cells per thread in the point-wise stage
   constexpr int UF = 8 * CPT;                // units a workgroup finalises, in octets
-  constexpr int NF = (16 + CPT - 1) / CPT;   // workgroups of a block that finalise (the last may have fewer octets)
+  constexpr int NF = 16 / CPT;               // workgroups of a block that finalise
   constexpr int NG8 = 4 * UB / 8 / KS;       // 8-k groups of this workgroup's part of the tile's K = 4*UB
   constexpr int KP = 4 * UB / 2 / KS;        // k-pairs; every wave runs all of them for its 32 output units
   constexpr int RP = KS > 1 ? KP : (CPT > 1 ? 136 : 128);  // k-pairs with weights in registers (more where the staging arrays are larger)
@@ -355,7 +355,7 @@ __global__ __launch_bounds__(256) void pers_bwdL_kernel(const PersBwdLArgs a) {
   constexpr int DEPTH3 = 6;                   // S3: groups requested ahead (more of them spill at UF = 16)
   constexpr int NPART = NBK * KS;            // partial sums of an output block
   constexpr int kPauseA = 16, kPauseP = 32;  // pauses before the first look at a counter, in units of 64 cycles
-  static_assert(CPT <= 2, "one or two cells per thread");
+  static_assert(CPT <= 2 && NF % kFlagSub == 0, "one or two cells per thread, arrivals spread evenly over the counter lines");
   extern __shared__ __attribute__((aligned(16))) float smem[];
   float* const stage = smem;              // [UB][32] partial sums of this step; also the bias-gradient reduction
   float* const xsA = smem + 4096;         // [UF/8 octets][4 gates][256] gate gradients of the finalised units, exchange order
@@ -366,7 +366,7 @@ __global__ __launch_bounds__(256) void pers_bwdL_kernel(const PersBwdLArgs a) {
   const int i = bid / NBK, j = bid % NBK;
   const int f = ks * NBK + i;
   const bool fin = f < NF;       // this workgroup finalises (adds the partial sums, point-wise stage, publication)
-  const int fi = min(f, NF - 1), noct = min(CPT, 16 - CPT * fi);  // its octets (the cells past them repeat the last one's and are not stored)
+  const int fi = min(f, NF - 1);  // whose units are its own (a workgroup that does not finalise looks at the last one's)
   const int g0 = ks * NG8;       // first 8-k group of this workgroup's part
   const int T = a.T, B = a.B;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -415,7 +415,7 @@ __global__ __launch_bounds__(256) void pers_bwdL_kernel(const PersBwdLArgs a) {
     }
   }
 
-  // ---- the cells this thread finalises: units UB*j + UF*i + 8*c + 2*wave + kk (c < CPT), batch row b0 + n
+  // ---- the cells this thread finalises: units UB*j + UF*fi + 8*c + 2*wave + kk (c < CPT), batch row b0 + n
   const int j8 = 2 * wave + kk;
   const int bb = a.b0 + 32 * sl + n;
   const bool valid = bb < B;
@@ -423,7 +423,7 @@ __global__ __launch_bounds__(256) void pers_bwdL_kernel(const PersBwdLArgs a) {
   float dc[CPT], dh_rec[CPT], dbsum[CPT][4];
 #pragma unroll
   for (int c = 0; c < CPT; ++c) {
-    cu[c] = UB * j + UF * fi + 8 * min(c, noct - 1) + j8;
+    cu[c] = UB * j + UF * fi + 8 * c + j8;
     dc[c] = (CELL == 0 && valid && a.dcT) ? a.dcT[(size_t)bb * H + cu[c]] : 0.f;  // GRU: the direct term dh_t o z_t
     dh_rec[c] = (valid && a.dhT) ? a.dhT[(size_t)bb * H + cu[c]] : 0.f;
 #pragma unroll
@@ -521,15 +521,15 @@ __global__ __launch_bounds__(256) void pers_bwdL_kernel(const PersBwdLArgs a) {
 #pragma unroll
       for (int q = 0; q < (384 * CPT + 255) / 256; ++q) {
         const int idx = threadIdx.x + 256 * q, c = idx / 384, z = (idx / 128) % 3;
-        if (idx < 384 * noct)
+        if (idx < 384 * CPT)
           xstore4(reinterpret_cast<float*>(partX(t, j, z) + (size_t)(4 * (CPT * fi + c)) * 512 + (idx & 127) * 16),
                   *reinterpret_cast<const floatx4*>(xsA + 4 * idx));
       }
     }
-    // the unit octets of this workgroup are k8 blocks 4*(UF/8*i + c) + gate of the block's slot: contiguous
+    // the unit octets of this workgroup are k8 blocks 4*(CPT*fi + c) + gate of the block's slot: contiguous
 #pragma unroll
     for (int c = 0; c < (S3 ? 0 : CPT); ++c)
-      if (c < noct) xstore4(slotX(t, j) + (size_t)(4 * (CPT * fi + c)) * 256 + 4 * threadIdx.x,
+      xstore4(slotX(t, j) + (size_t)(4 * (CPT * fi + c)) * 256 + 4 * threadIdx.x,
               *reinterpret_cast<const floatx4*>(xsA + c * 1024 + 4 * threadIdx.x));
     signal(flagA(t, j) + (f & (kFlagSub - 1)) * kFlagStride, a.full_fences);
     // standard layout for the weight-gradient products: (gate, batch row, four of the UF units) per store
@@ -538,7 +538,7 @@ __global__ __launch_bounds__(256) void pers_bwdL_kernel(const PersBwdLArgs a) {
       const int idx = threadIdx.x + 256 * q;
       const int g = idx / (8 * UF), l2 = (idx / (UF / 4)) % 32, hf = idx % (UF / 4);
       const int b2 = a.b0 + 32 * sl + l2;
-      if (b2 < B && hf < 2 * noct)
+      if (b2 < B)
         *reinterpret_cast<floatx4*>(a.dA + ((size_t)t * B + b2) * G + (size_t)g * H + UB * j + UF * fi + 4 * hf) =
             *reinterpret_cast<const floatx4*>(ro + (g * 32 + l2) * UF + 4 * hf);
     }
@@ -555,7 +555,7 @@ __global__ __launch_bounds__(256) void pers_bwdL_kernel(const PersBwdLArgs a) {
     tr.mark(t, 0);
     hide(rv);
     __builtin_amdgcn_s_sleep(kPauseA);
-    w.wait_uneven(flagA(t, i), NF);
+    w.wait(flagA(t, i), NF);
     tr.mark(t, 1);
     floatx16 acc;
 #pragma unroll
@@ -654,7 +654,7 @@ __global__ __launch_bounds__(256) void pers_bwdL_kernel(const PersBwdLArgs a) {
     for (int c = 0; c < CPT; ++c) {  // dh_rec of this thread's cells: the NBK partial sums in fixed order
       float pv[NPART];
 #pragma unroll
-      for (int ib = 0; ib < NPART; ++ib) pv[ib] = slotP(t, j, ib)[(UF * fi + 8 * min(c, noct - 1) + j8) * 32 + n];
+      for (int ib = 0; ib < NPART; ++ib) pv[ib] = slotP(t, j, ib)[(UF * fi + 8 * c + j8) * 32 + n];
       float sum = 0.f;
 #pragma unroll
       for (int ib = 0; ib < NPART; ++ib) sum += pv[ib];
@@ -683,7 +683,7 @@ __global__ __launch_bounds__(256) void pers_bwdL_kernel(const PersBwdLArgs a) {
 #pragma unroll
       for (int g = 0; g < 4; ++g) stage[(g * UF + 8 * c + j8) * 32 + n] = dbsum[c][g];
     __syncthreads();
-    if (threadIdx.x < NG * UF && (int)threadIdx.x % UF < 8 * noct) {
+    if (threadIdx.x < NG * UF) {
       float sum = 0.f;
 #pragma unroll
       for (int q = 0; q < 32; ++q) sum += stage[threadIdx.x * 32 + ((q + threadIdx.x) & 31)];

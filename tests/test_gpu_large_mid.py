@@ -1,5 +1,5 @@
-"""One-layer kernels of hidden sizes between 512, 1024 and 2048: blocks of the backward tiles whose units do not divide evenly over their
-workgroups (768, 896), groups of K that do not divide by four (640, 896), tiles cut in four and in two, several slices and
+"""One-layer kernels of hidden sizes between 512, 1024 and 2048: blocks of the backward tiles with more workgroups than finalise
+(one or two octets of units each), partial sums that do not spread evenly over the counter lines (640, 768, 896, 1536, 1792), groups of K that do not divide by four (640, 896), tiles cut in four and in two, several slices and
 launches, weights partly in LDS (1536, 1792); fp32 and bf16 products, repeated launches; sizes that are padded to them."""
 import pytest
 

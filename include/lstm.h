@@ -91,15 +91,17 @@ extern "C" {
  * Returns 0 if any dimension is non-positive.
  *
  * Hidden sizes below 512 other than 128 and 256 (with more than a few steps of one layer; above
- * 512 rows not the sizes from 257 to 415) are computed at the next of 128, 256, 512, and sizes between 512 and 1024 at 1024
+ * 512 rows not the sizes from 257 to 415) are computed at the next multiple of 64 from 128 on (a single sequence: 128, 256 or
+ * 512), and sizes between 512 and 1024 at 640, 768, 896 or 1024
  * (with up to 64 rows; up to 128 rows from 608, up to 256 from 640, up to 768 from 832), sizes from 1472 (up to
- * 32 rows) or 1664 (up to 64 rows) to 2047 at 2048: the library copies W, R, b, the initial states
+ * 32 rows) or 1664 (up to 64 rows) to 2047 at 1536, 1792 or 2048, whichever has kernels for that many rows: the library copies W, R, b, the initial states
  * and, backward, the upstream gradients into zero-padded buffers inside the workspace, runs the
  * padded network on the chosen path and copies the results back.  The result is that of the
  * given network: a hidden unit whose weights, bias and initial state are zero stays at h = c = 0
  * at every step and receives zero gradients.  The persistent kernels (Section 4) exist for those
  * sizes, and the padded run is faster than the per-step paths at the given size (three to
- * five times with four layers).  Reserve and workspace sizes are those of the padded network, and
+ * five times with four layers).  Reserve and workspace sizes are those of the network padded to the next of 128, 256, 512,
+ * 1024 and 2048 (or larger), and
  * the copies are part of the weight re-layout that Section 2.3 redoes every pass.  The smallest
  * networks (H = 8, 16 or 32 with I <= 64, B <= 8 and L (3 + B) <= 20) are not padded either: one
  * workgroup runs a whole pass of theirs as given, steps looped inside one launch (the low end of

@@ -17,20 +17,21 @@
  * layers stacked as Section 2.4 describes.  The reset gate multiplies the recurrent product, so the
  * three recurrent matrices run as one stacked product per step (the grouping of Section 2.1).
  *
- * What runs: with H = 128, 256 or 512 (H = 512: B <= 1024, single gate 512; H = 256: 2048 / 1024;
- * H = 128: 4096 / 2048) the
+ * What runs: with H a multiple of 64 from 128 to 512 (H > 256: B <= 1024, single gate 512; H = 192 and 256: 2048 / 1024;
+ * H = 128: 4096 / 2048; not short passes of 320 and 384 units with more than 512 rows) the
  * persistent kernels of lstm.h with the weights on chip for all T steps (Section 4) and the layers
  * as a wavefront inside one launch (2.4; as many layers per launch as L*H/8 workgroups fit the CUs,
  * deeper stacks as consecutive groups of layers): their 32-row tile per workgroup holds, for 8 hidden units,
  * r, z and the input and recurrent halves of n (GRU), or the one gate and three empty groups
- * (single gate); with H = 1024 (B <= 384; single gate 192) or H = 2048 (B <= 128; single gate 64) the one-layer persistent kernels
+ * (single gate); with H = 1024 (B <= 384; single gate 192) or H = 2048 (B <= 128; single gate 64), and the sizes between that lstm.h
+ * names, the one-layer persistent kernels
  * with the recurrent matrix spread over all CUs.  Every other shape runs on the rungs of the paper's ladder that do not depend on the
  * cell: the input products of a layer batched over all steps (Section 2.3), the gates grouped into
  * one recurrent product per step (2.1), one fused point-wise kernel per step (2.2.2).  Weight
  * gradients are large products after propagation (2.6) in both cases, on the library's MFMA GEMM
- * kernels.  Hidden sizes below 512 other than 128 and 256 run zero-padded to the next of 128, 256, 512,
- * sizes between 512 and 1024 padded to 1024, and sizes between 1024 and 2048 with few rows (GRU: up to 64, from 1472
- * on up to 128; single gate: up to 64) padded to 2048, on those persistent kernels (same rule, same reasoning and same effect on the reserve and workspace
+ * kernels.  Hidden sizes below 512 run zero-padded to the next multiple of 64 from 128 on,
+ * sizes between 512 and 1024 padded to 640, 768, 896 or 1024, and sizes between 1024 and 2048 with few rows (GRU: up to 64, from 1472
+ * on up to 128; single gate: up to 64) padded to 1536, 1792 or 2048 (the smallest with kernels for that many rows), on those persistent kernels (same rule, same reasoning and same effect on the reserve and workspace
  * sizes as in lstm.h: a padded unit stays at h = 0 and receives zero gradients, so the result is that of
  * the given network).  RNN_NO_PERSISTENT=1 in the environment keeps every shape, as given, on the
  * step-by-step path.

@@ -64,3 +64,11 @@ def test_many_rows(H, L, T, B, path):
         assert (binding.lstm_auto_path(L, T, B, 64, H, backward) == binding.LSTM_PATH_PERSISTENT) == (path == "on")
     run_case(cfg(L, T, B, 64, H), 3, 0)
     run_cell("gru", L, T, B, 64, H, seed=4)
+
+
+# One direction on chip, the other not: a reserve of either is read by the other.
+@pytest.mark.parametrize("L,T,B,H,on", [(2, 8, 513, 384, (False, True)), (3, 14, 513, 384, (True, False))])
+def test_many_rows_in_one_direction(L, T, B, H, on):
+    from paper_1604_01946_amd import binding
+    assert tuple(binding.lstm_auto_path(L, T, B, 64, H, k) == binding.LSTM_PATH_PERSISTENT for k in (0, 1)) == on
+    run_case(cfg(L, T, B, 64, H), 3, 0)

@@ -213,7 +213,7 @@ bool tiny_path(const Dims& d, int cell) {
   if (cell != 0 || d.B != 1 || !knobs().tiny) return false;
   if (!(d.H == 128 || d.H == 256 || d.H == 512)) return false;
   DeviceInfo di;
-  return device_info(di) && 32L * d.L <= di.cus;  // 32 workgroups per layer, one per CU
+  return device_info(di) && di.cus >= 256 && d.L <= 8;  // 32 workgroups per layer, on the 32 CUs of an XCD each
 }
 
 // The wide-batch backward kernel: two batch halves, 16 hidden units per workgroup.
@@ -731,7 +731,7 @@ int forward_layers(const FwdArgs& args, int cell) {
     PersFwdArgs k{};
     k.W = a.W; k.R = a.R; k.bias = a.b; k.P0 = P0; k.c0 = a.c0; k.h0 = a.h0; k.hx = hx; k.watchdog = g_watch_dev;
     k.res = a.reserve; k.y = a.y; k.hT = a.hT; k.cT = a.cT;
-    k.L = d.L; k.T = d.T; k.B = d.B; k.I = d.I; k.H = d.H; k.spin_limit = spin_limit();
+    k.L = d.L; k.T = d.T; k.B = d.B; k.I = d.I; k.H = d.H; k.spin_limit = spin_limit(); k.full_fences = full_fences();
     k.trace = (g_trace_bytes >= (size_t)d.T * 64) ? g_trace_buf : nullptr;
     k.trace_block = g_trace_block;
     ProfScope ps(LSTM_PHASE_FWD_RECURRENCE, s);
@@ -902,7 +902,7 @@ int backward_layers(const BwdArgs& a, int cell, bool* bias_done, bool with_weigh
     k.dh0 = a.dh0; k.dc0 = a.dc0; k.watchdog = g_watch_dev;
     k.dx0 = (a.dx && d.I == d.H) ? a.dx : nullptr;
     k.db = a.db;  // every element written by the one lane that owns the unit
-    k.L = d.L; k.T = d.T; k.B = d.B; k.I = d.I; k.H = d.H; k.spin_limit = spin_limit();
+    k.L = d.L; k.T = d.T; k.B = d.B; k.I = d.I; k.H = d.H; k.spin_limit = spin_limit(); k.full_fences = full_fences();
     k.trace = (g_trace_bytes >= (size_t)d.T * 64) ? g_trace_buf : nullptr;
     k.trace_block = g_trace_block;
     {

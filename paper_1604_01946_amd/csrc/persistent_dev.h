@@ -235,5 +235,17 @@ __device__ __forceinline__ void map_block(int groups, int members, int& g, int& 
   }
 }
 
+// The XCD that the wave runs on (hardware register XCC_ID).
+__device__ __forceinline__ int xcd_id() { return __builtin_amdgcn_s_getreg((31 << 11) | 20) & 15; }
+
+// blockIdx -> (group, member) with a whole group on one XCD, groups dealt round-robin to the XCDs, under the usual dealing of
+// workgroups (block i to XCD i % 8).  False: the block has no role.  The grid is xcd_grid(groups, members).
+__device__ __forceinline__ bool map_block_xcd(int groups, int members, int& g, int& m) {
+  const int i = (int)blockIdx.x >> 3;
+  g = 8 * (i / members) + ((int)blockIdx.x & 7);
+  m = i % members;
+  return g < groups;
+}
 }  // namespace
+inline int xcd_grid(int groups, int members) { return (groups + 7) / 8 * 8 * members; }
 }  // namespace lstm

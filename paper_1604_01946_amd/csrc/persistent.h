@@ -10,6 +10,8 @@
 //   persistent_pp3.hip    pers_fwd_pp3_kernel: the same on the bf16 matrix cores, operands in three parts
 //   persistent_bpp.hip    pers_bwd_pp_kernel: two quarter-slices of 16 rows alternating on the matrix cores
 //   persistent_tiny.hip   pers_fwd_tiny_kernel / pers_bwd_tiny_kernel: B = 1, the exchanged values are their own flags
+//   persistent_near_fwd.hip, persistent_near_bwd.hip  pers_fwd_near_kernel / pers_bwd_near_kernel: slices of 16 rows, H <= 512, all cells;
+//                         groups of workgroups on one XCD (near_dev.h)
 //   persistent_large_dev.h, persistent_large.hip, persistent_large_mid.hip  pers_fwdL_kernel / pers_bwdL_kernel: one layer per launch,
 //                         H = 1024 / 2048, and sizes between 512 and 2048
 //   persistent.hip        host side: residency, launches, which shapes run where, layer groups, batch slices
@@ -71,6 +73,7 @@ struct PersFwdArgs {
   int trace_block;
   int keep;           // wide kernel: 0 = inference call (no reserve wanted): only y, hT, cT are written
   float* dummy;       // pers_fwd_pp_kernel: 128 bytes of scratch that take the stores nobody wants
+  int spread = 0;     // pers_fwd_near_kernel: groups on all XCDs instead of one each
   int* redo = nullptr;  // pers_fwd_pp3_kernel: set where a sum is infinite or NaN; pers_fwd_pp_kernel: run only if it is set
 };
 
@@ -112,6 +115,8 @@ struct PersBwdArgs {
   long long* trace;
   int trace_block;
   const float* h0;     // [L][B][H] or null: read by the GRU variant of the wide kernel
+  int nsl = 1;         // pers_bwd_near_kernel: slices of 16 rows side by side in this launch; with more than one db takes their parts, [L][slices][4H]
+  int spread = 0;      // pers_bwd_near_kernel: as in PersFwdArgs
   float* dummy;        // pers_bwd_pp_kernel: 128 bytes of scratch that take the stores nobody wants
 };
 
@@ -211,6 +216,11 @@ hipError_t launch_bwd_pp(int cell, int H, const PersBwdArgs& a, int nbh, hipStre
 // (persistent_tiny.hip); hx [L][T+1][H], dAx [L][T][4H], dxbuf [L][T][H]
 hipError_t launch_fwd_tiny(int H, const PersFwdArgs& a, hipStream_t s);
 hipError_t launch_bwd_tiny(int H, const PersBwdArgs& a, hipStream_t s);
+
+// slices of 16 rows that exchange through an XCD's L2, `units` hidden units per workgroup (persistent_near_fwd.hip, persistent_near_bwd.hip)
+hipError_t launch_fwd_near(int cell, int H, int units, const PersFwdArgs& a, hipStream_t s);
+hipError_t launch_bwd_near(int cell, int H, int units, const PersBwdArgs& a, hipStream_t s);
+hipError_t launch_near_bias(const float* part, float* db, int L, int slices, int H, int gates, hipStream_t s);
 
 // s3: the variant on the bf16 matrix cores
 hipError_t launch_fwdL_any(int H, int cell, const PersFwdLArgs& k, hipStream_t s, bool s3);

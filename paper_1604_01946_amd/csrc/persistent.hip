@@ -216,6 +216,42 @@ bool tiny_path(const Dims& d, int cell) {
   return device_info(di) && di.cus >= 256 && d.L <= 8;  // 32 workgroups per layer, on the 32 CUs of an XCD each
 }
 
+// Kernels of slices of 16 rows that exchange through an XCD's L2 (persistent_near_fwd.hip, persistent_near_bwd.hip): hidden units
+// per workgroup (0: not these kernels), slices side by side in a launch, whether a (layer, slice) group of workgroups lies on
+// all XCDs.
+//   Few units per workgroup before many, since a step's products are what a workgroup spends most of it on, and a group on one
+//   XCD before one on all (L = 1, T = 100, B = 16, H = 256 LSTM forward / backward: 8 units 175 / 304 us on one, 230 / 332 on all;
+//   16 units 210 / 358 on one.  L = 3, T = 40, B = 17, H = 320 forward: 8 units on all 146 us, 16 on one 169).
+//   LSTM and GRU: where all slices run in one launch.  Against the kernels that come after this rule, 63 random shapes of that kind of
+//   all cells, 2 to 100 steps: forward 1.66, backward 1.55 times faster on average, none slower by more than 2 %.  In several
+//   launches the kernels with slices of 64 rows are ahead (GRU, L = 4, T = 50, B = 128, H = 256 305 / 530 us against 373 / 598).
+//   Single gate: at any number of rows, those kernels multiply three empty gates (tanh, L = 4, T = 100, B = 256, H = 256: 922 / 1596 us
+//   there, 504 / 894 here in two launches; L = 2, T = 5, B = 512, H = 512 334 / 416 and 154 / 216).
+struct NearPlan {
+  int units = 0, slices = 0, side = 0;
+  bool spread = false;
+};
+NearPlan near_plan(const Dims& d, int cell, bool backward) {
+  NearPlan p;
+  DeviceInfo di;
+  if (!knobs().near || !device_info(di) || di.cus < 256) return p;  // (eight XCDs of 32 CUs)
+  if ((backward ? knobs().bwd_narrow : knobs().fwd_narrow) >= 0 || knobs().two_chains || knobs().pingpong >= 0 || !knobs().rnn_pp) return p;  // another kernel is asked for
+  const bool single = cell >= 2;
+  p.slices = (d.B + 15) / 16;
+  for (int side = p.slices; side > 0 && (side == p.slices || single); --side)
+    for (int units = single ? 16 : 8; units <= (single ? 32 : 16); units *= 2)
+      for (int spread = 0; spread < 2; ++spread) {
+        const long groups = (long)d.L * side, members = d.H / units;
+        if (members > 64 || (!single && units == 16 && d.H > (backward ? 256 : 320))) continue;  // (no registers for 16 units' weights above)
+        if (spread ? groups * members > 256 : (groups + 7) / 8 * members > 32) continue;
+        p.units = units;
+        p.side = side;
+        p.spread = spread;
+        return p;
+      }
+  return p;
+}
+
 // The wide-batch backward kernel: two batch halves, 16 hidden units per workgroup.
 bool bwd_wide(const Dims& d) {
   if (d.B > 64) return true;
@@ -739,6 +775,28 @@ int forward_layers(const FwdArgs& args, int cell) {
     CK(launch_fwd_tiny(d.H, k, s), "persistent forward launch (single sequence)");
     return LSTM_OK;
   }
+  if (const NearPlan np = near_plan(d, cell, false); np.units) {
+    {
+      ProfScope ps(LSTM_PHASE_FWD_INPUT_GEMM, s);
+      GemmProblem p{a.x, a.W, P0, (int)TB, (int)G, d.I, d.I, 1, 1, d.I, (long)G, 0};
+      CK(launch_gemm_group(&p, 1, s, hx, a.w.flags - a.w.xchg), "input projection GEMM (layer 0)");
+    }
+    PersFwdArgs k{};
+    k.W = a.W; k.R = a.R; k.bias = a.b; k.P0 = P0; k.c0 = a.c0; k.h0 = a.h0; k.hx = hx; k.watchdog = g_watch_dev;
+    k.res = a.reserve; k.y = a.y; k.hT = a.hT; k.cT = a.cT;
+    k.L = d.L; k.T = d.T; k.B = d.B; k.I = d.I; k.H = d.H; k.spin_limit = spin_limit(); k.full_fences = full_fences();
+    k.spread = np.spread; k.keep = a.inference ? 0 : 1;
+    k.trace = (g_trace_bytes >= (size_t)d.T * 64) ? g_trace_buf : nullptr;
+    k.trace_block = g_trace_block;
+    ProfScope ps(LSTM_PHASE_FWD_RECURRENCE, s);
+    prof_flops(2.0 * G * d.B * d.T * d.H * (2 * d.L - 1), "pers_fwd_near_kernel");
+    for (int s0 = 0; s0 < np.slices; s0 += np.side) {
+      k.b0 = 16 * s0;
+      k.nsl = std::min(np.side, np.slices - s0);
+      CK(launch_fwd_near(cell, d.H, np.units, k, s), "persistent forward launch (slices of 16 rows)");
+    }
+    return LSTM_OK;
+  }
   // Wide kernel with I == H: layer 0 multiplies by W_0 inside the kernel like the layers above it (its workgroups
   // are otherwise idle half of every step), reading x from a copy in exchange layout that takes the place of the
   // projection in the workspace.  LSTM_FWD_BATCHED_INPUT=1 keeps the batched product of Section 2.3 instead.
@@ -918,6 +976,40 @@ int backward_layers(const BwdArgs& a, int cell, bool* bias_done, bool with_weigh
     }
     if (bias_done) *bias_done = a.db != nullptr;
     if (!with_weight_gradients) return LSTM_OK;
+    return weight_gradients(a, dA, true, a.db != nullptr);
+  }
+  if (const NearPlan np = near_plan(d, cell, true); np.units) {
+    PersBwdArgs k{};
+    k.W = a.W; k.R = a.R; k.res = a.reserve; k.c0 = a.c0; k.h0 = a.h0; k.dy = a.dy; k.dhT = a.dhT; k.dcT = a.dcT;
+    k.dA = dA; k.dAx = reinterpret_cast<float*>(a.ws + a.w.xchg); k.dxbuf = reinterpret_cast<float*>(a.ws + a.w.dx);
+    k.dh0 = a.dh0; k.dc0 = a.dc0; k.watchdog = g_watch_dev;
+    k.dx0 = (a.dx && d.I == d.H) ? a.dx : nullptr;
+    k.db = np.slices > 1 && a.db ? reinterpret_cast<float*>(a.ws + a.w.dbpart) : a.db;
+    k.L = d.L; k.T = d.T; k.B = d.B; k.I = d.I; k.H = d.H; k.spin_limit = spin_limit(); k.full_fences = full_fences();
+    k.spread = np.spread;
+    k.trace = (g_trace_bytes >= (size_t)d.T * 64) ? g_trace_buf : nullptr;
+    k.trace_block = g_trace_block;
+    {
+      ProfScope ps(LSTM_PHASE_BWD_RECURRENCE, s);
+      const double per = 2.0 * GW * d.B * d.T;
+      prof_flops(per * d.H * (2 * d.L - 1) + (k.dx0 ? per * d.I : 0.0), "pers_bwd_near_kernel");
+      for (int s0 = 0; s0 < np.slices; s0 += np.side) {
+        k.b0 = 16 * s0;
+        k.nsl = std::min(np.side, np.slices - s0);
+        CK(launch_bwd_near(cell, d.H, np.units, k, s), "persistent backward launch (slices of 16 rows)");
+      }
+    }
+    if (k.db != a.db) {
+      ProfScope ps(LSTM_PHASE_BIAS_GRAD, s);
+      CK(launch_near_bias(k.db, a.db, d.L, np.slices, d.H, gates_of_cell(cell), s), "bias gradient");
+    }
+    if (a.dx && !k.dx0) {  // layer 0's input gradient: all T steps in one product
+      ProfScope ps(LSTM_PHASE_BWD_INPUT_GEMM, s);
+      GemmProblem p{dA, a.W, a.dx, (int)TB, d.I, (int)GW, (long)G, 1, d.I, 1, d.I, 0};
+      CK(launch_gemm_group(&p, 1, s, reinterpret_cast<float*>(a.ws + a.w.xchg), a.w.flags - a.w.xchg), "input-gradient GEMM (layer 0)");
+    }
+    if (bias_done) *bias_done = a.db != nullptr;
+    if (cell != 0 || !with_weight_gradients) return LSTM_OK;
     return weight_gradients(a, dA, true, a.db != nullptr);
   }
   PersBwdArgs k;

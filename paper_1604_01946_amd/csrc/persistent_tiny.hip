@@ -25,33 +25,12 @@
 // Section 2.4's wavefront over layers is the same polling: layer l reads what layer l-1 (forward) or layer l+1 (backward)
 // handed over, two to three steps behind it.  Every poll is bounded (watchdog as in the other persistent kernels).
 #include "../../include/lstm.h"
-#include "persistent_dev.h"
+#include "near_dev.h"
 
 #include <algorithm>
 
 namespace lstm {
 namespace {
-
-constexpr unsigned kEmpty = 0x7FA5C3E1u;  // "not written yet"
-
-__device__ __forceinline__ float poll_load(const float* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-// near: every reader is on this XCD, whose L2 is as far as the value has to go
-__device__ __forceinline__ void publish(float* p, float v, bool near) {
-  unsigned b = __float_as_uint(v);
-  if (b == kEmpty) b = 0x7FC00000u;
-  if (near) __hip_atomic_store(reinterpret_cast<unsigned*>(p), b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-  else __hip_atomic_store(reinterpret_cast<unsigned*>(p), b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Four words of a slot of n floats at a wave-uniform address, for values that another XCD writes.
-typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ uintx4 remote_load4(const float* p, int n, int at) {
-  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), (short)0, 4 * n, 0x00020000);
-  asm volatile("" ::: "memory");  // (asked for again, it is read again)
-  return __builtin_amdgcn_raw_buffer_load_b128(r, 4 * at, 0, 16);  // sc1: as an agent-scope load
-}
 
 // The 16-byte request of the backward kernel is inline assembly (there is no 16-byte atomic load to ask the compiler
 // for), so the wait for it is written out as well, tied to the value it covers.  Every word is its own flag: a request
@@ -70,30 +49,7 @@ __device__ __forceinline__ void publish4(float* p, floatx4 v, bool near) {
   else asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 3" ::"v"(p), "v"(v) : "memory");
 }
 
-// Polls: one round after the other, without a pause (backward, L = 1, H = 256, T = 500: none 0.56 ms, 128 cycles before the first
-// round 0.57, 256 0.60, 512 0.66).  What a round costs grows with the bytes that all waves together ask for, so the waves of a
-// workgroup poll a share of the slot each and hand the shares to each other through LDS.
-struct TinyWaiter {
-  int* watchdog;
-  int limit;
-  bool dead;
-  __device__ __forceinline__ bool give_up(int& spins) {
-    if (dead) return true;
-    if (++spins > limit) {
-      dead = true;
-      __hip_atomic_store(watchdog, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-      return true;
-    }
-    return false;
-  }
-  // One value per lane.
-  __device__ __forceinline__ float poll1(const float* p) {
-    int spins = 0;
-    while (true) {
-      const float v = poll_load(p);
-      if (__all(__float_as_uint(v) != kEmpty) || give_up(spins)) return v;
-    }
-  }
+struct TinyWaiter : NearWaiter {
   // Four consecutive values per lane.
   __device__ __forceinline__ void poll4(const float* p, floatx4& v) {
     int spins = 0;
@@ -108,17 +64,8 @@ struct TinyWaiter {
   }
 };
 
-// Whether all workgroups of a layer run on one XCD: each leaves its XCD's number in the layer's table (kTinyGroups words, the
-// empty pattern before the launch) and reads the others'.  All read the same words, so all come to the same answer.
 constexpr int kTinyGroups = 32;  // workgroups per layer
 constexpr int kTinyChunk = 8;    // steps whose reserve values pass through LDS together
-__device__ __forceinline__ void leave_xcd(float* table, int member, int lane) {
-  if (lane == 0) publish(table + member, __int_as_float(xcd_id()), false);
-}
-__device__ __forceinline__ bool all_on_one_xcd(TinyWaiter& w, const float* table, int lane) {
-  const float v = w.poll1(table + (lane & (kTinyGroups - 1)));
-  return __all(__float_as_int(v) == xcd_id());
-}
 
 // Time stamps of one workgroup's first wave, eight per step (the time-stamped instance only).
 template <bool TRACE>
@@ -205,7 +152,7 @@ __global__ __launch_bounds__(HH + 64) void pers_fwd_tiny_kernel(const PersFwdArg
   auto slot = [&](int st) { return a.hx + ((size_t)l * (T + 1) + st) * H; };
   float* const hand = a.hx + (size_t)a.L * (T + 1) * H;  // the same values for the layer above, which is on another XCD
   auto xslot = [&](int layer, int t) { return hand + ((size_t)layer * T + t) * H; };
-  TinyWaiter w{a.watchdog, a.spin_limit, false};
+  TinyWaiter w{{a.watchdog, a.spin_limit, false}};
   const TinyTracer<TRACE> tr{(int)blockIdx.x == a.trace_block ? a.trace : nullptr};
   float* const table = hand + (size_t)a.L * T * H + l * kTinyGroups;
   // Steps by which the input is ahead of the step that multiplies it: one, unless the layers' distances are most of a pass (L = 8,
@@ -273,7 +220,7 @@ __global__ __launch_bounds__(HH + 64) void pers_fwd_tiny_kernel(const PersFwdArg
         if (T > 1) request_x(1);
       }
     }
-    const bool one = all_on_one_xcd(w, table, lane);
+    const bool one = all_on_one_xcd(w, table, kTinyGroups, lane);
     if (lane == 0) one_xcd = one;
     __syncthreads();
     for (int t = 0; t < T; ++t) {
@@ -436,7 +383,7 @@ __global__ __launch_bounds__(HH + 64) void pers_bwd_tiny_kernel(const PersBwdArg
   const bool has_up = l < a.L - 1;
   auto dslot = [&](int t) { return a.dAx + ((size_t)l * T + t) * G; };
   auto xslot = [&](int layer, int t) { return a.dxbuf + ((size_t)layer * T + t) * H; };
-  TinyWaiter w{a.watchdog, a.spin_limit, false};
+  TinyWaiter w{{a.watchdog, a.spin_limit, false}};
   const TinyTracer<TRACE> tr{(int)blockIdx.x == a.trace_block ? a.trace : nullptr};
   float* const table = a.dAx + (size_t)a.L * T * G + l * kTinyGroups;
 
@@ -499,7 +446,7 @@ __global__ __launch_bounds__(HH + 64) void pers_bwd_tiny_kernel(const PersBwdArg
     }
     request(T - 1);
     work_up(T - 1);
-    const bool one = all_on_one_xcd(w, table, lane);
+    const bool one = all_on_one_xcd(w, table, kTinyGroups, lane);
     if (lane == 0) one_xcd = one;
     request(T - 2);
     fetch(T - 4);

@@ -5,6 +5,7 @@ import pytest
 
 from paper_1604_01946_amd.inputs import Config
 from test_gpu_parity import BWD, FWD, run_case
+from test_gpu_rnn_cells import run as run_cell
 
 pytestmark = pytest.mark.gpu
 
@@ -22,3 +23,57 @@ def test_single_sequence(H, L, T, I, knobs):
     fast, _ = run_case(cfg(L, T, 1, I or H, H), 21, 6)
     for k in FWD + BWD:
         assert (getattr(slow, k) == getattr(fast, k)).all(), k
+
+
+# Slices of 16 rows: 8 and 16 (single gate 16 and 32) units per workgroup, groups on one XCD, two on one, on all; rows that do not
+# fill a slice; one, two and three steps; every size that has instances of its own.
+SLICES = [
+    (1, 3, 16, 0, 128), (2, 5, 17, 40, 128), (4, 3, 64, 0, 128), (8, 2, 5, 0, 128), (3, 4, 33, 24, 192), (2, 2, 100, 0, 192),
+    (1, 1, 40, 0, 256), (4, 6, 64, 0, 256), (2, 3, 2, 300, 256), (8, 3, 15, 24, 256), (3, 5, 17, 0, 320), (1, 17, 31, 0, 320),
+    (2, 4, 20, 24, 384), (1, 9, 64, 0, 384), (3, 2, 16, 0, 448), (4, 5, 3, 24, 512), (1, 10, 33, 0, 512),
+]
+
+
+@pytest.mark.parametrize("L,T,B,I,H", SLICES)
+def test_slices_lstm(L, T, B, I, H, knobs):
+    knobs(LSTM_FULL_FENCES="1")
+    slow, _ = run_case(cfg(L, T, B, I or H, H), 22, 6)
+    knobs(LSTM_FULL_FENCES=None)
+    fast, _ = run_case(cfg(L, T, B, I or H, H), 22, 6)
+    for k in FWD + BWD:
+        assert (getattr(slow, k) == getattr(fast, k)).all(), k
+
+
+@pytest.mark.parametrize("cell", ["gru", "tanh", "relu"])
+@pytest.mark.parametrize("L,T,B,I,H", SLICES + [(2, 3, 1, 0, 256), (3, 12, 1, 24, 512), (4, 3, 300, 0, 256), (1, 9, 530, 24, 512)])
+def test_slices_other_cells(cell, L, T, B, I, H):
+    run_cell(cell, L, T, B, I or H, H, seed=4)
+
+
+@pytest.mark.parametrize("H,B", [(256, 20), (320, 5)])
+def test_a_row_that_is_not_finite_spoils_no_other(H, B):
+    import torch
+
+    from paper_1604_01946_amd import binding
+    from paper_1604_01946_amd.inputs import make_inputs
+    from paper_1604_01946_amd.runner import LstmRunner
+
+    c = cfg(2, 4, B, 24, H)
+    d = make_inputs(c, 3)
+    whole = LstmRunner(c.dims, d)
+    binding.check(whole.forward())
+    binding.check(whole.backward())
+    d["x"][1, 2, 5] = float("nan")
+    d["x"][2, 3, :] = float("inf")
+    r = LstmRunner(c.dims, d)
+    binding.check(r.forward())
+    binding.check(r.backward())
+    torch.cuda.synchronize()
+    keep = [b for b in range(B) if b not in (2, 3)]
+    for a, b in ((r.y, whole.y), (r.hT, whole.hT), (r.cT, whole.cT), (r.dx, whole.dx), (r.dh0, whole.dh0), (r.dc0, whole.dc0)):
+        a, b = a.view(-1, B, a.shape[-1]), b.view(-1, B, b.shape[-1])
+        # (not the same bits: a product that finds a sum that is not finite works its tile out with other instructions; sums
+        # of up to 4 H terms, four steps)
+        assert (a[:, keep] - b[:, keep]).abs().max() <= 1e-5 * b.abs().max()
+    assert r.y[1:, 2].isnan().all()
+    binding.check(r.forward())  # no wait expired

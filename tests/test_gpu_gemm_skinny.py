@@ -1,0 +1,62 @@
+"""Products of up to 64 rows on the kernel whose operands go from memory to registers: remainders of its tiles of rows and blocks of 64
+columns, K from one unit of 32 to several slices, both layouts of B, strided operands and results, values that are not finite."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+M_ = (1, 5, 15, 17, 32, 33, 49, 64)
+
+
+def product(M, N, K, kn, acc=0, scratch=True, pad=8, poison=None):
+    import torch
+
+    from paper_1604_01946_amd import binding
+
+    g = torch.Generator().manual_seed(M * 1000 + N + K)
+    A = torch.randn(M, K + pad, generator=g).cuda()
+    B = torch.randn((K, N + pad) if kn else (N, K + pad), generator=g).cuda()
+    C = torch.randn(M, N + 3, generator=g).cuda()
+    if poison is not None:
+        A[0, min(3, K - 1)] = poison
+    a, b = A[:, :K].double(), (B[:, :N].double() if kn else B[:, :K].double().t())
+    ref = a @ b + (C[:, :N].double() if acc else 0)
+    bound = a.abs() @ b.abs() + C[:, :N].abs().double()
+    edge = C[:, N:].clone()
+    part = torch.empty(64 << 20, dtype=torch.uint8, device="cuda") if scratch else None
+    sb = (N + pad, 1) if kn else (1, K + pad)
+    binding.check(binding.lstm_gemm_f32_ws(M, N, K, A, K + pad, 1, B, *sb, C, N + 3, acc, part, part.numel() if scratch else 0))
+    torch.cuda.synchronize()
+    assert torch.equal(C[:, N:], edge)
+    return C[:, :N].double(), ref, bound
+
+
+# An error of half a unit in the last place per product and per addition of partial sums, random signs: below 2^-24 sqrt(K) of the sum of
+# magnitudes divided by sqrt(K); 2^-21 of the sum of magnitudes is eight times the largest single error.
+@pytest.mark.parametrize("kn", [False, True])
+@pytest.mark.parametrize("M", M_)
+@pytest.mark.parametrize("N,K", [(64, 32), (100, 96), (1028, 512), (640, 2592), (4096, 1024), (68, 8192)])
+def test_against_float64(M, N, K, kn):
+    for acc in (0, 1):
+        c, ref, bound = product(M, N, K, kn, acc)
+        assert ((c - ref).abs() <= 2.0 ** -21 * bound).all()
+
+
+@pytest.mark.parametrize("kn", [False, True])
+def test_without_scratch(kn):
+    c, ref, bound = product(40, 512, 4096, kn, scratch=False)
+    assert ((c - ref).abs() <= 2.0 ** -21 * bound).all()
+
+
+@pytest.mark.parametrize("kn", [False, True])
+@pytest.mark.parametrize("value", [float("inf"), float("nan"), 3e38])
+def test_values_that_are_not_finite(kn, value):
+    import torch
+
+    c, ref, bound = product(20, 256, 1024, kn, poison=value)
+    if value == 3e38:  # finite, above what the parts hold
+        ok = ref.abs() <= 3.4e38
+        assert ((c - ref).abs() <= 2.0 ** -21 * bound)[ok].all() and c[~ok].isinf().all()
+    else:
+        assert torch.equal(c[0].isnan(), ref[0].isnan()) and torch.equal(c[0].isinf(), ref[0].isinf())
+        assert (c[0][ref[0].isinf()] == ref[0][ref[0].isinf()]).all()
+    assert ((c - ref).abs() <= 2.0 ** -21 * bound)[1:].all()

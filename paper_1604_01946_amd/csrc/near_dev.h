@@ -7,7 +7,7 @@
 namespace lstm {
 namespace {
 
-constexpr unsigned kEmpty = 0x7FA5C3E1u;  // "not written yet"
+constexpr unsigned kEmpty = 0xFFFFFFFFu;  // "not written yet": a NaN that arithmetic never produces, and the largest word
 
 __device__ __forceinline__ float poll_load(const float* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -37,8 +37,10 @@ __device__ __forceinline__ floatx4 slot_load4(const float* slot, int n, int at) 
   const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(slot), (short)0, 4 * n, 0x00020000);
   return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(r, 4 * at, 0, SC1 ? 16 : 0));
 }
-__device__ __forceinline__ bool written4(floatx4 v) {
-  return __float_as_uint(v[0]) != kEmpty && __float_as_uint(v[1]) != kEmpty && __float_as_uint(v[2]) != kEmpty && __float_as_uint(v[3]) != kEmpty;
+// The largest word of a number of 16-byte pieces: kEmpty if any of them is.  (Two instructions a piece.)
+__device__ __forceinline__ unsigned umax3(unsigned a, unsigned b, unsigned c) { return max(max(a, b), c); }
+__device__ __forceinline__ unsigned top4(floatx4 v, unsigned m) {
+  return umax3(umax3(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2])), __float_as_uint(v[3]), m);
 }
 __device__ __forceinline__ float canonical(float v) { return __float_as_uint(v) == kEmpty ? __uint_as_float(0x7FC00000u) : v; }
 // near: plain stores, which end in the L2 that the readers share; else through it to memory

@@ -39,6 +39,18 @@ hipError_t with_on_chip_size(int H, F f) {
   return hipErrorInvalidValue;
 }
 
+// The sizes of the near kernels: those, and up to 1024 the sizes with one-layer kernels.
+template <typename F>
+hipError_t with_near_size(int H, F f) {
+  switch (H) {
+    case 640: return f(std::integral_constant<int, 640>{});
+    case 768: return f(std::integral_constant<int, 768>{});
+    case 896: return f(std::integral_constant<int, 896>{});
+    case 1024: return f(std::integral_constant<int, 1024>{});
+  }
+  return with_on_chip_size(H, f);
+}
+
 // A step counter is split into kFlagSub words, each on a cache line of its own (kFlagStride ints
 // apart).  Agent-scope atomics from many workgroups on one line are served one after the other by the
 // memory side, about 25 ns each (6.4 us for 256 arrivals on one line, measured), so arrivals are spread

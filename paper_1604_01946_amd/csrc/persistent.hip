@@ -236,14 +236,16 @@ NearPlan near_plan(const Dims& d, int cell, bool backward) {
   NearPlan p;
   DeviceInfo di;
   if (!knobs().near || !device_info(di) || di.cus < 256) return p;  // (eight XCDs of 32 CUs)
-  if ((backward ? knobs().bwd_narrow : knobs().fwd_narrow) >= 0 || knobs().two_chains || knobs().pingpong >= 0 || !knobs().rnn_pp) return p;  // another kernel is asked for
+  if ((backward ? knobs().bwd_narrow : knobs().fwd_narrow) >= 0 || knobs().two_chains || knobs().pingpong >= 0 || !knobs().rnn_pp || knobs().split3 >= 0) return p;  // another kernel is asked for
   const bool single = cell >= 2;
   p.slices = (d.B + 15) / 16;
   for (int side = p.slices; side > 0 && (side == p.slices || single); --side)
     for (int units = single ? 16 : 8; units <= (single ? 32 : 16); units *= 2)
       for (int spread = 0; spread < 2; ++spread) {
         const long groups = (long)d.L * side, members = d.H / units;
-        if (members > 64 || (!single && units == 16 && d.H > (backward ? 256 : 320))) continue;  // (no registers for 16 units' weights above)
+        // (no registers for more units' weights above these sizes; beyond 512 LSTM and GRU have instances of single layers on all XCDs)
+        if (single ? backward && units == 32 && d.H > 768 : units == 16 && d.H > (backward ? 256 : 320)) continue;
+        if (!single && d.H > 512 && (d.L > 1 || !spread)) continue;
         if (spread ? groups * members > 256 : (groups + 7) / 8 * members > 32) continue;
         p.units = units;
         p.side = side;
@@ -251,6 +253,25 @@ NearPlan near_plan(const Dims& d, int cell, bool backward) {
         return p;
       }
   return p;
+}
+
+// Layers per launch of those kernels at the sizes that have one-layer kernels as well, 0 where they don't take a shape or are slower: LSTM
+// and GRU, whose products there run in three bf16 parts and here in fp32, from one step on or only up to some steps.  One-layer
+// kernels / these, us (L, T, B):
+//   LSTM forward   H = 640 163 / 156 (1, 35, 16); 768 174 / 170, 418 / 433 (2, 35, 20); 896 531 / 578 (1, 100, 30), 96 / 91 (1, 12, 30); 1024
+//                  565 / 603 (1, 100, 30)
+//   GRU forward    640 347 / 311 (2, 35, 32); 768 375 / 347; 896 408 / 391, 490 / 500 (1, 100, 30); 1024 544 / 594
+//   LSTM backward  640 296 / 210 (1, 35, 16); 768 327 / 270, 839 / 598 (2, 35, 32); 896 905 / 699; 1024 86 / 102 (1, 4, 8), 813 / 951
+//   GRU backward   640 780 / 460 (2, 35, 32); 768 794 / 563; 896 75 / 77 (1, 4, 8), 865 / 670; 1024 80 / 102, 802 / 932
+//   single gate    tanh, H = 1024 941 / 266 and 1798 / 301 (4, 52, 1); 640 269 / 107 and 371 / 190 (1, 30, 100); 896 346 / 145 and 647 / 275 (3, 20, 20)
+int near_large_layers(const Dims& d, int cell, bool backward) {
+  if (d.H <= 512 || d.H > 1024) return 0;
+  if (d.H == 1024 && (cell < 2 || (d.L == 1 && d.B > 32))) return 0;  // (of one layer of more rows only the single gate's products would gain)
+  if (backward && cell < 2 && d.H > 768 && d.T < 8) return 0;
+  if (!backward && (cell == 0 ? d.H > 640 && d.T > 16 : cell == 1 && d.H > 768 && d.T > 64)) return 0;
+  int per = d.L;
+  while (per > 0 && !near_plan(Dims{per, d.T, d.B, d.I, d.H}, cell, backward).units) --per;
+  return per;
 }
 
 // The wide-batch backward kernel: two batch halves, 16 hidden units per workgroup.
@@ -709,11 +730,12 @@ int backward_layers(const BwdArgs& a, int cell, bool* bias_done, bool with_weigh
 // its input is the upstream gradient of the group below.
 int run_forward_persistent(const FwdArgs& a, int cell) {
   const Dims& d = a.d;
-  if (persistent_large(d, false)) {
+  const int near_per = near_large_layers(d, cell, false);
+  if (!near_per && persistent_large(d, false)) {
     if (!ensure_watchdog()) return LSTM_HIP_ERROR;
     return run_forward_persistent_large(a, cell);
   }
-  const int per = layers_per_launch(d);
+  const int per = near_per ? near_per : layers_per_launch(d);
   if (per <= 0) return LSTM_UNSUPPORTED;
   if (d.L <= per) return forward_layers(a, cell);
   const size_t TB = (size_t)d.T * d.B, BH = (size_t)d.B * d.H, G = (size_t)gates_of_cell(cell) * d.H;
@@ -897,11 +919,12 @@ int forward_layers(const FwdArgs& args, int cell) {
 // reports in *bias_done whether db is complete; the caller forms the weight gradients.
 int run_backward_persistent(const BwdArgs& a, int cell, bool* bias_done, LayerGradients* lg) {
   const Dims& d = a.d;
-  if (persistent_large(d, true)) {
+  const int near_per = near_large_layers(d, cell, true);
+  if (!near_per && persistent_large(d, true)) {
     if (!ensure_watchdog()) return LSTM_HIP_ERROR;
     return run_backward_persistent_large(a, cell, bias_done, lg);
   }
-  const int per = layers_per_launch(d);
+  const int per = near_per ? near_per : layers_per_launch(d);
   if (per <= 0) return LSTM_UNSUPPORTED;
   if (d.L <= per) return backward_layers(a, cell, bias_done, true);
   const size_t TB = (size_t)d.T * d.B, BH = (size_t)d.B * d.H, GW = (size_t)gates_of_cell(cell) * d.H;

@@ -19,7 +19,11 @@
 namespace lstm {
 namespace {
 
-template <int H, int CELL, int UB>
+// Loads of a lane's weights per wave that stay in registers; the rest is in LDS (one tile, LSTM and GRU above H = 512).
+constexpr int near_reg_loads(int H, int CELL) { return CELL < 2 ? (H > 512 ? 32 : H / 16) : H / 64; }
+
+// FAR: groups lie on all XCDs.
+template <int H, int CELL, int UB, bool FAR>
 __global__ __launch_bounds__(UB == 8 ? 320 : 576) void pers_bwd_near_kernel(const PersBwdArgs a) {
   constexpr int NG = CELL < 2 ? 4 : 1, NGP = CELL == 0 ? 4 : (CELL == 1 ? 3 : 1), GP = NGP * H, G = 4 * H, M = H / UB;
   constexpr bool both = UB == 8;                  // dh and dx rows in one tile
@@ -37,7 +41,7 @@ __global__ __launch_bounds__(UB == 8 ? 320 : 576) void pers_bwd_near_kernel(cons
   __shared__ __align__(16) float das[2][NG][16][UP];                 // [step parity]: gate gradients
   __shared__ int one_xcd;
   int g, m;
-  if (a.spread) map_block(a.L * a.nsl, M, g, m);
+  if constexpr (FAR) map_block(a.L * a.nsl, M, g, m);
   else if (!map_block_xcd(a.L * a.nsl, M, g, m)) return;
   const int l = g / a.nsl, sl = g % a.nsl, T = a.T, B = a.B, u0 = m * UB;
   const int b0 = a.b0 + 16 * sl, rows = min(16, B - b0);
@@ -49,7 +53,7 @@ __global__ __launch_bounds__(UB == 8 ? 320 : 576) void pers_bwd_near_kernel(cons
   NearWaiter w{a.watchdog, a.spin_limit, false};
 
   if (wave == SERVE) {  // ---- the wave that serves the others
-    leave_xcd(table, m, lane);
+    if constexpr (!FAR) leave_xcd(table, m, lane);
     const float* const res_l = a.res + (size_t)l * TB * (CELL == 0 ? 6 : (CELL == 1 ? 5 : 1)) * H;
     constexpr int NF = NR * 16 * Q, NFL = (NF + 63) / 64, ND = 16 * Q, NDL = (ND + 63) / 64, NS = NG * 16 * Q, NSL = (NS + 63) / 64;
     auto at_lds = [](int e) { return e / Q * UP + 4 * (e % Q); };  // 16-byte piece e of (array, row, four units) in LDS
@@ -100,10 +104,10 @@ __global__ __launch_bounds__(UB == 8 ? 320 : 576) void pers_bwd_near_kernel(cons
     auto take = [&](int t) {
       int spins = 0;
       while (has_up) {
-        bool ok = true;
+        unsigned m = 0;
 #pragma unroll
-        for (int i = 0; i < NDL; ++i) ok = ok && written4(vd[i]);
-        if (every_lane(ok) || w.give_up(spins)) break;
+        for (int i = 0; i < NDL; ++i) m = top4(vd[i], m);
+        if (every_lane(m != kEmpty) || w.give_up(spins)) break;
         asm volatile("" ::: "memory");
         request(t);
       }
@@ -138,8 +142,10 @@ __global__ __launch_bounds__(UB == 8 ? 320 : 576) void pers_bwd_near_kernel(cons
     if (T > 1) put(T - 2);
     request(T - 1);
     take(T - 1);
-    const bool one = all_on_one_xcd(w, table, M, lane);
-    if (lane == 0) one_xcd = one;
+    if constexpr (!FAR) {
+      const bool one = all_on_one_xcd(w, table, M, lane);
+      if (lane == 0) one_xcd = one;
+    }
     request(T - 2);
     fetch(T - 3);
     __syncthreads();
@@ -180,9 +186,13 @@ __global__ __launch_bounds__(UB == 8 ? 320 : 576) void pers_bwd_near_kernel(cons
   }
 
   // ---- weights: lane (q, n) holds row n of tile i (a column of R_l or W_l) at k = (wave % 4) * NG * H/4 + 16 j + 4 q + r
+  // (beyond 32 j, above H = 512, they lie in LDS)
   const bool second = wave >= 4;  // waves of the dx tiles
   const int wk = wave & 3;
-  floatx4 wt[NT][NL];
+  constexpr int NLR = near_reg_loads(H, CELL);
+  extern __shared__ __align__(16) floatx4 wlds[];
+  floatx4* const wl = wlds + (size_t)wk * (NL - NLR) * 64 + lane;
+  floatx4 wt[NT][NLR];
   {
     const float* const Rl = a.R + (size_t)l * GP * H;
     const float* const Wl = l > 0 ? a.W + (size_t)GP * a.I + (size_t)(l - 1) * GP * H : a.W;  // layer 0: [GP][I], I == H
@@ -191,29 +201,38 @@ __global__ __launch_bounds__(UB == 8 ? 320 : 576) void pers_bwd_near_kernel(cons
 #pragma unroll
     for (int i = 0; i < NT; ++i)
 #pragma unroll
-      for (int j = 0; j < NL; ++j)
+      for (int j = 0; j < NL; ++j) {
+        floatx4 v;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int unit = NG == 4 ? wk * (H / 4) + 4 * j + q : wk * (H / 4) + 16 * j + 4 * q + r, gate = NG == 4 ? r : 0;
           const bool has = from_w ? dx_live && (CELL != 1 || gate != 3) : CELL != 1 || gate != 2;
-          wt[i][j][r] = has ? mat[(size_t)((CELL == 1 && gate == 3 ? 2 : gate) * H + unit) * H + 16 * i] : 0.f;
+          v[r] = has ? mat[(size_t)((CELL == 1 && gate == 3 ? 2 : gate) * H + unit) * H + 16 * i] : 0.f;
         }
+        if (j < NLR) wt[i][j] = v;
+        else wl[(j - NLR) * 64] = v;
+      }
   }
   const int kbase = (wk * (NG * H / 16) + q) * 64 + 4 * n;  // float of the lane's first operand piece in a slot; 16 k on: 256 floats
-  // Operands come in chunks of CH loads.  The first chunk is polled for alone (a round of all of them moves 64 KB per CU at
-  // H = 256, LSTM: 0.45 us whether they are there or not); once it is there the others are, and are asked for under its products.
-  constexpr int CH = NL % 4 == 0 ? 4 : (NL % 5 == 0 ? 5 : (NL % 3 == 0 ? 3 : NL)), NCH = NL / CH, DEEP = NCH < 4 ? NCH : 4;
-  floatx4 op[DEEP * CH];  // DEEP chunks at a time
-  auto ask = [&](const float* slot, int c) {
+  // Operands come in chunks of CH loads, up to DEEP chunks at a time.  On one XCD the first chunk is polled for alone (a round of all of them
+  // moves 64 KB per CU at H = 256, LSTM: 0.45 us whether they are there or not); once it is there the others are, and are asked for under
+  // its products.  FAR: as in the forward kernel.
+  constexpr int CH = NL % 4 == 0 ? 4 : (NL % 5 == 0 ? 5 : (NL % 3 == 0 ? 3 : (NL % 7 == 0 ? 7 : NL))), NCH = NL / CH;
+  constexpr int DMAX = CELL < 2 ? (H > 768 ? 2 : (H > 512 ? 3 : 4)) : (UB == 32 && H > 640 ? 2 : 4), DEEP = NCH < DMAX ? NCH : DMAX;  // (as many as there are registers for)
+  floatx4 op[DEEP * CH];
+  auto ask = [&](auto past, const float* slot, int c) {
 #pragma unroll
-    for (int j = 0; j < CH; ++j) op[c % DEEP * CH + j] = slot_load4<true>(slot, SLOT, kbase + 256 * (c * CH + j));
+    for (int j = 0; j < CH; ++j) op[c % DEEP * CH + j] = slot_load4<decltype(past)::value>(slot, SLOT, kbase + 256 * (c * CH + j));
   };
   auto written = [&](int c) {
-    bool ok = true;
+    unsigned m = 0;
 #pragma unroll
-    for (int j = 0; j < CH; ++j) ok = ok && written4(op[c % DEEP * CH + j]);
-    return every_lane(ok);
+    for (int j = 0; j < CH; ++j) m = top4(op[c % DEEP * CH + j], m);
+    return every_lane(m != kEmpty);
   };
+  const auto past = std::true_type{};
+  const auto through = std::bool_constant<!FAR>{};  // past the caches, unless FAR
+  const int sample = (wk * (H / 16) + min(lane, H / 16 - 1)) * 64 * NG + 64 * NG - 1;
   // asked: the first DEEP chunks have been
   auto multiply = [&](const float* slot, bool asked, floatx4 (&to)[NT][64]) {
     floatx4 acc[NT];
@@ -221,26 +240,37 @@ __global__ __launch_bounds__(UB == 8 ? 320 : 576) void pers_bwd_near_kernel(cons
     for (int i = 0; i < NT; ++i) acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
     int spins = 0;
     if (!asked) {
-      do {
-        asm volatile("" ::: "memory");
-        ask(slot, 0);
-      } while (!written(0) && !w.give_up(spins));
+      if constexpr (FAR) {
+        while (!every_lane(__float_as_uint(poll_load(slot + sample)) != kEmpty) && !w.give_up(spins)) {
+        }
+        ask(through, slot, 0);
+      } else {
+        do {
+          asm volatile("" ::: "memory");
+          ask(past, slot, 0);
+        } while (!written(0) && !w.give_up(spins));
+      }
 #pragma unroll
-      for (int c = 1; c < DEEP; ++c) ask(slot, c);
+      for (int c = 1; c < DEEP; ++c) ask(through, slot, c);
     }
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
-      while ((c > 0 || asked) && !written(c) && !w.give_up(spins)) {
+      while ((c > 0 || FAR || asked) && !written(c) && !w.give_up(spins)) {
         asm volatile("" ::: "memory");
-        ask(slot, c);
+        ask(past, slot, c);
       }
 #pragma unroll
-      for (int j = 0; j < CH; ++j)
+      for (int j = 0; j < CH; ++j) {
+        const int jj = c * CH + j;
+        floatx4 v[NT];
+#pragma unroll
+        for (int i = 0; i < NT; ++i) v[i] = jj < NLR ? wt[i][jj < NLR ? jj : 0] : wl[(jj - NLR) * 64];
 #pragma unroll
         for (int r = 0; r < 4; ++r)
 #pragma unroll
-          for (int i = 0; i < NT; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(wt[i][c * CH + j][r], op[c % DEEP * CH + j][r], acc[i], 0, 0, 0);
-      if (c + DEEP < NCH) ask(slot, c + DEEP);
+          for (int i = 0; i < NT; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[i][r], op[c % DEEP * CH + j][r], acc[i], 0, 0, 0);
+      }
+      if (c + DEEP < NCH) ask(through, slot, c + DEEP);
     }
 #pragma unroll
     for (int i = 0; i < NT; ++i) to[i][lane] = acc[i];
@@ -253,7 +283,7 @@ __global__ __launch_bounds__(UB == 8 ? 320 : 576) void pers_bwd_near_kernel(cons
         if (dx_live && t + 1 < T) {
           const float* const slot = own + (size_t)(t + 1) * SLOT;
 #pragma unroll
-          for (int c = 0; c < DEEP; ++c) ask(slot, c);
+          for (int c = 0; c < DEEP; ++c) ask(through, slot, c);
           // (as in the forward kernel: the point-wise stage on the same SIMD first)
           __builtin_amdgcn_s_sleep(2);
           multiply(slot, true, xpart[t & 1][wk]);
@@ -304,7 +334,7 @@ __global__ __launch_bounds__(UB == 8 ? 320 : 576) void pers_bwd_near_kernel(cons
   };
   const Tracer tr{(int)blockIdx.x == a.trace_block ? a.trace : nullptr};
   __syncthreads();
-  const bool near = one_xcd && !a.full_fences;
+  const bool near = !FAR && one_xcd && !a.full_fences;
   if (fin) work_up(T - 1);
   __syncthreads();
   for (int t = T - 1; t >= 0; --t) {
@@ -381,26 +411,39 @@ __global__ __launch_bounds__(256) void near_bias_kernel(const float* __restrict_
   db[(size_t)l * cols + c] = v;
 }
 
-template <int H, int CELL, int UB>
+template <int H, int CELL, int UB, bool FAR>
 hipError_t launch(const PersBwdArgs& a, hipStream_t s) {
   const int groups = a.L * a.nsl, M = H / UB;
   const long n = (long)groups * (4L * (CELL < 2 ? 4 : 1) * H * a.T + 16), n2 = (long)(a.L - 1) * a.T * a.B * H / 4;
   hipLaunchKernelGGL(near_empty_kernel, dim3((unsigned)std::min<long>((n + n2 + 255) / 256, 2048)), dim3(256), 0, s,
                      reinterpret_cast<floatx4*>(a.dAx), n, reinterpret_cast<floatx4*>(a.dxbuf + (size_t)a.T * a.B * H), n2);  // (layer 0 hands nothing over)
+  const void* const fn = (const void*)pers_bwd_near_kernel<H, CELL, UB, FAR>;
+  constexpr size_t smem = (size_t)4 * ((CELL < 2 ? H / 16 : H / 64) - near_reg_loads(H, CELL)) * 1024;
+  static bool ready;
+  if (smem)
+    if (const hipError_t e = allow_dynamic_lds(fn, smem, ready); e != hipSuccess) return e;
   void* params[] = {const_cast<PersBwdArgs*>(&a)};
-  return launch_resident((const void*)pers_bwd_near_kernel<H, CELL, UB>, a.spread ? groups * M : xcd_grid(groups, M), params, 0, s, UB == 8 ? 320 : 576);
+  return launch_resident(fn, FAR ? groups * M : xcd_grid(groups, M), params, (unsigned)smem, s, UB == 8 ? 320 : 576);
+}
+
+// The instances that near_plan asks for.
+template <int H, int CELL, int UB>
+hipError_t launch_where(const PersBwdArgs& a, hipStream_t s) {
+  if (a.spread) return launch<H, CELL, UB, true>(a, s);
+  if constexpr (H / UB <= 32) return launch<H, CELL, UB, false>(a, s);
+  return hipErrorInvalidValue;
 }
 
 template <int H, int CELL>
 hipError_t launch_units(int units, const PersBwdArgs& a, hipStream_t s) {
-  if constexpr (CELL < 2) {
-    if (units == 8) return launch<H, CELL, 8>(a, s);
+  if constexpr (CELL < 2 && H <= 896) {
+    if (units == 8) return launch_where<H, CELL, 8>(a, s);
   }
   if constexpr (CELL >= 2 || H <= 256) {
-    if (units == 16) return launch<H, CELL, 16>(a, s);
+    if (units == 16) return launch_where<H, CELL, 16>(a, s);
   }
-  if constexpr (CELL >= 2) {
-    if (units == 32) return launch<H, CELL, 32>(a, s);
+  if constexpr (CELL >= 2 && H <= 768) {
+    if (units == 32) return launch_where<H, CELL, 32>(a, s);
   }
   return hipErrorInvalidValue;
 }
@@ -414,7 +457,7 @@ hipError_t launch_near_bias(const float* part, float* db, int L, int slices, int
 }
 
 hipError_t launch_bwd_near(int cell, int H, int units, const PersBwdArgs& a, hipStream_t s) {
-  return with_on_chip_size(H, [&](auto h) {
+  return with_near_size(H, [&](auto h) {
     constexpr int HH = decltype(h)::value;
     switch (cell) {
       case 0: return launch_units<HH, 0>(units, a, s);

@@ -21,17 +21,18 @@
 namespace lstm {
 namespace {
 
-template <int H, int CELL, int MT>
-__global__ __launch_bounds__(576) void pers_fwd_near_kernel(const PersFwdArgs a) {
+// FAR: groups lie on all XCDs.  IN: with the waves of the input half (layers above the launch's first).
+template <int H, int CELL, int MT, bool FAR, bool IN>
+__global__ __launch_bounds__(IN ? 576 : 320) void pers_fwd_near_kernel(const PersFwdArgs a) {
   constexpr int NG = CELL < 2 ? 4 : 1, NGP = CELL == 0 ? 4 : (CELL == 1 ? 3 : 1), U = 16 * MT / NG, M = H / U, GP = NGP * H;
   constexpr int NA = CELL == 0 ? 6 : (CELL == 1 ? 5 : 1), NL = H / 64, SLOT = 16 * H;
-  __shared__ __align__(16) floatx4 part[2][8][MT][64];  // [step parity][wave][tile][lane]: sums over a quarter of K (waves 4..7: input half)
+  __shared__ __align__(16) floatx4 part[2][IN ? 8 : 4][MT][64];  // [step parity][wave][tile][lane]: sums over a quarter of K (waves 4..7: input half)
   constexpr int UP = U + 4;                             // (rows of units in LDS: no bank conflicts)
   __shared__ __align__(16) float pins[2][NGP][16][UP];  // [step parity][gate][row][unit]: input product (layer 0)
   __shared__ __align__(16) float outs[2][NA][16][UP];   // [step parity][i, f, o, c', c, h (GRU r, z, n, R_n h, h)][row][unit]
   __shared__ int one_xcd;
   int g, m;
-  if (a.spread) map_block(a.L * a.nsl, M, g, m);
+  if constexpr (FAR) map_block(a.L * a.nsl, M, g, m);
   else if (!map_block_xcd(a.L * a.nsl, M, g, m)) return;
   const int l = g / a.nsl, sl = g % a.nsl, T = a.T, B = a.B, u0 = m * U;
   const int b0 = a.b0 + 16 * sl, rows = min(16, B - b0);  // the slice's batch rows; a tile's columns past them are computed and not kept
@@ -41,8 +42,8 @@ __global__ __launch_bounds__(576) void pers_fwd_near_kernel(const PersFwdArgs a)
   float* const table = a.hx + (size_t)a.L * a.nsl * group + 64 * g;
   NearWaiter w{a.watchdog, a.spin_limit, false};
 
-  if (wave == 8) {  // ---- the wave that serves the others
-    leave_xcd(table, m, lane);
+  if (wave == (IN ? 8 : 4)) {  // ---- the wave that serves the others
+    if constexpr (!FAR) leave_xcd(table, m, lane);
     float* const hand = own + (size_t)(T + 1) * SLOT;
     constexpr int Q = U / 4, NP = NGP * 16 * Q, NPL = (NP + 63) / 64, NO = NA * 16 * Q, NH = 16 * Q;
     auto at_lds = [](int e) { return e / Q * UP + 4 * (e % Q); };  // 16-byte piece e of (array, row, four units) in LDS
@@ -94,8 +95,10 @@ __global__ __launch_bounds__(576) void pers_fwd_near_kernel(const PersFwdArgs a)
       put_pins(0);
       fetch_pins(1);
     }
-    const bool one = all_on_one_xcd(w, table, M, lane);
-    if (lane == 0) one_xcd = one;
+    if constexpr (!FAR) {
+      const bool one = all_on_one_xcd(w, table, M, lane);
+      if (lane == 0) one_xcd = one;
+    }
     __syncthreads();
     for (int t = 0; t < T; ++t) {
       __syncthreads();  // the waves' sums of step t, and their results of step t - 1
@@ -112,7 +115,7 @@ __global__ __launch_bounds__(576) void pers_fwd_near_kernel(const PersFwdArgs a)
 
   // ---- weights of waves 0..3 (recurrent half) and 4..7 (input half): lane (q, n) holds row n of tile mt at k = (wave % 4) * H/4 +
   // 16 j + 4 q + r
-  const bool input = wave >= 4;
+  const bool input = IN && wave >= 4;
   const int wk = wave & 3;
   floatx4 wt[MT][NL];
   {
@@ -127,57 +130,74 @@ __global__ __launch_bounds__(576) void pers_fwd_near_kernel(const PersFwdArgs a)
     }
   }
   const int kbase = (wk * (H / 16) + q) * 64 + 4 * n;  // float of the lane's first operand piece in a slot; 16 k on: 256 floats
-  // Operands come in chunks of CH loads: the first is polled for alone, and once it is there the others are, and are asked for under
-  // its products.
-  constexpr int CH = NL % 4 == 0 ? 4 : (NL % 5 == 0 ? 5 : (NL % 3 == 0 ? 3 : NL)), NCH = NL / CH;
-  floatx4 op[NL];
-  auto ask = [&](const float* slot, int c) {
+  // Operands come in chunks of CH loads, up to DEEP chunks at a time.  On one XCD the first chunk is polled for alone; once it is there the
+  // others are, and are asked for under its products.  FAR a word of each run of four units is polled for (a lane each), and then all are read
+  // through the L2, once for the workgroups of an XCD; what was there too early is read again past it.
+  constexpr int CH = NG == 1 && H > 768 ? 2 : (NL % 4 == 0 ? 4 : (NL % 5 == 0 ? 5 : (NL % 3 == 0 ? 3 : (NL % 7 == 0 ? 7 : NL)))), NCH = NL / CH, DMAX = IN ? 2 : 4, DEEP = NCH < DMAX ? NCH : DMAX;
+  floatx4 op[DEEP * CH];
+  auto ask = [&](auto past, const float* slot, int c) {
 #pragma unroll
-    for (int j = 0; j < CH; ++j) op[c * CH + j] = slot_load4<true>(slot, SLOT, kbase + 256 * (c * CH + j));
+    for (int j = 0; j < CH; ++j) op[c % DEEP * CH + j] = slot_load4<decltype(past)::value>(slot, SLOT, kbase + 256 * (c * CH + j));
   };
   auto written = [&](int c) {
-    bool ok = true;
+    unsigned m = 0;
 #pragma unroll
-    for (int j = 0; j < CH; ++j) ok = ok && written4(op[c * CH + j]);
-    return every_lane(ok);
+    for (int j = 0; j < CH; ++j) m = top4(op[c % DEEP * CH + j], m);
+    return every_lane(m != kEmpty);
   };
-  // asked: all chunks have been, through the caches
+  const auto past = std::true_type{};
+  const auto cached = std::false_type{};
+  const int sample = (wk * (H / 16) + min(lane, H / 16 - 1)) * 64 + 63;
+  // asked: the first DEEP chunks have been, through the caches
   auto multiply = [&](const float* slot, bool asked, floatx4 (&to)[MT][64]) {
     floatx4 acc[MT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) acc[mt] = floatx4{0.f, 0.f, 0.f, 0.f};
     int spins = 0;
     if (!asked) {
-      do {
-        asm volatile("" ::: "memory");
-        ask(slot, 0);
-      } while (!written(0) && !w.give_up(spins));
+      if constexpr (FAR) {
+        while (!every_lane(__float_as_uint(poll_load(slot + sample)) != kEmpty) && !w.give_up(spins)) {
+        }
 #pragma unroll
-      for (int c = 1; c < NCH; ++c) ask(slot, c);
+        for (int c = 0; c < DEEP; ++c) ask(cached, slot, c);
+      } else {
+        do {
+          asm volatile("" ::: "memory");
+          ask(past, slot, 0);
+        } while (!written(0) && !w.give_up(spins));
+#pragma unroll
+        for (int c = 1; c < DEEP; ++c) ask(past, slot, c);
+      }
     }
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
-      while ((c > 0 || asked) && !written(c) && !w.give_up(spins)) {
+      while ((c > 0 || FAR || asked) && !written(c) && !w.give_up(spins)) {
         asm volatile("" ::: "memory");
-        ask(slot, c);
+        ask(past, slot, c);
       }
 #pragma unroll
-      for (int j = c * CH; j < (c + 1) * CH; ++j)
+      for (int j = 0; j < CH; ++j)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
 #pragma unroll
-          for (int mt = 0; mt < MT; ++mt) acc[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(wt[mt][j][r], op[j][r], acc[mt], 0, 0, 0);
+          for (int mt = 0; mt < MT; ++mt)
+            acc[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(wt[mt][c * CH + j][r], op[c % DEEP * CH + j][r], acc[mt], 0, 0, 0);
+      if (c + DEEP < NCH) {
+        if (FAR || asked) ask(cached, slot, c + DEEP);
+        else ask(past, slot, c + DEEP);
+      }
     }
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) to[mt][lane] = acc[mt];
   };
   const Tracer tr{(int)blockIdx.x == a.trace_block ? a.trace : nullptr};
 
-  if (input) {  // ---- the input half of a step, beside the recurrent one
+  if constexpr (IN)
+   if (input) {  // ---- the input half of a step, beside the recurrent one
     const float* const below = a.hx + (g - a.nsl) * group + (size_t)(T + 1) * SLOT;  // (layer l > 0)
     auto request = [&](int t) {  // through the caches, which the group shares: usually there when it is looked at
 #pragma unroll
-      for (int j = 0; j < NL; ++j) op[j] = slot_load4<false>(below + (size_t)t * SLOT, SLOT, kbase + 256 * j);
+      for (int c = 0; c < DEEP; ++c) ask(cached, below + (size_t)t * SLOT, c);
     };
     __syncthreads();
     if (l > 0) request(0);
@@ -208,7 +228,7 @@ __global__ __launch_bounds__(576) void pers_fwd_near_kernel(const PersFwdArgs a)
     if (NG == 4 && valid && s0) state = s0[se];
   }
   __syncthreads();
-  const bool near = one_xcd && !a.full_fences;
+  const bool near = !FAR && one_xcd && !a.full_fences;
   __builtin_amdgcn_s_setprio(3);  // (a step waits for these waves: the input half fills their gaps)
   for (int t = 0; t < T; ++t) {
     const int par = t & 1;
@@ -219,9 +239,11 @@ __global__ __launch_bounds__(576) void pers_fwd_near_kernel(const PersFwdArgs a)
     __syncthreads();
     tr.mark(t, 3);
     if (fin) {
-      const floatx4 (&p)[8][MT][64] = part[par];
+      const auto& p = part[par];
       floatx4 s = (p[0][wave][lane] + p[1][wave][lane]) + (p[2][wave][lane] + p[3][wave][lane]);
-      if (l > 0) s += (p[4][wave][lane] + p[5][wave][lane]) + (p[6][wave][lane] + p[7][wave][lane]);
+      if constexpr (IN) {
+        if (l > 0) s += (p[4][wave][lane] + p[5][wave][lane]) + (p[6][wave][lane] + p[7][wave][lane]);
+      }
       float* const o = &outs[par][0][0][0];
       if constexpr (NG == 4) {
         float sg[4];
@@ -296,7 +318,7 @@ __global__ __launch_bounds__(256) void near_prepare_fwd_kernel(floatx4* __restri
   }
 }
 
-template <int H, int CELL, int MT>
+template <int H, int CELL, int MT, bool FAR, bool IN>
 hipError_t launch(const PersFwdArgs& a, hipStream_t s) {
   constexpr int M = H * (CELL < 2 ? 4 : 1) / (16 * MT);
   const int groups = a.L * a.nsl;
@@ -304,18 +326,33 @@ hipError_t launch(const PersFwdArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(near_prepare_fwd_kernel, dim3((unsigned)std::min<long>((n + 255) / 256, 2048)), dim3(256), 0, s,
                      reinterpret_cast<floatx4*>(a.hx), a.h0, groups, a.nsl, a.T, a.B, H, a.b0);
   void* params[] = {const_cast<PersFwdArgs*>(&a)};
-  return launch_resident((const void*)pers_fwd_near_kernel<H, CELL, MT>, a.spread ? groups * M : xcd_grid(groups, M), params, 0, s, 576);
+  return launch_resident((const void*)pers_fwd_near_kernel<H, CELL, MT, FAR, IN>, FAR ? groups * M : xcd_grid(groups, M), params, 0, s, IN ? 576 : 320);
+}
+
+// The instances that near_plan asks for.
+template <int H, int CELL, int MT>
+hipError_t launch_where(const PersFwdArgs& a, hipStream_t s) {
+  constexpr int M = H * (CELL < 2 ? 4 : 1) / (16 * MT);
+  if constexpr (H > 896 && CELL < 2) {
+    return hipErrorInvalidValue;
+  } else if constexpr (H > 512 && CELL < 2) {
+    return a.L == 1 && a.spread ? launch<H, CELL, MT, true, false>(a, s) : hipErrorInvalidValue;
+  } else {
+    if (a.spread) return launch<H, CELL, MT, true, true>(a, s);
+    if constexpr (M <= 32) return launch<H, CELL, MT, false, true>(a, s);
+    return hipErrorInvalidValue;
+  }
 }
 
 template <int H, int CELL>
 hipError_t launch_units(int units, const PersFwdArgs& a, hipStream_t s) {
   constexpr int NG = CELL < 2 ? 4 : 1;
-  if (units == 32 / NG) return launch<H, CELL, 2>(a, s);  // 8 units with four rows, 32 with one
+  if (units == 32 / NG) return launch_where<H, CELL, 2>(a, s);  // 8 units with four rows, 32 with one
   if constexpr (NG == 4 && H <= 320) {
-    if (units == 16) return launch<H, CELL, 4>(a, s);
+    if (units == 16) return launch_where<H, CELL, 4>(a, s);
   }
   if constexpr (NG == 1) {
-    if (units == 16) return launch<H, CELL, 1>(a, s);
+    if (units == 16) return launch_where<H, CELL, 1>(a, s);
   }
   return hipErrorInvalidValue;
 }
@@ -323,7 +360,7 @@ hipError_t launch_units(int units, const PersFwdArgs& a, hipStream_t s) {
 }  // namespace
 
 hipError_t launch_fwd_near(int cell, int H, int units, const PersFwdArgs& a, hipStream_t s) {
-  return with_on_chip_size(H, [&](auto h) {
+  return with_near_size(H, [&](auto h) {
     constexpr int HH = decltype(h)::value;
     switch (cell) {
       case 0: return launch_units<HH, 0>(units, a, s);

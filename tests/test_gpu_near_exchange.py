@@ -50,6 +50,22 @@ def test_slices_other_cells(cell, L, T, B, I, H):
     run_cell(cell, L, T, B, I or H, H, seed=4)
 
 
+# Sizes with one-layer kernels as well: LSTM and GRU up to 896 layer by layer, lengths on both sides of the lines between the kernels, the single
+# gate with all layers in a launch, with groups of them, and in several launches; padded to these sizes.
+LARGE = [(1, 1, 16, 0, 640), (2, 9, 33, 24, 640), (2, 5, 32, 0, 768), (1, 17, 17, 0, 768), (3, 8, 5, 24, 896), (1, 3, 32, 0, 896), (2, 6, 20, 0, 1024), (2, 4, 3, 40, 700)]
+
+
+@pytest.mark.parametrize("L,T,B,I,H", LARGE)
+def test_large_lstm(L, T, B, I, H):
+    run_case(cfg(L, T, B, I or H, H), 23, 0)
+
+
+@pytest.mark.parametrize("cell", ["gru", "tanh", "relu"])
+@pytest.mark.parametrize("L,T,B,I,H", LARGE + [(6, 3, 20, 0, 896), (5, 4, 3, 0, 1024), (1, 5, 100, 0, 1024), (2, 3, 130, 24, 768)])
+def test_large_other_cells(cell, L, T, B, I, H):
+    run_cell(cell, L, T, B, I or H, H, seed=4)
+
+
 @pytest.mark.parametrize("H,B", [(256, 20), (320, 5)])
 def test_a_row_that_is_not_finite_spoils_no_other(H, B):
     import torch

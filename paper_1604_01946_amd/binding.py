@@ -121,10 +121,18 @@ def _ptr(t):
     return t.data_ptr()
 
 
+def _current_stream():
+    """Handle of the current stream of the current device.  torch.cuda.current_stream() builds an object around it, 2.6 us of a
+    call's 4.9 in Python; the handle alone takes 0.3."""
+    import torch
+    if torch.cuda.is_initialized() and hasattr(torch._C, "_cuda_getCurrentRawStream"):
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return torch.cuda.current_stream().cuda_stream
+
+
 def _stream(stream):
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream

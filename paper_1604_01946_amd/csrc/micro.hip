@@ -469,13 +469,17 @@ hipError_t launch_bwd_t(const MicroBwdArgs& a, size_t lds, hipStream_t s) {
 
 // Shapes that run as one workgroup per pass.  The kernels take H = 8 / 16 / 32 with I <= 64 and B <= 8 (LSTM_MICRO=2:
 // all of those); by default only where they were measured faster than the persistent kernels on the hidden size
-// padded to 128.  Those overlap the layers and cost about 6.6 us per step, forward and backward together, for up to
-// four layers; here the layers run one after the other at about 1.1 + 0.34 B us per layer and step:
-// L (3 + B) <= 20 is where the two meet.  LSTM_MICRO=0 keeps every shape on the other kernels.
+// padded to 128 (504 shapes, forward and backward together).  Those cost about 40 us per pass more in launches, and
+// 1.7 us per step with one row, 3.0 with more, for all layers together; here the layers run one after the other at
+// 0.5 + 0.01 H + (0.2 + 0.005 H) B us per layer and step.  L = 1, B = 4, H = 32: T = 8 here 34 us, there 103, T = 250 575 and 692;
+// L = 4, B = 1, H = 32: T = 8 88 and 84, T = 250 1182 and 474.  L (3 + B) <= 20 is as far as the shapes measured go.
+// LSTM_MICRO=0 keeps every shape on the other kernels.
 bool micro_shape(const Dims& d) {
   const int level = knobs().micro;
   if (level == 0 || !(d.H == 8 || d.H == 16 || d.H == 32) || d.I > kMicroMaxI || d.B > kMicroMaxB) return false;
-  return level == 2 || d.L * (3 + d.B) <= 20;
+  if (level == 2) return true;
+  const double step = d.L * (0.5 + 0.01 * d.H + (0.2 + 0.005 * d.H) * d.B), there = d.B == 1 ? 1.7 : 3.0;
+  return d.L * (3 + d.B) <= 20 && d.T * (step - there) <= 40.0;
 }
 
 hipError_t launch_micro_forward(const FwdArgs& f) {

@@ -59,9 +59,12 @@ int padded_hidden_rule(const Dims& d);  // the same without looking at LSTM_NO_P
 int reported_hidden(const Dims& d);     // the size that buffers are reported for, at least padded_hidden_rule
 int granular_hidden(const Dims& d);     // the next size with kernels of its own, for that many rows
 // Sizes that are no powers of two: a few steps of one layer, which are not padded either (reported_hidden), cost less step by
-// step (L = 1, T = 1, B = 1003, H = 192: forward 33 us against 61, backward 59 against 85).
+// step (L = 1, I = 64, H = 192 and 384, forward and backward, step by step over on chip: T = 1 0.7 with one row, 0.6 to 1.0 with 500;
+// T = 2 0.8 to 0.9 and 0.8 to 1.1, 1.2 to 1.8 with 6 to 128 rows, GRU H = 384 with 200 rows 0.9; T = 4 1.0 to 2.3, GRU H = 320 and 384
+// with 500 rows 0.7 to 0.9, and with as many 0.8 to 1.0 at T = 6).
 inline bool too_short_on_chip(const Dims& d) {
-  return (d.H & (d.H - 1)) != 0 && d.H <= 512 && d.L == 1 && (d.T < 8 || (d.T < 16 && d.B < 48));
+  return (d.H & (d.H - 1)) != 0 && d.H <= 512 && d.L == 1 &&
+         (d.T < 2 || (d.T < 4 && (d.B == 1 || d.B > (d.H > 256 ? 128 : 256))) || (d.T < 8 && d.B > 384 && d.H > 256));
 }
 // Hidden sizes between 512, 1024 and 2048 with one-layer kernels of their own, and the rows with which they are taken: none where
 // the given size itself would not be padded (reported_hidden), and none where the backward recurrence would need more launches

@@ -72,3 +72,22 @@ def test_many_rows_in_one_direction(L, T, B, H, on):
     from paper_1604_01946_amd import binding
     assert tuple(binding.lstm_auto_path(L, T, B, 64, H, k) == binding.LSTM_PATH_PERSISTENT for k in (0, 1)) == on
     run_case(cfg(L, T, B, 64, H), 3, 0)
+
+
+# A few steps of one layer: both sides of the lines between the kernels on chip and the steps one by one.
+@pytest.mark.parametrize("T,B,H,path", [(3, 20, 100, "off"), (4, 20, 100, "on"), (4, 1, 300, "on"), (4, 257, 300, "off"), (4, 257, 200, "on"),
+                                        (1, 20, 192, "off"), (2, 20, 192, "on"), (2, 1, 192, "off"), (3, 256, 192, "on"), (3, 129, 320, "off"),
+                                        (7, 385, 384, "off"), (8, 385, 384, "on")])
+def test_short_passes(T, B, H, path):
+    from paper_1604_01946_amd import binding
+    for backward in (0, 1):
+        assert (binding.lstm_auto_path(1, T, B, 64, H, backward) == binding.LSTM_PATH_PERSISTENT) == (path == "on")
+    run_case(cfg(1, T, B, 64, H), 3, 0)
+    for cell in ("gru", "tanh"):
+        run_cell(cell, 1, T, B, 64, H, seed=4)
+
+
+# One workgroup per pass or the kernels that overlap the layers: both sides of the line.
+@pytest.mark.parametrize("L,T,B,H", [(4, 40, 1, 32), (4, 90, 1, 32), (2, 30, 7, 16), (2, 60, 7, 16)])
+def test_micro_line(L, T, B, H):
+    run_case(cfg(L, T, B, H, H), 3, 0)

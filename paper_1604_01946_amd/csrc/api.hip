@@ -266,10 +266,10 @@ int reported_hidden(const Dims& d) {
   // B = 64: H = 1536 43.0, H = 1792 48.7)
   if (d.H > 1024 && d.H < 2048 && ((d.B <= 32 && d.H >= 1472) || (d.B <= 64 && d.H >= 1664))) return 2048;
   if (d.H >= 512 || d.B > 16384) return d.H;  // B: the limit of the persistent kernels
-  // a few steps of one layer: the copies and the weights' way onto the chip cost more than they save (L = 1, I = 64, forward and
-  // backward as given over padded: T = 2 H = 300 0.8 to 1.3 and H = 40 0.9 to 1.1; T = 4 1.0 to 1.7, with 500 rows H = 300 1.2, 450 0.9,
-  // GRU 0.9 and 1.0; T = 8 up to 47 rows 1.3 to 2.2, T = 15 1.6 to 2.7; GRU and tanh 2.0 to 2.5 at T = 4, 3 to 5.6 at T = 15)
-  if (d.L == 1 && (d.T < 4 || (d.T < 8 && d.B > 256 && d.H > 256))) return d.H;
+  // a few steps of one layer as given: drawn when the copies and the weights' way onto the chip cost more than they saved.  On chip is
+  // faster from T = 4 on by now (L = 1, I = 64, H = 40 to 511: LSTM 1.1 to 2.7, GRU and tanh 2 to 5.6 times; below 0.7 to 1.3), but
+  // callers' reserves have the size that this line has always answered for.
+  if (few_steps(d)) return d.H;
   const int p = d.H <= 128 ? 128 : (d.H <= 256 ? 256 : 512);
   // Above 512 rows the per-step kernels and the GEMM rung have enough to do at the given size, and padding to 512
   // pays only while it adds little arithmetic (L = 4, B = 1024: H = 448 75 TFLOP/s padded against 62 as given,

@@ -185,6 +185,7 @@ BatchPlan batch_plan(int B) {
 // two layers at H = 512, up to four at H = 256; L = 1, H = 512, B = 64, T = 100: forward recurrence 0.40 ms on four
 // slices of 16 rows, 0.53 on two of 32, 0.74 on the wide kernel; backward 0.65 against 1.14).  `env` names the
 // setting that pins the choice (LSTM_FWD_NARROW / LSTM_BWD_NARROW): 1 = one slice on the narrow kernel (B <= 64), 0 = never slices.
+// What near_plan takes does not come here: slices of 32 rows forward at H = 384 to 512 are left, and all of it with LSTM_NEAR=0.
 // Backward, from H = 256 on, slices of 32 rows lose to the kernel with two alternating chains per slice of 64 rows
 // (whole iterations, T = 100: L = 2, H = 512, B = 64 2.46 -> 2.28 ms; L = 4, H = 256, B = 64 1.46 -> 1.37; L = 2, H = 256,
 // B = 128 1.55 -> 1.44), while slices of 16 rows stay ahead of it (L = 1, H = 512, B = 64 1.40 against 2.02 ms).
@@ -412,7 +413,7 @@ bool persistent_large(const Dims& d, bool backward) {
 
 bool persistent_supported(const Dims& d, bool backward) {
   if (persistent_large(d, backward)) return true;
-  if (!on_chip_size(d.H) || too_short_on_chip(d)) return false;
+  if (!on_chip_size(d.H) || too_short_on_chip(d, 0)) return false;
   // Slices of 64 rows, one after the other once the chip is full: the rate does not depend on their number.  The GEMM rungs
   // gain with the batch and with short sequences (a launch here costs 70 us before its first step).  Forward and backward
   // of four layers, these kernels / the fused rung: T = 60, H = 512 23.0 / 30.7 ms at 1024 rows and 92 / 90 at 4096, H = 256

@@ -1,5 +1,5 @@
 // Backward recurrence in slices of 16 batch rows whose workgroups exchange gate gradients through the L2 of one XCD:
-// pers_bwd_near_kernel, all cells, multiples of 64 up to 512.  The forward kernel (persistent_near_fwd.hip) names what bounds a step
+// pers_bwd_near_kernel, all cells, multiples of 64 up to 512, 640, 768, 896 and 1024.  The forward kernel (persistent_near_fwd.hip) names what bounds a step
 // and what is done about it: values that are their own flags, a group of workgroups on an XCD of its own, a wave that
 // serves the others, through LDS, with everything that comes from or goes to memory.
 //

@@ -1,5 +1,5 @@
 // Forward recurrence in slices of 16 batch rows whose workgroups exchange h through the L2 of one XCD: pers_fwd_near_kernel, all
-// cells, multiples of 64 up to 512.  (Backward: persistent_near_bwd.hip.)
+// cells, multiples of 64 up to 512, 640, 768, 896 and 1024.  (Backward: persistent_near_bwd.hip.)
 //
 // What bounds a step here is not its products but the way from workgroup to workgroup.  The kernels with step counters pay per step
 // a store, its acknowledgement, a barrier, an atomic, the poll of the counter, the fetch of the data and another barrier, about 3 us.

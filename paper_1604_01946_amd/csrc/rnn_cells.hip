@@ -137,7 +137,7 @@ inline bool gru_persistent_shape(int cell, const Dims& d) {
   //   H = 256 GRU 1.35 and 1.26 at 1024, 1.03 at 2048, 0.83 at 4096; single gate 1.18 and 1.12 at 1024, 0.72 at 2048
   //   H = 128 GRU 1.45 and 1.46 at 2048, 1.02 at 4096, 0.78 at 8192; single gate 1.20 and 1.20 at 2048, 0.74 at 4096
   // (sizes between these as the next of them)
-  if (d.H > 512 || d.H < 128 || d.H % 64 != 0 || too_short_on_chip(d) || steps_beat_chip(d, 1, false)) return false;
+  if (d.H > 512 || d.H < 128 || d.H % 64 != 0 || too_short_on_chip(d, 1) || steps_beat_chip(d, 1, false)) return false;
   const int rows = d.H > 256 ? 1024 : (d.H > 128 ? 2048 : 4096);
   return d.B <= (gru ? rows : rows / 2);
 }

@@ -59,12 +59,14 @@ int padded_hidden_rule(const Dims& d);  // the same without looking at LSTM_NO_P
 int reported_hidden(const Dims& d);     // the size that buffers are reported for, at least padded_hidden_rule
 int granular_hidden(const Dims& d);     // the next size with kernels of its own, for that many rows
 // Sizes that are no powers of two: a few steps of one layer, which are not padded either (reported_hidden), cost less step by
-// step (L = 1, I = 64, H = 192 and 384, forward and backward, step by step over on chip: T = 1 0.7 with one row, 0.6 to 1.0 with 500;
-// T = 2 0.8 to 0.9 and 0.8 to 1.1, 1.2 to 1.8 with 6 to 128 rows, GRU H = 384 with 200 rows 0.9; T = 4 1.0 to 2.3, GRU H = 320 and 384
-// with 500 rows 0.7 to 0.9, and with as many 0.8 to 1.0 at T = 6).
-inline bool too_short_on_chip(const Dims& d) {
-  return (d.H & (d.H - 1)) != 0 && d.H <= 512 && d.L == 1 &&
-         (d.T < 2 || (d.T < 4 && (d.B == 1 || d.B > (d.H > 256 ? 128 : 256))) || (d.T < 8 && d.B > 384 && d.H > 256));
+// step (LSTM, L = 1, I = 64, H = 192 and 384, forward and backward, step by step over on chip: T = 1 0.7 with one row, 0.6 to 1.0 with
+// 500; T = 2 0.8 to 0.9 and 0.8 to 1.1, 1.2 to 1.8 with 6 to 128 rows; T = 4 1.0 to 2.3, H = 448 with 500 rows 0.95.  GRU H = 320 and 384 with 500 rows
+// 0.7 to 0.9 at T = 4; the other cells' buffers of such passes are those of the steps, so all of few_steps stays with them).
+inline bool few_steps(const Dims& d) { return d.L == 1 && (d.T < 8 || (d.T < 16 && d.B < 48)); }
+inline bool too_short_on_chip(const Dims& d, int cell) {
+  if ((d.H & (d.H - 1)) == 0 || d.H > 512 || d.L > 1) return false;
+  if (cell != 0) return few_steps(d);
+  return d.T < 2 || (d.T < 4 && (d.B == 1 || d.B > 256)) || (d.T < 8 && d.B > 384 && d.H > 384);
 }
 // Hidden sizes between 512, 1024 and 2048 with one-layer kernels of their own, and the rows with which they are taken: none where
 // the given size itself would not be padded (reported_hidden), and none where the backward recurrence would need more launches

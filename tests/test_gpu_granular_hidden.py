@@ -74,10 +74,9 @@ def test_many_rows_in_one_direction(L, T, B, H, on):
     run_case(cfg(L, T, B, 64, H), 3, 0)
 
 
-# A few steps of one layer: both sides of the lines between the kernels on chip and the steps one by one.
-@pytest.mark.parametrize("T,B,H,path", [(3, 20, 100, "off"), (4, 20, 100, "on"), (4, 1, 300, "on"), (4, 257, 300, "off"), (4, 257, 200, "on"),
-                                        (1, 20, 192, "off"), (2, 20, 192, "on"), (2, 1, 192, "off"), (3, 256, 192, "on"), (3, 129, 320, "off"),
-                                        (7, 385, 384, "off"), (8, 385, 384, "on")])
+# A few steps of one LSTM layer at a size with kernels of its own: both sides of the lines between them and the steps one by one.
+@pytest.mark.parametrize("T,B,H,path", [(1, 20, 192, "off"), (2, 20, 192, "on"), (2, 1, 192, "off"), (3, 256, 192, "on"), (3, 257, 192, "off"),
+                                        (4, 1, 320, "on"), (2, 129, 320, "on"), (4, 385, 384, "on"), (4, 300, 448, "on"), (7, 385, 448, "off")])
 def test_short_passes(T, B, H, path):
     from paper_1604_01946_amd import binding
     for backward in (0, 1):

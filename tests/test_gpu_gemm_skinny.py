@@ -41,6 +41,22 @@ def test_against_float64(M, N, K, kn):
         assert ((c - ref).abs() <= 2.0 ** -21 * bound).all()
 
 
+def error(M, N, K, kn):
+    c, ref, _ = product(M, N, K, kn)
+    return ((c - ref).norm() / ref.norm()).item()
+
+
+# Products that fp32 instructions form (up to 8 rows with both operands contiguous along K, short ones) and products of tiles in
+# three parts: with this kernel in the place of some of them no error is larger.  The norms of 10000 elements and more scatter by
+# less than 1 % each; 3 % is three times the scatter of their ratio.
+@pytest.mark.parametrize("M,N,K,kn", [(5, 16384, 4096, False), (8, 16384, 4096, False), (5, 2560, 640, False), (8, 2560, 640, False), (8, 8192, 2048, False),
+                                      (16, 2048, 256, True), (33, 1024, 256, False), (12, 4096, 384, False), (16, 2048, 2048, False), (64, 4096, 4096, True)])
+def test_no_larger_error_than_without(M, N, K, kn, knobs):
+    got = error(M, N, K, kn)
+    knobs(LSTM_GEMM_SKINNY="0")
+    assert got <= 1.03 * error(M, N, K, kn)
+
+
 @pytest.mark.parametrize("kn", [False, True])
 def test_without_scratch(kn):
     c, ref, bound = product(40, 512, 4096, kn, scratch=False)

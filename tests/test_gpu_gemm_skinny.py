@@ -50,7 +50,8 @@ def error(M, N, K, kn):
 # three parts: with this kernel in the place of some of them no error is larger.  The norms of 10000 elements and more scatter by
 # less than 1 % each; 3 % is three times the scatter of their ratio.
 @pytest.mark.parametrize("M,N,K,kn", [(5, 16384, 4096, False), (8, 16384, 4096, False), (5, 2560, 640, False), (8, 2560, 640, False), (8, 8192, 2048, False),
-                                      (16, 2048, 256, True), (33, 1024, 256, False), (12, 4096, 384, False), (16, 2048, 2048, False), (64, 4096, 4096, True)])
+                                      (16, 2048, 256, True), (33, 1024, 256, False), (12, 4096, 384, False), (16, 2048, 2048, False), (64, 4096, 4096, True),
+                                      (16, 1024, 960, True), (8, 1024, 960, True), (32, 640, 704, True), (16, 1024, 1152, False)])
 def test_no_larger_error_than_without(M, N, K, kn, knobs):
     got = error(M, N, K, kn)
     knobs(LSTM_GEMM_SKINNY="0")

@@ -50,7 +50,7 @@ const Knobs& knobs() {
     k.no_pad = env_is("LSTM_NO_PAD", '1');
     k.gemm_staged = env_is("LSTM_GEMM_STAGED", '1');
     k.gemm_short = !env_is("LSTM_GEMM_SHORT", '0');
-    k.gemm_skinny = !env_is("LSTM_GEMM_SKINNY", '0');
+    k.gemm_skinny = env_int("LSTM_GEMM_SKINNY", 0, 18, 1);
     k.gemm_split = !env_is("LSTM_GEMM_SPLIT", '0');
     k.cell_step = !env_is("LSTM_CELL_STEP", '0');
     k.tiny = !env_is("LSTM_TINY", '0');

@@ -9,7 +9,7 @@ struct Knobs {
   bool no_pad;               // LSTM_NO_PAD=1: hidden sizes run as given instead of zero-padded to a persistent kernel's
   bool gemm_staged;          // LSTM_GEMM_STAGED=1: the fp32 GEMM kernel everywhere
   bool gemm_short;           // LSTM_GEMM_SHORT=0: short products stay on the bf16 matrix cores too (never on the fp32 kernels)
-  bool gemm_skinny;          // LSTM_GEMM_SKINNY=0: products of up to 64 rows never on the kernel without LDS tiles
+  int gemm_skinny;           // LSTM_GEMM_SKINNY=0: products of up to 64 rows never on the kernel without LDS tiles; 2: all that it takes; 2 + s: in s slices
   bool rnn_pp;               // RNN_PINGPONG=0: the GRU and the single-gate cells on the one-chain wide kernels instead of the alternating ones
   int split3;                // LSTM_SPLIT3: recurrences on the bf16 matrix cores: -1 unset, 0 never, 1 wherever the shape allows, 2 as 1, and
                              // every launch is run again on the fp32 ones as after a sum that is not finite

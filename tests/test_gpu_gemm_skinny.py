@@ -1,5 +1,6 @@
 """Products of up to 64 rows on the kernel whose operands go from memory to registers: remainders of its tiles of rows and blocks of 64
-columns, K from one unit of 32 to several slices, both layouts of B, strided operands and results, values that are not finite."""
+columns, K from one unit of 32 to several slices, both layouts of B, strided operands and results, values that are not finite.  What
+runs on it by itself depends on models of times: LSTM_GEMM_SKINNY=2 and above runs whatever it can take, in a given number of slices."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -41,6 +42,25 @@ def test_against_float64(M, N, K, kn):
         assert ((c - ref).abs() <= 2.0 ** -21 * bound).all()
 
 
+# On that kernel for certain (other bits than without it): all numbers of row tiles, whole and not; a last block of 64 columns that is full,
+# nearly empty and over half full; waves without any k, slices without any; without and with scratch for the slices.
+@pytest.mark.parametrize("kn", [False, True])
+@pytest.mark.parametrize("M", [1, 8, 16, 17, 32, 33, 48, 49, 64])
+@pytest.mark.parametrize("N,K,knob", [(64, 32, 2), (68, 96, 3), (100, 224, 4), (128, 256, 2), (64, 288, 5), (68, 96, 18), (132, 2048, 10), (324, 992, 18)])
+def test_every_product_that_it_takes(M, N, K, knob, kn, knobs):
+    import torch
+
+    N = N if kn or N % 64 == 0 else N - 3
+    knobs(LSTM_GEMM_SKINNY=knob)
+    for acc in (0, 1):
+        c, ref, bound = product(M, N, K, kn, acc)
+        assert ((c - ref).abs() <= 2.0 ** -21 * bound).all()
+    whole, ref, bound = product(M, N, K, kn, scratch=False)
+    assert ((whole - ref).abs() <= 2.0 ** -21 * bound).all()
+    knobs(LSTM_GEMM_SKINNY="0")
+    assert not torch.equal(c, product(M, N, K, kn, 1)[0])
+
+
 def error(M, N, K, kn):
     c, ref, _ = product(M, N, K, kn)
     return ((c - ref).norm() / ref.norm()).item()
@@ -66,9 +86,10 @@ def test_without_scratch(kn):
 
 @pytest.mark.parametrize("kn", [False, True])
 @pytest.mark.parametrize("value", [float("inf"), float("nan"), 3e38])
-def test_values_that_are_not_finite(kn, value):
+def test_values_that_are_not_finite(kn, value, knobs):
     import torch
 
+    knobs(LSTM_GEMM_SKINNY="2")
     c, ref, bound = product(20, 256, 1024, kn, poison=value)
     if value == 3e38:  # finite, above what the parts hold
         ok = ref.abs() <= 3.4e38

@@ -127,7 +127,7 @@ struct PersBwdArgs {
   long long* trace;
   int trace_block;
   const float* h0;     // [L][B][H] or null: read by the GRU variant of the wide kernel
-  int nsl = 1;         // pers_bwd_near_kernel: slices of 16 rows side by side in this launch; with more than one db takes their parts, [L][slices][4H]
+  int nsl = 1;         // pers_bwd_near_kernel: slices of 16 rows side by side in this launch; with more than one db takes their parts, [L][slices][gates H]
   int spread = 0;      // pers_bwd_near_kernel: as in PersFwdArgs
   float* dummy;        // pers_bwd_pp_kernel: 128 bytes of scratch that take the stores nobody wants
 };

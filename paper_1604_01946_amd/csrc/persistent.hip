@@ -240,6 +240,8 @@ NearPlan near_plan(const Dims& d, int cell, bool backward) {
   if ((backward ? knobs().bwd_narrow : knobs().fwd_narrow) >= 0 || knobs().two_chains || knobs().pingpong >= 0 || !knobs().rnn_pp || knobs().split3 >= 0) return p;  // another kernel is asked for
   const bool single = cell >= 2;
   p.slices = (d.B + 15) / 16;
+  // (the slices' bias gradients, [L][slices][gates H], lie in the workspace's area of [L][64][4H])
+  if (backward && p.slices * (single ? 1 : 4) > 64 * 4) return NearPlan{};
   for (int side = p.slices; side > 0 && (side == p.slices || single); --side)
     for (int units = single ? 16 : 8; units <= (single ? 32 : 16); units *= 2)
       for (int spread = 0; spread < 2; ++spread) {

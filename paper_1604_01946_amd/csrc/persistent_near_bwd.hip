@@ -180,7 +180,7 @@ __global__ __launch_bounds__(UB == 8 ? 320 : 576) void pers_bwd_near_kernel(cons
       float v = 0.f;
       for (int row = 0; row < rows; ++row) v += sum[(e / UB * 16 + row) * UP + e % UB];
       // (one slice: the caller's array)
-      if (a.db) a.db[(S == 1 ? (size_t)l * GP : ((size_t)l * S + b0 / 16) * G) + e / UB * H + u0 + e % UB] = v;
+      if (a.db) a.db[((size_t)l * S + b0 / 16) * GP + e / UB * H + u0 + e % UB] = v;
     }
     return;
   }
@@ -402,12 +402,12 @@ __global__ __launch_bounds__(256) void near_empty_kernel(floatx4* __restrict__ p
   for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n + n2; i += (long)gridDim.x * blockDim.x) (i < n ? p[i] : p2[i - n]) = floatx4{e, e, e, e};
 }
 
-// db[l][c] = sum over slices of part[l][slice][c], c < cols of 4H
-__global__ __launch_bounds__(256) void near_bias_kernel(const float* __restrict__ part, float* __restrict__ db, int slices, int G, int cols) {
+// db[l][c] = sum over slices of part[l][slice][c], c < cols
+__global__ __launch_bounds__(256) void near_bias_kernel(const float* __restrict__ part, float* __restrict__ db, int slices, int cols) {
   const int c = blockIdx.x * blockDim.x + threadIdx.x, l = blockIdx.y;
   if (c >= cols) return;
   float v = 0.f;
-  for (int s = 0; s < slices; ++s) v += part[((size_t)l * slices + s) * G + c];
+  for (int s = 0; s < slices; ++s) v += part[((size_t)l * slices + s) * cols + c];
   db[(size_t)l * cols + c] = v;
 }
 
@@ -450,9 +450,9 @@ hipError_t launch_units(int units, const PersBwdArgs& a, hipStream_t s) {
 
 }  // namespace
 
-// db (the caller's, [L][3H or so]) from the slices' parts that launch_bwd_near left in a.db [L][slices][4H]
+// db (the caller's, [L][gates H]) from the slices' parts that launch_bwd_near left in a.db [L][slices][gates H]
 hipError_t launch_near_bias(const float* part, float* db, int L, int slices, int H, int gates, hipStream_t s) {
-  hipLaunchKernelGGL(near_bias_kernel, dim3((gates * H + 255) / 256, L), dim3(256), 0, s, part, db, slices, 4 * H, gates * H);
+  hipLaunchKernelGGL(near_bias_kernel, dim3((gates * H + 255) / 256, L), dim3(256), 0, s, part, db, slices, gates * H);
   return hipGetLastError();
 }
 

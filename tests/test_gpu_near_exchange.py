@@ -50,6 +50,37 @@ def test_slices_other_cells(cell, L, T, B, I, H):
     run_cell(cell, L, T, B, I or H, H, seed=4)
 
 
+# Many slices: their bias gradients fill up to half of the area that they are left in, which holds 64 rows of 4H.  (One of 16 x 64 rows, one
+# more, as many as these cells have on chip, and a padded size.)
+@pytest.mark.parametrize("cell", ["tanh", "relu"])
+@pytest.mark.parametrize("B,H", [(1024, 128), (1025, 128), (2048, 128), (2040, 100)])
+@pytest.mark.parametrize("with_h0", [True, False])
+def test_many_slices(cell, B, H, with_h0):
+    run_cell(cell, 2, 2, B, 24, H, seed=4, with_h0=with_h0)
+
+
+def test_bias_gradients_of_many_slices_stay_in_their_area():
+    """Behind that area the workspace has [8][B][4H] floats for paths that run unfused, which these kernels leave alone: the longest
+    run of words that a pass of one step does not write (the exchange area and the stand-in of the reserve together are smaller)."""
+    import torch
+
+    from paper_1604_01946_amd import binding as Bd
+    from test_gpu_rnn_cells import make
+
+    cell, L, T, B, I, H = "tanh", 2, 1, 2048, 24, 128
+    c, t = Bd.RNN_CELLS[cell], {k: torch.from_numpy(v).cuda() for k, v in make(cell, L, T, B, I, H, 4).items()}
+    rb, wb = Bd.rnn_reserve_bytes(c, L, T, B, I, H), Bd.rnn_workspace_bytes(c, L, T, B, I, H)
+    res, ws = torch.empty(rb // 4, device="cuda"), torch.empty(wb // 4, dtype=torch.int32, device="cuda")
+    y, new = torch.empty(T, B, H, device="cuda"), lambda k: torch.empty_like(t[k])
+    Bd.check(Bd.rnn_forward(c, L, T, B, I, H, t["x"], t["h0"], t["W"], t["R"], t["b"], y, None, res, ws, wb), "rnn_forward")
+    ws.fill_(0x7EADBEEF)
+    Bd.check(Bd.rnn_backward(c, L, T, B, I, H, t["x"], t["h0"], t["W"], t["R"], res, t["dy"], t["dhT"], new("x"), new("h0"), new("W"), new("R"),
+                             new("b"), ws, wb), "rnn_backward")
+    written = torch.nonzero(ws != 0x7EADBEEF).flatten()
+    ends = torch.cat([written.new_tensor([-1]), written, written.new_tensor([ws.numel()])])
+    assert (ends.diff().max() - 1).item() >= 8 * B * 4 * H
+
+
 # Sizes with one-layer kernels as well: LSTM and GRU up to 896 layer by layer, lengths on both sides of the lines between the kernels, the single
 # gate with all layers in a launch, with groups of them, and in several launches; padded to these sizes.
 LARGE = [(1, 1, 16, 0, 640), (2, 9, 33, 24, 640), (2, 5, 32, 0, 768), (1, 17, 17, 0, 768), (3, 8, 5, 24, 896), (1, 3, 32, 0, 896), (2, 6, 20, 0, 1024), (2, 4, 3, 40, 700)]

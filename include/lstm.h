@@ -103,11 +103,12 @@ extern "C" {
  * five times with four layers).  Reserve and workspace sizes are those of the network padded to the next of 128, 256, 512,
  * 1024 and 2048 (or larger), and
  * the copies are part of the weight re-layout that Section 2.3 redoes every pass.  The smallest
- * networks (H = 8, 16 or 32 with I <= 64, B <= 8 and L (3 + B) <= 20, as long as their layers one after
- * the other take no longer than the padded run's, which overlap) are not padded either: one
+ * networks (H = 8, 16 or 32 with I <= 64, B <= 8 and L (3 + B) <= 20) are not padded either: one
  * workgroup runs a whole pass of theirs as given, steps looped inside one launch (the low end of
  * Section 3.1's range, where a launch costs more than a step); LSTM_MICRO=0 in the environment
- * switches that off.  LSTM_NO_PAD=1 in the
+ * switches that off.  Where their layers one after the other take longer than the padded run's, which overlap (long
+ * sequences through several layers), the automatic choice is the padded run, and the other paths run
+ * as given.  LSTM_NO_PAD=1 in the
  * environment runs every shape as given; both size queries return the larger of the padded and the
  * as-given requirement, so a buffer sized under one setting is never too small under the other (the
  * reserve's layout still differs: forward and backward of one reserve must run under one setting of both variables, which

@@ -357,6 +357,41 @@ int forward_padded(const Dims& d, const Dims& p, const float* x, const float* h0
   return LSTM_OK;
 }
 
+// The networks that micro_takes, where they are padded for the sake of the persistent kernels (long sequences of few rows), on any other
+// path: as given, as every network of that size was before (L = 4, T = 250, B = 1, H = 32 forward and backward on the step path: 1.2 ms, padded 8.5).  Only the reserve
+// has the padded layout, so that either direction reads the other's whatever their paths: one copy behind a forward pass (the columns past
+// H are zeros, which give zero gradients) and one in front of a backward pass.
+bool runs_as_given(const Dims& d, unsigned path) { return path != LSTM_PATH_PERSISTENT && micro_takes(d); }
+
+int forward_as_given(FwdArgs a, const Dims& p, unsigned path) {
+  float* const out = a.reserve;
+  a.w = ws_layout(a.d);
+  a.reserve = reinterpret_cast<float*>(a.ws + a.w.resv);
+  a.inference = out == nullptr;
+  const int st = run_forward(a, path);
+  if (st != LSTM_OK || !out) return st;
+  ProfScope ps(LSTM_PHASE_FWD_PACK, a.stream);
+  ResizeGroup g;
+  const int rows = 6 * a.d.L * a.d.T * a.d.B;
+  g.add(out, a.reserve, 1, rows, p.H, rows, a.d.H);
+  CK(launch_resize_group(g, a.stream), "pad reserve");
+  return LSTM_OK;
+}
+
+int backward_as_given(BwdArgs a, const Dims& p, unsigned path) {
+  a.w = ws_layout(a.d);
+  float* const res = reinterpret_cast<float*>(a.ws + a.w.resv);
+  {
+    ProfScope ps(LSTM_PHASE_BWD_PACK, a.stream);
+    ResizeGroup g;
+    const int rows = 6 * a.d.L * a.d.T * a.d.B;
+    g.add(res, a.reserve, 1, rows, a.d.H, rows, p.H);
+    CK(launch_resize_group(g, a.stream), "crop reserve");
+  }
+  a.reserve = res;
+  return run_backward(a, path);
+}
+
 int backward_padded(const Dims& d, const Dims& p, const float* x, const float* h0, const float* c0, const float* W,
                     const float* R, const void* reserve, const float* dy, const float* dhT, const float* dcT, float* dx,
                     float* dh0, float* dc0, float* dW, float* dR, float* db, char* ws, hipStream_t s, unsigned flags) {
@@ -618,6 +653,12 @@ int forward_call(int L, int T, int B, int I, int H, const float* x, const float*
     if (cell_step_takes(a)) return run_cell_step(a);
   }
   if (p.H != d.H) {
+    unsigned path = flags & LSTM_PATH_MASK;
+    if (path == LSTM_PATH_AUTO) path = resolve_auto_path(d, false);
+    if (runs_as_given(d, path)) {
+      if (no_new_resources && path == LSTM_PATH_WAVEFRONT) path = LSTM_PATH_STEP;
+      return forward_as_given(FwdArgs{d, x, h0, c0, W, R, b, y, hT, cT, (float*)reserve, (char*)workspace, WsLayout{}, (hipStream_t)stream}, p, path);
+    }
     return forward_padded(d, p, x, h0, c0, W, R, b, y, hT, cT, reserve, (char*)workspace, (hipStream_t)stream, flags,
                           no_new_resources);
   }
@@ -650,6 +691,11 @@ int lstm_backward(int L, int T, int B, int I, int H, const float* x, const float
   if (workspace_bytes < lstm_workspace_bytes(L, T, B, I, H)) return LSTM_BUFFER_TOO_SMALL;
   if (take_watchdog()) return LSTM_INTERNAL;  // an earlier call's persistent kernel gave up waiting: reported once, here
   if (p.H != d.H) {
+    unsigned path = flags & LSTM_PATH_MASK;
+    if (path == LSTM_PATH_AUTO) path = resolve_auto_path(d, true);
+    if (runs_as_given(d, path))
+      return backward_as_given(BwdArgs{d, x, h0, c0, W, R, (const float*)reserve, dy, dhT, dcT, dx, dh0, dc0, dW, dR, db, (char*)workspace,
+                                       WsLayout{}, (hipStream_t)stream}, p, path);
     return backward_padded(d, p, x, h0, c0, W, R, reserve, dy, dhT, dcT, dx, dh0, dc0, dW, dR, db, (char*)workspace,
                            (hipStream_t)stream, flags);
   }

@@ -474,17 +474,21 @@ hipError_t launch_bwd_t(const MicroBwdArgs& a, size_t lds, hipStream_t s) {
 // 0.5 + 0.01 H + (0.2 + 0.005 H) B us per layer and step.  L = 1, B = 4, H = 32: T = 8 here 34 us, there 103, T = 250 575 and 692;
 // L = 4, B = 1, H = 32: T = 8 88 and 84, T = 250 1182 and 474.  L (3 + B) <= 20 is as far as the shapes measured go.
 // LSTM_MICRO=0 keeps every shape on the other kernels.
-bool micro_shape(const Dims& d) {
+// micro_takes: what the step path runs like this.  micro_shape: what the automatic choice does, and what is not padded.
+bool micro_takes(const Dims& d) {
   const int level = knobs().micro;
   if (level == 0 || !(d.H == 8 || d.H == 16 || d.H == 32) || d.I > kMicroMaxI || d.B > kMicroMaxB) return false;
-  if (level == 2) return true;
+  return level == 2 || d.L * (3 + d.B) <= 20;
+}
+bool micro_shape(const Dims& d) {
+  if (!micro_takes(d) || knobs().micro == 2) return micro_takes(d);
   const double step = d.L * (0.5 + 0.01 * d.H + (0.2 + 0.005 * d.H) * d.B), there = d.B == 1 ? 1.7 : 3.0;
-  return d.L * (3 + d.B) <= 20 && d.T * (step - there) <= 40.0;
+  return d.T * (step - there) <= 40.0;
 }
 
 hipError_t launch_micro_forward(const FwdArgs& f) {
   const Dims& d = f.d;
-  if (!micro_shape(d)) return hipErrorInvalidValue;
+  if (!micro_takes(d)) return hipErrorInvalidValue;
   const int C = fwd_chunk(d);
   MicroFwdArgs a{f.x, f.h0, f.c0, f.W, f.R, f.b, f.y, f.hT, f.cT, f.reserve, d.L, d.T, d.B, d.I, C};
   const size_t lds = ((size_t)C * d.B * std::max(d.I, d.H) * sizeof(float) + 15) & ~(size_t)15;
@@ -501,7 +505,7 @@ hipError_t launch_micro_forward(const FwdArgs& f) {
 
 hipError_t launch_micro_backward(const BwdArgs& g) {
   const Dims& d = g.d;
-  if (!micro_shape(d)) return hipErrorInvalidValue;
+  if (!micro_takes(d)) return hipErrorInvalidValue;
   const int C = bwd_chunk(d);
   MicroBwdArgs a{g.x, g.h0, g.c0, g.W, g.R, g.reserve, g.dy, g.dhT, g.dcT, g.dx, g.dh0, g.dc0, g.dW, g.dR, g.db,
                  reinterpret_cast<float*>(g.ws + g.w.dx), d.L, d.T, d.B, d.I, C};

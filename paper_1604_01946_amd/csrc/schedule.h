@@ -51,6 +51,7 @@ struct BwdArgs {
 // persistent kernels exist for the multiples of 64 from 128 to 512, and any other hidden size below 512 runs faster (several
 // times, with more than one layer) padded to the next of them than on the per-step paths.  LSTM_NO_PAD=1 in the environment disables it.
 // micro.hip: a whole pass in one workgroup, for the smallest networks (part of the step path)
+bool micro_takes(const Dims& d);
 bool micro_shape(const Dims& d);
 hipError_t launch_micro_forward(const FwdArgs& a);
 hipError_t launch_micro_backward(const BwdArgs& a);

@@ -73,7 +73,7 @@ std::vector<ChunkOverride> g_chunk_table;
 
 int set_wavefront_chunks(const Dims& user, int chunks) {
   if (chunks < 0) return LSTM_INVALID_ARG;
-  const Dims d = padded_dims(user);  // the shape the paths run at
+  const Dims d = micro_takes(user) ? user : padded_dims(user);  // the shape the path runs at
   std::lock_guard<std::mutex> lk(g_path_mu);
   for (size_t i = 0; i < g_chunk_table.size(); ++i)
     if (same_shape(g_chunk_table[i].d, d)) {
@@ -126,8 +126,9 @@ unsigned resolve_auto_path(const Dims& user, bool backward) {
     for (const PathOverride& o : g_path_table)
       if (same_shape(o.d, user) && o.backward == backward) return o.path;
   }
-  if (micro_shape(user)) return LSTM_PATH_STEP;  // one launch per pass, steps looped inside (micro.hip)
   const Dims d = padded_dims(user);  // what the kernels will run
+  // one launch per pass, steps looped inside (micro.hip)
+  if (micro_shape(user) || (micro_takes(user) && !persistent_supported(d, backward))) return LSTM_PATH_STEP;
   if (persistent_supported(d, backward) && !steps_beat_chip(d, 0, backward))
     return steps_beat_large(d, backward) ? LSTM_PATH_STEP : LSTM_PATH_PERSISTENT;
   const int cus = device_cu_count();
@@ -171,7 +172,7 @@ int fwd_step(const FwdArgs& a) {
   const Dims& d = a.d;
   const size_t TB = (size_t)d.T * d.B, G = 4 * (size_t)d.H, BH = (size_t)d.B * d.H;
   hipStream_t s = a.stream;
-  if (micro_shape(d)) {  // a launch per step would cost more than the step: all of them in one launch
+  if (micro_takes(d)) {  // a launch per step would cost more than the step: all of them in one launch
     ProfScope ps(LSTM_PHASE_FWD_RECURRENCE, s);
     CK(launch_micro_forward(a), "forward pass in one workgroup");
     return LSTM_OK;
@@ -367,7 +368,7 @@ int bwd_step(const BwdArgs& a) {
   const size_t TB = (size_t)d.T * d.B, G = 4 * (size_t)d.H, BH = (size_t)d.B * d.H, BG = (size_t)d.B * G;
   const int H = d.H, B = d.B, T = d.T;
   hipStream_t s = a.stream;
-  if (micro_shape(d)) {
+  if (micro_takes(d)) {
     ProfScope ps(LSTM_PHASE_BWD_RECURRENCE, s);
     CK(launch_micro_backward(a), "backward pass in one workgroup");
     return LSTM_OK;

@@ -4,6 +4,7 @@ slices of 16 and 64 rows, several launches, inputs wider than the hidden size, s
 import pytest
 
 from paper_1604_01946_amd.inputs import Config
+from parity import BWD_TOL, FWD_TOL, assert_close, oracle_results, recurrence_kernels
 from test_gpu_parity import run_case
 from test_gpu_rnn_cells import run as run_cell
 
@@ -90,3 +91,35 @@ def test_short_passes(T, B, H, path):
 @pytest.mark.parametrize("L,T,B,H", [(4, 40, 1, 32), (4, 90, 1, 32), (2, 30, 7, 16), (2, 60, 7, 16)])
 def test_micro_line(L, T, B, H):
     run_case(cfg(L, T, B, H, H), 3, 0)
+
+
+# Tiny networks beyond that line: the step path still is one workgroup and the other rungs run as given, whatever the automatic choice does;
+# a reserve of any path is read by the backward pass of any other.
+@pytest.mark.parametrize("L,T,B,I,H", [(4, 40, 1, 24, 32), (2, 60, 7, 16, 16)])
+def test_tiny_networks_on_named_paths(L, T, B, I, H, knobs):
+    import torch
+    from paper_1604_01946_amd import binding
+    from paper_1604_01946_amd.runner import LstmRunner
+
+    c, micro = cfg(L, T, B, I, H), ("lstm_micro_fwd_kernel", "lstm_micro_bwd_kernel")
+    d, ref = oracle_results(c, 3)
+    assert binding.lstm_auto_path(*c.dims, 0) == binding.LSTM_PATH_PERSISTENT
+
+    def both(f, b):
+        r = LstmRunner(c.dims, d)
+        r.poison()
+        print(c.dims, f, b, flush=True)
+        names = recurrence_kernels(lambda: (binding.check(r.forward(flags=f)), binding.check(r.backward(flags=b))))
+        assert_close(r.fwd_outputs(), ref, ("y", "hT", "cT"), FWD_TOL, f"{f}")
+        assert_close(r.bwd_outputs(), ref, ("dx", "dh0", "dc0", "dW", "dR", "db"), BWD_TOL, f"{b}")
+        return names
+
+    for f in range(7):
+        for b in range(7):
+            names = both(f, b)
+            assert (f != binding.LSTM_PATH_STEP or names[0] == micro[0]) and (b != binding.LSTM_PATH_STEP or names[1] == micro[1])
+    for k in (0, 1):
+        binding.check(binding.lstm_set_path(*c.dims, k, binding.LSTM_PATH_STEP))
+    assert both(0, 0) == micro
+    knobs(LSTM_NO_PAD="1")  # (and without kernels for the padded size)
+    assert both(0, 0) == micro

@@ -32,34 +32,15 @@
 namespace lstm {
 namespace {
 
-// The 16-byte request of the backward kernel is inline assembly (there is no 16-byte atomic load to ask the compiler
-// for), so the wait for it is written out as well, tied to the value it covers.  Every word is its own flag: a request
-// that is served while the producer is writing is simply partly empty.
-__device__ __forceinline__ floatx4 request4(const float* p) {
-  floatx4 v;
-  asm volatile("global_load_dwordx4 %0, %1, off sc1" : "=v"(v) : "v"(p) : "memory");
-  return v;
-}
-__device__ __forceinline__ void landed(floatx4& v) { asm volatile("s_waitcnt vmcnt(0)" : "+v"(v)::"memory"); }
-__device__ __forceinline__ void publish4(float* p, floatx4 v, bool near) {
-#pragma unroll
-  for (int c = 0; c < 4; ++c)
-    if (__float_as_uint(v[c]) == kEmpty) v[c] = __uint_as_float(0x7FC00000u);
-  if (near) asm volatile("global_store_dwordx4 %0, %1, off\n\ts_nop 3" ::"v"(p), "v"(v) : "memory");
-  else asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 3" ::"v"(p), "v"(v) : "memory");
-}
-
 struct TinyWaiter : NearWaiter {
-  // Four consecutive values per lane.
-  __device__ __forceinline__ void poll4(const float* p, floatx4& v) {
+  // Four consecutive values per lane of a slot of n floats.  Every word is its own flag: a request that is served while the
+  // producer is writing is simply partly empty.
+  __device__ __forceinline__ floatx4 poll4(const float* slot, int n, int at) {
     int spins = 0;
     while (true) {
-      v = request4(p);
-      landed(v);
-      bool ok = true;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) ok = ok && __float_as_uint(v[c]) != kEmpty;
-      if (__all(ok) || give_up(spins)) return;
+      asm volatile("" ::: "memory");  // (asked for again, it is read again)
+      const floatx4 v = slot_load4<true>(slot, n, at);
+      if (every_lane(top4(v, 0) != kEmpty) || give_up(spins)) return v;
     }
   }
 };
@@ -536,7 +517,7 @@ __global__ __launch_bounds__(HH + 64) void pers_bwd_tiny_kernel(const PersBwdArg
     const float dcv = dc + dh * ka[0];
     const float d[4] = {dcv * ka[1], dcv * ka[2], dh * ka[3], dcv * kb[0]};
     dc = dcv * kb[1];
-    if (fin) publish4(dslot(t) + 4 * uj, floatx4{d[0], d[1], d[2], d[3]}, near);
+    if (fin) slot_store4(dslot(t), G, 4 * uj, floatx4{d[0], d[1], d[2], d[3]}, near);
     tr.mark(t, 1);
     if (lane < 8) das[par][lane >> 1][ul] = lane < 4 ? (lane < 2 ? d[0] : d[1]) : (lane < 6 ? d[2] : d[3]);
     // ---- dx of the step after, while the gate gradients are on their way
@@ -546,8 +527,7 @@ __global__ __launch_bounds__(HH + 64) void pers_bwd_tiny_kernel(const PersBwdArg
     }
     tr.mark(t, 2);
     // ---- dh_{t-1}: needs dA_t of every unit of the layer (wave w polls words 256 w ... of the slot)
-    floatx4 share;
-    w.poll4(dslot(t) + mine, share);
+    const floatx4 share = w.poll4(dslot(t), G, mine);
     tr.mark(t, 3);
     *reinterpret_cast<floatx4*>(&ds[par][mine]) = share;
     __syncthreads();  // (one barrier per step is enough: see the forward kernel)

@@ -203,3 +203,14 @@ def test_rnn_workspace_of_calls_that_run_step_by_step():
         assert B.rnn_workspace_bytes(B.RNN_CELLS[cell], *dims) == steps(cell, *dims), (cell, dims)
     # long enough, they do
     assert B.rnn_workspace_bytes(B.RNN_CELL_GRU, 1, 8, 80, 5, 448) > steps("gru", 1, 8, 80, 5, 448)
+
+
+def test_loads_in_inline_assembly_wait_where_they_are():
+    """The compiler takes the outputs of an assembly statement as there: a load of registers whose wait is another statement could have its
+    destination copied or reused while it is in flight.  (Loads into LDS write no register.)"""
+    import glob
+    src = os.path.join(ROOT, "paper_1604_01946_amd", "csrc")
+    for path in sorted(glob.glob(os.path.join(src, "*.hip")) + glob.glob(os.path.join(src, "*.h"))):
+        for text in re.findall(r"\basm\s+volatile\s*\(((?:\s*\"[^\"]*\")+)", open(path).read()):
+            if re.search(r"(global|flat|buffer|scratch|ds)_(load|read)|s_load|s_buffer_load", text) and "_lds" not in text:
+                assert "s_waitcnt" in text, (os.path.basename(path), text)

@@ -238,6 +238,7 @@ NearPlan near_plan(const Dims& d, int cell, bool backward) {
   DeviceInfo di;
   if (!knobs().near || !device_info(di) || di.cus < 256) return p;  // (eight XCDs of 32 CUs)
   if ((backward ? knobs().bwd_narrow : knobs().fwd_narrow) >= 0 || knobs().two_chains || knobs().pingpong >= 0 || !knobs().rnn_pp || knobs().split3 >= 0) return p;  // another kernel is asked for
+  if (cell == 0 && d.B == 1 && !knobs().tiny) return p;  // (single sequences on the kernels with step counters)
   const bool single = cell >= 2;
   p.slices = (d.B + 15) / 16;
   // (the slices' bias gradients, [L][slices][gates H], lie in the workspace's area of [L][64][4H])

@@ -4,6 +4,7 @@ steps whose reserve values pass through LDS together, one and more layers; the s
 import pytest
 
 from paper_1604_01946_amd.inputs import Config
+from parity import recurrence_kernels
 from test_gpu_parity import BWD, FWD, run_case
 from test_gpu_rnn_cells import run as run_cell
 
@@ -23,6 +24,35 @@ def test_single_sequence(H, L, T, I, knobs):
     fast, _ = run_case(cfg(L, T, 1, I or H, H), 21, 6)
     for k in FWD + BWD:
         assert (getattr(slow, k) == getattr(fast, k)).all(), k
+
+
+# The kernels with step counters, which run where these two settings ask for them or the device has fewer CUs: a single sequence, a batch of
+# one slice, slices of 16 rows side by side; the other cells on the alternating kernels.
+NARROW = [(2, 5, 1, 0, 192), (2, 9, 1, 24, 256), (2, 5, 16, 0, 128), (1, 4, 17, 24, 256), (2, 3, 64, 0, 256), (1, 9, 64, 0, 512), (3, 4, 33, 24, 192)]
+
+
+@pytest.mark.parametrize("L,T,B,I,H", NARROW)
+def test_lstm_on_the_kernels_with_step_counters(L, T, B, I, H, knobs):
+    c = cfg(L, T, B, I or H, H)
+    if B == 1:
+        knobs(LSTM_TINY="0")
+        assert recurrence_kernels(lambda: run_case(c, 25, 6)) == ("pers_fwd_kernel", "pers_bwd_kernel")
+        knobs(LSTM_TINY=None)
+        assert recurrence_kernels(lambda: run_case(c, 25, 6)) == ("pers_fwd_tiny_kernel", "pers_bwd_tiny_kernel")
+    else:
+        knobs(LSTM_NEAR="0")
+        assert recurrence_kernels(lambda: run_case(c, 25, 6)) == ("pers_fwd_kernel", "pers_bwd_kernel")
+        knobs(LSTM_NEAR=None)
+        assert recurrence_kernels(lambda: run_case(c, 25, 6)) == ("pers_fwd_near_kernel", "pers_bwd_near_kernel")
+
+
+@pytest.mark.parametrize("cell", ["gru", "tanh", "relu"])
+@pytest.mark.parametrize("L,T,B,I,H", [(2, 5, 1, 0, 192), (2, 5, 16, 0, 128), (1, 4, 17, 24, 256), (2, 3, 32, 0, 512)])
+def test_other_cells_on_the_alternating_kernels(cell, L, T, B, I, H, knobs):
+    call = lambda: run_cell(cell, L, T, B, I or H, H, seed=4)  # noqa: E731
+    assert recurrence_kernels(call) == ("pers_fwd_near_kernel", "pers_bwd_near_kernel")
+    knobs(LSTM_NEAR="0")
+    assert recurrence_kernels(call)[1] == "pers_bwd_pp_kernel"
 
 
 # Slices of 16 rows: 8 and 16 (single gate 16 and 32) units per workgroup, groups on one XCD, two on one, on all; rows that do not

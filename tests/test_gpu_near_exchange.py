@@ -5,6 +5,8 @@ import pytest
 
 from paper_1604_01946_amd.inputs import Config
 from parity import recurrence_kernels
+from test_gpu_in_place import lstm as lstm_pass, same
+from test_gpu_in_place import test_cells as test_states_in_place_of_other_cells  # noqa: F401  (there without these kernels)
 from test_gpu_parity import BWD, FWD, run_case
 from test_gpu_rnn_cells import run as run_cell
 
@@ -125,6 +127,49 @@ def test_large_lstm(L, T, B, I, H):
 @pytest.mark.parametrize("L,T,B,I,H", LARGE + [(6, 3, 20, 0, 896), (5, 4, 3, 0, 1024), (1, 5, 100, 0, 1024), (2, 3, 130, 24, 768)])
 def test_large_other_cells(cell, L, T, B, I, H):
     run_cell(cell, L, T, B, I or H, H, seed=4)
+
+
+# hT = h0, cT = c0, dh0 = dhT, dc0 = dcT: one XCD and all, one launch per layer and all layers in one, a single sequence.
+@pytest.mark.parametrize("dims", [(2, 9, 1, 24, 256), (4, 3, 64, 128, 128), (3, 5, 17, 320, 320), (2, 4, 20, 24, 384), (1, 10, 33, 512, 512), (2, 9, 33, 24, 640)])
+@pytest.mark.parametrize("nan", [False, True])
+def test_states_in_place(dims, nan):
+    got = {}
+    assert recurrence_kernels(lambda: got.update(lstm_pass(dims, nan, True, 0)))[0] == ("pers_fwd_tiny_kernel" if dims[2] == 1 else "pers_fwd_near_kernel")
+    same(lstm_pass(dims, nan, False, 0), got)
+
+
+@pytest.mark.parametrize("cell", ["gru", "tanh", "relu"])
+@pytest.mark.parametrize("H,B", [(256, 20), (320, 5), (896, 18)])
+def test_a_row_of_other_cells_that_is_not_finite_spoils_no_other(cell, H, B):
+    import numpy as np
+    import torch
+
+    from paper_1604_01946_amd import binding as Bd
+    from test_gpu_rnn_cells import make
+
+    L, T, I, c, out = 2, 4, 24, Bd.RNN_CELLS[cell], []
+    for spoil in (False, True):
+        d = make(cell, L, T, B, I, H, 4)
+        if spoil:
+            d["x"][1, 2, 5], d["x"][2, 3, :], d["h0"][:, 4, 7] = np.nan, np.inf, np.nan
+        t = {k: torch.from_numpy(v).cuda() for k, v in d.items()}
+        rb, wb = Bd.rnn_reserve_bytes(c, L, T, B, I, H), Bd.rnn_workspace_bytes(c, L, T, B, I, H)
+        res, ws = torch.empty(rb // 4, device="cuda"), torch.empty(wb // 4, device="cuda")
+        y, new = torch.empty(T, B, H, device="cuda"), lambda k: torch.empty_like(t[k])
+        hT, dx, dh0 = new("h0"), new("x"), new("h0")
+
+        def call():
+            Bd.check(Bd.rnn_forward(c, L, T, B, I, H, t["x"], t["h0"], t["W"], t["R"], t["b"], y, hT, res, ws, wb), "rnn_forward")
+            Bd.check(Bd.rnn_backward(c, L, T, B, I, H, t["x"], t["h0"], t["W"], t["R"], res, t["dy"], t["dhT"], dx, dh0, new("W"), new("R"), new("b"), ws, wb), "rnn_backward")
+
+        assert recurrence_kernels(call) == ("pers_fwd_near_kernel", "pers_bwd_near_kernel" if H < 896 or cell not in ("gru",) else "pers_bwdL_kernel")
+        out.append((y, hT, dx, dh0))
+    keep = [b for b in range(B) if b not in (2, 3, 4)]
+    for a, b in zip(*out):
+        # (as above: sums of a tile with one that is not finite are worked out with other instructions)
+        assert (a[:, keep] - b[:, keep]).abs().max() <= 1e-5 * a.abs().max()
+    if cell != "relu":  # (there the larger of NaN and 0 is 0)
+        assert out[1][0][1:, 2].isnan().all() and out[1][0][:, 4].isnan().any()
 
 
 @pytest.mark.parametrize("H,B", [(256, 20), (320, 5)])

@@ -397,9 +397,13 @@ __global__ __launch_bounds__(UB == 8 ? 320 : 576) void pers_bwd_near_kernel(cons
   __syncthreads();
 }
 
-__global__ __launch_bounds__(256) void near_empty_kernel(floatx4* __restrict__ p, long n, floatx4* __restrict__ p2, long n2) {
+// The empty pattern to n pieces at p, and to the first `own` of every `row` pieces at p2, n2 in all.
+__global__ __launch_bounds__(256) void near_empty_kernel(floatx4* __restrict__ p, long n, floatx4* __restrict__ p2, long n2, int own, int row) {
   const float e = __uint_as_float(kEmpty);
-  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n + n2; i += (long)gridDim.x * blockDim.x) (i < n ? p[i] : p2[i - n]) = floatx4{e, e, e, e};
+  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n + n2; i += (long)gridDim.x * blockDim.x) {
+    const long j = i - n;
+    (i < n ? p[i] : p2[own == row ? j : j / own * row + j % own]) = floatx4{e, e, e, e};
+  }
 }
 
 // db[l][c] = sum over slices of part[l][slice][c], c < cols
@@ -414,9 +418,11 @@ __global__ __launch_bounds__(256) void near_bias_kernel(const float* __restrict_
 template <int H, int CELL, int UB, bool FAR>
 hipError_t launch(const PersBwdArgs& a, hipStream_t s) {
   const int groups = a.L * a.nsl, M = H / UB;
-  const long n = (long)groups * (4L * (CELL < 2 ? 4 : 1) * H * a.T + 16), n2 = (long)(a.L - 1) * a.T * a.B * H / 4;
+  // (of the hand-over array [L][T][B][H] the launch's rows; layer 0 hands nothing over)
+  const int row4 = a.B * H / 4, own4 = std::min(16 * a.nsl, a.B - a.b0) * H / 4;
+  const long n = (long)groups * (4L * (CELL < 2 ? 4 : 1) * H * a.T + 16), n2 = (long)(a.L - 1) * a.T * own4;
   hipLaunchKernelGGL(near_empty_kernel, dim3((unsigned)std::min<long>((n + n2 + 255) / 256, 2048)), dim3(256), 0, s,
-                     reinterpret_cast<floatx4*>(a.dAx), n, reinterpret_cast<floatx4*>(a.dxbuf + (size_t)a.T * a.B * H), n2);  // (layer 0 hands nothing over)
+                     reinterpret_cast<floatx4*>(a.dAx), n, reinterpret_cast<floatx4*>(a.dxbuf + ((size_t)a.T * a.B + a.b0) * H), n2, own4, row4);
   const void* const fn = (const void*)pers_bwd_near_kernel<H, CELL, UB, FAR>;
   constexpr size_t smem = (size_t)4 * ((CELL < 2 ? H / 16 : H / 64) - near_reg_loads(H, CELL)) * 1024;
   static bool ready;

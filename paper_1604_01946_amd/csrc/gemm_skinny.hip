@@ -1,5 +1,5 @@
-// Products of 9 to 64 rows with a large second operand (the recurrent product of a step, H above what fits on chip):
-// gemm_skinny_kernel.
+// Products of up to 64 rows with a large second operand (the recurrent product of a step, H above what fits on chip; up to 8 rows
+// where B has its unit stride along n, the others row by row): gemm_skinny_kernel.
 //
 // Bound: the second operand, read once, and the cutting of both operands into three bf16 parts (split3.h).  The tiles of
 // gemm_split3_kernel pass through LDS with two barriers per 16 k, and a round of 64 x 64 tiles leaves one workgroup per CU, which waits

@@ -1,5 +1,5 @@
 // Device-side helpers of the kernels whose workgroups exchange values that are their own flags (persistent_tiny.hip,
-// persistent_near.hip): an exchange slot holds the empty pattern until it is written, once, and whoever needs it reads it until no
+// persistent_near_fwd.hip, persistent_near_bwd.hip): an exchange slot holds the empty pattern until it is written, once, and whoever needs it reads it until no
 // word shows the pattern any more.
 #pragma once
 #include "persistent_dev.h"

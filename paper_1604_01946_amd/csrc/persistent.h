@@ -10,8 +10,8 @@
 //   persistent_pp3.hip    pers_fwd_pp3_kernel: the same on the bf16 matrix cores, operands in three parts
 //   persistent_bpp.hip    pers_bwd_pp_kernel: two quarter-slices of 16 rows alternating on the matrix cores
 //   persistent_tiny.hip   pers_fwd_tiny_kernel / pers_bwd_tiny_kernel: B = 1, the exchanged values are their own flags
-//   persistent_near_fwd.hip, persistent_near_bwd.hip  pers_fwd_near_kernel / pers_bwd_near_kernel: slices of 16 rows, H <= 512, all cells;
-//                         groups of workgroups on one XCD (near_dev.h)
+//   persistent_near_fwd.hip, persistent_near_bwd.hip  pers_fwd_near_kernel / pers_bwd_near_kernel: slices of 16 rows, all cells, H <= 512,
+//                         640, 768, 896 and (single gates) 1024; groups of workgroups on one XCD or on all (near_dev.h)
 //   persistent_large_dev.h, persistent_large.hip, persistent_large_mid.hip  pers_fwdL_kernel / pers_bwdL_kernel: one layer per launch,
 //                         H = 1024 / 2048, and sizes between 512 and 2048
 //   persistent.hip        host side: residency, launches, which shapes run where, layer groups, batch slices

@@ -122,8 +122,12 @@ inline size_t res_layer_floats(int cell, const Dims& d) {
 // library's, so the buffer must hold either layout.
 inline bool gru_persistent_shape(int cell, const Dims& d) {
   if (gates_of(cell) == 0) return false;
-  // one-layer kernels: up to the batch where the step-by-step path with its large products measured faster (the
-  // single gate leaves three quarters of the persistent kernels' tiles empty, so its break-even comes earlier)
+  // one-layer kernels: up to the batch where the step-by-step path with its large products measured faster (the single gate leaves three
+  // quarters of those kernels' tiles empty, so its break-even comes earlier).  The single gate's lines and ratios are those of such
+  // tiles.  Its passes on the kernels of 16-row slices, up to H = 1024 (near_plan, near_large_layers), take half the time and less, so the
+  // lines could lie higher by now, but the sizes of callers' buffers follow them.  Step by step over what runs now, as below:
+  //   H = 640 2.7 and 3.0 at 192 rows, 512 2.4 and 2.2 at 512, 256 2.4 and 2.3 at 1024, 128 2.5 and 2.6 at 2048
+  //   (one-layer kernels: H = 896 0.9 and 1.3 at 192, H = 1024 0.9 and 1.3 at 192 and 1.4 and 1.8 at 128, H = 2048 1.0 and 1.2 at 64)
   const bool gru = cell == RNN_CELL_GRU;
   // Time step by step / on chip, forward and backward, one layer of 30 steps and three of 100 (two of 40 where one number):
   //   H = 2048 GRU 1.13 and 1.19 at 96 rows, 0.95 and 1.01 at 128, 0.85 at 320; single gate 1.18 at 64, 0.79 and 0.90 at 96

@@ -54,7 +54,7 @@ const Knobs& knobs() {
     k.gemm_split = !env_is("LSTM_GEMM_SPLIT", '0');
     k.cell_step = !env_is("LSTM_CELL_STEP", '0');
     k.tiny = !env_is("LSTM_TINY", '0');
-    k.near = !env_is("LSTM_NEAR", '0');
+    k.near = env_int("LSTM_NEAR", 0, 2, 1);
     k.split3 = env_int("LSTM_SPLIT3", 0, 2, -1);
     k.large_ksplit = !env_is("LSTM_LARGE_KSPLIT", '0');
     k.rnn_pp = !env_is("RNN_PINGPONG", '0');

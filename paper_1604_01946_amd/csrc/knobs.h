@@ -16,7 +16,7 @@ struct Knobs {
   bool large_ksplit;         // LSTM_LARGE_KSPLIT=0: a single slice at H = 1024 backward on 64 workgroups instead of 256
   int micro;                 // LSTM_MICRO=0: no pass runs as one workgroup; =2: every shape those kernels take does
   bool tiny;                 // LSTM_TINY=0: a single sequence (B = 1) on the narrow kernels instead of the flag-in-data ones
-  bool near;                 // LSTM_NEAR=0: no slices of 16 rows that exchange through an XCD's L2
+  int near;                  // LSTM_NEAR=0: no slices of 16 rows that exchange through an XCD's L2; 2: above 512 units wherever those kernels take a shape
   bool cell_step;            // LSTM_CELL_STEP=0: inference calls of one step and few rows on the paths for sequences
   bool gemm_split;           // LSTM_GEMM_SPLIT=0: no K slices for a product's last partial round of tiles
   int spin_limit;            // LSTM_SPIN_LIMIT: polls before a persistent kernel's wait gives up

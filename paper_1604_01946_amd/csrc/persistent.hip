@@ -268,13 +268,43 @@ NearPlan near_plan(const Dims& d, int cell, bool backward) {
 //   LSTM backward  640 296 / 210 (1, 35, 16); 768 327 / 270, 839 / 598 (2, 35, 32); 896 905 / 699; 1024 86 / 102 (1, 4, 8), 813 / 951
 //   GRU backward   640 780 / 460 (2, 35, 32); 768 794 / 563; 896 75 / 77 (1, 4, 8), 865 / 670; 1024 80 / 102, 802 / 932
 //   single gate    tanh, H = 1024 941 / 266 and 1798 / 301 (4, 52, 1); 640 269 / 107 and 371 / 190 (1, 30, 100); 896 346 / 145 and 647 / 275 (3, 20, 20)
+//   Steps from which the backward recurrence of LSTM and GRU gains (whole calls): one layer, 640 with 20 rows 0.90 (LSTM) and 0.94 (GRU) at one step,
+//   0.97 and 1.10 at two, 1.09 at three; 768 with 5 rows 0.93 at one, 1.02 at three (756 padded to it 0.95 at four), with 20 rows 0.75 at one, 0.97 at three, 1.03 at
+//   eight; 896 0.92 to 1.07 at eight, 1.0 to 1.1 at 16.  Several layers, each a launch: 768 with 20 rows 0.91 at one and 1.13 at three.
+//   Single gate, short passes of several layers: a launch of many layers has to fill and drain them, and slices that don't fit side by side are
+//   launches of their own, each with all weights to fetch (tanh, T = 2, backward: L = 4, B = 177, H = 896 515 us on one-layer kernels, 692 here; L = 2, B = 65, H = 1024 159 and 137;
+//   forward L = 8, B = 192, H = 1024 863 and 1139, B = 20 ten steps 664 and 391).  Microseconds of the one-layer kernels' launches and of these, with 5 to
+//   15 % against the latter, another tenth above four layers, fitted to 1600 recurrences of up to 8 layers, 40 steps and 192 rows: of those that it takes
+//   none was slower by more than 3 %, and it leaves one in 30 that would have gained more than 5 %.
+bool single_gate_gains(const Dims& d, int per, bool backward) {
+  struct Model { double there, there_step, here, here_step, here_layer; };  // of a launch, of a step in it, of a layer behind the first in it
+  constexpr Model fwd[4] = {{17.7, 3.8, 0.0, 4.4, 4.7}, {22.0, 4.0, 6.2, 4.4, 6.5}, {22.7, 4.4, 3.9, 5.2, 5.6}, {19.9, 5.2, 5.5, 6.5, 8.6}};
+  constexpr Model bwd[4] = {{28.8, 8.1, 13.5, 5.9, 8.7}, {26.2, 8.5, 1.9, 7.8, 10.4}, {28.6, 7.9, 14.0, 3.7, 6.1}, {19.3, 2.9, 11.6, 0.52, 4.8}};
+  constexpr int fwd_side[4] = {3, 2, 2, 2}, bwd_side[4] = {4, 3, 2, 4};  // slices of 32 rows in a launch of theirs
+  if (d.L == 1 || d.T > 24) return true;
+  const int i = (d.H - 640) / 128, side = (backward ? bwd_side : fwd_side)[i];
+  const Model& m = (backward ? bwd : fwd)[i];
+  const double there = d.L * (((d.B + 31) / 32 + side - 1) / side) * (m.there + d.T * m.there_step);
+  double here = 0.0;
+  for (int l = 0; l < d.L; l += per) {
+    const Dims g{std::min(per, d.L - l), d.T, d.B, d.I, d.H};
+    const NearPlan p = near_plan(g, 2, backward);
+    here += (p.slices + p.side - 1) / p.side * (m.here + d.T * m.here_step + (g.L - 1) * m.here_layer);
+  }
+  return here * (d.L > 4 ? 1.1 : 1.0) < there;
+}
 int near_large_layers(const Dims& d, int cell, bool backward) {
   if (d.H <= 512 || d.H > 1024) return 0;
-  if (d.H == 1024 && (cell < 2 || (d.L == 1 && d.B > 32))) return 0;  // (of one layer of more rows only the single gate's products would gain)
-  if (backward && cell < 2 && d.H > 768 && d.T < 8) return 0;
-  if (!backward && (cell == 0 ? d.H > 640 && d.T > 16 : cell == 1 && d.H > 768 && d.T > 64)) return 0;
+  if (d.H == 1024 && cell < 2) return 0;
+  if (knobs().near < 2) {
+    if (d.H == 1024 && d.L == 1 && d.B > 32) return 0;  // (of one layer of more rows only the single gate's products would gain)
+    constexpr int least[3][2][2] = {{{1, 3}, {1, 1}}, {{6, 8}, {1, 3}}, {{16, 16}, {8, 8}}};  // [640, 768, 896][several layers][above 16 rows]
+    if (backward && cell < 2 && d.T < least[(d.H - 640) / 128][d.L > 1][d.B > 16]) return 0;
+    if (!backward && (cell == 0 ? d.H > 640 && d.T > 16 : cell == 1 && d.H > 768 && d.T > 64)) return 0;
+  }
   int per = d.L;
   while (per > 0 && !near_plan(Dims{per, d.T, d.B, d.I, d.H}, cell, backward).units) --per;
+  if (per > 0 && cell >= 2 && knobs().near < 2 && !single_gate_gains(d, per, backward)) return 0;
   return per;
 }
 

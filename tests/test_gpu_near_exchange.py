@@ -129,6 +129,16 @@ def test_large_other_cells(cell, L, T, B, I, H):
     run_cell(cell, L, T, B, I or H, H, seed=4)
 
 
+# Short passes above 512 units: both sides of the lines between these kernels and the one-layer kernels.
+@pytest.mark.parametrize("cell,L,T,B,H,near", [
+    ("tanh", 4, 2, 177, 846, (1, 0)), ("tanh", 6, 3, 98, 896, (0, 0)), ("tanh", 3, 3, 180, 1024, (1, 0)), ("tanh", 2, 3, 65, 1024, (1, 1)), ("tanh", 4, 14, 98, 1024, (1, 1)),
+    ("relu", 7, 2, 112, 896, (0, 0)), ("lstm", 1, 2, 10, 708, (1, 0)), ("lstm", 1, 8, 20, 768, (1, 1)), ("lstm", 2, 3, 20, 768, (1, 1)), ("gru", 1, 2, 6, 734, (1, 0)),
+    ("gru", 1, 12, 20, 896, (1, 0)), ("gru", 1, 3, 20, 640, (1, 1)), ("lstm", 1, 2, 20, 640, (1, 0))])
+def test_short_passes_above_512_units(cell, L, T, B, H, near):
+    names = recurrence_kernels(lambda: run_case(cfg(L, T, B, 24, H), 26, 0) if cell == "lstm" else run_cell(cell, L, T, B, 24, H, seed=4))
+    assert (names[0] == "pers_fwd_near_kernel", names[1] == "pers_bwd_near_kernel") == tuple(map(bool, near)), names
+
+
 # hT = h0, cT = c0, dh0 = dhT, dc0 = dcT: one XCD and all, one launch per layer and all layers in one, a single sequence.
 @pytest.mark.parametrize("dims", [(2, 9, 1, 24, 256), (4, 3, 64, 128, 128), (3, 5, 17, 320, 320), (2, 4, 20, 24, 384), (1, 10, 33, 512, 512), (2, 9, 33, 24, 640)])
 @pytest.mark.parametrize("nan", [False, True])

@@ -59,7 +59,7 @@ const Knobs& knobs() {
     k.large_ksplit = !env_is("LSTM_LARGE_KSPLIT", '0');
     k.rnn_pp = !env_is("RNN_PINGPONG", '0');
     k.micro = env_is("LSTM_MICRO", '0') ? 0 : (env_is("LSTM_MICRO", '2') ? 2 : 1);
-    k.spin_limit = env_int("LSTM_SPIN_LIMIT", 1, (1L << 30) - 1, 1 << 21);
+    k.spin_limit = env_int("LSTM_SPIN_LIMIT", 1, (1L << 30) - 1, 1 << 23);
     const char* ff = getenv("LSTM_FULL_FENCES");
     k.full_fences = ff && *ff && *ff != '0';
     k.coop_launch = env_is("LSTM_COOP_LAUNCH", '1');

@@ -3,8 +3,8 @@
 //
 // Bound: the second operand, read once, and the cutting of both operands into three bf16 parts (split3.h).  The tiles of
 // gemm_split3_kernel pass through LDS with two barriers per 16 k, and a round of 64 x 64 tiles leaves one workgroup per CU, which waits
-// at them: 16 x 16384 x 4096, 268 MB, takes 65 us there and 43 us = 6.2 TB/s here, 32 rows 71 and 50, 64 rows 85 and 69 (the cutting
-// and the matrix instructions then take longer than the reading).  Here a wave multiplies all rows by 64 columns and has its own run of k: operands go from memory to registers in the layout of the matrix instructions,
+// at them: 16 x 16384 x 4096, 268 MB, takes 65 us there and 43 us = 6.2 TB/s here, 32 rows 71 and 50, 64 rows 76 and 73 (the cutting
+// and the matrix instructions then take longer than the reading; 64 x 4096 x 16384 along n 82 and 66).  Here a wave multiplies all rows by 64 columns and has its own run of k: operands go from memory to registers in the layout of the matrix instructions,
 // no barrier before the end, where the eight waves of a workgroup add up through LDS.
 //   v_mfma_f32_16x16x32_bf16, the tile's rows are columns of the product.  Lane (q, r) needs eight k of column r (of row r of A);
 //   which eight is free as long as both operands agree:

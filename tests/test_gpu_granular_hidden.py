@@ -1,5 +1,5 @@
 """Hidden sizes between 128, 256 and 512: kernels for every multiple of 64, whose K quarters and counter lines are no powers of
-two.  At the size itself, one below it (padded by a column) and one above the size before it; few rows (narrow kernels),
+two.  At the size itself, one below it (padded by a column) and one above the size before it; few rows (slices of 16 rows; the narrow kernels in test_gpu_step_counters.py),
 slices of 16 and 64 rows, several launches, inputs wider than the hidden size, short and long enough for every variant."""
 import pytest
 

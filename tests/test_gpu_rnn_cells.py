@@ -146,8 +146,8 @@ def test_persistent_shapes(dims, cell, with_h0):
     run(cell, *dims, seed=5, with_h0=with_h0)
 
 
-# These cells run on the kernels with two alternating chains per slice (where x is multiplied inside the kernel, I == H,
-# forward; always backward); RNN_PINGPONG=0 keeps the one-chain kernels covered at those shapes.
+# Beyond one launch of 16-row slices the GRU runs on the kernels with two alternating chains per slice (where x is multiplied inside the
+# kernel, I == H, forward; always backward), and with LSTM_NEAR=0 every cell does (test_gpu_step_counters.py); RNN_PINGPONG=0 keeps the one-chain kernels covered at those shapes.
 @pytest.mark.parametrize("cell", ["gru", "tanh", "relu"])
 @pytest.mark.parametrize("dims", [PERSISTENT[0], PERSISTENT[1], PERSISTENT[3], PERSISTENT[7], PERSISTENT[9]],
                          ids=["4x7x64x512x512", "2x5x33x72x256", "1x3x48x512x512", "4x5x1x512x512", "3x3x130x256x256"])
